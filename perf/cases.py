@@ -11,7 +11,8 @@ HBM:
     average   Context.ddp_partial_average alone, what a worker runs that exchanges and averages without stepping
 
 `arenas` says how the tensors lie: "dense" is the framework's own slab (every stream one flat arena), "separate" gives every
-tensor a start of its own at a multiple of 512 bytes, as a caching allocator places tensors that were created one by one.
+tensor a start of its own at a multiple of 512 bytes and something else in between, as a caching allocator places tensors
+that were created one by one.
 """
 from __future__ import annotations
 
@@ -139,7 +140,7 @@ def _layout(case):
     starts, pos = [], 0
     for n in numel:
         starts.append(pos)
-        pos += n if case["arenas"] == "dense" else -(-n // 256) * 256      # 256 bf16 elements = 512 bytes
+        pos += n if case["arenas"] == "dense" else -(-n // 256) * 256 + 256      # 256 bf16 elements = 512 bytes
     layers = _slot_layers(case, w.n_layers)
     order = [t for l in layers for t in range(len(numel)) if layer[t] == l]
     return numel, layer, starts, pos, order, layers
