@@ -282,14 +282,16 @@ extern "C" int ddp_register_model(ddp_ctx *ctx, int L, int T, const int32_t *lay
         }
         ctx->dense = dense;
 
-        // update table: every tensor cut into runs of update_chunk elements
+        // update table: every tensor cut into runs of update_chunk elements that end on the parameters' 16-byte boundaries, so
+        // that only a tensor's first and last chunk have elements outside a whole vector
         std::vector<UpdateChunk> uc;
         ctx->tensor_chunk_base.assign((size_t)T + 1, 0);
         for (int t = 0; t < T; ++t) {
             ctx->tensor_chunk_base[(size_t)t] = (int32_t)uc.size();
-            for (int64_t b = 0; b < numel[t]; b += ctx->update_chunk) {
-                int64_t n = std::min<int64_t>(ctx->update_chunk, numel[t] - b);
-                uc.push_back({b, t, (int32_t)n});
+            const int64_t past = (int64_t)((reinterpret_cast<uintptr_t>(ts[(size_t)t].sync) >> 2) & 3u);  // elements past such a boundary
+            for (int64_t b = 0, e; b < numel[t]; b = e) {
+                e = std::min<int64_t>(numel[t], (b + past) / ctx->update_chunk * ctx->update_chunk + ctx->update_chunk - past);
+                uc.push_back({b, t, (int32_t)(e - b)});
             }
         }
         if (uc.size() > (size_t)0x7fffffff) {

@@ -50,6 +50,42 @@ __device__ __forceinline__ void st(T *p, T v) {
         *p = v;
 }
 
+// Groups of four elements that start at any element: gfx950 takes 128- and 64-bit global accesses at any address, so a
+// stream whose start is not a multiple of its vector needs no scalar loop.  A wavefront's 1 KiB then touches one cache
+// line more than an aligned one.
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
+typedef u16x4 u16x4_any __attribute__((aligned(2)));
+
+// (the alignment belongs to the typedef and would be lost in a template argument: no ld<> / st<> here)
+template <bool NT>
+__device__ __forceinline__ f32x4 ld4(const float *p) {
+    const f32x4_any *q = reinterpret_cast<const f32x4_any *>(p);
+    if constexpr (NT) return __builtin_nontemporal_load(q);
+    return *q;
+}
+template <bool NT>
+__device__ __forceinline__ u16x4 ld4(const unsigned short *p) {
+    const u16x4_any *q = reinterpret_cast<const u16x4_any *>(p);
+    if constexpr (NT) return __builtin_nontemporal_load(q);
+    return *q;
+}
+template <bool NT>
+__device__ __forceinline__ void st4(float *p, f32x4 v) {
+    f32x4_any *q = reinterpret_cast<f32x4_any *>(p);
+    if constexpr (NT)
+        __builtin_nontemporal_store(v, q);
+    else
+        *q = v;
+}
+template <bool NT>
+__device__ __forceinline__ void st4(unsigned short *p, u16x4 v) {
+    u16x4_any *q = reinterpret_cast<u16x4_any *>(p);
+    if constexpr (NT)
+        __builtin_nontemporal_store(v, q);
+    else
+        *q = v;
+}
+
 // fp32 -> bf16, round to nearest, ties to even (add 0x7fff plus the lowest kept bit, then truncate); NaN -> quiet NaN.
 __device__ __forceinline__ unsigned short bf16_rne(float f) {
     unsigned int u = __float_as_uint(f);
@@ -95,11 +131,13 @@ template <bool W16>
 struct WireVec;
 template <>
 struct WireVec<false> {
+    typedef float elem;
     typedef f32x4 type;
     static __device__ __forceinline__ f32x4 widen(f32x4 v) { return v; }
 };
 template <>
 struct WireVec<true> {
+    typedef unsigned short elem;
     typedef u16x4 type;
     static __device__ __forceinline__ f32x4 widen(u16x4 v) { return bf16_widen4(v); }
 };
@@ -237,27 +275,9 @@ __device__ __forceinline__ void update_chunk_body(const TensorDesc &td, const Up
         if constexpr (MODEL) mdl[i] = bf16_rne(pi);
     };
 
-    // 128-bit path needs every stream to reach its vector alignment after the same head
+    // the parameters' accesses are aligned; a stream that lies differently against its own vectors takes unaligned ones
     const int h = head_to_16B(p, n);
-    bool vec_ok = (reinterpret_cast<uintptr_t>(s0 + h) & 15u) == 0;
-    if constexpr (ADAM) vec_ok = vec_ok && (reinterpret_cast<uintptr_t>(s1 + h) & 15u) == 0;
-    vec_ok = vec_ok && (reinterpret_cast<uintptr_t>(g + h) & (sizeof(gvec) - 1)) == 0;
-    if constexpr (MODEL) vec_ok = vec_ok && (reinterpret_cast<uintptr_t>(mdl + h) & 7u) == 0;
-    if (!vec_ok) {
-        for (int i = tid; i < n; i += kThreads) one(i);
-        return;
-    }
-
-    if (tid < h) one(tid);
     const int nv = (n - h) >> 2;
-    const int tail0 = h + 4 * nv;
-    if (tid < n - tail0) one(tail0 + tid);
-
-    f32x4 *p4 = reinterpret_cast<f32x4 *>(p + h);
-    f32x4 *a4 = reinterpret_cast<f32x4 *>(s0 + h);
-    f32x4 *b4 = reinterpret_cast<f32x4 *>(s1 + h);
-    const gvec *g4 = reinterpret_cast<const gvec *>(g + h);
-    u16x4 *m4 = reinterpret_cast<u16x4 *>(mdl + h);
 
     auto compute_store = [&](int v, gvec gv, f32x4 pv, f32x4 av, f32x4 bv) {
         const f32x4 gw = G::widen(gv);
@@ -273,34 +293,37 @@ __device__ __forceinline__ void update_chunk_body(const TensorDesc &td, const Up
                 sgdm_one(G4[j], P4[j], A4[j], s);
         }
         const f32x4 pn{P4[0], P4[1], P4[2], P4[3]};
-        st<NT>(p4 + v, pn);
-        st<NT>(a4 + v, f32x4{A4[0], A4[1], A4[2], A4[3]});
-        if constexpr (ADAM) st<NT>(b4 + v, f32x4{B4[0], B4[1], B4[2], B4[3]});
-        if constexpr (MODEL) st<NT>(m4 + v, bf16_rne4(pn));
+        st4<NT>(p + h + 4 * v, pn);
+        st4<NT>(s0 + h + 4 * v, f32x4{A4[0], A4[1], A4[2], A4[3]});
+        if constexpr (ADAM) st4<NT>(s1 + h + 4 * v, f32x4{B4[0], B4[1], B4[2], B4[3]});
+        if constexpr (MODEL) st4<NT>(mdl + h + 4 * v, bf16_rne4(pn));
     };
 
     int v = tid;
     for (; v + kThreads < nv; v += 2 * kThreads) {
-        const int w = v + kThreads;
-        gvec g0 = ld<NT>(g4 + v), g1 = ld<NT>(g4 + w);
-        f32x4 p0 = ld<NT>(p4 + v), p1 = ld<NT>(p4 + w);
-        f32x4 a0 = ld<NT>(a4 + v), a1 = ld<NT>(a4 + w);
+        const int i = h + 4 * v, j = i + 4 * kThreads;
+        const gvec g0 = ld4<NT>(g + i), g1 = ld4<NT>(g + j);
+        const f32x4 p0 = ld4<NT>(p + i), p1 = ld4<NT>(p + j);
+        const f32x4 a0 = ld4<NT>(s0 + i), a1 = ld4<NT>(s0 + j);
         f32x4 b0{}, b1{};
         if constexpr (ADAM) {
-            b0 = ld<NT>(b4 + v);
-            b1 = ld<NT>(b4 + w);
+            b0 = ld4<NT>(s1 + i);
+            b1 = ld4<NT>(s1 + j);
         }
         compute_store(v, g0, p0, a0, b0);
-        compute_store(w, g1, p1, a1, b1);
+        compute_store(v + kThreads, g1, p1, a1, b1);
     }
     for (; v < nv; v += kThreads) {
-        gvec g0 = ld<NT>(g4 + v);
-        f32x4 p0 = ld<NT>(p4 + v);
-        f32x4 a0 = ld<NT>(a4 + v);
+        const int i = h + 4 * v;
+        const gvec g0 = ld4<NT>(g + i);
+        const f32x4 p0 = ld4<NT>(p + i);
+        const f32x4 a0 = ld4<NT>(s0 + i);
         f32x4 b0{};
-        if constexpr (ADAM) b0 = ld<NT>(b4 + v);
+        if constexpr (ADAM) b0 = ld4<NT>(s1 + i);
         compute_store(v, g0, p0, a0, b0);
     }
+    // head and tail together, behind the vectors: only a tensor's first and last chunk have any
+    if (tid < n - 4 * nv) one(tid < h ? tid : 4 * nv + tid);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -322,12 +345,12 @@ struct DenseArgs {
 // fused synchronisation + update
 // ---------------------------------------------------------------------------------------------------------------
 
-// One group of four elements of a scheduled tensor, N known at compile time: pv = the N-1 peers' values (rank order,
-// local rank left out), x = the local parameter on entry and the value to store on return, av / bv = optimizer state
+// One group of four elements of a scheduled tensor, N known at compile time: raw = the N-1 peers' values as they sit in
+// memory (rank order, local rank left out), x = the local parameter on entry and the value to store on return, av / bv = optimizer state
 // (updated in place).  The local contribution (x, stepped first if UTS, rounded to bf16 if W16) is put at position
 // lr with register selects (lr is wave-uniform); rank-order fp32 sum, one multiply by 1/N; statistics in fp64.
 template <bool ADAM, bool GBF16, int NREP, bool STATS, bool W16, bool UTS>
-__device__ __forceinline__ void fused_math4(const f32x4 (&pv)[NREP - 1], typename GradVec<GBF16>::vec gv, f32x4 &x, f32x4 &av, f32x4 &bv,
+__device__ __forceinline__ void fused_math4(const typename WireVec<W16>::type (&raw)[NREP - 1], typename GradVec<GBF16>::vec gv, f32x4 &x, f32x4 &av, f32x4 &bv,
                                             int lr, float inv_n, const UpdateScalars &s, double &gsum, double &msum) {
     auto step4 = [&](f32x4 &q) {
         const f32x4 gw = GradVec<GBF16>::widen(gv);
@@ -349,7 +372,9 @@ __device__ __forceinline__ void fused_math4(const f32x4 (&pv)[NREP - 1], typenam
     if constexpr (UTS) step4(x);
     f32x4 loc = x;
     if constexpr (W16) loc = bf16_widen4(bf16_rne4(x));
-    f32x4 r[NREP];
+    f32x4 pv[NREP - 1], r[NREP];
+#pragma unroll
+    for (int j = 0; j < NREP - 1; ++j) pv[j] = WireVec<W16>::widen(raw[j]);
 #pragma unroll
     for (int k = 0; k < NREP; ++k) {
         const f32x4 before = pv[k < NREP - 1 ? k : NREP - 2], after = pv[k > 0 ? k - 1 : 0];

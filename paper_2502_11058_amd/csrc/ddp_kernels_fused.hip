@@ -70,7 +70,7 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedArgs a) {
             sgdm_one(gi, x, av, s);
     };
 
-    // one element: scalar head and tail, and chunks whose streams are not mutually aligned
+    // one element: head and tail
     auto one = [&](int i) {
         float pl = p[i], av = s0[i], bv = ADAM ? s1[i] : 0.0f;
         const float gi = G::widen1(g[i]);
@@ -96,126 +96,119 @@ __global__ __launch_bounds__(kThreads) void fused_kernel(const FusedArgs a) {
         if constexpr (MODEL) mdl[i] = bf16_rne(res);
     };
 
+    // The parameters' accesses are aligned; the peers' flat offset, and any stream that lies differently against its own
+    // vectors, take unaligned ones.  Bound by HBM either way: a slot whose flat offsets are odd runs at the rate of an aligned
+    // one (28 M parameters, N = 24, fp32 peers: 583 us with a scalar loop over such chunks, 259 us so, 259 us aligned).
     const int h = head_to_16B(p, n);
-    bool vec_ok = (reinterpret_cast<uintptr_t>(s0 + h) & 15u) == 0 && ((fo + h) & 3) == 0;
-    if constexpr (ADAM) vec_ok = vec_ok && (reinterpret_cast<uintptr_t>(s1 + h) & 15u) == 0;
-    vec_ok = vec_ok && (reinterpret_cast<uintptr_t>(g + h) & (sizeof(gvec) - 1)) == 0;
-    if constexpr (MODEL) vec_ok = vec_ok && (reinterpret_cast<uintptr_t>(mdl + h) & 7u) == 0;
-    if (!vec_ok) {
-        for (int i = tid; i < n; i += kThreads) one(i);
+    const int nv = (n - h) >> 2;
+    typedef typename WireVec<W16>::elem xelem;
+    typedef typename WireVec<W16>::type raw4;
+    auto stats4 = [&](f32x4 m, f32x4 x) {
+        const f32x4 d = m - x;
+        gsum += (double)d.x * (double)d.x;
+        gsum += (double)d.y * (double)d.y;
+        gsum += (double)d.z * (double)d.z;
+        gsum += (double)d.w * (double)d.w;
+    };
+    auto msq4 = [&](f32x4 m) {
+        msum += (double)m.x * (double)m.x;
+        msum += (double)m.y * (double)m.y;
+        msum += (double)m.z * (double)m.z;
+        msum += (double)m.w * (double)m.w;
+    };
+    auto step4 = [&](gvec gv, f32x4 &x, f32x4 &av, f32x4 &bv) {
+        const f32x4 gw = G::widen(gv);
+        float G4[4] = {gw.x, gw.y, gw.z, gw.w};
+        float P4[4] = {x.x, x.y, x.z, x.w};
+        float A4[4] = {av.x, av.y, av.z, av.w};
+        float B4[4] = {bv.x, bv.y, bv.z, bv.w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) step1(G4[j], P4[j], A4[j], B4[j]);
+        x = f32x4{P4[0], P4[1], P4[2], P4[3]};
+        av = f32x4{A4[0], A4[1], A4[2], A4[3]};
+        bv = f32x4{B4[0], B4[1], B4[2], B4[3]};
+    };
+    auto store4 = [&](int v, f32x4 res, f32x4 av, f32x4 bv) {
+        st4<NT>(p + h + 4 * v, res);
+        st4<NT>(s0 + h + 4 * v, av);
+        if constexpr (ADAM) st4<NT>(s1 + h + 4 * v, bv);
+        if constexpr (MODEL) st4<NT>(mdl + h + 4 * v, bf16_rne4(res));
+    };
+    if constexpr (NREP > 1) {
+        // The local contribution may be computed (updated and / or rounded) and a branch per replica would
+        // serialise the loads: load the N-1 peers unconditionally, all in flight before the first use.
+        for (int v = tid; v < nv; v += kThreads) {
+            const int i = h + 4 * v;
+            raw4 pv[NREP - 1];
+#pragma unroll
+            for (int j = 0; j < NREP - 1; ++j) pv[j] = ld4<NT>(reinterpret_cast<const xelem *>(a.x[j + (j >= lr ? 1 : 0)]) + fo + i);
+            f32x4 pl = ld4<NT>(p + i);
+            const gvec gv = ld4<NT>(g + i);
+            f32x4 av = ld4<NT>(s0 + i);
+            f32x4 bv{};
+            if constexpr (ADAM) bv = ld4<NT>(s1 + i);
+            fused_math4<ADAM, GBF16, NREP, STATS, W16, UTS>(pv, gv, pl, av, bv, lr, inv_n, s, gsum, msum);
+            store4(v, pl, av, bv);
+        }
     } else {
-        if (tid < h) one(tid);
-        const int nv = (n - h) >> 2;
-        const int tail0 = h + 4 * nv;
-        if (tid < n - tail0) one(tail0 + tid);
-        f32x4 *p4 = reinterpret_cast<f32x4 *>(p + h);
-        f32x4 *a4 = reinterpret_cast<f32x4 *>(s0 + h);
-        f32x4 *b4 = reinterpret_cast<f32x4 *>(s1 + h);
-        const gvec *g4 = reinterpret_cast<const gvec *>(g + h);
-        u16x4 *m4 = reinterpret_cast<u16x4 *>(mdl + h);
-        const int64_t vfo = (fo + h) >> 2;  // peers' index of the body's first group of four
-        auto stats4 = [&](f32x4 m, f32x4 x) {
-            const f32x4 d = m - x;
-            gsum += (double)d.x * (double)d.x;
-            gsum += (double)d.y * (double)d.y;
-            gsum += (double)d.z * (double)d.z;
-            gsum += (double)d.w * (double)d.w;
-        };
-        auto msq4 = [&](f32x4 m) {
-            msum += (double)m.x * (double)m.x;
-            msum += (double)m.y * (double)m.y;
-            msum += (double)m.z * (double)m.z;
-            msum += (double)m.w * (double)m.w;
-        };
-        auto step4 = [&](gvec gv, f32x4 &x, f32x4 &av, f32x4 &bv) {
-            const f32x4 gw = G::widen(gv);
-            float G4[4] = {gw.x, gw.y, gw.z, gw.w};
-            float P4[4] = {x.x, x.y, x.z, x.w};
-            float A4[4] = {av.x, av.y, av.z, av.w};
-            float B4[4] = {bv.x, bv.y, bv.z, bv.w};
+        // run-time replica count; with statistics the terms beyond the first kRegReps are parked in LDS (see
+        // stage_threads) so that the peers are fetched once; only the first `vt` threads take part (all of them
+        // up to 32 replicas)
+        extern __shared__ __align__(16) unsigned char dyn_lds[];
+        f32x4 *stage = reinterpret_cast<f32x4 *>(dyn_lds);
+        const int vt = STATS ? a.stage_threads : kThreads;
+        for (int v = tid; v < nv && tid < vt; v += vt) {
+            const int i = h + 4 * v;
+            f32x4 pl = ld4<NT>(p + i);
+            const gvec gv = ld4<NT>(g + i);
+            f32x4 av = ld4<NT>(s0 + i);
+            f32x4 bv{};
+            if constexpr (ADAM) bv = ld4<NT>(s1 + i);
+            if constexpr (UTS) step4(gv, pl, av, bv);
+            f32x4 loc = pl;
+            if constexpr (W16) loc = bf16_widen4(bf16_rne4(pl));
+            auto term = [&](int k) -> f32x4 { return k == lr ? loc : WireVec<W16>::widen(ld4<NT>(reinterpret_cast<const xelem *>(a.x[k]) + fo + i)); };
+            // the first kRegReps terms of the rank-order sum stay in registers, the rest are parked in LDS
+            f32x4 r[kRegReps];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) step1(G4[j], P4[j], A4[j], B4[j]);
-            x = f32x4{P4[0], P4[1], P4[2], P4[3]};
-            av = f32x4{A4[0], A4[1], A4[2], A4[3]};
-            bv = f32x4{B4[0], B4[1], B4[2], B4[3]};
-        };
-        auto store4 = [&](int v, f32x4 res, f32x4 av, f32x4 bv) {
-            st<NT>(p4 + v, res);
-            st<NT>(a4 + v, av);
-            if constexpr (ADAM) st<NT>(b4 + v, bv);
-            if constexpr (MODEL) st<NT>(m4 + v, bf16_rne4(res));
-        };
-        if constexpr (NREP > 1) {
-            // The local contribution may be computed (updated and / or rounded) and a branch per replica would
-            // serialise the loads: load the N-1 peers unconditionally, all in flight before the first use.
-            for (int v = tid; v < nv; v += kThreads) {
-                f32x4 pv[NREP - 1];
+            for (int k = 0; k < kRegReps; ++k)
+                if (k < nrep) r[k] = term(k);
+            f32x4 acc = r[0];
 #pragma unroll
-                for (int j = 0; j < NREP - 1; ++j) pv[j] = wire4<W16, NT>(a.x[j + (j >= lr ? 1 : 0)], vfo + v);
-                f32x4 pl = ld<NT>(p4 + v);
-                const gvec gv = ld<NT>(g4 + v);
-                f32x4 av = ld<NT>(a4 + v);
-                f32x4 bv{};
-                if constexpr (ADAM) bv = ld<NT>(b4 + v);
-                fused_math4<ADAM, GBF16, NREP, STATS, W16, UTS>(pv, gv, pl, av, bv, lr, inv_n, s, gsum, msum);
-                store4(v, pl, av, bv);
+            for (int k = 1; k < kRegReps; ++k)
+                if (k < nrep) acc = acc + r[k];
+            for (int k0 = kRegReps; k0 < nrep; k0 += 8) {  // eight more peers in flight, then park and add them in rank order
+                f32x4 x[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (k0 + j < nrep) x[j] = term(k0 + j);
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (k0 + j < nrep) {
+                        if constexpr (STATS) stage[(k0 + j - kRegReps) * vt + tid] = x[j];
+                        acc = acc + x[j];
+                    }
             }
-        } else {
-            // run-time replica count; with statistics the terms beyond the first kRegReps are parked in LDS (see
-            // stage_threads) so that the peers are fetched once; only the first `vt` threads take part (all of them
-            // up to 32 replicas)
-            extern __shared__ __align__(16) unsigned char dyn_lds[];
-            f32x4 *stage = reinterpret_cast<f32x4 *>(dyn_lds);
-            const int vt = STATS ? a.stage_threads : kThreads;
-            for (int v = tid; v < nv && tid < vt; v += vt) {
-                f32x4 pl = ld<NT>(p4 + v);
-                const gvec gv = ld<NT>(g4 + v);
-                f32x4 av = ld<NT>(a4 + v);
-                f32x4 bv{};
-                if constexpr (ADAM) bv = ld<NT>(b4 + v);
-                if constexpr (UTS) step4(gv, pl, av, bv);
-                f32x4 loc = pl;
-                if constexpr (W16) loc = bf16_widen4(bf16_rne4(pl));
-                auto term = [&](int k) -> f32x4 { return k == lr ? loc : wire4<W16, NT>(a.x[k], vfo + v); };
-                // the first kRegReps terms of the rank-order sum stay in registers, the rest are parked in LDS
-                f32x4 r[kRegReps];
+            f32x4 m = acc * inv_n;
+            if constexpr (STATS) {
 #pragma unroll
                 for (int k = 0; k < kRegReps; ++k)
-                    if (k < nrep) r[k] = term(k);
-                f32x4 acc = r[0];
-#pragma unroll
-                for (int k = 1; k < kRegReps; ++k)
-                    if (k < nrep) acc = acc + r[k];
-                for (int k0 = kRegReps; k0 < nrep; k0 += 8) {  // eight more peers in flight, then park and add them in rank order
-                    f32x4 x[8];
-#pragma unroll
-                    for (int j = 0; j < 8; ++j)
-                        if (k0 + j < nrep) x[j] = term(k0 + j);
-#pragma unroll
-                    for (int j = 0; j < 8; ++j)
-                        if (k0 + j < nrep) {
-                            if constexpr (STATS) stage[(k0 + j - kRegReps) * vt + tid] = x[j];
-                            acc = acc + x[j];
-                        }
-                }
-                f32x4 m = acc * inv_n;
-                if constexpr (STATS) {
-#pragma unroll
-                    for (int k = 0; k < kRegReps; ++k)
-                        if (k < nrep) stats4(m, r[k]);
-                    for (int k = kRegReps; k < nrep; ++k) stats4(m, stage[(k - kRegReps) * vt + tid]);
-                    msq4(m);
-                }
-                if constexpr (!UTS) step4(gv, m, av, bv);
-                store4(v, m, av, bv);
+                    if (k < nrep) stats4(m, r[k]);
+                for (int k = kRegReps; k < nrep; ++k) stats4(m, stage[(k - kRegReps) * vt + tid]);
+                msq4(m);
             }
+            if constexpr (!UTS) step4(gv, m, av, bv);
+            store4(v, m, av, bv);
         }
     }
+    // head and tail together, behind the vectors: only a tensor's first and last chunk have any
+    if (tid < n - 4 * nv) one(tid < h ? tid : 4 * nv + tid);
     if constexpr (STATS) {
         const double gt = block_sum(gsum, lds[0]);
         const double mt = block_sum(msum, lds[1]);
         if (tid == 0) {
-            const int64_t pi = (int64_t)a.tensor_chunk_base[ch.tensor] + ch.begin / a.chunk_elems;
+            // chunks end at the parameters' 16-byte boundaries: chunk c of a tensor begins 0..3 elements before c * chunk_elems
+            const int64_t pi = (int64_t)a.tensor_chunk_base[ch.tensor] + (ch.begin + 3) / a.chunk_elems;
             a.partials[2 * pi] = gt;
             a.partials[2 * pi + 1] = mt;
         }

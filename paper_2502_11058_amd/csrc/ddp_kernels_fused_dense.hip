@@ -45,14 +45,9 @@ __global__ __launch_bounds__(kThreads) void fused_dense_kernel(const FusedDenseA
         rx[j] = make_rsrc(reinterpret_cast<const char *>(a.x[j + (j >= lr ? 1 : 0)]) + (a.fo0 + b) * (XB / 4), nv * XB);
     double gsum = 0.0, msum = 0.0;
     for (int v = tid; v < nv; v += kThreads) {
-        f32x4 pv[NREP - 1];
+        typename WireVec<W16>::type pv[NREP - 1];
 #pragma unroll
-        for (int j = 0; j < NREP - 1; ++j) {
-            if constexpr (W16)
-                pv[j] = bf16_widen4(bld<AUX, u16x4>(rx[j], v * XB));
-            else
-                pv[j] = bld<AUX, f32x4>(rx[j], v * XB);
-        }
+        for (int j = 0; j < NREP - 1; ++j) pv[j] = bld<AUX, typename WireVec<W16>::type>(rx[j], v * XB);
         f32x4 x = bld<AUX, f32x4>(rp, v * 16);
         const gvec gv = bld<AUX, gvec>(rg, v * (int)sizeof(gvec));
         f32x4 av = bld<AUX, f32x4>(ra, v * 16);
