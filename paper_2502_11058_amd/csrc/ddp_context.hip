@@ -738,7 +738,7 @@ static int fused_dense(ddp_ctx *ctx, const char *who, const SlotTables *st, cons
         const int i = pos[(size_t)l];
         FusedDenseLaunch f{};
         dense_range(ctx, l, 1, f.d);
-        for (int k = 0; k < N; ++k) f.x[k] = x[k];
+        for (int k = 0; k + 1 < N; ++k) f.x[k] = x[k];
         f.wire16 = wire16;
         f.update_first = update_first;
         f.n_replicas = N;
@@ -789,12 +789,9 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     int64_t c0 = 0, c1 = ctx->n_update;
     if (!whole && (rc = layer_chunk_range(ctx, who, first, count, &c0, &c1)) != DDP_OK) return rc;
     FusedLaunch f{};
-    int p = 0;
-    for (int k = 0; k < N; ++k) {
-        if (k == local_rank) continue;
-        const void *q = peers[p++];
-        if (st->numel > 0 && (rc = check_flat(ctx, q, who, "a peer buffer")) != DDP_OK) return rc;
-        f.x[k] = q;
+    for (int k = 0; k + 1 < N; ++k) {
+        if (st->numel > 0 && (rc = check_flat(ctx, peers[k], who, "a peer buffer")) != DDP_OK) return rc;
+        f.x[k] = peers[k];
     }
     if (c1 == c0) return DDP_OK;
     {

@@ -33,6 +33,8 @@ constexpr int kWave = 64;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 template <bool NT, class T>
 __device__ __forceinline__ T ld(const T *p) {
@@ -138,16 +140,27 @@ struct WireVec<false> {
 template <>
 struct WireVec<true> {
     typedef unsigned short elem;
-    typedef u16x4 type;
-    static __device__ __forceinline__ f32x4 widen(u16x4 v) { return bf16_widen4(v); }
+    typedef u32x2 type;  // whole registers: 16-bit lanes kept over the loads of a group make the compiler copy them about
+    static __device__ __forceinline__ f32x4 widen(u32x2 v) {
+        return f32x4{__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u)};
+    }
 };
+// The group for its second use: bf16 is widened anew, or the compiler keeps the widened form, twice the registers, from the
+// first use on.
+template <bool W16>
+__device__ __forceinline__ f32x4 widen_again(typename WireVec<W16>::type v) {
+    if constexpr (W16) asm("" : "+v"(v));
+    return WireVec<W16>::widen(v);
+}
+// ... loaded from any element of the replica.
+template <bool W16, bool NT>
+__device__ __forceinline__ typename WireVec<W16>::type wire_raw4(const void *base, int64_t i) {
+    return __builtin_bit_cast(typename WireVec<W16>::type, ld4<NT>(reinterpret_cast<const typename WireVec<W16>::elem *>(base) + i));
+}
 
 // Buffer (MUBUF) accesses: a per-workgroup descriptor (base in SGPRs, extent = the workgroup's part of the stream)
 // plus a 32-bit byte offset per lane.  Accesses past the extent read zero / are dropped by the hardware.
 // AUX: cache policy bits of the instruction (2 = nt, the streaming hint; 0 = default).
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *base, int bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, bytes, 0x00020000);  // raw dword format
 }
@@ -345,13 +358,30 @@ struct DenseArgs {
 // fused synchronisation + update
 // ---------------------------------------------------------------------------------------------------------------
 
-// One group of four elements of a scheduled tensor, N known at compile time: raw = the N-1 peers' values as they sit in
-// memory (rank order, local rank left out), x = the local parameter on entry and the value to store on return, av / bv = optimizer state
-// (updated in place).  The local contribution (x, stepped first if UTS, rounded to bf16 if W16) is put at position
-// lr with register selects (lr is wave-uniform); rank-order fp32 sum, one multiply by 1/N; statistics in fp64.
-template <bool ADAM, bool GBF16, int NREP, bool STATS, bool W16, bool UTS>
-__device__ __forceinline__ void fused_math4(const typename WireVec<W16>::type (&raw)[NREP - 1], typename GradVec<GBF16>::vec gv, f32x4 &x, f32x4 &av, f32x4 &bv,
-                                            int lr, float inv_n, const UpdateScalars &s, double &gsum, double &msum) {
+// Peers that every replica count served by a fused kernel has: all of them when the kernel is compiled for one count
+// (EXACT), half the registers' worth when it serves the counts above NREP / 2 (and none for the smallest such kernel).
+template <int NREP, bool EXACT>
+constexpr int kPeersAlways = EXACT ? NREP - 1 : (NREP > 4 ? NREP / 2 : 0);
+
+// A wave-uniform value that the compiler takes for a new one: conditions on it are formed where they are used, instead of
+// being kept for a whole loop in more scalar registers than there are.
+__device__ __forceinline__ int fresh(int v) {
+    asm volatile("" : "+s"(v));
+    return v;
+}
+
+// One group of four elements of a scheduled tensor: raw = the peers' values as they sit in memory (rank order, local rank
+// left out), x = the local parameter on entry and the value to store on return, av / bv = optimizer state (updated in
+// place).  NREP is the replica count (EXACT) or the largest count that the kernel's registers are laid out for, n the count
+// itself.  Rank-order fp32 sum with the local contribution (x, stepped first if UTS, rounded to bf16 if W16) before the peer
+// at position lr; the sum starts from -0, which leaves the first term as it is, whatever it is.  One multiply by 1/N;
+// statistics in fp64.
+template <bool ADAM, bool GBF16, int NREP, bool EXACT, bool STATS, bool W16, bool UTS>
+__device__ __forceinline__ void fused_math4(const typename WireVec<W16>::type (&raw)[NREP - 1], typename GradVec<GBF16>::vec gv, f32x4 &x,
+                                            f32x4 &av, f32x4 &bv, int n_, int lr_, float inv_n, const UpdateScalars &s, double &gsum,
+                                            double &msum) {
+    constexpr int ALWAYS = kPeersAlways<NREP, EXACT>;
+    const int n = fresh(n_), lr = fresh(lr_);
     auto step4 = [&](f32x4 &q) {
         const f32x4 gw = GradVec<GBF16>::widen(gv);
         float G4[4] = {gw.x, gw.y, gw.z, gw.w};
@@ -372,31 +402,30 @@ __device__ __forceinline__ void fused_math4(const typename WireVec<W16>::type (&
     if constexpr (UTS) step4(x);
     f32x4 loc = x;
     if constexpr (W16) loc = bf16_widen4(bf16_rne4(x));
-    f32x4 pv[NREP - 1], r[NREP];
+    typedef WireVec<W16> V;
+    f32x4 acc{-0.0f, -0.0f, -0.0f, -0.0f};
 #pragma unroll
-    for (int j = 0; j < NREP - 1; ++j) pv[j] = WireVec<W16>::widen(raw[j]);
-#pragma unroll
-    for (int k = 0; k < NREP; ++k) {
-        const f32x4 before = pv[k < NREP - 1 ? k : NREP - 2], after = pv[k > 0 ? k - 1 : 0];
-        r[k] = k == lr ? loc : (k < lr ? before : after);
+    for (int j = 0; j < NREP - 1; ++j) {
+        if (j == lr) acc = acc + loc;
+        if (j < ALWAYS || j < n - 1) acc = acc + V::widen(raw[j]);
     }
-    f32x4 acc = r[0];
-#pragma unroll
-    for (int k = 1; k < NREP; ++k) acc = acc + r[k];
+    if constexpr (EXACT)  // otherwise n < NREP and the loop has come past the last position
+        if (lr == NREP - 1) acc = acc + loc;
     f32x4 m = acc * inv_n;
     if constexpr (STATS) {
+        auto add_sq = [](double &sum, f32x4 d) {
+            sum += (double)d.x * (double)d.x;
+            sum += (double)d.y * (double)d.y;
+            sum += (double)d.z * (double)d.z;
+            sum += (double)d.w * (double)d.w;
+        };
 #pragma unroll
-        for (int k = 0; k < NREP; ++k) {
-            const f32x4 d = m - r[k];
-            gsum += (double)d.x * (double)d.x;
-            gsum += (double)d.y * (double)d.y;
-            gsum += (double)d.z * (double)d.z;
-            gsum += (double)d.w * (double)d.w;
+        for (int j = 0; j < NREP - 1; ++j) {
+            if (j < ALWAYS || j < n - 1) add_sq(gsum, m - widen_again<W16>(raw[j]));
+            if (NREP > 16 && j % 8 == 7) __builtin_amdgcn_sched_barrier(0);  // few differences in flight: the peers fill the registers
         }
-        msum += (double)m.x * (double)m.x;
-        msum += (double)m.y * (double)m.y;
-        msum += (double)m.z * (double)m.z;
-        msum += (double)m.w * (double)m.w;
+        add_sq(gsum, m - loc);
+        add_sq(msum, m);
     }
     if constexpr (!UTS) step4(m);
     x = m;

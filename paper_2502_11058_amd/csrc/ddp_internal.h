@@ -128,7 +128,7 @@ int launch_stats(const double *partials, double *slice_sums, const int32_t *rang
 int launch_pack16(const TensorDesc *tensors, const CopyChunk *chunks, int64_t n_chunks, uint16_t *flat16, bool nontemporal, int lds_pad,
                   void *stream);
 struct FusedLaunch {
-    const void *x[DDP_MAX_REPLICAS];  // peers in rank order (entry local_rank unused); fp32, or bf16 when wire16
+    const void *x[DDP_MAX_REPLICAS - 1];  // the N-1 peers in rank order; fp32, or bf16 when wire16
     bool wire16;
     bool update_first;  // Eq. (5) as printed: the local value takes the optimizer step before it is averaged
     int n_replicas, local_rank;
@@ -167,7 +167,7 @@ int launch_update_dense(int kind, int grad_dtype, bool with_model, const DenseLa
 // (nullptr: no statistics).  Replica counts fused_dense_supports() accepts only.
 struct FusedDenseLaunch {
     DenseLaunch d;
-    const void *x[DDP_MAX_REPLICAS];
+    const void *x[DDP_MAX_REPLICAS - 1];
     bool wire16, update_first;
     int n_replicas, local_rank;
     float inv_n;

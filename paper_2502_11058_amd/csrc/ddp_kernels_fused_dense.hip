@@ -6,7 +6,7 @@ namespace {
 
 struct FusedDenseArgs {
     DenseArgs d;                       // the scheduled layer's local streams; d.n is a multiple of 4
-    const void *x[DDP_MAX_REPLICAS];   // peers' whole flat buffers in rank order; entry local_rank is unused
+    const void *x[DDP_MAX_REPLICAS - 1];  // the N-1 peers' whole flat buffers in rank order
     int64_t fo0;                       // flat index of the layer's first element (a multiple of 4)
     double *partials;                  // workgroup b writes its pair at partials[2 * (pbase + b)]
     int64_t pbase;
@@ -42,7 +42,7 @@ __global__ __launch_bounds__(kThreads) void fused_dense_kernel(const FusedDenseA
     __amdgpu_buffer_rsrc_t rx[NREP - 1];
 #pragma unroll
     for (int j = 0; j < NREP - 1; ++j)
-        rx[j] = make_rsrc(reinterpret_cast<const char *>(a.x[j + (j >= lr ? 1 : 0)]) + (a.fo0 + b) * (XB / 4), nv * XB);
+        rx[j] = make_rsrc(reinterpret_cast<const char *>(a.x[j]) + (a.fo0 + b) * (XB / 4), nv * XB);
     double gsum = 0.0, msum = 0.0;
     for (int v = tid; v < nv; v += kThreads) {
         typename WireVec<W16>::type pv[NREP - 1];
@@ -53,7 +53,7 @@ __global__ __launch_bounds__(kThreads) void fused_dense_kernel(const FusedDenseA
         f32x4 av = bld<AUX, f32x4>(ra, v * 16);
         f32x4 bv{};
         if constexpr (ADAM) bv = bld<AUX, f32x4>(rb, v * 16);
-        fused_math4<ADAM, GBF16, NREP, STATS, W16, UTS>(pv, gv, x, av, bv, lr, a.inv_n, a.d.s, gsum, msum);
+        fused_math4<ADAM, GBF16, NREP, true, STATS, W16, UTS>(pv, gv, x, av, bv, NREP, lr, a.inv_n, a.d.s, gsum, msum);
         bst<AUX>(rp, v * 16, x);
         bst<AUX>(ra, v * 16, av);
         if constexpr (ADAM) bst<AUX>(rb, v * 16, bv);
@@ -99,7 +99,7 @@ int launch_fused_dense(const FusedDenseLaunch &f, void *stream) {
     fa.d.n = f.d.n;
     fa.d.chunk = f.d.chunk;
     fa.d.s = f.s;
-    for (int k = 0; k < f.n_replicas; ++k) fa.x[k] = f.x[k];
+    for (int k = 0; k + 1 < f.n_replicas; ++k) fa.x[k] = f.x[k];
     fa.fo0 = f.fo0;
     fa.partials = f.partials;
     fa.pbase = f.pbase;

@@ -1,4 +1,6 @@
 // partial average (Eq. (5), second case) and the per-layer statistics (Sec. 3.4).
+#include <type_traits>
+
 #include "ddp_device.h"
 
 namespace ddp {
@@ -14,16 +16,19 @@ struct MeanArgs {
     int stage_threads;  // run-time replica count with statistics: threads that take part in the vector loop
 };
 
-// Eq. (5), second case.  NREP > 0: replica count known at compile time (pointer loads and the sum fully
-// unrolled); NREP == 0: run-time count.  The sum runs left to right over replicas in rank order, in fp32, then
-// one multiply by 1/N.  STATS adds, per chunk, sum_k sum_i (out_i - x_k,i)^2 and sum_i out_i^2 in fp64.
-template <int NREP, bool STATS, bool NT, bool W16 = false>
+// Eq. (5), second case.  NREP > 0: the replica count (EXACT), or the largest count that the kernel's registers are laid out
+// for, serving the counts above half of it (loads and sum fully unrolled, wave-uniform conditions on the upper half);
+// NREP == 0: run-time count.  The sum runs left to right over replicas in rank order, in fp32, then one multiply by 1/N.
+// STATS adds, per chunk, sum_k sum_i (out_i - x_k,i)^2 and sum_i out_i^2 in fp64.
+// Bound by HBM; with bf16 replicas also by how many wavefronts the registers let in, so a group is kept as it was loaded and
+// widened at each use (N = 32: 241 -> 82 VGPRs).
+template <int NREP, bool EXACT, bool STATS, bool NT, bool W16>
 __global__ __launch_bounds__(kThreads) void mean_kernel(const MeanArgs a) {
     __shared__ double lds[2][kThreads / kWave];
     const MeanChunk ch = a.chunks[blockIdx.x];
     const int n = ch.count;
     const int tid = threadIdx.x;
-    const int nrep = NREP > 0 ? NREP : a.n;
+    const int nrep = EXACT ? NREP : a.n;
     const float inv_n = a.inv_n;
     const int64_t base = ch.begin;
     double gsum = 0.0, msum = 0.0;
@@ -72,45 +77,39 @@ __global__ __launch_bounds__(kThreads) void mean_kernel(const MeanArgs a) {
         // vector, so that the loads still fit the register file
         constexpr int B = NREP > 16 ? 1 : 2;
         // a replica's vector as it sits in memory: kept in that form (bf16: half the registers) until it is used
-        typedef typename WireVec<W16>::type raw4;
-        auto rep4 = [&](int k, int idx) -> raw4 { return ld<NT>(reinterpret_cast<const raw4 *>(a.x[k]) + vbase + idx); };
-        auto put4 = [&](int idx, f32x4 m) { st<NT>(o4 + idx, m); };
-        int v = tid;
-        for (; v + (B - 1) * kThreads < nv; v += B * kThreads) {
-            raw4 x[B][NREP];
+        typedef WireVec<W16> V;
+        typedef typename V::type raw4;
+        auto groups = [&](int v, auto count) {
+            constexpr int C = decltype(count)::value;
+            raw4 x[C][NREP];
 #pragma unroll
-            for (int b = 0; b < B; ++b)
+            for (int b = 0; b < C; ++b)
 #pragma unroll
-                for (int k = 0; k < NREP; ++k) x[b][k] = rep4(k, v + b * kThreads);
+                for (int k = 0; k < NREP; ++k) {
+                    x[b][k] = raw4{};
+                    if (EXACT || k <= NREP / 2 || k < nrep) x[b][k] = ld<NT>(reinterpret_cast<const raw4 *>(a.x[k]) + vbase + v + b * kThreads);
+                }
+            const int n = fresh(nrep);
 #pragma unroll
-            for (int b = 0; b < B; ++b) {
-                f32x4 acc = WireVec<W16>::widen(x[b][0]);
+            for (int b = 0; b < C; ++b) {
+                f32x4 acc = V::widen(x[b][0]);
 #pragma unroll
-                for (int k = 1; k < NREP; ++k) acc = acc + WireVec<W16>::widen(x[b][k]);
+                for (int k = 1; k < NREP; ++k)
+                    if (EXACT || k <= NREP / 2 || k < n) acc = acc + V::widen(x[b][k]);
                 const f32x4 m = acc * inv_n;
                 if constexpr (STATS) {
 #pragma unroll
-                    for (int k = 0; k < NREP; ++k) stats4(m, WireVec<W16>::widen(x[b][k]));
+                    for (int k = 0; k < NREP; ++k)
+                        if (EXACT || k <= NREP / 2 || k < n) stats4(m, widen_again<W16>(x[b][k]));
                     msq4(m);
                 }
-                put4(v + b * kThreads, m);
+                st<NT>(o4 + v + b * kThreads, m);
             }
-        }
-        for (; v < nv; v += kThreads) {
-            raw4 x[NREP];
-#pragma unroll
-            for (int k = 0; k < NREP; ++k) x[k] = rep4(k, v);
-            f32x4 acc = WireVec<W16>::widen(x[0]);
-#pragma unroll
-            for (int k = 1; k < NREP; ++k) acc = acc + WireVec<W16>::widen(x[k]);
-            const f32x4 m = acc * inv_n;
-            if constexpr (STATS) {
-#pragma unroll
-                for (int k = 0; k < NREP; ++k) stats4(m, WireVec<W16>::widen(x[k]));
-                msq4(m);
-            }
-            put4(v, m);
-        }
+        };
+        int v = tid;
+        for (; v + (B - 1) * kThreads < nv; v += B * kThreads) groups(v, std::integral_constant<int, B>());
+        if constexpr (B > 1)
+            for (; v < nv; v += kThreads) groups(v, std::integral_constant<int, 1>());
     } else if constexpr (STATS) {
         // Run-time replica count with statistics: the first kRegReps replicas of a vector stay in registers, the rest are
         // parked in LDS (one column per thread), so every replica is fetched from memory once and, up to 32 replicas,
@@ -232,16 +231,16 @@ int mean_lds(const MeanLaunch &a) {
     return a.lds_pad > need ? a.lds_pad : need;
 }
 
-template <int NREP>
-int launch_mean16_n(const MeanArgs &ma, const MeanLaunch &a, void *stream) {
-    if (a.partials) return launch(mean_kernel<NREP, true, true, true>, a.n_chunks, stream, mean_lds<NREP>(a), ma);
-    return launch(mean_kernel<NREP, false, true, true>, a.n_chunks, stream, a.lds_pad, ma);
-}
-
-template <int NREP>
+template <int NREP, bool EXACT>
 int launch_mean_n(const MeanArgs &ma, const MeanLaunch &a, void *stream) {
-    if (a.partials) return a.nontemporal ? launch(mean_kernel<NREP, true, true>, a.n_chunks, stream, mean_lds<NREP>(a), ma) : launch(mean_kernel<NREP, true, false>, a.n_chunks, stream, mean_lds<NREP>(a), ma);
-    return a.nontemporal ? launch(mean_kernel<NREP, false, true>, a.n_chunks, stream, a.lds_pad, ma) : launch(mean_kernel<NREP, false, false>, a.n_chunks, stream, a.lds_pad, ma);
+    if (a.wire16) {
+        if (a.partials) return launch(mean_kernel<NREP, EXACT, true, true, true>, a.n_chunks, stream, mean_lds<NREP>(a), ma);
+        return launch(mean_kernel<NREP, EXACT, false, true, true>, a.n_chunks, stream, a.lds_pad, ma);
+    }
+    if (a.partials) return a.nontemporal ? launch(mean_kernel<NREP, EXACT, true, true, false>, a.n_chunks, stream, mean_lds<NREP>(a), ma)
+                                         : launch(mean_kernel<NREP, EXACT, true, false, false>, a.n_chunks, stream, mean_lds<NREP>(a), ma);
+    return a.nontemporal ? launch(mean_kernel<NREP, EXACT, false, true, false>, a.n_chunks, stream, a.lds_pad, ma)
+                         : launch(mean_kernel<NREP, EXACT, false, false, false>, a.n_chunks, stream, a.lds_pad, ma);
 }
 
 }  // namespace
@@ -273,36 +272,25 @@ int launch_mean(const MeanLaunch &a, void *stream) {
     ma.n = a.n_replicas;
     ma.stage_threads = stage_threads(a.n_replicas > kRegReps ? a.n_replicas - kRegReps : 0);   // the replicas beyond the registers are staged
     int rc;
-    if (a.wire16) {
-        switch (a.n_replicas) {
-            case 2: rc = launch_mean16_n<2>(ma, a, stream); break;
-            case 4: rc = launch_mean16_n<4>(ma, a, stream); break;
-            case 8: rc = launch_mean16_n<8>(ma, a, stream); break;
-            case 16: rc = launch_mean16_n<16>(ma, a, stream); break;
-            case 32: rc = launch_mean16_n<32>(ma, a, stream); break;
-            default: rc = launch_mean16_n<0>(ma, a, stream); break;
-        }
-    } else {
-        switch (a.n_replicas) {
-            case 1: rc = launch_mean_n<1>(ma, a, stream); break;
-            case 2: rc = launch_mean_n<2>(ma, a, stream); break;
-            case 3: rc = launch_mean_n<3>(ma, a, stream); break;
-            case 4: rc = launch_mean_n<4>(ma, a, stream); break;
-            case 5: rc = launch_mean_n<5>(ma, a, stream); break;
-            case 6: rc = launch_mean_n<6>(ma, a, stream); break;
-            case 7: rc = launch_mean_n<7>(ma, a, stream); break;
-            case 8: rc = launch_mean_n<8>(ma, a, stream); break;
-            case 9: rc = launch_mean_n<9>(ma, a, stream); break;
-            case 10: rc = launch_mean_n<10>(ma, a, stream); break;
-            case 11: rc = launch_mean_n<11>(ma, a, stream); break;
-            case 12: rc = launch_mean_n<12>(ma, a, stream); break;
-            case 13: rc = launch_mean_n<13>(ma, a, stream); break;
-            case 14: rc = launch_mean_n<14>(ma, a, stream); break;
-            case 15: rc = launch_mean_n<15>(ma, a, stream); break;
-            case 16: rc = launch_mean_n<16>(ma, a, stream); break;
-            case 32: rc = launch_mean_n<32>(ma, a, stream); break;
-            default: rc = launch_mean_n<0>(ma, a, stream); break;
-        }
+    switch (a.n_replicas) {
+        case 1: rc = launch_mean_n<1, true>(ma, a, stream); break;
+        case 2: rc = launch_mean_n<2, true>(ma, a, stream); break;
+        case 3: rc = launch_mean_n<3, true>(ma, a, stream); break;
+        case 4: rc = launch_mean_n<4, true>(ma, a, stream); break;
+        case 5: rc = launch_mean_n<5, true>(ma, a, stream); break;
+        case 6: rc = launch_mean_n<6, true>(ma, a, stream); break;
+        case 7: rc = launch_mean_n<7, true>(ma, a, stream); break;
+        case 8: rc = launch_mean_n<8, true>(ma, a, stream); break;
+        case 9: rc = launch_mean_n<9, true>(ma, a, stream); break;
+        case 10: rc = launch_mean_n<10, true>(ma, a, stream); break;
+        case 11: rc = launch_mean_n<11, true>(ma, a, stream); break;
+        case 12: rc = launch_mean_n<12, true>(ma, a, stream); break;
+        case 13: rc = launch_mean_n<13, true>(ma, a, stream); break;
+        case 14: rc = launch_mean_n<14, true>(ma, a, stream); break;
+        case 15: rc = launch_mean_n<15, true>(ma, a, stream); break;
+        case 16: rc = launch_mean_n<16, true>(ma, a, stream); break;
+        case 32: rc = launch_mean_n<32, true>(ma, a, stream); break;
+        default: rc = a.n_replicas < 32 ? launch_mean_n<32, false>(ma, a, stream) : launch_mean_n<0, false>(ma, a, stream); break;
     }
     if (rc != 0 || !a.partials) return rc;
     return launch_stats(a.partials, a.slice_sums, a.layer_ranges, a.n_layers, a.n_replicas, a.stats, a.max_partials_per_layer, stream);
