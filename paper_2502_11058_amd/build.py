@@ -15,10 +15,12 @@ CSRC = os.path.join(HERE, "csrc")
 LIB_DIR = os.path.join(HERE, "lib")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(LIB_DIR, "libdreamddp.so")
-# (source, object name, extra flags); the table-driven fused kernel has the most instantiations and is built in two halves
+# (source, object name, extra flags); the fused kernels have the most instantiations and are built in two halves each
 SOURCES = [("ddp_kernels_fused.hip", "ddp_kernels_fused_adamw", ["-DDDP_FUSED_ADAM=1"]),
            ("ddp_kernels_fused.hip", "ddp_kernels_fused_sgdm", ["-DDDP_FUSED_ADAM=0"]),
-           ("ddp_kernels_fused_dense.hip", "ddp_kernels_fused_dense", []), ("ddp_kernels_mean.hip", "ddp_kernels_mean", []),
+           ("ddp_kernels_fused_dense.hip", "ddp_kernels_fused_dense_adamw", ["-DDDP_FUSED_ADAM=1"]),
+           ("ddp_kernels_fused_dense.hip", "ddp_kernels_fused_dense_sgdm", ["-DDDP_FUSED_ADAM=0"]),
+           ("ddp_kernels_mean.hip", "ddp_kernels_mean", []),
            ("ddp_kernels_update.hip", "ddp_kernels_update", []), ("ddp_kernels_copy.hip", "ddp_kernels_copy", []),
            ("ddp_context.hip", "ddp_context", []), ("ddp_noalloc.hip", "ddp_noalloc", []), ("ddp_probe.hip", "ddp_probe", []),
            ("ddp_stream.hip", "ddp_stream", []), ("ddp_schedule.cpp", "ddp_schedule", [])]

@@ -126,6 +126,87 @@ static int residency_pad(const ddp_ctx *c, int wg_per_cu) {
     return pad > 0 ? pad : 0;
 }
 
+// Workgroups of the table-free fused kernel over elements [e0, e1) of the arenas: chunks counted from the multiple of four at
+// or below e0, where every stream is vector-aligned.
+static int64_t dense_workgroups(int64_t e0, int64_t e1, int64_t chunk) { return (e1 - e0 / 4 * 4 + chunk - 1) / chunk; }
+
+// The launches of the fused step over layers [first, first + count) of dense arenas.  A segment is a scheduled layer or a run
+// of unscheduled ones.  Where segments average fewer than 2^25 elements all of them share one launch (one per kMaxSegments),
+// cut into pieces of about the same width: a launch of its own costs a segment some 3 us of ramp (GPT-2 small, AdamW, N = 8,
+// 20 M per segment: 701 us in one launch, 726 in six; 12 layers of 512^2: 25 against 47).  Larger ones get a launch each, the
+// unscheduled ones that of the plain update, whose workgroups start sooner (Llama-2-7B blocks, 380 M per segment: 11.8 ms in
+// one launch, 11.5 in five; about equal at 40 M).
+// (One layer at a time, as backward hooks call it, skips the search: one_layer_pass.)
+static std::vector<DensePass> plan_dense(const ddp_ctx *ctx, const SlotTables &st, int first, int count) {
+    constexpr int kMaxSegments = 20;
+    const int64_t chunk = ctx->update_chunk;
+    auto elem0 = [&](int l) { return ctx->tensor_elem_off[(size_t)ctx->layer_first_tensor[(size_t)l]]; };
+    struct Segment {
+        int64_t begin, end, flat0, pbase, wg;
+    };
+    std::vector<Segment> all;
+    for (int l = first; l < first + count;) {
+        const int i = st.layer_pos[(size_t)l];
+        int m = l + 1;
+        while (i < 0 && m < first + count && st.layer_pos[(size_t)m] < 0) ++m;
+        all.push_back({elem0(l), elem0(m), i < 0 ? -1 : st.layer_begin[(size_t)i], i < 0 ? 0 : st.dense_ranges[2 * (size_t)i],
+                       dense_workgroups(elem0(l), elem0(m), chunk)});
+        l = m;
+    }
+    std::vector<DensePass> passes;
+    if (all.empty()) return passes;
+    const bool apart = (all.back().end - all[0].begin) / (int64_t)all.size() >= (int64_t)1 << 25;
+    for (size_t i = 0; i < all.size();) {
+        const Segment *seg = &all[i];
+        const int n = (int)std::min<size_t>(apart ? 1 : kMaxSegments, all.size() - i);
+        i += (size_t)n;
+        passes.emplace_back();
+        DensePass &p = passes.back();
+        p.width = p.n_pieces = 0;
+        p.begin = seg[0].begin;
+        p.end = seg[n - 1].end;
+        if (n == 1 && seg[0].flat0 < 0 && seg[0].begin % 4 == 0) continue;
+        // the width that leaves the fewest workgroups without work among those that cut some segment evenly; the widest that
+        // 32-bit indexes allow makes at most one piece of every 2^31 elements
+        const int64_t widest = INT32_MAX / chunk - 1;
+        int64_t width = widest, best = INT64_MAX;
+        for (int k = 0; k < n; ++k)
+            for (int64_t parts : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24}) {
+                const int64_t w = (seg[k].wg + parts - 1) / parts;
+                if (w > widest) continue;
+                int64_t rows = 0;
+                for (int j = 0; j < n; ++j) rows += (seg[j].wg + w - 1) / w;
+                if (rows <= kMaxPieces && (rows * w < best || (rows * w == best && w > width))) {
+                    best = rows * w;
+                    width = w;
+                }
+            }
+        p.width = (int)width;
+        for (int k = 0; k < n; ++k)
+            for (int64_t b = 0; b < seg[k].wg; b += width) {
+                const int64_t base = seg[k].begin / 4 * 4, at = b == 0 ? seg[k].begin : base + b * chunk;
+                const int64_t end = std::min(seg[k].end, base + (b + width) * chunk);
+                p.pieces[p.n_pieces++] = {at, seg[k].flat0 < 0 ? -1 : seg[k].flat0 + (at - seg[k].begin), (int32_t)(end - at),
+                                          (int32_t)(seg[k].pbase + b)};
+            }
+    }
+    return passes;
+}
+
+static bool one_layer_pass(const ddp_ctx *ctx, const SlotTables &st, int l, DensePass &p) {
+    const int64_t begin = ctx->tensor_elem_off[(size_t)ctx->layer_first_tensor[(size_t)l]];
+    const int64_t end = ctx->tensor_elem_off[(size_t)ctx->layer_first_tensor[(size_t)l + 1]];
+    const int64_t wg = dense_workgroups(begin, end, ctx->update_chunk);
+    if (wg > INT32_MAX / ctx->update_chunk - 1) return false;
+    const int i = st.layer_pos[(size_t)l];
+    p.begin = begin;
+    p.end = end;
+    p.width = i < 0 && begin % 4 == 0 ? 0 : (int)wg;
+    p.n_pieces = 1;
+    p.pieces[0] = {begin, i < 0 ? -1 : st.layer_begin[(size_t)i], (int32_t)(end - begin), i < 0 ? 0 : st.dense_ranges[2 * (size_t)i]};
+    return true;
+}
+
 static bool aligned(const void *p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
 
 }  // namespace ddp
@@ -341,9 +422,9 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
         // table has chunks, so the reduction scratch sized for the table covers them)
         std::vector<int64_t> dense_wg_base((size_t)ctx->L + 1, 0);
         for (int l = 0; l < ctx->L; ++l) {
-            const int64_t n = ctx->tensor_elem_off[(size_t)ctx->layer_first_tensor[(size_t)l + 1]] -
-                              ctx->tensor_elem_off[(size_t)ctx->layer_first_tensor[(size_t)l]];
-            dense_wg_base[(size_t)l + 1] = dense_wg_base[(size_t)l] + (n + ctx->update_chunk - 1) / ctx->update_chunk;
+            const int64_t e0 = ctx->tensor_elem_off[(size_t)ctx->layer_first_tensor[(size_t)l]];
+            const int64_t e1 = ctx->tensor_elem_off[(size_t)ctx->layer_first_tensor[(size_t)l + 1]];
+            dense_wg_base[(size_t)l + 1] = dense_wg_base[(size_t)l] + dense_workgroups(e0, e1, ctx->update_chunk);
         }
         int64_t max_mean_chunks = 0;
         for (int s = 0; s < H; ++s) {
@@ -412,6 +493,7 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
             if (rc == DDP_OK) rc = upload(ctx, tflat, &st.d_tensor_flat_off);
             if (rc == DDP_OK) rc = upload(ctx, fused_ranges, &st.d_fused_ranges);
             if (rc == DDP_OK) rc = upload(ctx, st.dense_ranges, &st.d_dense_ranges);
+            if (ctx->dense) st.dense_passes = plan_dense(ctx, st, 0, ctx->L);
             if (rc != DDP_OK) {
                 for (auto &x : slots) free_slot(x);
                 return rc;
@@ -701,75 +783,30 @@ extern "C" int ddp_local_update_layers(ddp_ctx *ctx, int layer_first, int layer_
     });
 }
 
-// The fused step over layers [first, first + count) of a model registered as dense arenas: one table-free launch per
-// scheduled layer and one per run of unscheduled layers.  *done = false (nothing launched) when the model, the
-// options, the replica count or an alignment rule the table-free kernels out; the caller then takes the table.
-static int fused_dense(ddp_ctx *ctx, const char *who, const SlotTables *st, const void *const *x, bool wire16, bool update_first, int first,
-                       int count, int N, int local_rank, double *layer_stats, const ddp_opt *opt, const UpdateScalars &s, void *stream,
-                       bool *done) {
-    *done = false;
-    if (!ctx->dense || !ctx->dense_path || !ctx->nontemporal || !fused_dense_supports(N)) return DDP_OK;
-    const std::vector<int32_t> &pos = st->layer_pos;  // layer -> position in the slot, -1 if not scheduled
-    auto elem0 = [&](int l) { return ctx->tensor_elem_off[(size_t)ctx->layer_first_tensor[(size_t)l]]; };
-    // every launch must start on a vector boundary in the model and, for a scheduled layer, in the flat buffer
-    int64_t launches = 0;
-    for (int l = first; l < first + count; ++l) {
-        const bool sched = pos[(size_t)l] >= 0, run_start = l == first || sched || pos[(size_t)l - 1] >= 0;
-        if (run_start && elem0(l) % 4 != 0) return DDP_OK;
-        if (sched && ((elem0(l + 1) - elem0(l)) % 4 != 0 || st->layer_begin[(size_t)pos[(size_t)l]] % 4 != 0)) return DDP_OK;
-        launches += run_start;
-    }
-    // one launch per scheduled layer only pays when the launches are long: small layers stay with the single
-    // table-driven launch
-    if (launches > 1 && (elem0(first + count) - elem0(first)) / launches < (int64_t)1 << 18) return DDP_OK;
-    *done = true;
-    const bool stats = layer_stats != nullptr;
+// The kernels of the fused step over a model registered as dense arenas.
+static int fused_dense(const ddp_ctx *ctx, const DensePass *passes, size_t n, const FusedLaunch &common, void *stream) {
+    FusedDense f;
+    static_cast<FusedLaunch &>(f) = common;
+    const TensorDesc &t0 = ctx->tensors[0];
+    f.d = {t0.grad, t0.sync, t0.state0, t0.state1, t0.model, 0, (int)ctx->update_chunk};
     int rc = 0;
-    for (int l = first; l < first + count && rc == 0;) {
-        DenseLaunch d{};
-        if (pos[(size_t)l] < 0) {
-            int m = l + 1;
-            while (m < first + count && pos[(size_t)m] < 0) ++m;
-            dense_range(ctx, l, m - l, d);
-            rc = launch_update_dense(opt->kind, ctx->grad_dtype, ctx->param_dtype == DDP_BF16, d, s, true, ctx->update_lds, stream);
-            l = m;
+    for (size_t i = 0; i < n && rc == 0; ++i) {
+        f.pass = &passes[i];
+        if (f.pass->width > 0) {
+            rc = launch_fused_dense(f, stream);
             continue;
         }
-        const int i = pos[(size_t)l];
-        FusedDenseLaunch f{};
-        dense_range(ctx, l, 1, f.d);
-        for (int k = 0; k + 1 < N; ++k) f.x[k] = x[k];
-        f.wire16 = wire16;
-        f.update_first = update_first;
-        f.n_replicas = N;
-        f.local_rank = local_rank;
-        f.inv_n = 1.0f / (float)N;
-        f.kind = opt->kind;
-        f.grad_dtype = ctx->grad_dtype;
-        f.with_model = ctx->param_dtype == DDP_BF16;
-        f.fo0 = st->layer_begin[(size_t)i];
-        f.s = s;
-        f.partials = stats ? ctx->d_partials : nullptr;
-        f.pbase = st->dense_ranges[2 * (size_t)i];
-        f.lds_pad = ctx->update_lds;
-        rc = launch_fused_dense(f, stream);
-        ++l;
+        const int64_t e = f.pass->begin;
+        DenseLaunch d = f.d;
+        d.g = (const char *)d.g + e * (ctx->grad_dtype == DDP_F32 ? 4 : 2);
+        d.p += e;
+        d.s0 += e;
+        d.s1 = d.s1 ? d.s1 + e : nullptr;
+        d.mdl = d.mdl ? d.mdl + e : nullptr;
+        d.n = f.pass->end - e;
+        rc = launch_update_dense(f.kind, f.grad_dtype, f.with_model, d, f.s, true, f.lds_pad, stream);
     }
-    // statistics of the slot's layers inside the range: one reduction per run of consecutive slot positions
-    const int nl = (int)st->layers.size();
-    for (int i = 0; stats && rc == 0 && i < nl;) {
-        auto inside = [&](int j) { return st->layers[(size_t)j] >= first && st->layers[(size_t)j] < first + count; };
-        if (!inside(i)) {
-            ++i;
-            continue;
-        }
-        int j = i + 1;
-        while (j < nl && inside(j)) ++j;
-        rc = launch_stats(ctx->d_partials, ctx->d_slice_sums + (int64_t)i * 2 * kStatSlices, st->d_dense_ranges + 2 * i, j - i, N,
-                          layer_stats + 2 * i, st->max_dense_partials, stream);
-        i = j;
-    }
-    return after_launch(ctx, who, rc);
+    return rc;
 }
 
 // whole: every layer (any dispatch order).  Otherwise layers [first, first + count) only: their chunks of the update
@@ -788,18 +825,22 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     if (layer_stats && !aligned(layer_stats, 8)) return fail(ctx, DDP_EALIGN, std::string(who) + ": layer_stats must be 8-byte aligned");
     int64_t c0 = 0, c1 = ctx->n_update;
     if (!whole && (rc = layer_chunk_range(ctx, who, first, count, &c0, &c1)) != DDP_OK) return rc;
-    FusedLaunch f{};
+    FusedTable f;
     for (int k = 0; k + 1 < N; ++k) {
         if (st->numel > 0 && (rc = check_flat(ctx, peers[k], who, "a peer buffer")) != DDP_OK) return rc;
         f.x[k] = peers[k];
     }
     if (c1 == c0) return DDP_OK;
-    {
-        bool done = false;
-        rc = fused_dense(ctx, who, st, f.x, wire16, update_first, whole ? 0 : first, whole ? ctx->L : count, N, local_rank, layer_stats,
-                         opt, s, stream, &done);
-        if (done) return rc;
+    if (whole) {
+        first = 0;
+        count = ctx->L;
     }
+    // Statistics: one reduction per run of consecutive slot positions inside the range (a schedule in backward order gives a
+    // single run).
+    const int nl = (int)st->layers.size();
+    auto inside = [&](int i) { return i < nl && st->layers[(size_t)i] >= first && st->layers[(size_t)i] < first + count; };
+    bool any = false;
+    for (int i = 0; layer_stats && i < nl && !any; ++i) any = inside(i);
     f.wire16 = wire16;
     f.update_first = update_first;
     f.n_replicas = N;
@@ -808,51 +849,36 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     f.kind = opt->kind;
     f.grad_dtype = ctx->grad_dtype;
     f.with_model = ctx->param_dtype == DDP_BF16;
-    f.tensors = ctx->d_tensors;
-    f.chunks = ctx->d_update + c0;
-    f.n_chunks = c1 - c0;
-    f.tensor_flat_off = st->d_tensor_flat_off;
-    f.tensor_chunk_base = ctx->d_tensor_chunk_base;
-    f.chunk_elems = (int)ctx->update_chunk;
     f.s = s;
+    f.partials = any ? ctx->d_partials : nullptr;
     f.lds_pad = ctx->update_lds;
-    const int nl = (int)st->layers.size();
-    if (!layer_stats || nl == 0) return after_launch(ctx, who, launch_fused(f, stream));
-    f.partials = ctx->d_partials;
-    f.max_partials_per_layer = st->max_fused_partials;
-    if (whole) {
-        f.slice_sums = ctx->d_slice_sums;
-        f.layer_ranges = st->d_fused_ranges;
-        f.n_layers = nl;
-        f.stats = layer_stats;
-        return after_launch(ctx, who, launch_fused(f, stream));
-    }
-    // Statistics of the slot's layers inside the range: one reduction per run of consecutive slot positions (a
-    // schedule in backward order gives a single run).  The first launch also carries the kernel itself.
-    bool launched = false;
-    for (int i = 0; i < nl;) {
-        if (st->layers[(size_t)i] < first || st->layers[(size_t)i] >= first + count) {
-            ++i;
-            continue;
-        }
-        int j = i + 1;
-        while (j < nl && st->layers[(size_t)j] >= first && st->layers[(size_t)j] < first + count) ++j;
-        f.slice_sums = ctx->d_slice_sums + (int64_t)i * 2 * kStatSlices;
-        f.layer_ranges = st->d_fused_ranges + 2 * i;
-        f.n_layers = j - i;
-        f.stats = layer_stats + 2 * i;
-        if (!launched) {
-            rc = launch_fused(f, stream);
-            launched = true;
+    const bool dense = ctx->dense && ctx->dense_path;
+    if (dense) {
+        DensePass one;
+        if (whole) {
+            rc = fused_dense(ctx, st->dense_passes.data(), st->dense_passes.size(), f, stream);
+        } else if (count == 1 && one_layer_pass(ctx, *st, first, one)) {
+            rc = fused_dense(ctx, &one, 1, f, stream);
         } else {
-            rc = launch_stats(f.partials, f.slice_sums, f.layer_ranges, f.n_layers, N, f.stats, f.max_partials_per_layer, stream);
+            const std::vector<DensePass> passes = plan_dense(ctx, *st, first, count);
+            rc = fused_dense(ctx, passes.data(), passes.size(), f, stream);
         }
-        if (rc != 0) return after_launch(ctx, who, rc);
-        i = j;
-    }
-    if (!launched) {  // no scheduled layer in the range: plain update of these layers, no partials written
-        f.partials = nullptr;
+    } else {
+        f.tensors = ctx->d_tensors;
+        f.chunks = ctx->d_update + c0;
+        f.n_chunks = c1 - c0;
+        f.tensor_flat_off = st->d_tensor_flat_off;
+        f.tensor_chunk_base = ctx->d_tensor_chunk_base;
+        f.chunk_elems = (int)ctx->update_chunk;
         rc = launch_fused(f, stream);
+    }
+    for (int i = 0; any && i < nl && rc == 0;) {
+        int j = i;
+        while (inside(j)) ++j;
+        if (j > i)
+            rc = launch_stats(f.partials, ctx->d_slice_sums + (int64_t)i * 2 * kStatSlices, (dense ? st->d_dense_ranges : st->d_fused_ranges) + 2 * i,
+                              j - i, N, layer_stats + 2 * i, dense ? st->max_dense_partials : st->max_fused_partials, stream);
+        i = j + 1;
     }
     return after_launch(ctx, who, rc);
 }

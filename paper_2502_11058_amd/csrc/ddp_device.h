@@ -52,40 +52,60 @@ __device__ __forceinline__ void st(T *p, T v) {
         *p = v;
 }
 
-// Groups of four elements that start at any element: gfx950 takes 128- and 64-bit global accesses at any address, so a
-// stream whose start is not a multiple of its vector needs no scalar loop.  A wavefront's 1 KiB then touches one cache
-// line more than an aligned one.
+// Groups of four elements at any element: gfx950 takes 128- and 64-bit global accesses at any address, so a stream whose
+// start is not a multiple of its vector needs no scalar loop.  A wavefront's 1 KiB then touches one cache line more than an
+// aligned one.  base is wave-uniform and i, an element index, an unsigned 32-bit one: the access takes its base from scalar
+// registers and one offset register serves all streams of a type.  The address space is stated because a pointer that a
+// kernel reads from a table is a generic one, whose accesses (flat) also wait for and occupy the LDS counter.
+#define DDP_GLOBAL __attribute__((address_space(1)))
 typedef f32x4 f32x4_any __attribute__((aligned(4)));
 typedef u16x4 u16x4_any __attribute__((aligned(2)));
 
-// (the alignment belongs to the typedef and would be lost in a template argument: no ld<> / st<> here)
-template <bool NT>
-__device__ __forceinline__ f32x4 ld4(const float *p) {
-    const f32x4_any *q = reinterpret_cast<const f32x4_any *>(p);
-    if constexpr (NT) return __builtin_nontemporal_load(q);
-    return *q;
+template <class T>
+struct AnyVec;  // element type -> its group of four with the alignment of one element
+template <>
+struct AnyVec<float> {
+    typedef f32x4 vec;
+    static __device__ __forceinline__ const DDP_GLOBAL f32x4_any *at(const float *p, unsigned i) {
+        return (const DDP_GLOBAL f32x4_any *)((const DDP_GLOBAL char *)p + 4u * i);
+    }
+};
+template <>
+struct AnyVec<unsigned short> {
+    typedef u16x4 vec;
+    static __device__ __forceinline__ const DDP_GLOBAL u16x4_any *at(const unsigned short *p, unsigned i) {
+        return (const DDP_GLOBAL u16x4_any *)((const DDP_GLOBAL char *)p + 2u * i);
+    }
+};
+
+template <bool NT, class T>
+__device__ __forceinline__ typename AnyVec<T>::vec ld4(const T *base, unsigned i) {
+    if constexpr (NT) return __builtin_nontemporal_load(AnyVec<T>::at(base, i));
+    return *AnyVec<T>::at(base, i);
+}
+__device__ __forceinline__ float ld1(const float *base, unsigned i) { return *(const DDP_GLOBAL float *)((const DDP_GLOBAL char *)base + 4u * i); }
+__device__ __forceinline__ unsigned short ld1(const unsigned short *base, unsigned i) {
+    return *(const DDP_GLOBAL unsigned short *)((const DDP_GLOBAL char *)base + 2u * i);
 }
 template <bool NT>
-__device__ __forceinline__ u16x4 ld4(const unsigned short *p) {
-    const u16x4_any *q = reinterpret_cast<const u16x4_any *>(p);
-    if constexpr (NT) return __builtin_nontemporal_load(q);
-    return *q;
-}
-template <bool NT>
-__device__ __forceinline__ void st4(float *p, f32x4 v) {
-    f32x4_any *q = reinterpret_cast<f32x4_any *>(p);
+__device__ __forceinline__ void st4(float *base, unsigned i, f32x4 v) {
+    DDP_GLOBAL f32x4_any *q = (DDP_GLOBAL f32x4_any *)((DDP_GLOBAL char *)base + 4u * i);
     if constexpr (NT)
         __builtin_nontemporal_store(v, q);
     else
         *q = v;
 }
 template <bool NT>
-__device__ __forceinline__ void st4(unsigned short *p, u16x4 v) {
-    u16x4_any *q = reinterpret_cast<u16x4_any *>(p);
+__device__ __forceinline__ void st4(unsigned short *base, unsigned i, u16x4 v) {
+    DDP_GLOBAL u16x4_any *q = (DDP_GLOBAL u16x4_any *)((DDP_GLOBAL char *)base + 2u * i);
     if constexpr (NT)
         __builtin_nontemporal_store(v, q);
     else
         *q = v;
+}
+__device__ __forceinline__ void st1(float *base, unsigned i, float v) { *(DDP_GLOBAL float *)((DDP_GLOBAL char *)base + 4u * i) = v; }
+__device__ __forceinline__ void st1(unsigned short *base, unsigned i, unsigned short v) {
+    *(DDP_GLOBAL unsigned short *)((DDP_GLOBAL char *)base + 2u * i) = v;
 }
 
 // fp32 -> bf16, round to nearest, ties to even (add 0x7fff plus the lowest kept bit, then truncate); NaN -> quiet NaN.
@@ -152,10 +172,10 @@ __device__ __forceinline__ f32x4 widen_again(typename WireVec<W16>::type v) {
     if constexpr (W16) asm("" : "+v"(v));
     return WireVec<W16>::widen(v);
 }
-// ... loaded from any element of the replica.
+// ... loaded from element first + i of the replica (first wave-uniform).
 template <bool W16, bool NT>
-__device__ __forceinline__ typename WireVec<W16>::type wire_raw4(const void *base, int64_t i) {
-    return __builtin_bit_cast(typename WireVec<W16>::type, ld4<NT>(reinterpret_cast<const typename WireVec<W16>::elem *>(base) + i));
+__device__ __forceinline__ typename WireVec<W16>::type wire_raw4(const void *base, int64_t first, unsigned i) {
+    return __builtin_bit_cast(typename WireVec<W16>::type, ld4<NT>(reinterpret_cast<const typename WireVec<W16>::elem *>(base) + first, i));
 }
 
 // Buffer (MUBUF) accesses: a per-workgroup descriptor (base in SGPRs, extent = the workgroup's part of the stream)
@@ -182,6 +202,37 @@ __device__ __forceinline__ void bst(__amdgpu_buffer_rsrc_t r, int byte_off, T v)
     else
         __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, byte_off, 0, AUX);
 }
+
+// One stream of a run of whole vectors, nv groups of four from a wave-uniform base on: through a buffer descriptor (BUF; the
+// base must be dword-aligned) or as global accesses.
+template <bool BUF, class T>
+struct Stream;
+template <class T>
+struct Stream<true, T> {
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ Stream(const T *base, int nv) : r(make_rsrc(base, nv * 4 * (int)sizeof(T))) {}
+    template <bool NT>
+    __device__ __forceinline__ typename AnyVec<T>::vec ld(unsigned i) const {
+        return bld<NT ? 2 : 0, typename AnyVec<T>::vec>(r, (int)(i * (unsigned)sizeof(T)));
+    }
+    template <bool NT>
+    __device__ __forceinline__ void st(unsigned i, typename AnyVec<T>::vec v) const {
+        bst<NT ? 2 : 0>(r, (int)(i * (unsigned)sizeof(T)), v);
+    }
+};
+template <class T>
+struct Stream<false, T> {
+    T *p;
+    __device__ __forceinline__ Stream(const T *base, int) : p(const_cast<T *>(base)) {}
+    template <bool NT>
+    __device__ __forceinline__ typename AnyVec<T>::vec ld(unsigned i) const {
+        return ld4<NT>(p, i);
+    }
+    template <bool NT>
+    __device__ __forceinline__ void st(unsigned i, typename AnyVec<T>::vec v) const {
+        st4<NT>(p, i, v);
+    }
+};
 
 __device__ __forceinline__ int head_to_16B(const void *p, int n) {  // fp32 elements until p is 16-byte aligned
     int h = (int)((4u - (unsigned)((reinterpret_cast<uintptr_t>(p) >> 2) & 3u)) & 3u);
@@ -258,41 +309,44 @@ struct GradVec<true> {
     static __device__ __forceinline__ float widen1(unsigned short g) { return bf16_widen(g); }
 };
 
+// The local streams of one run of n elements (wave-uniform pointers to its first element; s1 and mdl unused without AdamW /
+// a model copy).
+template <bool GBF16>
+struct Streams {
+    typedef typename GradVec<GBF16>::elem gelem;
+    const gelem *g;
+    float *p, *s0, *s1;
+    unsigned short *mdl;
+    int n;
+};
+// ... and their whole vectors, nv groups of four from element h on.
+template <bool GBF16, bool BUF>
+struct Vectors {
+    Stream<BUF, typename GradVec<GBF16>::elem> g;
+    Stream<BUF, float> p, s0, s1;
+    Stream<BUF, unsigned short> mdl;
+    __device__ __forceinline__ Vectors(const Streams<GBF16> &c, int h, int nv)
+        : g(c.g + h, nv), p(c.p + h, nv), s0(c.s0 + h, nv), s1(c.s1 + h, nv), mdl(c.mdl + h, nv) {}
+};
+
+template <bool GBF16>
+__device__ __forceinline__ Streams<GBF16> chunk_streams(const TensorDesc &td, const UpdateChunk &ch) {
+    return {reinterpret_cast<const typename GradVec<GBF16>::elem *>(td.grad) + ch.begin, td.sync + ch.begin, td.state0 + ch.begin,
+            td.state1 + ch.begin, td.model + ch.begin, ch.count};
+}
+
 // Eq. (5), first case, fused: one pass reads gradient, parameter and optimizer state and writes parameter,
 // state and (if present) the bf16 model copy.  ADAM selects AdamW, else SGD with momentum.
-template <bool ADAM, bool GBF16, bool MODEL, bool NT>
-__device__ __forceinline__ void update_chunk_body(const TensorDesc &td, const UpdateChunk &ch, const UpdateScalars &s) {
+template <bool ADAM, bool GBF16, bool MODEL, bool NT, bool BUF>
+__device__ __forceinline__ void update_body(const Streams<GBF16> c, const UpdateScalars &s) {
     typedef GradVec<GBF16> G;
-    typedef typename G::elem gelem;
     typedef typename G::vec gvec;
-    float *p = td.sync + ch.begin;
-    float *s0 = td.state0 + ch.begin;
-    float *s1 = ADAM ? td.state1 + ch.begin : s0;  // unused without ADAM
-    const gelem *g = reinterpret_cast<const gelem *>(td.grad) + ch.begin;
-    unsigned short *mdl = MODEL ? td.model + ch.begin : reinterpret_cast<unsigned short *>(p);  // unused without MODEL
-    const int n = ch.count;
-    const int tid = threadIdx.x;
-
-    auto one = [&](int i) {
-        float pi = p[i], a = s0[i];
-        const float gi = G::widen1(g[i]);
-        if constexpr (ADAM) {
-            float b = s1[i];
-            adamw_one(gi, pi, a, b, s);
-            s1[i] = b;
-        } else {
-            sgdm_one(gi, pi, a, s);
-        }
-        p[i] = pi;
-        s0[i] = a;
-        if constexpr (MODEL) mdl[i] = bf16_rne(pi);
-    };
-
     // the parameters' accesses are aligned; a stream that lies differently against its own vectors takes unaligned ones
-    const int h = head_to_16B(p, n);
-    const int nv = (n - h) >> 2;
+    const int h = head_to_16B(c.p, c.n);
+    const int nv = (c.n - h) >> 2;
+    const Vectors<GBF16, BUF> b(c, h, nv);
 
-    auto compute_store = [&](int v, gvec gv, f32x4 pv, f32x4 av, f32x4 bv) {
+    auto compute_store = [&](unsigned i, gvec gv, f32x4 pv, f32x4 av, f32x4 bv) {
         const f32x4 gw = G::widen(gv);
         float G4[4] = {gw.x, gw.y, gw.z, gw.w};
         float P4[4] = {pv.x, pv.y, pv.z, pv.w};
@@ -306,37 +360,51 @@ __device__ __forceinline__ void update_chunk_body(const TensorDesc &td, const Up
                 sgdm_one(G4[j], P4[j], A4[j], s);
         }
         const f32x4 pn{P4[0], P4[1], P4[2], P4[3]};
-        st4<NT>(p + h + 4 * v, pn);
-        st4<NT>(s0 + h + 4 * v, f32x4{A4[0], A4[1], A4[2], A4[3]});
-        if constexpr (ADAM) st4<NT>(s1 + h + 4 * v, f32x4{B4[0], B4[1], B4[2], B4[3]});
-        if constexpr (MODEL) st4<NT>(mdl + h + 4 * v, bf16_rne4(pn));
+        b.p.template st<NT>(i, pn);
+        b.s0.template st<NT>(i, f32x4{A4[0], A4[1], A4[2], A4[3]});
+        if constexpr (ADAM) b.s1.template st<NT>(i, f32x4{B4[0], B4[1], B4[2], B4[3]});
+        if constexpr (MODEL) b.mdl.template st<NT>(i, bf16_rne4(pn));
     };
 
-    int v = tid;
+    int v = threadIdx.x;
     for (; v + kThreads < nv; v += 2 * kThreads) {
-        const int i = h + 4 * v, j = i + 4 * kThreads;
-        const gvec g0 = ld4<NT>(g + i), g1 = ld4<NT>(g + j);
-        const f32x4 p0 = ld4<NT>(p + i), p1 = ld4<NT>(p + j);
-        const f32x4 a0 = ld4<NT>(s0 + i), a1 = ld4<NT>(s0 + j);
+        const unsigned i = 4u * v, j = i + 4u * kThreads;
+        const gvec g0 = b.g.template ld<NT>(i), g1 = b.g.template ld<NT>(j);
+        const f32x4 p0 = b.p.template ld<NT>(i), p1 = b.p.template ld<NT>(j);
+        const f32x4 a0 = b.s0.template ld<NT>(i), a1 = b.s0.template ld<NT>(j);
         f32x4 b0{}, b1{};
         if constexpr (ADAM) {
-            b0 = ld4<NT>(s1 + i);
-            b1 = ld4<NT>(s1 + j);
+            b0 = b.s1.template ld<NT>(i);
+            b1 = b.s1.template ld<NT>(j);
         }
-        compute_store(v, g0, p0, a0, b0);
-        compute_store(v + kThreads, g1, p1, a1, b1);
+        compute_store(i, g0, p0, a0, b0);
+        compute_store(j, g1, p1, a1, b1);
     }
     for (; v < nv; v += kThreads) {
-        const int i = h + 4 * v;
-        const gvec g0 = ld4<NT>(g + i);
-        const f32x4 p0 = ld4<NT>(p + i);
-        const f32x4 a0 = ld4<NT>(s0 + i);
+        const unsigned i = 4u * v;
+        const gvec g0 = b.g.template ld<NT>(i);
+        const f32x4 p0 = b.p.template ld<NT>(i);
+        const f32x4 a0 = b.s0.template ld<NT>(i);
         f32x4 b0{};
-        if constexpr (ADAM) b0 = ld4<NT>(s1 + i);
-        compute_store(v, g0, p0, a0, b0);
+        if constexpr (ADAM) b0 = b.s1.template ld<NT>(i);
+        compute_store(i, g0, p0, a0, b0);
     }
     // head and tail together, behind the vectors: only a tensor's first and last chunk have any
-    if (tid < n - 4 * nv) one(tid < h ? tid : 4 * nv + tid);
+    if ((int)threadIdx.x < c.n - 4 * nv) {
+        const unsigned i = (int)threadIdx.x < h ? threadIdx.x : 4 * nv + threadIdx.x;
+        float pi = ld1(c.p, i), av = ld1(c.s0, i);
+        const float gi = G::widen1(ld1(c.g, i));
+        if constexpr (ADAM) {
+            float bv = ld1(c.s1, i);
+            adamw_one(gi, pi, av, bv, s);
+            st1(c.s1, i, bv);
+        } else {
+            sgdm_one(gi, pi, av, s);
+        }
+        st1(c.p, i, pi);
+        st1(c.s0, i, av);
+        if constexpr (MODEL) st1(c.mdl, i, bf16_rne(pi));
+    }
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -448,11 +516,15 @@ static_assert(kStageBytes / 16 / DDP_MAX_REPLICAS >= kWave, "the staging area mu
 // lds_pad: bytes of dynamic LDS requested per workgroup although no kernel uses them.  A CU has 160 KiB, so the pad
 // caps how many workgroups are resident per CU, i.e. how wide the window of addresses in flight is.
 template <class K, class... Args>
-int launch(K kernel, int64_t grid, void *stream, int lds_pad, Args... args) {
-    if (grid <= 0) return 0;
-    if (grid > 0x7fffffff) return (int)hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kThreads), (size_t)lds_pad, (hipStream_t)stream, args...);
+int launch2(K kernel, int64_t grid, int rows, void *stream, int lds_pad, const Args &...args) {
+    if (grid <= 0 || rows <= 0) return 0;
+    if (grid > 0x7fffffff || rows > 65535) return (int)hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid, (unsigned)rows), dim3(kThreads), (size_t)lds_pad, (hipStream_t)stream, args...);
     return (int)hipGetLastError();
+}
+template <class K, class... Args>
+int launch(K kernel, int64_t grid, void *stream, int lds_pad, const Args &...args) {
+    return launch2(kernel, grid, 1, stream, lds_pad, args...);
 }
 
 }  // namespace

@@ -1,0 +1,243 @@
+// The averaging + update of one run of elements, shared by the table-driven and the table-free fused kernels.
+#ifndef DDP_FUSED_H
+#define DDP_FUSED_H
+
+#include "ddp_device.h"
+
+#pragma clang fp contract(off)
+
+namespace ddp {
+namespace {
+
+struct Peers {
+    const void *x[DDP_MAX_REPLICAS - 1];  // the N-1 peers' flat buffers (fp32 or bf16) in rank order
+    float inv_n;
+    int n;
+    int local_rank;
+    int stage_threads;  // run-time replica count with statistics: threads that take part in the vector loop
+};
+
+// (entries from N-1 on are never read and stay as they are)
+inline void fill_peers(Peers &p, const FusedLaunch &f) {
+    for (int k = 0; k + 1 < f.n_replicas; ++k) p.x[k] = f.x[k];
+    p.inv_n = f.inv_n;
+    p.n = f.n_replicas;
+    p.local_rank = f.local_rank;
+    p.stage_threads = stage_threads(f.n_replicas > kRegReps ? f.n_replicas - kRegReps : 0);  // only the terms beyond the registers are staged
+}
+
+// Both cases of Eq. (5) in one pass over the run c, whose peers' values start at flat index fo: the average over the N
+// replicas is formed from the local tensor and the peers' flat buffers (same rank-ordered fp32 sum and 1/N multiply as
+// mean_kernel) and the optimizer step is applied.
+//   UTS = false: average, then update the average (the bits of pack -> partial average -> unpack -> local update);
+//   UTS = true:  update the local value, then average it with the peers (Eq. (5) and Algorithm 1 as printed: the
+//                replicas that are averaged have taken this iteration's step; the bits of local update -> pack ->
+//                partial average -> unpack).
+// W16: peers are bf16 and the local replica contributes its bf16 rounding.  NREP > 0: the replica count (EXACT), or the
+// largest one that the registers are laid out for; 0: run-time loop.  gsum, msum: this thread's statistics (STATS).
+template <bool ADAM, bool GBF16, bool MODEL, int NREP, bool EXACT, bool STATS, bool W16, bool UTS, bool BUF>
+__device__ __forceinline__ void fused_body(const Streams<GBF16> c, int64_t fo, const Peers &a, const UpdateScalars &s, double &gsum, double &msum) {
+    typedef GradVec<GBF16> G;
+    typedef typename G::vec gvec;
+    constexpr bool NT = true;
+    const int tid = threadIdx.x;
+    const int nrep = EXACT ? NREP : a.n;
+    const int lr = a.local_rank;
+    const float inv_n = a.inv_n;
+    auto step1 = [&](float gi, float &x, float &av, float &bv) {
+        if constexpr (ADAM)
+            adamw_one(gi, x, av, bv, s);
+        else
+            sgdm_one(gi, x, av, s);
+    };
+
+    // The parameters' accesses are aligned; the peers' flat offset, and any stream that lies differently against its own
+    // vectors, take unaligned ones.  Bound by HBM either way: a slot whose flat offsets are odd runs at the rate of an aligned
+    // one (28 M parameters, N = 24, fp32 peers: 583 us with a scalar loop over such chunks, 259 us so, 259 us aligned).
+    const int h = head_to_16B(c.p, c.n);
+    const int nv = (c.n - h) >> 2;
+    const Vectors<GBF16, BUF> b(c, h, nv);
+    const int64_t bfo = fo + h;
+    typedef typename WireVec<W16>::elem xelem;
+
+    auto stats4 = [&](f32x4 m, f32x4 x) {
+        const f32x4 d = m - x;
+        gsum += (double)d.x * (double)d.x;
+        gsum += (double)d.y * (double)d.y;
+        gsum += (double)d.z * (double)d.z;
+        gsum += (double)d.w * (double)d.w;
+    };
+    auto msq4 = [&](f32x4 m) {
+        msum += (double)m.x * (double)m.x;
+        msum += (double)m.y * (double)m.y;
+        msum += (double)m.z * (double)m.z;
+        msum += (double)m.w * (double)m.w;
+    };
+    auto step4 = [&](gvec gv, f32x4 &x, f32x4 &av, f32x4 &bv) {
+        const f32x4 gw = G::widen(gv);
+        float G4[4] = {gw.x, gw.y, gw.z, gw.w};
+        float P4[4] = {x.x, x.y, x.z, x.w};
+        float A4[4] = {av.x, av.y, av.z, av.w};
+        float B4[4] = {bv.x, bv.y, bv.z, bv.w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) step1(G4[j], P4[j], A4[j], B4[j]);
+        x = f32x4{P4[0], P4[1], P4[2], P4[3]};
+        av = f32x4{A4[0], A4[1], A4[2], A4[3]};
+        bv = f32x4{B4[0], B4[1], B4[2], B4[3]};
+    };
+    auto store4 = [&](unsigned i, f32x4 res, f32x4 av, f32x4 bv) {
+        b.p.template st<NT>(i, res);
+        b.s0.template st<NT>(i, av);
+        if constexpr (ADAM) b.s1.template st<NT>(i, bv);
+        if constexpr (MODEL) b.mdl.template st<NT>(i, bf16_rne4(res));
+    };
+    if constexpr (NREP > 1) {
+        // The local contribution may be computed (updated and / or rounded) and a branch on it per replica would serialise
+        // the loads: the N-1 peers are loaded by their position among the peers, all in flight before the first use.
+        for (int v = tid; v < nv; v += kThreads) {
+            const unsigned i = 4u * v;
+            typename WireVec<W16>::type pv[NREP - 1];
+#pragma unroll
+            for (int j = 0; j < NREP - 1; ++j) {
+                pv[j] = typename WireVec<W16>::type{};
+                if (j < kPeersAlways<NREP, EXACT> || j < nrep - 1) {
+                    // (a buffer's base must be dword-aligned, which a bf16 peer's need not be)
+                    const Stream<BUF && !W16, xelem> x(reinterpret_cast<const xelem *>(a.x[j]) + bfo, nv);
+                    pv[j] = __builtin_bit_cast(typename WireVec<W16>::type, x.template ld<NT>(i));
+                }
+            }
+            f32x4 pl = b.p.template ld<NT>(i);
+            const gvec gv = b.g.template ld<NT>(i);
+            f32x4 av = b.s0.template ld<NT>(i);
+            f32x4 bv{};
+            if constexpr (ADAM) bv = b.s1.template ld<NT>(i);
+            fused_math4<ADAM, GBF16, NREP, EXACT, STATS, W16, UTS>(pv, gv, pl, av, bv, nrep, lr, inv_n, s, gsum, msum);
+            store4(i, pl, av, bv);
+        }
+    } else {
+        // run-time replica count; with statistics the terms beyond the first kRegReps are parked in LDS (see
+        // stage_threads) so that the peers are fetched once; only the first `vt` threads take part (all of them
+        // up to 32 replicas)
+        extern __shared__ __align__(16) unsigned char dyn_lds[];
+        f32x4 *stage = reinterpret_cast<f32x4 *>(dyn_lds);
+        const int vt = STATS ? a.stage_threads : kThreads;
+        for (int v = tid; v < nv && tid < vt; v += vt) {
+            const unsigned i = 4u * v;
+            f32x4 pl = b.p.template ld<NT>(i);
+            const gvec gv = b.g.template ld<NT>(i);
+            f32x4 av = b.s0.template ld<NT>(i);
+            f32x4 bv{};
+            if constexpr (ADAM) bv = b.s1.template ld<NT>(i);
+            if constexpr (UTS) step4(gv, pl, av, bv);
+            f32x4 loc = pl;
+            if constexpr (W16) loc = bf16_widen4(bf16_rne4(pl));
+            auto term = [&](int k) -> f32x4 { return k == lr ? loc : WireVec<W16>::widen(wire_raw4<W16, NT>(a.x[k - (k > lr ? 1 : 0)], bfo, i)); };
+            // the first kRegReps terms of the rank-order sum stay in registers, the rest are parked in LDS
+            f32x4 r[kRegReps];
+#pragma unroll
+            for (int k = 0; k < kRegReps; ++k)
+                if (k < nrep) r[k] = term(k);
+            f32x4 acc = r[0];
+#pragma unroll
+            for (int k = 1; k < kRegReps; ++k)
+                if (k < nrep) acc = acc + r[k];
+            for (int k0 = kRegReps; k0 < nrep; k0 += 8) {  // eight more peers in flight, then park and add them in rank order
+                f32x4 x[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (k0 + j < nrep) x[j] = term(k0 + j);
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (k0 + j < nrep) {
+                        if constexpr (STATS) stage[(k0 + j - kRegReps) * vt + tid] = x[j];
+                        acc = acc + x[j];
+                    }
+            }
+            f32x4 m = acc * inv_n;
+            if constexpr (STATS) {
+#pragma unroll
+                for (int k = 0; k < kRegReps; ++k)
+                    if (k < nrep) stats4(m, r[k]);
+                for (int k = kRegReps; k < nrep; ++k) stats4(m, stage[(k - kRegReps) * vt + tid]);
+                msq4(m);
+            }
+            if constexpr (!UTS) step4(gv, m, av, bv);
+            store4(i, m, av, bv);
+        }
+    }
+    // head and tail together, element by element, behind the vectors: only a tensor's first and last chunk have any
+    if (tid < c.n - 4 * nv) {
+        const unsigned i = tid < h ? tid : 4 * nv + tid;
+        float pl = ld1(c.p, i), av = ld1(c.s0, i), bv = ADAM ? ld1(c.s1, i) : 0.0f;
+        const float gi = G::widen1(ld1(c.g, i));
+        if constexpr (UTS) step1(gi, pl, av, bv);
+        // what this worker contributes: its value, rounded to bf16 first if that is what its peers received
+        const float loc = W16 ? bf16_widen(bf16_rne(pl)) : pl;
+        auto term = [&](int k) -> float { return k == lr ? loc : wire1<W16>(a.x[k - (k > lr ? 1 : 0)], fo + i); };
+        float acc = term(0);
+        for (int k = 1; k < nrep; ++k) acc = acc + term(k);
+        const float m = acc * inv_n;
+        if constexpr (STATS) {
+            for (int k = 0; k < nrep; ++k) {
+                const float d = m - term(k);
+                gsum += (double)d * (double)d;
+            }
+            msum += (double)m * (double)m;
+        }
+        float res = m;
+        if constexpr (!UTS) step1(gi, res, av, bv);
+        st1(c.p, i, res);
+        st1(c.s0, i, av);
+        if constexpr (ADAM) st1(c.s1, i, bv);
+        if constexpr (MODEL) st1(c.mdl, i, bf16_rne(res));
+    }
+}
+
+// The instantiation for a launch: K::go<ADAM, GBF16, MODEL, NREP, EXACT, STATS, W16, UTS>(lds), lds = the dynamic LDS it needs
+// (the residency pad, or the staging area of the run-time replica count if that is larger).
+template <bool A, bool G, bool M, int NR, bool EXACT, class K>
+int dispatch_fused_n(const FusedLaunch &f, const K &k) {
+    const int staged = f.n_replicas > kRegReps ? f.n_replicas - kRegReps : 0;
+    const int need = NR == 0 && f.partials ? staged * stage_threads(staged) * 16 : 0;
+    const int lds = f.lds_pad > need ? f.lds_pad : need;
+    if (f.wire16) {
+        if (f.update_first) return f.partials ? k.template go<A, G, M, NR, EXACT, true, true, true>(lds) : k.template go<A, G, M, NR, EXACT, false, true, true>(lds);
+        return f.partials ? k.template go<A, G, M, NR, EXACT, true, true, false>(lds) : k.template go<A, G, M, NR, EXACT, false, true, false>(lds);
+    }
+    if (f.update_first) return f.partials ? k.template go<A, G, M, NR, EXACT, true, false, true>(lds) : k.template go<A, G, M, NR, EXACT, false, false, true>(lds);
+    return f.partials ? k.template go<A, G, M, NR, EXACT, true, false, false>(lds) : k.template go<A, G, M, NR, EXACT, false, false, false>(lds);
+}
+
+template <bool A, bool G, bool M, class K>
+int dispatch_fused_t(const FusedLaunch &f, const K &k) {
+    const int n = f.n_replicas;
+    switch (n) {
+        case 2: return dispatch_fused_n<A, G, M, 2, true>(f, k);
+        case 4: return dispatch_fused_n<A, G, M, 4, true>(f, k);
+        case 8: return dispatch_fused_n<A, G, M, 8, true>(f, k);
+        case 16: return dispatch_fused_n<A, G, M, 16, true>(f, k);
+        case 32: return dispatch_fused_n<A, G, M, 32, true>(f, k);
+    }
+    // Other counts up to 31 take the kernel laid out for the next power of two, whose upper loads are conditional: within 3 %
+    // of the rate of the exact kernels beside them (28 M parameters, SGD-m, bf16 peers, N = 12: 130 us; 192 us with the
+    // run-time loop, which stays for what does not fit the registers).
+    if (n < 4) return dispatch_fused_n<A, G, M, 4, false>(f, k);
+    if (n < 8) return dispatch_fused_n<A, G, M, 8, false>(f, k);
+    if (n < 16) return dispatch_fused_n<A, G, M, 16, false>(f, k);
+    if (n < 32) return dispatch_fused_n<A, G, M, 32, false>(f, k);
+    return dispatch_fused_n<A, G, M, 0, false>(f, k);
+}
+
+template <bool A, class K>
+int dispatch_fused(const FusedLaunch &f, const K &k) {
+    const bool gb = f.grad_dtype == DDP_BF16;
+    if (!gb && !f.with_model) return dispatch_fused_t<A, false, false>(f, k);
+    if (!gb) return dispatch_fused_t<A, false, true>(f, k);
+    if (!f.with_model) return dispatch_fused_t<A, true, false>(f, k);
+    return dispatch_fused_t<A, true, true>(f, k);
+}
+
+}  // namespace
+}  // namespace ddp
+
+#endif

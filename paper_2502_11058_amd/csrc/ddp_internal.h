@@ -67,6 +67,23 @@ struct MeanChunk {  // partial_average: flat elements [begin, +count), all insid
     int32_t partial;  // where this chunk's partial sums go: its index in flat order, whatever the dispatch order
 };
 
+// One launch of the fused step over dense arenas: consecutive pieces of the model, each part of a scheduled layer or of a run
+// of unscheduled ones.  Workgroup (x, y) takes chunk x of piece y, counted from the multiple of four at or below the piece's
+// first element; it writes its partial pair at partials[2 * (pbase + x)].
+constexpr int kMaxPieces = 32;  // the pieces travel with the launch's arguments
+struct Piece {
+    int64_t begin;  // first element of the arenas
+    int64_t flat0;  // its flat index, -1 if the piece is not scheduled
+    int32_t count;  // elements
+    int32_t pbase;
+};
+struct DensePass {
+    int width;          // chunks of the widest piece; 0: a plain update of elements [begin, end)
+    int n_pieces;
+    int64_t begin, end;
+    Piece pieces[kMaxPieces];
+};
+
 struct SlotTables {
     // host copies (introspection, validation)
     std::vector<int32_t> layers;       // layer ids in flat order
@@ -83,11 +100,12 @@ struct SlotTables {
     int64_t *d_tensor_flat_off = nullptr;  // per registered tensor: first flat index in this slot, -1 if unscheduled
     int32_t *d_fused_ranges = nullptr;     // per layer of the slot: [first, last) update chunk (registration order)
     // dense arenas: per layer of the slot [first, last) index of its workgroups' partials (layers numbered in
-    // registration order, ceil(layer elements / update_chunk) workgroups each)
+    // registration order)
     std::vector<int32_t> dense_ranges;
     int64_t max_mean_partials = 0, max_fused_partials = 0, max_dense_partials = 0;  // largest per-layer count of each range table
     std::vector<int32_t> layer_pos;  // [L] layer -> position in this slot, -1 if not scheduled
     int32_t *d_dense_ranges = nullptr;
+    std::vector<DensePass> dense_passes;  // dense arenas: the launches of the fused step over the whole model
 };
 
 // ---- launchers (ddp_kernels.hip) -------------------------------------------------------------------------------
@@ -127,6 +145,7 @@ int launch_stats(const double *partials, double *slice_sums, const int32_t *rang
                  int64_t max_partials_per_layer, void *stream);
 int launch_pack16(const TensorDesc *tensors, const CopyChunk *chunks, int64_t n_chunks, uint16_t *flat16, bool nontemporal, int lds_pad,
                   void *stream);
+// The fused step: what both forms of the kernel take ...
 struct FusedLaunch {
     const void *x[DDP_MAX_REPLICAS - 1];  // the N-1 peers in rank order; fp32, or bf16 when wire16
     bool wire16;
@@ -135,22 +154,20 @@ struct FusedLaunch {
     float inv_n;
     int kind, grad_dtype;
     bool with_model;
+    UpdateScalars s;
+    double *partials;  // nullptr: no statistics
+    int lds_pad;
+};
+// ... the table-driven one, over chunks of the update table ...
+struct FusedTable : FusedLaunch {
     const TensorDesc *tensors;
     const UpdateChunk *chunks;
     int64_t n_chunks;
     const int64_t *tensor_flat_off;
     const int32_t *tensor_chunk_base;
     int chunk_elems;
-    UpdateScalars s;
-    double *partials;  // nullptr: no statistics
-    double *slice_sums;
-    const int32_t *layer_ranges;
-    int n_layers;
-    int64_t max_partials_per_layer;
-    double *stats;
-    int lds_pad;
 };
-int launch_fused(const FusedLaunch &f, void *stream);
+int launch_fused(const FusedTable &f, void *stream);
 // The update over tensors that lie back to back in every stream: the range's first element in each stream (aligned
 // for 128-bit access, bf16 streams for 64-bit), its length and the elements per workgroup.
 struct DenseLaunch {
@@ -162,25 +179,12 @@ struct DenseLaunch {
 };
 int launch_update_dense(int kind, int grad_dtype, bool with_model, const DenseLaunch &d, const UpdateScalars &s, bool nontemporal,
                         int lds_pad, void *stream);
-// One scheduled layer of a dense model through the fused kernel: local streams d (d.n a multiple of 4), peers' flat
-// buffers x, the layer's first flat index fo0 (a multiple of 4); workgroup b's partial pair goes to partials[2 * (pbase + b)]
-// (nullptr: no statistics).  Replica counts fused_dense_supports() accepts only.
-struct FusedDenseLaunch {
+// ... and the one over dense arenas (d: the arenas' first elements; d.n is not used).
+struct FusedDense : FusedLaunch {
     DenseLaunch d;
-    const void *x[DDP_MAX_REPLICAS - 1];
-    bool wire16, update_first;
-    int n_replicas, local_rank;
-    float inv_n;
-    int kind, grad_dtype;
-    bool with_model;
-    int64_t fo0;
-    UpdateScalars s;
-    double *partials;
-    int64_t pbase;
-    int lds_pad;
+    const DensePass *pass;
 };
-bool fused_dense_supports(int n_replicas);
-int launch_fused_dense(const FusedDenseLaunch &f, void *stream);
+int launch_fused_dense(const FusedDense &f, void *stream);
 int launch_update(int kind, int grad_dtype, bool with_model, const TensorDesc *tensors, const UpdateChunk *chunks,
                   int64_t n_chunks, const UpdateScalars &s, bool nontemporal, int lds_pad, void *stream);
 

@@ -1,131 +1,96 @@
 // fused synchronisation + update over dense arenas (table-free).
-#include "ddp_device.h"
+//
+// Compiled twice, once per optimizer, like the table-driven kernel.
+#include "ddp_fused.h"
+
+#ifndef DDP_FUSED_ADAM
+#error "compile with -DDDP_FUSED_ADAM=0 or -DDDP_FUSED_ADAM=1"
+#endif
 
 namespace ddp {
 namespace {
 
 struct FusedDenseArgs {
-    DenseArgs d;                       // the scheduled layer's local streams; d.n is a multiple of 4
-    const void *x[DDP_MAX_REPLICAS - 1];  // the N-1 peers' whole flat buffers in rank order
-    int64_t fo0;                       // flat index of the layer's first element (a multiple of 4)
-    double *partials;                  // workgroup b writes its pair at partials[2 * (pbase + b)]
-    int64_t pbase;
-    float inv_n;
-    int local_rank;
+    Peers peers;
+    DenseLaunch d;
+    double *partials;
+    UpdateScalars s;
+    Piece pieces[kMaxPieces];
 };
 
-// fused_kernel for one scheduled layer of a model registered as dense arenas: table-free addressing, buffer accesses
-// for all streams, the arithmetic of fused_math4.  Launched once per scheduled layer; the layers in between take
-// update_dense_kernel.
-template <bool ADAM, bool GBF16, bool MODEL, int NREP, bool STATS, bool W16, bool UTS>
-__global__ __launch_bounds__(kThreads) void fused_dense_kernel(const FusedDenseArgs a) {
-    typedef GradVec<GBF16> G;
-    typedef typename G::elem gelem;
-    typedef typename G::vec gvec;
-    static_assert(NREP > 1, "compile-time replica count");
-    constexpr int AUX = 2;                  // nt
-    constexpr int XB = W16 ? 8 : 16;        // bytes of one peer's group of four
+// fused_kernel for a model registered as dense arenas: a workgroup's addresses follow from its indexes and its piece, which is
+// part of the launch's arguments.  Bound by HBM with two workgroups per CU, so what a workgroup spends before its first load
+// counts: with the pieces searched by workgroup index instead of indexed (about 0.2 us) TinyLlama-1.1B at N = 2 took 5450 us,
+// so 5220.
+template <bool ADAM, bool GBF16, bool MODEL, int NREP, bool EXACT, bool STATS, bool W16, bool UTS>
+__global__ __launch_bounds__(kThreads, 2) void fused_dense_kernel(const FusedDenseArgs a) {
     __shared__ double lds[2][kThreads / kWave];
-    const int64_t b = (int64_t)blockIdx.x * a.d.chunk;
-    const int64_t left = a.d.n - b;
-    const int count = left < (int64_t)a.d.chunk ? (int)left : a.d.chunk;
-    const int nv = count >> 2;
-    const int tid = threadIdx.x;
-    const int lr = a.local_rank;
-    float *p = a.d.p + b;
-    float *s0 = a.d.s0 + b;
-    float *s1 = ADAM ? a.d.s1 + b : s0;
-    const gelem *g = reinterpret_cast<const gelem *>(a.d.g) + b;
-    unsigned short *mdl = MODEL ? a.d.mdl + b : reinterpret_cast<unsigned short *>(p);
-    const __amdgpu_buffer_rsrc_t rp = make_rsrc(p, nv * 16), ra = make_rsrc(s0, nv * 16), rb = make_rsrc(s1, nv * 16),
-                                 rg = make_rsrc(g, nv * (int)sizeof(gvec)), rm = make_rsrc(mdl, nv * 8);
-    __amdgpu_buffer_rsrc_t rx[NREP - 1];
+    const Piece t = a.pieces[blockIdx.y];
+    // Two workgroups per CU do not hide what one spends before its first load: the arguments are requested together, not
+    // where each is first used behind a branch.
+    asm volatile("" ::"s"(a.d.g), "s"(a.d.p), "s"(a.d.s0), "s"(a.d.s1), "s"(a.d.mdl));
 #pragma unroll
-    for (int j = 0; j < NREP - 1; ++j)
-        rx[j] = make_rsrc(reinterpret_cast<const char *>(a.x[j]) + (a.fo0 + b) * (XB / 4), nv * XB);
-    double gsum = 0.0, msum = 0.0;
-    for (int v = tid; v < nv; v += kThreads) {
-        typename WireVec<W16>::type pv[NREP - 1];
-#pragma unroll
-        for (int j = 0; j < NREP - 1; ++j) pv[j] = bld<AUX, typename WireVec<W16>::type>(rx[j], v * XB);
-        f32x4 x = bld<AUX, f32x4>(rp, v * 16);
-        const gvec gv = bld<AUX, gvec>(rg, v * (int)sizeof(gvec));
-        f32x4 av = bld<AUX, f32x4>(ra, v * 16);
-        f32x4 bv{};
-        if constexpr (ADAM) bv = bld<AUX, f32x4>(rb, v * 16);
-        fused_math4<ADAM, GBF16, NREP, true, STATS, W16, UTS>(pv, gv, x, av, bv, NREP, lr, a.inv_n, a.d.s, gsum, msum);
-        bst<AUX>(rp, v * 16, x);
-        bst<AUX>(ra, v * 16, av);
-        if constexpr (ADAM) bst<AUX>(rb, v * 16, bv);
-        if constexpr (MODEL) bst<AUX>(rm, v * 8, bf16_rne4(x));
+    for (int j = 0; j < (NREP < 16 ? NREP : 16) - 1; ++j) asm volatile("" ::"s"(a.peers.x[j]));
+    const int past = (int)t.begin & 3;                       // chunks end at multiples of four
+    const int hi = ((int)blockIdx.x + 1) * a.d.chunk - past;
+    int at = hi - a.d.chunk;
+    at = at > 0 ? at : 0;
+    const int n = (hi < t.count ? hi : t.count) - at;
+    if (n <= 0) return;  // a piece narrower than the widest
+    const int64_t begin = t.begin + at;
+    const Streams<GBF16> c{reinterpret_cast<const typename GradVec<GBF16>::elem *>(a.d.g) + begin, a.d.p + begin, a.d.s0 + begin, a.d.s1 + begin,
+                           a.d.mdl + begin, n};
+    if (t.flat0 < 0) {
+        update_body<ADAM, GBF16, MODEL, true, true>(c, a.s);
+        return;
     }
+    double gsum = 0.0, msum = 0.0;
+    fused_body<ADAM, GBF16, MODEL, NREP, EXACT, STATS, W16, UTS, true>(c, t.flat0 + at, a.peers, a.s, gsum, msum);
     if constexpr (STATS) {
         const double gt = block_sum(gsum, lds[0]);
         const double mt = block_sum(msum, lds[1]);
-        if (tid == 0) {
-            a.partials[2 * (a.pbase + blockIdx.x)] = gt;
-            a.partials[2 * (a.pbase + blockIdx.x) + 1] = mt;
+        if (threadIdx.x == 0) {
+            const int64_t pi = (int64_t)t.pbase + blockIdx.x;
+            a.partials[2 * pi] = gt;
+            a.partials[2 * pi + 1] = mt;
         }
     }
 }
+
+struct LaunchDense {
+    const FusedDense &f;
+    const FusedDenseArgs &a;
+    void *stream;
+    template <bool A, bool G, bool M, int NR, bool EXACT, bool STATS, bool W, bool U>
+    int go(int lds) const {
+        return launch2(fused_dense_kernel<A, G, M, NR, EXACT, STATS, W, U>, f.pass->width, f.pass->n_pieces, stream, lds, a);
+    }
+};
 
 }  // namespace
 
-template <bool A, bool G, bool M, int NR>
-static int launch_fused_dense_n(const FusedDenseLaunch &f, const FusedDenseArgs &fa, int64_t grid, void *stream) {
-    const bool st = f.partials != nullptr;
-#define DDP_FUSED(W, U)                                                                             \
-    return st ? launch(fused_dense_kernel<A, G, M, NR, true, W, U>, grid, stream, f.lds_pad, fa)    \
-              : launch(fused_dense_kernel<A, G, M, NR, false, W, U>, grid, stream, f.lds_pad, fa);
-    if (f.wire16) {
-        if (f.update_first) { DDP_FUSED(true, true) }
-        DDP_FUSED(true, false)
-    }
-    if (f.update_first) { DDP_FUSED(false, true) }
-    DDP_FUSED(false, false)
-#undef DDP_FUSED
+#if DDP_FUSED_ADAM
+#define DDP_FUSED_HALF launch_fused_dense_adamw
+#else
+#define DDP_FUSED_HALF launch_fused_dense_sgdm
+#endif
+
+int DDP_FUSED_HALF(const FusedDense &f, void *stream) {
+    FusedDenseArgs a;
+    fill_peers(a.peers, f);
+    a.d = f.d;
+    a.partials = f.partials;
+    a.s = f.s;
+    for (int i = 0; i < f.pass->n_pieces; ++i) a.pieces[i] = f.pass->pieces[i];
+    return dispatch_fused<DDP_FUSED_ADAM != 0>(f, LaunchDense{f, a, stream});
 }
 
-bool fused_dense_supports(int n_replicas) { return n_replicas == 2 || n_replicas == 4 || n_replicas == 8 || n_replicas == 16 || n_replicas == 32; }
+#if !DDP_FUSED_ADAM
+int launch_fused_dense_adamw(const FusedDense &f, void *stream);
 
-int launch_fused_dense(const FusedDenseLaunch &f, void *stream) {
-    if (f.d.n <= 0) return 0;
-    FusedDenseArgs fa{};
-    fa.d.g = f.d.g;
-    fa.d.p = f.d.p;
-    fa.d.s0 = f.d.s0;
-    fa.d.s1 = f.d.s1;
-    fa.d.mdl = f.d.mdl;
-    fa.d.n = f.d.n;
-    fa.d.chunk = f.d.chunk;
-    fa.d.s = f.s;
-    for (int k = 0; k + 1 < f.n_replicas; ++k) fa.x[k] = f.x[k];
-    fa.fo0 = f.fo0;
-    fa.partials = f.partials;
-    fa.pbase = f.pbase;
-    fa.inv_n = f.inv_n;
-    fa.local_rank = f.local_rank;
-    const int64_t grid = (f.d.n + f.d.chunk - 1) / f.d.chunk;
-    const bool adam = f.kind == DDP_OPT_ADAMW, gb = f.grad_dtype == DDP_BF16, md = f.with_model;
-#define DDP_F(A, G, M)                                                                                  \
-    if (adam == A && gb == G && md == M) switch (f.n_replicas) {                                        \
-            case 2: return launch_fused_dense_n<A, G, M, 2>(f, fa, grid, stream);                       \
-            case 4: return launch_fused_dense_n<A, G, M, 4>(f, fa, grid, stream);                       \
-            case 8: return launch_fused_dense_n<A, G, M, 8>(f, fa, grid, stream);                       \
-            case 16: return launch_fused_dense_n<A, G, M, 16>(f, fa, grid, stream);                     \
-            case 32: return launch_fused_dense_n<A, G, M, 32>(f, fa, grid, stream);                     \
-            default: return (int)hipErrorInvalidValue;                                                  \
-        }
-    DDP_F(false, false, false)
-    DDP_F(false, false, true)
-    DDP_F(false, true, false)
-    DDP_F(false, true, true)
-    DDP_F(true, false, false)
-    DDP_F(true, false, true)
-    DDP_F(true, true, false)
-    DDP_F(true, true, true)
-#undef DDP_F
-    return (int)hipErrorInvalidValue;
+int launch_fused_dense(const FusedDense &f, void *stream) {
+    return f.kind == DDP_OPT_ADAMW ? launch_fused_dense_adamw(f, stream) : launch_fused_dense_sgdm(f, stream);
 }
+#endif
 
 }  // namespace ddp
