@@ -187,20 +187,31 @@ def sets_from_csr(set_ptr, set_layers) -> List[List[int]]:
 # context
 # ------------------------------------------------------------------------------------------------------------
 
+_raw_stream = None       # (bad fork?, current device, raw handle of a device's current stream), once torch's GPU state is up
+
+
+def _current_stream() -> int:
+    """Handle of torch's current stream on the current device.  torch.cuda.current_stream() builds a Stream object for it
+    (2.9 us, as long as the launch itself); the raw query takes 0.1 us."""
+    global _raw_stream
+    if _raw_stream is None or _raw_stream[0]():
+        import torch
+        handle = torch.cuda.current_stream().cuda_stream      # initialises, or says why it cannot
+        _raw_stream = (torch._C._cuda_isInBadFork, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+        return handle
+    return _raw_stream[2](_raw_stream[1]())
+
+
 def _stream_handle(stream) -> Optional[int]:
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
 
 
 def _dev_ptrs(tensors) -> "C.Array":
-    arr = (C.c_void_p * len(tensors))()
-    for i, t in enumerate(tensors):
-        arr[i] = None if t is None else (t if isinstance(t, int) else t.data_ptr())
-    return arr
+    return (C.c_void_p * len(tensors))(*[t if t is None or isinstance(t, int) else t.data_ptr() for t in tensors])
 
 
 def device_pointer_array(tensors) -> "C.Array":
