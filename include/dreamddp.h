@@ -19,7 +19,7 @@
  *   - The four per-iteration calls only enqueue kernels on the caller's stream (a hipStream_t passed as
  *     void*, NULL = the default stream).  They never allocate, free, copy to the host or synchronise.
  *   - A context holds nothing of the training state: only tables derived from the registration and the schedule, and a
- *     reduction scratch that every call writes before it reads.  Parameters, optimizer state, model copy and the step
+ *     reduction scratch that every call writes before it reads (and a counter per layer that is zero between calls).  Parameters, optimizer state, model copy and the step
  *     counter (ddp_opt.step) are the caller's: a checkpoint is those tensors plus the iteration number, and a new
  *     context registered over the restored tensors continues with the bits of the uninterrupted run.
  *   - A context is not thread-safe; calls that share a context or device buffers must be ordered by the caller
@@ -285,7 +285,7 @@ int ddp_fused_sync_update_layers(ddp_ctx *ctx, int slot, int layer_first, int la
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc): ddp_partial_average with its reduction scratch (one pair of fp64 partial sums per chunk of
  * mean_chunk elements, then 64 slice sums per layer of the slot) in a fixed array of DDP_STATIC_SCRATCH_BYTES inside the
- * library's device image, one copy per GPU, instead of memory owned by the context.  Same arguments, same kernels and
+ * library's device image, one copy per GPU, instead of memory owned by the context.  Same arguments, same averaging kernel and
  * bit for bit the same flat_out and layer_stats as ddp_partial_average.  Neither this call nor anything it calls
  * allocates or frees device or pinned memory; the device address of the array is resolved once per device in ddp_create
  * (if that fails, the context still works and this call alone returns DDP_ESTATE with the reason).

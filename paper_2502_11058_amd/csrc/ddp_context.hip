@@ -45,14 +45,14 @@ static void free_slot(SlotTables &s) {
     if (s.d_copy) (void)hipFree(s.d_copy);
     if (s.d_mean) (void)hipFree(s.d_mean);
     if (s.d_layer_ranges) (void)hipFree(s.d_layer_ranges);
-    if (s.d_tensor_flat_off) (void)hipFree(s.d_tensor_flat_off);
+    if (s.d_tensor_slot) (void)hipFree(s.d_tensor_slot);
     if (s.d_fused_ranges) (void)hipFree(s.d_fused_ranges);
     if (s.d_dense_ranges) (void)hipFree(s.d_dense_ranges);
     s.d_dense_ranges = nullptr;
     s.d_copy = nullptr;
     s.d_mean = nullptr;
     s.d_layer_ranges = nullptr;
-    s.d_tensor_flat_off = nullptr;
+    s.d_tensor_slot = nullptr;
     s.d_fused_ranges = nullptr;
 }
 
@@ -64,6 +64,7 @@ static void drop_schedule(ddp_ctx *c) {
     c->d_partials = nullptr;
     c->d_slice_sums = nullptr;
     c->partials_cap = 0;
+    c->d_counters = nullptr;
 }
 
 static void drop_model(ddp_ctx *c) {
@@ -126,6 +127,12 @@ static int residency_pad(const ddp_ctx *c, int wg_per_cu) {
     return pad > 0 ? pad : 0;
 }
 
+// Whether the workgroups of a launch put the layers' statistics together themselves.  That saves a launch (3 us of host time;
+// fused step over 8 layers of 256^2: 8.4 -> 7.9 us on the GPU as well), but every workgroup then makes its partials visible
+// to the other XCDs before it ends, which writes its L2 back: with 257 workgroups nothing is lost, with 514 an average of
+// 7.3 us takes 10.7, with 3500 one of 48 takes 178.  Hence: not much more than one workgroup per CU.
+static bool fold_stats(const ddp_ctx *ctx, int64_t workgroups) { return 4 * workgroups <= 5 * (int64_t)ctx->cus; }
+
 // Workgroups of the table-free fused kernel over elements [e0, e1) of the arenas: chunks counted from the multiple of four at
 // or below e0, where every stream is vector-aligned.
 static int64_t dense_workgroups(int64_t e0, int64_t e1, int64_t chunk) { return (e1 - e0 / 4 * 4 + chunk - 1) / chunk; }
@@ -143,6 +150,7 @@ static std::vector<DensePass> plan_dense(const ddp_ctx *ctx, const SlotTables &s
     auto elem0 = [&](int l) { return ctx->tensor_elem_off[(size_t)ctx->layer_first_tensor[(size_t)l]]; };
     struct Segment {
         int64_t begin, end, flat0, pbase, wg;
+        int32_t pos, layer;
     };
     std::vector<Segment> all;
     for (int l = first; l < first + count;) {
@@ -150,7 +158,7 @@ static std::vector<DensePass> plan_dense(const ddp_ctx *ctx, const SlotTables &s
         int m = l + 1;
         while (i < 0 && m < first + count && st.layer_pos[(size_t)m] < 0) ++m;
         all.push_back({elem0(l), elem0(m), i < 0 ? -1 : st.layer_begin[(size_t)i], i < 0 ? 0 : st.dense_ranges[2 * (size_t)i],
-                       dense_workgroups(elem0(l), elem0(m), chunk)});
+                       dense_workgroups(elem0(l), elem0(m), chunk), i, l});
         l = m;
     }
     std::vector<DensePass> passes;
@@ -187,7 +195,7 @@ static std::vector<DensePass> plan_dense(const ddp_ctx *ctx, const SlotTables &s
                 const int64_t base = seg[k].begin / 4 * 4, at = b == 0 ? seg[k].begin : base + b * chunk;
                 const int64_t end = std::min(seg[k].end, base + (b + width) * chunk);
                 p.pieces[p.n_pieces++] = {at, seg[k].flat0 < 0 ? -1 : seg[k].flat0 + (at - seg[k].begin), (int32_t)(end - at),
-                                          (int32_t)(seg[k].pbase + b)};
+                                          (int32_t)(seg[k].pbase + b), seg[k].pos, seg[k].layer};
             }
     }
     return passes;
@@ -203,7 +211,7 @@ static bool one_layer_pass(const ddp_ctx *ctx, const SlotTables &st, int l, Dens
     p.end = end;
     p.width = i < 0 && begin % 4 == 0 ? 0 : (int)wg;
     p.n_pieces = 1;
-    p.pieces[0] = {begin, i < 0 ? -1 : st.layer_begin[(size_t)i], (int32_t)(end - begin), i < 0 ? 0 : st.dense_ranges[2 * (size_t)i]};
+    p.pieces[0] = {begin, i < 0 ? -1 : st.layer_begin[(size_t)i], (int32_t)(end - begin), i < 0 ? 0 : st.dense_ranges[2 * (size_t)i], i, l};
     return true;
 }
 
@@ -235,6 +243,8 @@ extern "C" int ddp_create(ddp_ctx **out, int device) {
         c->lds_per_cu = lds_cu;
         c->lds_per_wg_max = lds_wg;
     }
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess && cus > 0) c->cus = cus;
     c->update_lds = residency_pad(c, 2);
     c->mean_lds = residency_pad(c, 2);
     c->copy_lds = residency_pad(c, 6);
@@ -433,7 +443,7 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
             std::vector<CopyChunk> cc;
             std::vector<MeanChunk> mc;
             std::vector<int32_t> lcp, fused_ranges;
-            std::vector<int64_t> tflat((size_t)ctx->T, -1);
+            std::vector<TensorSlot> tslot((size_t)ctx->T, TensorSlot{-1, -1, -1});
             int64_t off = 0;
             for (int j = set_ptr[s]; j < set_ptr[s + 1]; ++j) {
                 const int l = set_layers[j];
@@ -449,7 +459,7 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
                 for (int t = ctx->layer_first_tensor[(size_t)l]; t < ctx->layer_first_tensor[(size_t)l + 1]; ++t) {
                     st.tensors.push_back(t);
                     st.tensor_off.push_back(off);
-                    tflat[(size_t)t] = off;
+                    tslot[(size_t)t] = {off, st.layer_pos[(size_t)l], l};
                     for (int64_t b = 0; b < ctx->numel[(size_t)t]; b += ctx->copy_chunk) {
                         int64_t n = std::min<int64_t>(ctx->copy_chunk, ctx->numel[(size_t)t] - b);
                         cc.push_back({b, off + b, t, (int32_t)n});
@@ -489,8 +499,10 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
                 st.max_fused_partials = std::max<int64_t>(st.max_fused_partials, fused_ranges[i + 1] - fused_ranges[i]);
                 st.max_dense_partials = std::max<int64_t>(st.max_dense_partials, st.dense_ranges[i + 1] - st.dense_ranges[i]);
             }
+            if (fold_stats(ctx, st.n_mean))
+                for (size_t i = 0; i + 1 < lcp.size(); ++i) mean_ranges.insert(mean_ranges.end(), (size_t)(lcp[i + 1] - lcp[i]), (int32_t)i);
             if (rc == DDP_OK) rc = upload(ctx, mean_ranges, &st.d_layer_ranges);
-            if (rc == DDP_OK) rc = upload(ctx, tflat, &st.d_tensor_flat_off);
+            if (rc == DDP_OK) rc = upload(ctx, tslot, &st.d_tensor_slot);
             if (rc == DDP_OK) rc = upload(ctx, fused_ranges, &st.d_fused_ranges);
             if (rc == DDP_OK) rc = upload(ctx, st.dense_ranges, &st.d_dense_ranges);
             if (ctx->dense) st.dense_passes = plan_dense(ctx, st, 0, ctx->L);
@@ -501,11 +513,20 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
         }
         max_mean_chunks = std::max(max_mean_chunks, ctx->n_update);  // the fused step keeps one partial per update chunk
         if (max_mean_chunks > 0) {
-            hipError_t e = hipMalloc((void **)&ctx->d_partials, ((size_t)max_mean_chunks + (size_t)ctx->L * kStatSlices) * 2 * sizeof(double));
+            const size_t sums = ((size_t)max_mean_chunks + (size_t)ctx->L * kStatSlices) * 2;
+            const std::vector<int32_t> zeros((size_t)ctx->L, 0);
+            hipError_t e = hipMalloc((void **)&ctx->d_partials, sums * sizeof(double) + zeros.size() * sizeof(int32_t));
             if (e != hipSuccess) {
                 ctx->d_partials = nullptr;
                 for (auto &x : slots) free_slot(x);
                 return fail(ctx, DDP_ENOMEM, std::string("ddp_set_schedule: hipMalloc of the reduction scratch failed: ") + hipGetErrorString(e));
+            }
+            ctx->d_counters = reinterpret_cast<int32_t *>(ctx->d_partials + sums);
+            e = hipMemcpy(ctx->d_counters, zeros.data(), zeros.size() * sizeof(int32_t), hipMemcpyHostToDevice);
+            if (e != hipSuccess) {
+                for (auto &x : slots) free_slot(x);
+                drop_schedule(ctx);
+                return hip_fail(ctx, e, "hipMemcpy of the counters");
             }
             ctx->partials_cap = max_mean_chunks;
             ctx->d_slice_sums = ctx->d_partials + 2 * max_mean_chunks;
@@ -652,16 +673,15 @@ int ddp::partial_average_impl(ddp_ctx *ctx, const char *who, bool wire16, int sl
     a.out = flat_out;
     a.chunks = s->d_mean;
     a.n_chunks = s->n_mean;
-    a.partials = layer_stats ? partials : nullptr;
-    a.slice_sums = slice_sums;
-    a.layer_ranges = s->d_layer_ranges;
-    a.n_layers = (int)s->layers.size();
-    a.max_partials_per_layer = s->max_mean_partials;
-    a.stats = layer_stats;
+    const bool fold = layer_stats && !scratch && fold_stats(ctx, s->n_mean);
+    a.st = {layer_stats ? partials : nullptr, s->d_layer_ranges, layer_stats, fold ? ctx->d_counters : nullptr};
+    a.chunk_pos = s->d_layer_ranges + 2 * s->layers.size();
     a.nontemporal = ctx->nontemporal;
     // bf16 replicas put half the bytes per workgroup in flight: half the pad, twice the workgroups per CU
     a.lds_pad = wire16 ? ctx->mean_lds / 2 : ctx->mean_lds;
     rc = launch_mean(a, stream);
+    if (rc == 0 && layer_stats && !fold)
+        rc = launch_stats(partials, slice_sums, s->d_layer_ranges, (int)s->layers.size(), N, layer_stats, s->max_mean_partials, stream);
     return after_launch(ctx, who, rc);
 }
 
@@ -850,9 +870,11 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     f.grad_dtype = ctx->grad_dtype;
     f.with_model = ctx->param_dtype == DDP_BF16;
     f.s = s;
-    f.partials = any ? ctx->d_partials : nullptr;
     f.lds_pad = ctx->update_lds;
     const bool dense = ctx->dense && ctx->dense_path;
+    const bool fold = any && fold_stats(ctx, c1 - c0);
+    const int32_t *ranges = dense ? st->d_dense_ranges : st->d_fused_ranges;
+    f.st = {any ? ctx->d_partials : nullptr, ranges, layer_stats, fold ? ctx->d_counters : nullptr};
     if (dense) {
         DensePass one;
         if (whole) {
@@ -867,17 +889,17 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
         f.tensors = ctx->d_tensors;
         f.chunks = ctx->d_update + c0;
         f.n_chunks = c1 - c0;
-        f.tensor_flat_off = st->d_tensor_flat_off;
+        f.tensor_slot = st->d_tensor_slot;
         f.tensor_chunk_base = ctx->d_tensor_chunk_base;
         f.chunk_elems = (int)ctx->update_chunk;
         rc = launch_fused(f, stream);
     }
-    for (int i = 0; any && i < nl && rc == 0;) {
+    for (int i = 0; any && !fold && i < nl && rc == 0;) {
         int j = i;
         while (inside(j)) ++j;
         if (j > i)
-            rc = launch_stats(f.partials, ctx->d_slice_sums + (int64_t)i * 2 * kStatSlices, (dense ? st->d_dense_ranges : st->d_fused_ranges) + 2 * i,
-                              j - i, N, layer_stats + 2 * i, dense ? st->max_dense_partials : st->max_fused_partials, stream);
+            rc = launch_stats(f.st.partials, ctx->d_slice_sums + (int64_t)i * 2 * kStatSlices, ranges + 2 * i, j - i, N, layer_stats + 2 * i,
+                              dense ? st->max_dense_partials : st->max_fused_partials, stream);
         i = j + 1;
     }
     return after_launch(ctx, who, rc);

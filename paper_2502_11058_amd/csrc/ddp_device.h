@@ -256,6 +256,61 @@ __device__ __forceinline__ double block_sum(double v, double *lds) {
     return r;
 }
 
+// The sums of a layer from its partials, in a fixed order: thread-strided, then the workgroup tree.  Eight pairs in flight
+// per thread: the loop is bound by latency (3456 partials: 4.4 us one pair at a time, 3.2 us so).
+__device__ __forceinline__ void sum_partials(const double *partials, int64_t c0, int64_t c1, int n_replicas, double *stats, double (*lds)[kThreads / kWave]) {
+    double g = 0.0, m = 0.0;
+    constexpr int U = 8;  // pairs in flight per thread
+    for (int64_t c = c0 + (int64_t)threadIdx.x; c < c1; c += U * kThreads) {
+        double x[U], y[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            x[j] = y[j] = 0.0;
+            if (c + j * kThreads < c1) {
+                x[j] = __hip_atomic_load(partials + 2 * (c + j * kThreads), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                y[j] = __hip_atomic_load(partials + 2 * (c + j * kThreads) + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < U; ++j) {  // (both sums are of squares: adding zero changes nothing)
+            g += x[j];
+            m += y[j];
+        }
+    }
+    g = block_sum(g, lds[0]);
+    m = block_sum(m, lds[1]);
+    if (threadIdx.x == 0) {
+        stats[0] = g / (double)n_replicas;
+        stats[1] = m;
+    }
+}
+
+// A workgroup's partial pair of the statistics (valid in thread 0) and, with counters, the layer's sums: the last workgroup of a
+// layer to arrive adds the partials up, in the order of sum_partials whichever it is.  Partials and counter are accessed at
+// agent scope: the workgroups of a layer run on several XCDs, each with an L2 of its own.
+__device__ __forceinline__ void put_partial(const StatsLaunch &st, int64_t partial, int pos, int layer, int n_replicas, double g, double m,
+                                            double (*lds)[kThreads / kWave]) {
+    if (st.counters == nullptr) {
+        if (threadIdx.x == 0) {
+            st.partials[2 * partial] = g;
+            st.partials[2 * partial + 1] = m;
+        }
+        return;
+    }
+    __shared__ int is_last;
+    const int64_t c0 = st.layer_ranges[2 * pos], c1 = st.layer_ranges[2 * pos + 1];
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(st.partials + 2 * partial, g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(st.partials + 2 * partial + 1, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int done = __hip_atomic_fetch_add(st.counters + layer, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        is_last = done + 1 == (int)(c1 - c0);
+    }
+    __syncthreads();
+    if (!is_last) return;
+    sum_partials(st.partials, c0, c1, n_replicas, st.stats + 2 * pos, lds);
+    if (threadIdx.x == 0) __hip_atomic_store(st.counters + layer, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
+}
+
 // ---------------------------------------------------------------------------------------------------------------
 // local update
 // ---------------------------------------------------------------------------------------------------------------

@@ -198,14 +198,14 @@ __device__ __forceinline__ void fused_body(const Streams<GBF16> c, int64_t fo, c
 template <bool A, bool G, bool M, int NR, bool EXACT, class K>
 int dispatch_fused_n(const FusedLaunch &f, const K &k) {
     const int staged = f.n_replicas > kRegReps ? f.n_replicas - kRegReps : 0;
-    const int need = NR == 0 && f.partials ? staged * stage_threads(staged) * 16 : 0;
+    const int need = NR == 0 && f.st.partials ? staged * stage_threads(staged) * 16 : 0;
     const int lds = f.lds_pad > need ? f.lds_pad : need;
     if (f.wire16) {
-        if (f.update_first) return f.partials ? k.template go<A, G, M, NR, EXACT, true, true, true>(lds) : k.template go<A, G, M, NR, EXACT, false, true, true>(lds);
-        return f.partials ? k.template go<A, G, M, NR, EXACT, true, true, false>(lds) : k.template go<A, G, M, NR, EXACT, false, true, false>(lds);
+        if (f.update_first) return f.st.partials ? k.template go<A, G, M, NR, EXACT, true, true, true>(lds) : k.template go<A, G, M, NR, EXACT, false, true, true>(lds);
+        return f.st.partials ? k.template go<A, G, M, NR, EXACT, true, true, false>(lds) : k.template go<A, G, M, NR, EXACT, false, true, false>(lds);
     }
-    if (f.update_first) return f.partials ? k.template go<A, G, M, NR, EXACT, true, false, true>(lds) : k.template go<A, G, M, NR, EXACT, false, false, true>(lds);
-    return f.partials ? k.template go<A, G, M, NR, EXACT, true, false, false>(lds) : k.template go<A, G, M, NR, EXACT, false, false, false>(lds);
+    if (f.update_first) return f.st.partials ? k.template go<A, G, M, NR, EXACT, true, false, true>(lds) : k.template go<A, G, M, NR, EXACT, false, false, true>(lds);
+    return f.st.partials ? k.template go<A, G, M, NR, EXACT, true, false, false>(lds) : k.template go<A, G, M, NR, EXACT, false, false, false>(lds);
 }
 
 template <bool A, bool G, bool M, class K>

@@ -67,6 +67,12 @@ struct MeanChunk {  // partial_average: flat elements [begin, +count), all insid
     int32_t partial;  // where this chunk's partial sums go: its index in flat order, whatever the dispatch order
 };
 
+struct TensorSlot {  // a registered tensor in one slot
+    int64_t flat0;   // first flat index, -1 if it is not scheduled
+    int32_t pos;     // position of its layer in the slot
+    int32_t layer;
+};
+
 // One launch of the fused step over dense arenas: consecutive pieces of the model, each part of a scheduled layer or of a run
 // of unscheduled ones.  Workgroup (x, y) takes chunk x of piece y, counted from the multiple of four at or below the piece's
 // first element; it writes its partial pair at partials[2 * (pbase + x)].
@@ -76,6 +82,7 @@ struct Piece {
     int64_t flat0;  // its flat index, -1 if the piece is not scheduled
     int32_t count;  // elements
     int32_t pbase;
+    int32_t pos, layer;  // position of the layer in the slot, and the layer
 };
 struct DensePass {
     int width;          // chunks of the widest piece; 0: a plain update of elements [begin, end)
@@ -96,8 +103,9 @@ struct SlotTables {
     int64_t n_copy = 0;
     MeanChunk *d_mean = nullptr;
     int64_t n_mean = 0;
-    int32_t *d_layer_ranges = nullptr;     // per layer of the slot: [first, last) mean chunk
-    int64_t *d_tensor_flat_off = nullptr;  // per registered tensor: first flat index in this slot, -1 if unscheduled
+    int32_t *d_layer_ranges = nullptr;     // per layer of the slot: [first, last) mean chunk; behind them, in a slot whose
+                                           // statistics are folded (fold_stats), the layer position of every mean chunk
+    TensorSlot *d_tensor_slot = nullptr;   // per registered tensor
     int32_t *d_fused_ranges = nullptr;     // per layer of the slot: [first, last) update chunk (registration order)
     // dense arenas: per layer of the slot [first, last) index of its workgroups' partials (layers numbered in
     // registration order)
@@ -106,6 +114,15 @@ struct SlotTables {
     std::vector<int32_t> layer_pos;  // [L] layer -> position in this slot, -1 if not scheduled
     int32_t *d_dense_ranges = nullptr;
     std::vector<DensePass> dense_passes;  // dense arenas: the launches of the fused step over the whole model
+};
+
+// How the per-layer statistics of a launch are put together from its workgroups' partial pairs.
+struct StatsLaunch {
+    double *partials;             // nullptr: no statistics
+    const int32_t *layer_ranges;  // per position in the slot [first, last) partial index
+    double *stats;                // [positions][2]
+    int32_t *counters;            // per layer, zero between launches: the layer's last workgroup adds the partials up in the kernel
+                                  // itself; nullptr: a launch of its own follows (launch_stats)
 };
 
 // ---- launchers (ddp_kernels.hip) -------------------------------------------------------------------------------
@@ -117,12 +134,8 @@ struct MeanLaunch {
     float *out;
     const MeanChunk *chunks;
     int64_t n_chunks;
-    double *partials;  // [n_chunks][2] or nullptr when no statistics are wanted
-    double *slice_sums;  // [n_layers][64][2] scratch of the two-stage reduction
-    const int32_t *layer_ranges;  // per layer [first, last) partial index
-    int n_layers;
-    int64_t max_partials_per_layer;
-    double *stats;  // [n_layers][2]
+    StatsLaunch st;
+    const int32_t *chunk_pos;  // with st.counters: per chunk, by its partial index, the position of its layer
     bool nontemporal;
     int lds_pad;
 };
@@ -155,7 +168,7 @@ struct FusedLaunch {
     int kind, grad_dtype;
     bool with_model;
     UpdateScalars s;
-    double *partials;  // nullptr: no statistics
+    StatsLaunch st;
     int lds_pad;
 };
 // ... the table-driven one, over chunks of the update table ...
@@ -163,7 +176,7 @@ struct FusedTable : FusedLaunch {
     const TensorDesc *tensors;
     const UpdateChunk *chunks;
     int64_t n_chunks;
-    const int64_t *tensor_flat_off;
+    const TensorSlot *tensor_slot;
     const int32_t *tensor_chunk_base;
     int chunk_elems;
 };
@@ -229,6 +242,8 @@ struct ddp_ctx {
     std::vector<ddp::SlotTables> slots;
     double *d_partials = nullptr;  // reduction scratch for per-layer statistics: one partial pair per chunk ...
     double *d_slice_sums = nullptr;  // ... followed by 64 slice sums per layer (same allocation)
+    int32_t *d_counters = nullptr;   // ... and a counter per layer, zero between launches (StatsLaunch)
+    int cus = 256;                   // compute units of the device (ddp_create)
     int64_t partials_cap = 0;
     double *static_scratch = nullptr;  // this device's copy of the library's fixed scratch array (ddp_partial_average_static)
     std::string static_scratch_err;    // why it could not be resolved, if it could not

@@ -15,9 +15,9 @@ struct FusedArgs {
     Peers peers;
     const TensorDesc *tensors;
     const UpdateChunk *chunks;
-    const int64_t *tensor_flat_off;     // per tensor: first flat index in this slot, or -1 if not scheduled
+    const TensorSlot *tensor_slot;
     const int32_t *tensor_chunk_base;   // per tensor: index of its first chunk in registration order
-    double *partials;                   // [n_chunks][2], only touched for scheduled chunks
+    StatsLaunch st;                     // partials: [n_chunks][2], only touched for scheduled chunks
     UpdateScalars s;
     int chunk_elems;
 };
@@ -29,23 +29,19 @@ __global__ __launch_bounds__(kThreads, 2) void fused_kernel(const FusedArgs a) {
     __shared__ double lds[2][kThreads / kWave];
     const UpdateChunk ch = a.chunks[blockIdx.x];
     const TensorDesc td = a.tensors[ch.tensor];
-    const int64_t toff = a.tensor_flat_off[ch.tensor];
+    const TensorSlot ts = a.tensor_slot[ch.tensor];
     const Streams<GBF16> c = chunk_streams<GBF16>(td, ch);
-    if (toff < 0) {  // uniform for the workgroup
+    if (ts.flat0 < 0) {  // uniform for the workgroup
         update_body<ADAM, GBF16, MODEL, true, false>(c, a.s);
         return;
     }
     double gsum = 0.0, msum = 0.0;
-    fused_body<ADAM, GBF16, MODEL, NREP, EXACT, STATS, W16, UTS, false>(c, toff + ch.begin, a.peers, a.s, gsum, msum);
+    fused_body<ADAM, GBF16, MODEL, NREP, EXACT, STATS, W16, UTS, false>(c, ts.flat0 + ch.begin, a.peers, a.s, gsum, msum);
     if constexpr (STATS) {
         const double gt = block_sum(gsum, lds[0]);
         const double mt = block_sum(msum, lds[1]);
-        if (threadIdx.x == 0) {
-            // chunks end at the parameters' 16-byte boundaries: chunk c of a tensor begins 0..3 elements before c * chunk_elems
-            const int64_t pi = (int64_t)a.tensor_chunk_base[ch.tensor] + (ch.begin + 3) / a.chunk_elems;
-            a.partials[2 * pi] = gt;
-            a.partials[2 * pi + 1] = mt;
-        }
+        // chunks end at the parameters' 16-byte boundaries: chunk c of a tensor begins 0..3 elements before c * chunk_elems
+        put_partial(a.st, (int64_t)a.tensor_chunk_base[ch.tensor] + (ch.begin + 3) / a.chunk_elems, ts.pos, ts.layer, a.peers.n, gt, mt, lds);
     }
 }
 
@@ -77,9 +73,9 @@ int DDP_FUSED_HALF(const FusedTable &f, void *stream) {
     fill_peers(a.peers, f);
     a.tensors = f.tensors;
     a.chunks = f.chunks;
-    a.tensor_flat_off = f.tensor_flat_off;
+    a.tensor_slot = f.tensor_slot;
     a.tensor_chunk_base = f.tensor_chunk_base;
-    a.partials = f.partials;
+    a.st = f.st;
     a.s = f.s;
     a.chunk_elems = f.chunk_elems;
     return dispatch_fused<DDP_FUSED_ADAM != 0>(f, LaunchTable{f, a, stream});

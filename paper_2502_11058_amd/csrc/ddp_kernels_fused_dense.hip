@@ -13,7 +13,7 @@ namespace {
 struct FusedDenseArgs {
     Peers peers;
     DenseLaunch d;
-    double *partials;
+    StatsLaunch st;
     UpdateScalars s;
     Piece pieces[kMaxPieces];
 };
@@ -49,11 +49,7 @@ __global__ __launch_bounds__(kThreads, 2) void fused_dense_kernel(const FusedDen
     if constexpr (STATS) {
         const double gt = block_sum(gsum, lds[0]);
         const double mt = block_sum(msum, lds[1]);
-        if (threadIdx.x == 0) {
-            const int64_t pi = (int64_t)t.pbase + blockIdx.x;
-            a.partials[2 * pi] = gt;
-            a.partials[2 * pi + 1] = mt;
-        }
+        put_partial(a.st, (int64_t)t.pbase + blockIdx.x, t.pos, t.layer, a.peers.n, gt, mt, lds);
     }
 }
 
@@ -79,7 +75,7 @@ int DDP_FUSED_HALF(const FusedDense &f, void *stream) {
     FusedDenseArgs a;
     fill_peers(a.peers, f);
     a.d = f.d;
-    a.partials = f.partials;
+    a.st = f.st;
     a.s = f.s;
     for (int i = 0; i < f.pass->n_pieces; ++i) a.pieces[i] = f.pass->pieces[i];
     return dispatch_fused<DDP_FUSED_ADAM != 0>(f, LaunchDense{f, a, stream});

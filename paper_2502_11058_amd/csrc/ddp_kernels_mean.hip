@@ -10,7 +10,8 @@ struct MeanArgs {
     const void *x[DDP_MAX_REPLICAS];  // fp32 or bf16 flat buffers, rank order
     float *out;
     const MeanChunk *chunks;
-    double *partials;
+    StatsLaunch st;
+    const int32_t *chunk_pos;
     float inv_n;
     int n;
     int stage_threads;  // run-time replica count with statistics: threads that take part in the vector loop
@@ -159,10 +160,8 @@ __global__ __launch_bounds__(kThreads) void mean_kernel(const MeanArgs a) {
     if constexpr (STATS) {
         const double g = block_sum(gsum, lds[0]);
         const double m = block_sum(msum, lds[1]);
-        if (tid == 0) {
-            a.partials[2 * (int64_t)ch.partial] = g;
-            a.partials[2 * (int64_t)ch.partial + 1] = m;
-        }
+        const int pos = a.st.counters ? a.chunk_pos[ch.partial] : 0;
+        put_partial(a.st, ch.partial, pos, pos, nrep, g, m, lds);
     }
 }
 
@@ -209,35 +208,24 @@ __global__ __launch_bounds__(kThreads) void stats_single_kernel(const double *__
                                                                 int n_replicas, double *__restrict__ stats) {
     __shared__ double lds[2][kThreads / kWave];
     const int l = blockIdx.x;
-    const int64_t c0 = ranges[2 * l], c1 = ranges[2 * l + 1];
-    double g = 0.0, m = 0.0;
-    for (int64_t c = c0 + (int64_t)threadIdx.x; c < c1; c += kThreads) {
-        g += partials[2 * c];
-        m += partials[2 * c + 1];
-    }
-    g = block_sum(g, lds[0]);
-    m = block_sum(m, lds[1]);
-    if (threadIdx.x == 0) {
-        stats[2 * l] = g / (double)n_replicas;
-        stats[2 * l + 1] = m;
-    }
+    sum_partials(partials, ranges[2 * l], ranges[2 * l + 1], n_replicas, stats + 2 * l, lds);
 }
 
 // Dynamic LDS of a launch: the residency pad, or the staging area of the run-time replica count if that is larger.
 template <int NREP>
 int mean_lds(const MeanLaunch &a) {
     const int staged = a.n_replicas > kRegReps ? a.n_replicas - kRegReps : 0;
-    const int need = NREP == 0 && a.partials ? staged * stage_threads(staged) * 16 : 0;
+    const int need = NREP == 0 && a.st.partials ? staged * stage_threads(staged) * 16 : 0;
     return a.lds_pad > need ? a.lds_pad : need;
 }
 
 template <int NREP, bool EXACT>
 int launch_mean_n(const MeanArgs &ma, const MeanLaunch &a, void *stream) {
     if (a.wire16) {
-        if (a.partials) return launch(mean_kernel<NREP, EXACT, true, true, true>, a.n_chunks, stream, mean_lds<NREP>(a), ma);
+        if (a.st.partials) return launch(mean_kernel<NREP, EXACT, true, true, true>, a.n_chunks, stream, mean_lds<NREP>(a), ma);
         return launch(mean_kernel<NREP, EXACT, false, true, true>, a.n_chunks, stream, a.lds_pad, ma);
     }
-    if (a.partials) return a.nontemporal ? launch(mean_kernel<NREP, EXACT, true, true, false>, a.n_chunks, stream, mean_lds<NREP>(a), ma)
+    if (a.st.partials) return a.nontemporal ? launch(mean_kernel<NREP, EXACT, true, true, false>, a.n_chunks, stream, mean_lds<NREP>(a), ma)
                                          : launch(mean_kernel<NREP, EXACT, true, false, false>, a.n_chunks, stream, mean_lds<NREP>(a), ma);
     return a.nontemporal ? launch(mean_kernel<NREP, EXACT, false, true, false>, a.n_chunks, stream, a.lds_pad, ma)
                          : launch(mean_kernel<NREP, EXACT, false, false, false>, a.n_chunks, stream, a.lds_pad, ma);
@@ -267,7 +255,8 @@ int launch_mean(const MeanLaunch &a, void *stream) {
     for (int k = 0; k < a.n_replicas; ++k) ma.x[k] = a.x[k];
     ma.out = a.out;
     ma.chunks = a.chunks;
-    ma.partials = a.partials;
+    ma.st = a.st;
+    ma.chunk_pos = a.chunk_pos;
     ma.inv_n = a.inv_n;
     ma.n = a.n_replicas;
     ma.stage_threads = stage_threads(a.n_replicas > kRegReps ? a.n_replicas - kRegReps : 0);   // the replicas beyond the registers are staged
@@ -292,8 +281,7 @@ int launch_mean(const MeanLaunch &a, void *stream) {
         case 32: rc = launch_mean_n<32, true>(ma, a, stream); break;
         default: rc = a.n_replicas < 32 ? launch_mean_n<32, false>(ma, a, stream) : launch_mean_n<0, false>(ma, a, stream); break;
     }
-    if (rc != 0 || !a.partials) return rc;
-    return launch_stats(a.partials, a.slice_sums, a.layer_ranges, a.n_layers, a.n_replicas, a.stats, a.max_partials_per_layer, stream);
+    return rc;
 }
 
 }  // namespace ddp

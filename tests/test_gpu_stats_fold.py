@@ -1,0 +1,75 @@
+"""Statistics that the workgroups put together themselves (launches of about one workgroup per CU) and those of a launch of
+their own, on both sides of the rule's line: against the oracle, the same bits on every repetition, the same bits for the
+allocation-free entry point (which never folds), and through a captured graph that is replayed between eager calls."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2502_11058_amd import workloads as W
+from paper_2502_11058_amd.harness import DeviceReplica
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("per_layer", [[1], [3, 5], [64] * 4, [319], [320], [321], [200, 1, 119], [1] * 40, [900, 2]])
+def test_both_sides_of_the_line(oracle, per_layer):
+    assert torch.cuda.is_available(), "no GPU visible"
+    n = 4
+    ts = [W.TensorSpec(f"l{l}", l, 1024 * k - (l % 3)) for l, k in enumerate(per_layer)]
+    w = W.Workload(f"fold{len(per_layer)}_{per_layer[0]}", ts, n_replicas=n, period=1, optimizer="sgdm", param_dtype="f32", lr=1e-2,
+                   sigma_drift=1e-3, policy="every")
+    rep = DeviceReplica(w, 0, options={"update_chunk": 1024, "mean_chunk": 1024})
+    rep.init_params()
+    rep.fill_grads(0)
+    wk = oracle.Worker(rep.layer_of, [t.cpu().numpy() for t in rep.sync], "sgdm", dict(lr=w.lr, momentum=w.momentum), False)
+    flat, off, order, total = wk.pack_slot(rep.sets[0])
+    local = torch.from_numpy(flat).to(rep.dev)
+    rep.fill_peers_from(local, 0, total)
+    reps = [flat] + [p[:total].cpu().numpy() for p in rep.peers]
+    mean = oracle.mean(reps)
+    ref = np.array([v for b, e in wk.layer_ranges(rep.sets[0], off, order) for v in oracle.layer_stats(reps, mean, b, e)])
+    k = 2 * len(per_layer)
+    out = torch.zeros_like(rep.flat)
+    src = torch.zeros_like(rep.flat)
+    src[:total] = local
+
+    def call(fn):
+        rep.stats.fill_(-1.0)
+        fn(0, src, rep._peers_arr, n, 0, out, rep.stats)
+        return rep.stats.cpu().numpy()[:k].copy()
+
+    first = call(rep.ctx.ddp_partial_average)
+    np.testing.assert_allclose(first, ref, rtol=1e-10)
+    for _ in range(3):
+        assert np.array_equal(call(rep.ctx.ddp_partial_average), first)
+    assert np.array_equal(call(rep.ctx.ddp_partial_average_static), first)
+
+    g = torch.cuda.CUDAGraph()
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        with torch.cuda.graph(g, stream=s):
+            rep.ctx.ddp_partial_average(0, src, rep._peers_arr, n, 0, out, rep.stats, s)
+    for _ in range(3):
+        rep.stats.fill_(-1.0)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(rep.stats.cpu().numpy()[:k], first)
+        assert np.array_equal(call(rep.ctx.ddp_partial_average), first)
+
+    saved = [a.clone() for a in (rep.a_sync, rep.a_s0)]
+    seen = []
+    for layers in (None, None, 1, 3):                              # whole model twice, then range by range
+        rep.a_sync.copy_(saved[0])
+        rep.a_s0.copy_(saved[1])
+        rep.stats.fill_(-1.0)
+        if layers is None:
+            rep.fused_step(0)
+        else:
+            for lo in range(0, len(per_layer), layers):
+                rep.ctx.ddp_fused_sync_update_layers(0, lo, min(layers, len(per_layer) - lo), rep.peers, 0, 0, n, 0, rep.stats,
+                                                     rep.opt_struct(1))
+        seen.append(rep.stats.cpu().numpy()[:k].copy())
+        np.testing.assert_allclose(seen[-1], ref, rtol=1e-10)
+    assert all(np.array_equal(x, seen[0]) for x in seen)
+    rep.close()
