@@ -141,7 +141,9 @@ int ddp_destroy(ddp_ctx *ctx);
  *                                               requesting (not using) dynamic LDS: LDS-per-CU / k bytes per workgroup, from the
  *                                               sizes the device reports, so the cap holds on parts with another LDS size; a
  *                                               kernel that needs LDS of its own gets the larger of the two.  The bf16-wire
- *                                               average runs at twice mean_wg_per_cu (half the bytes per workgroup in flight)
+ *                                               average runs at twice mean_wg_per_cu (half the bytes per workgroup in flight).
+ *                                               Unless the caller sets it, averages of up to 4 replicas run at 3 and of up to
+ *                                               2 at 4: less would be in flight than the memory needs
  *   "update_lds", "mean_lds", "copy_lds"        0..65536: the same cap given directly as bytes of LDS per workgroup (for sweeps)
  *   "nontemporal"                               0/1 (default 1): streaming cache hints on loads and stores
  *   "dense_path"                                0/1 (default 1): when the registered tensors lie back to back in every

@@ -284,11 +284,13 @@ extern "C" int ddp_set_option(ddp_ctx *ctx, const char *name, int64_t value) {
         }
         if (k == "update_wg_per_cu" || k == "mean_wg_per_cu" || k == "copy_wg_per_cu") {
             if (value < 0 || value > 32) return fail(ctx, DDP_EINVAL, "ddp_set_option: workgroups per CU must be in [0, 32] (0 = no cap)");
+            ctx->mean_lds_set = ctx->mean_lds_set || k == "mean_wg_per_cu";
             (k == "update_wg_per_cu" ? ctx->update_lds : k == "mean_wg_per_cu" ? ctx->mean_lds : ctx->copy_lds) = residency_pad(ctx, (int)value);
             return DDP_OK;
         }
         if (k == "update_lds" || k == "mean_lds" || k == "copy_lds") {
             if (value < 0 || value > 65536) return fail(ctx, DDP_EINVAL, "ddp_set_option: LDS pad must be in [0, 65536] bytes");
+            ctx->mean_lds_set = ctx->mean_lds_set || k == "mean_lds";
             (k == "update_lds" ? ctx->update_lds : k == "mean_lds" ? ctx->mean_lds : ctx->copy_lds) = (int)value;
             return DDP_OK;
         }
@@ -677,8 +679,13 @@ int ddp::partial_average_impl(ddp_ctx *ctx, const char *who, bool wire16, int sl
     a.st = {layer_stats ? partials : nullptr, s->d_layer_ranges, layer_stats, fold ? ctx->d_counters : nullptr};
     a.chunk_pos = s->d_layer_ranges + 2 * s->layers.size();
     a.nontemporal = ctx->nontemporal;
+    // Two workgroups per CU pace the requests of many replicas best, but few replicas leave too little in flight (TinyLlama-1.1B,
+    // us with 2 / 3 / 4 per CU: N = 2 662 / 539 / 502, N = 4 964 / 837 / 895, N = 6 1207 / 1256 / 1280; GPT-2 small N = 2
+    // 73 / 65 / 61, N = 4 108 / 93 / 96; the same line with a bf16 wire).
+    int pad = ctx->mean_lds;
+    if (!ctx->mean_lds_set && N <= 4) pad = residency_pad(ctx, N <= 2 ? 4 : 3);
     // bf16 replicas put half the bytes per workgroup in flight: half the pad, twice the workgroups per CU
-    a.lds_pad = wire16 ? ctx->mean_lds / 2 : ctx->mean_lds;
+    a.lds_pad = wire16 ? pad / 2 : pad;
     rc = launch_mean(a, stream);
     if (rc == 0 && layer_stats && !fold)
         rc = launch_stats(partials, slice_sums, s->d_layer_ranges, (int)s->layers.size(), N, layer_stats, s->max_mean_partials, stream);

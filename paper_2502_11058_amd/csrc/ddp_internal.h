@@ -220,6 +220,7 @@ struct ddp_ctx {
     int dispatch_ways = 1;
     int lds_per_cu = 163840, lds_per_wg_max = 65536;  // what the device reports (ddp_create); gfx950 values until then
     int update_lds = 64512, mean_lds = 64512, copy_lds = 26112;  // dynamic-LDS pad per workgroup: caps residency per CU (2 / 2 / 6)
+    bool mean_lds_set = false;  // the average's residency was given by the caller, whatever the replica count
     // model
     bool registered = false;
     int L = 0, T = 0;
