@@ -879,8 +879,11 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     f.s = s;
     f.lds_pad = ctx->update_lds;
     const bool dense = ctx->dense && ctx->dense_path;
-    const bool fold = any && fold_stats(ctx, c1 - c0);
     const int32_t *ranges = dense ? st->d_dense_ranges : st->d_fused_ranges;
+    const int64_t max_partials = dense ? st->max_dense_partials : st->max_fused_partials;
+    // One order of summation for a slot, whatever range the call has: the workgroups add a layer's partials up in the order of
+    // the one-launch reduction, so they do it only in slots that this reduction serves.
+    const bool fold = any && max_partials <= kStatSingleMax && fold_stats(ctx, c1 - c0);
     f.st = {any ? ctx->d_partials : nullptr, ranges, layer_stats, fold ? ctx->d_counters : nullptr};
     if (dense) {
         DensePass one;
@@ -905,8 +908,8 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
         int j = i;
         while (inside(j)) ++j;
         if (j > i)
-            rc = launch_stats(f.st.partials, ctx->d_slice_sums + (int64_t)i * 2 * kStatSlices, ranges + 2 * i, j - i, N, layer_stats + 2 * i,
-                              dense ? st->max_dense_partials : st->max_fused_partials, stream);
+            rc = launch_stats(f.st.partials, ctx->d_slice_sums + (int64_t)i * 2 * kStatSlices, ranges + 2 * i, j - i, N, layer_stats + 2 * i, max_partials,
+                              stream);
         i = j + 1;
     }
     return after_launch(ctx, who, rc);

@@ -73,3 +73,36 @@ def test_both_sides_of_the_line(oracle, per_layer):
         np.testing.assert_allclose(seen[-1], ref, rtol=1e-10)
     assert all(np.array_equal(x, seen[0]) for x in seen)
     rep.close()
+
+
+@pytest.mark.parametrize("dense_path", [1, 0])
+@pytest.mark.parametrize("per_layer", [[60, 4097, 3, 120, 7, 300], [60, 4096, 3, 120, 7, 300]])
+def test_small_layers_beside_a_large_one(per_layer, dense_path):
+    """One layer on either side of the number of partials from which a slot's statistics take the two-stage reduction: the
+    small layers' statistics have the same bits from the whole-model call and from every partition into ranges."""
+    assert torch.cuda.is_available(), "no GPU visible"
+    ts = [W.TensorSpec(f"l{l}", l, 1024 * k) for l, k in enumerate(per_layer)]
+    w = W.Workload(f"order{per_layer[1]}", ts, n_replicas=3, period=1, optimizer="sgdm", param_dtype="f32", lr=1e-2, sigma_drift=1e-3,
+                   policy="every")
+    rep = DeviceReplica(w, 0, options={"update_chunk": 1024, "mean_chunk": 1024, "dense_path": dense_path})
+    rep.init_params()
+    rep.fill_grads(0)
+    S = rep.sets[0]
+    flat = torch.cat([rep.sync[l] for l in S])
+    rep.fill_peers_from(flat, 0, flat.numel())
+    saved = [a.clone() for a in (rep.a_sync, rep.a_s0)]
+    seen = []
+    for layers in (None, 1, 2, 3, len(per_layer)):
+        rep.a_sync.copy_(saved[0])
+        rep.a_s0.copy_(saved[1])
+        rep.stats.fill_(-1.0)
+        if layers is None:
+            rep.fused_step(0)
+        else:
+            for lo in range(0, len(per_layer), layers):
+                rep.ctx.ddp_fused_sync_update_layers(0, lo, min(layers, len(per_layer) - lo), rep.peers, 0, 0, 3, 0, rep.stats,
+                                                     rep.opt_struct(1))
+        seen.append(rep.stats.cpu().numpy()[:2 * len(per_layer)].copy())
+        assert (seen[-1] >= 0.0).all()
+        assert np.array_equal(seen[-1], seen[0]), layers
+    rep.close()
