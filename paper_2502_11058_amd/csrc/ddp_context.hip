@@ -9,7 +9,7 @@
 #include <string>
 #include <vector>
 
-#include "ddp_internal.h"
+#include "ddp_plan.h"
 
 namespace ddp {
 
@@ -133,87 +133,8 @@ static int residency_pad(const ddp_ctx *c, int wg_per_cu) {
 // 7.3 us takes 10.7, with 3500 one of 48 takes 178.  Hence: not much more than one workgroup per CU.
 static bool fold_stats(const ddp_ctx *ctx, int64_t workgroups) { return 4 * workgroups <= 5 * (int64_t)ctx->cus; }
 
-// Workgroups of the table-free fused kernel over elements [e0, e1) of the arenas: chunks counted from the multiple of four at
-// or below e0, where every stream is vector-aligned.
-static int64_t dense_workgroups(int64_t e0, int64_t e1, int64_t chunk) { return (e1 - e0 / 4 * 4 + chunk - 1) / chunk; }
-
-// The launches of the fused step over layers [first, first + count) of dense arenas.  A segment is a scheduled layer or a run
-// of unscheduled ones.  Where segments average fewer than 2^25 elements all of them share one launch (one per kMaxSegments),
-// cut into pieces of about the same width: a launch of its own costs a segment some 3 us of ramp (GPT-2 small, AdamW, N = 8,
-// 20 M per segment: 701 us in one launch, 726 in six; 12 layers of 512^2: 25 against 47).  Larger ones get a launch each, the
-// unscheduled ones that of the plain update, whose workgroups start sooner (Llama-2-7B blocks, 380 M per segment: 11.8 ms in
-// one launch, 11.5 in five; about equal at 40 M).
-// (One layer at a time, as backward hooks call it, skips the search: one_layer_pass.)
-static std::vector<DensePass> plan_dense(const ddp_ctx *ctx, const SlotTables &st, int first, int count) {
-    constexpr int kMaxSegments = 20;
-    const int64_t chunk = ctx->update_chunk;
-    auto elem0 = [&](int l) { return ctx->tensor_elem_off[(size_t)ctx->layer_first_tensor[(size_t)l]]; };
-    struct Segment {
-        int64_t begin, end, flat0, pbase, wg;
-        int32_t pos, layer;
-    };
-    std::vector<Segment> all;
-    for (int l = first; l < first + count;) {
-        const int i = st.layer_pos[(size_t)l];
-        int m = l + 1;
-        while (i < 0 && m < first + count && st.layer_pos[(size_t)m] < 0) ++m;
-        all.push_back({elem0(l), elem0(m), i < 0 ? -1 : st.layer_begin[(size_t)i], i < 0 ? 0 : st.dense_ranges[2 * (size_t)i],
-                       dense_workgroups(elem0(l), elem0(m), chunk), i, l});
-        l = m;
-    }
-    std::vector<DensePass> passes;
-    if (all.empty()) return passes;
-    const bool apart = (all.back().end - all[0].begin) / (int64_t)all.size() >= (int64_t)1 << 25;
-    for (size_t i = 0; i < all.size();) {
-        const Segment *seg = &all[i];
-        const int n = (int)std::min<size_t>(apart ? 1 : kMaxSegments, all.size() - i);
-        i += (size_t)n;
-        passes.emplace_back();
-        DensePass &p = passes.back();
-        p.width = p.n_pieces = 0;
-        p.begin = seg[0].begin;
-        p.end = seg[n - 1].end;
-        if (n == 1 && seg[0].flat0 < 0 && seg[0].begin % 4 == 0) continue;
-        // the width that leaves the fewest workgroups without work among those that cut some segment evenly; the widest that
-        // 32-bit indexes allow makes at most one piece of every 2^31 elements
-        const int64_t widest = INT32_MAX / chunk - 1;
-        int64_t width = widest, best = INT64_MAX;
-        for (int k = 0; k < n; ++k)
-            for (int64_t parts : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24}) {
-                const int64_t w = (seg[k].wg + parts - 1) / parts;
-                if (w > widest) continue;
-                int64_t rows = 0;
-                for (int j = 0; j < n; ++j) rows += (seg[j].wg + w - 1) / w;
-                if (rows <= kMaxPieces && (rows * w < best || (rows * w == best && w > width))) {
-                    best = rows * w;
-                    width = w;
-                }
-            }
-        p.width = (int)width;
-        for (int k = 0; k < n; ++k)
-            for (int64_t b = 0; b < seg[k].wg; b += width) {
-                const int64_t base = seg[k].begin / 4 * 4, at = b == 0 ? seg[k].begin : base + b * chunk;
-                const int64_t end = std::min(seg[k].end, base + (b + width) * chunk);
-                p.pieces[p.n_pieces++] = {at, seg[k].flat0 < 0 ? -1 : seg[k].flat0 + (at - seg[k].begin), (int32_t)(end - at),
-                                          (int32_t)(seg[k].pbase + b), seg[k].pos, seg[k].layer};
-            }
-    }
-    return passes;
-}
-
-static bool one_layer_pass(const ddp_ctx *ctx, const SlotTables &st, int l, DensePass &p) {
-    const int64_t begin = ctx->tensor_elem_off[(size_t)ctx->layer_first_tensor[(size_t)l]];
-    const int64_t end = ctx->tensor_elem_off[(size_t)ctx->layer_first_tensor[(size_t)l + 1]];
-    const int64_t wg = dense_workgroups(begin, end, ctx->update_chunk);
-    if (wg > INT32_MAX / ctx->update_chunk - 1) return false;
-    const int i = st.layer_pos[(size_t)l];
-    p.begin = begin;
-    p.end = end;
-    p.width = i < 0 && begin % 4 == 0 ? 0 : (int)wg;
-    p.n_pieces = 1;
-    p.pieces[0] = {begin, i < 0 ? -1 : st.layer_begin[(size_t)i], (int32_t)(end - begin), i < 0 ? 0 : st.dense_ranges[2 * (size_t)i], i, l};
-    return true;
-}
+// First element of layer l in registration order (l = L: the number of elements).
+static int64_t layer_elem0(const ddp_ctx *ctx, int l) { return ctx->tensor_elem_off[(size_t)ctx->layer_first_tensor[(size_t)l]]; }
 
 static bool aligned(const void *p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
 
@@ -434,9 +355,7 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
         // table has chunks, so the reduction scratch sized for the table covers them)
         std::vector<int64_t> dense_wg_base((size_t)ctx->L + 1, 0);
         for (int l = 0; l < ctx->L; ++l) {
-            const int64_t e0 = ctx->tensor_elem_off[(size_t)ctx->layer_first_tensor[(size_t)l]];
-            const int64_t e1 = ctx->tensor_elem_off[(size_t)ctx->layer_first_tensor[(size_t)l + 1]];
-            dense_wg_base[(size_t)l + 1] = dense_wg_base[(size_t)l] + dense_workgroups(e0, e1, ctx->update_chunk);
+            dense_wg_base[(size_t)l + 1] = dense_wg_base[(size_t)l] + dense_workgroups(layer_elem0(ctx, l), layer_elem0(ctx, l + 1), ctx->update_chunk);
         }
         int64_t max_mean_chunks = 0;
         for (int s = 0; s < H; ++s) {
@@ -507,7 +426,7 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
             if (rc == DDP_OK) rc = upload(ctx, tslot, &st.d_tensor_slot);
             if (rc == DDP_OK) rc = upload(ctx, fused_ranges, &st.d_fused_ranges);
             if (rc == DDP_OK) rc = upload(ctx, st.dense_ranges, &st.d_dense_ranges);
-            if (ctx->dense) st.dense_passes = plan_dense(ctx, st, 0, ctx->L);
+            if (ctx->dense) st.dense_passes = plan_dense(st, ctx->L, [&](int l) { return layer_elem0(ctx, l); }, ctx->update_chunk);
             if (rc != DDP_OK) {
                 for (auto &x : slots) free_slot(x);
                 return rc;
@@ -764,8 +683,7 @@ static int layer_chunk_range(ddp_ctx *ctx, const char *who, int first, int count
 // allows it and the range starts on a vector boundary.
 static bool dense_range(const ddp_ctx *ctx, int first, int count, DenseLaunch &d) {
     if (!ctx->dense || !ctx->dense_path) return false;
-    const int64_t e0 = ctx->tensor_elem_off[(size_t)ctx->layer_first_tensor[(size_t)first]];
-    const int64_t e1 = ctx->tensor_elem_off[(size_t)ctx->layer_first_tensor[(size_t)(first + count)]];
+    const int64_t e0 = layer_elem0(ctx, first), e1 = layer_elem0(ctx, first + count);
     if (e0 % 4 != 0) return false;
     const TensorDesc &t0 = ctx->tensors[0];
     d.p = t0.sync + e0;
@@ -810,15 +728,22 @@ extern "C" int ddp_local_update_layers(ddp_ctx *ctx, int layer_first, int layer_
     });
 }
 
-// The kernels of the fused step over a model registered as dense arenas.
-static int fused_dense(const ddp_ctx *ctx, const DensePass *passes, size_t n, const FusedLaunch &common, void *stream) {
+// The kernels of the fused step over layers [first, first + count) of a model registered as dense arenas.
+static int fused_dense(const ddp_ctx *ctx, const SlotTables &st, int first, int count, const FusedLaunch &common, void *stream) {
+    const int64_t e0 = layer_elem0(ctx, first), e1 = layer_elem0(ctx, first + count);
     FusedDense f;
     static_cast<FusedLaunch &>(f) = common;
     const TensorDesc &t0 = ctx->tensors[0];
     f.d = {t0.grad, t0.sync, t0.state0, t0.state1, t0.model, 0, (int)ctx->update_chunk};
     int rc = 0;
-    for (size_t i = 0; i < n && rc == 0; ++i) {
-        f.pass = &passes[i];
+    auto at = std::upper_bound(st.dense_passes.begin(), st.dense_passes.end(), e0, [](int64_t e, const DensePass &p) { return e < p.end; });
+    for (; at != st.dense_passes.end() && at->begin < e1 && rc == 0; ++at) {
+        DensePass part;
+        f.pass = &*at;
+        if (at->begin < e0 || at->end > e1) {
+            clip_pass(*at, e0, e1, ctx->update_chunk, part);
+            f.pass = &part;
+        }
         if (f.pass->width > 0) {
             rc = launch_fused_dense(f, stream);
             continue;
@@ -878,7 +803,7 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     f.with_model = ctx->param_dtype == DDP_BF16;
     f.s = s;
     f.lds_pad = ctx->update_lds;
-    const bool dense = ctx->dense && ctx->dense_path;
+    const bool dense = ctx->dense_path && !st->dense_passes.empty();
     const int32_t *ranges = dense ? st->d_dense_ranges : st->d_fused_ranges;
     const int64_t max_partials = dense ? st->max_dense_partials : st->max_fused_partials;
     // One order of summation for a slot, whatever range the call has: the workgroups add a layer's partials up in the order of
@@ -886,15 +811,7 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     const bool fold = any && max_partials <= kStatSingleMax && fold_stats(ctx, c1 - c0);
     f.st = {any ? ctx->d_partials : nullptr, ranges, layer_stats, fold ? ctx->d_counters : nullptr};
     if (dense) {
-        DensePass one;
-        if (whole) {
-            rc = fused_dense(ctx, st->dense_passes.data(), st->dense_passes.size(), f, stream);
-        } else if (count == 1 && one_layer_pass(ctx, *st, first, one)) {
-            rc = fused_dense(ctx, &one, 1, f, stream);
-        } else {
-            const std::vector<DensePass> passes = plan_dense(ctx, *st, first, count);
-            rc = fused_dense(ctx, passes.data(), passes.size(), f, stream);
-        }
+        rc = fused_dense(ctx, *st, first, count, f, stream);
     } else {
         f.tensors = ctx->d_tensors;
         f.chunks = ctx->d_update + c0;
