@@ -28,12 +28,17 @@ inline void add_pieces(DensePass &p, int64_t begin, int64_t end, int64_t flat0, 
 }
 
 // The launches over the whole model of L layers, layer l being elements [elem0(l), elem0(l + 1)) of the arenas.  A segment is a
-// scheduled layer or a run of unscheduled ones.  Where segments average fewer than 2^25 elements all of them share one launch
-// (one per kMaxSegments), cut into pieces of about the same width: a launch of its own costs a segment some 3 us of ramp (GPT-2
-// small, AdamW, N = 8, 20 M per segment: 701 us in one launch, 726 in six; 12 layers of 512^2: 25 against 47).  Larger ones get
-// a launch each, the unscheduled ones that of the plain update, whose workgroups start sooner (Llama-2-7B blocks, 380 M per
-// segment: 11.8 ms in one launch, 11.5 in five; about equal at 40 M), and small ones between them share.  Empty where a launch would need more than kMaxPieces
-// pieces (segments of tens of 2^31 elements): such a slot takes the table.
+// scheduled layer or a run of unscheduled ones.
+// Segments of kAlone elements and more get a launch each, the unscheduled ones that of the plain update, whose workgroups start
+// sooner; neighbours below that share one, cut into pieces of about the same width, because a launch of its own costs a segment
+// some 3 us of ramp.  Shared against own launches, N = 2 / 4 / 8: 20 layers of 10 M 0.94 / 0.95 / 0.92 of the time, of 20 M
+// 0.99 / 1.00 / 0.99 (8 of them 0.98 / 0.98 / 0.96, 40 of them 0.99 / 1.02 / 1.02), of 25 M 1.00 / 1.01 / 1.00, of 30 M
+// 1.00 / 1.03 / 1.03: the line is where it breaks even.
+// A launch takes kMaxSegments; where that makes several and the model is small, the slot takes the table, whose single launch
+// starts its workgroups later but is one (no plan is made; ranges of layers take the table too, so that the statistics of a slot
+// have one grouping).  Pieces against the table in us, N = 4: 400 layers of 1000 elements 83 / 8, 21 of 64 K 17.0 / 12.5, of
+// 256 K 37.9 / 34.3, of 1 M 117 / 115; N = 2: 21 of 1 M 126 / 129, 40 of 4 M 836 / 868.
+// No plan either where a launch would need more than kMaxPieces pieces.
 template <class Elem0>
 std::vector<DensePass> plan_dense(const SlotTables &st, int L, Elem0 &&elem0, int64_t chunk) {
     constexpr int kMaxSegments = 20;
@@ -52,14 +57,20 @@ std::vector<DensePass> plan_dense(const SlotTables &st, int L, Elem0 &&elem0, in
     }
     std::vector<DensePass> passes;
     if (all.empty()) return passes;
-    constexpr int64_t kApart = (int64_t)1 << 25;
-    const bool apart = (all.back().end - all[0].begin) / (int64_t)all.size() >= kApart;
-    auto alone = [&](size_t k) { return apart && all[k].end - all[k].begin >= kApart; };
+    constexpr int64_t kAlone = (int64_t)3 << 23, kPerLaunch = (int64_t)1 << 24;  // 25 M; elements that a launch more is worth
+    auto group = [&](size_t k) {  // segments that share the launch of segment k, the first one of it
+        size_t n = 1;
+        auto large = [&](size_t j) { return all[j].end - all[j].begin >= kAlone; };
+        while (!large(k) && n < kMaxSegments && k + n < all.size() && !large(k + n)) ++n;
+        return n;
+    };
+    int64_t shared = 0;
+    for (size_t k = 0; k < all.size(); k += group(k)) shared += all[k].end - all[k].begin < kAlone;
+    if (all.back().end - all[0].begin < (shared - 1) * kPerLaunch) return passes;
     const int64_t widest = widest_piece(chunk);
     for (size_t i = 0; i < all.size();) {
         const Segment *seg = &all[i];
-        int n = 1;
-        while (!alone(i) && n < kMaxSegments && i + (size_t)n < all.size() && !alone(i + (size_t)n)) ++n;
+        const int n = (int)group(i);
         i += (size_t)n;
         int64_t least = 0;
         for (int k = 0; k < n; ++k) least += (seg[k].wg + widest - 1) / widest;

@@ -151,6 +151,18 @@ int main(int argc, char **argv) {
         for (int first = 0; first < 9; ++first)
             for (int count = 1; first + count <= 9; ++count) check_call(u, first, count);
     }
+    // the number of launches, on both sides of each line; 0: the table's single one
+    auto launches = [&](std::vector<int64_t> sizes) {
+        std::vector<int> order;
+        for (int l = (int)sizes.size() - 1; l >= 0; --l) order.push_back(l);
+        return (int)make(sizes, order, 2048).passes.size();
+    };
+    auto layers = [](size_t n, int64_t size) { return std::vector<int64_t>(n, size); };
+    const int64_t large = (int64_t)3 << 23;
+    CHECK(launches(layers(20, 1)) == 1 && launches(layers(21, 1)) == 0 && launches(layers(400, 1000)) == 0);
+    CHECK(launches(layers(32, 1 << 19)) == 2 && launches(layers(32, (1 << 19) - 1)) == 0);
+    CHECK(launches(layers(20, large - 1)) == 1 && launches(layers(20, large)) == 20);
+    CHECK(launches({large, 5, 7, large, 9}) == 4 && launches({5, large, 7}) == 3 && launches({5, large - 1, 7, large - 1, 9}) == 1);
     // more pieces of 2^31 elements than a launch takes: no plan (the slot takes the table), and nothing written out of range
     CHECK(make({(int64_t)1 << 37, 5}, {1, 0}, 2048 * 64).passes.empty());
     CHECK(make({5, (int64_t)1 << 37}, {0}, 2048 * 64).passes.empty());

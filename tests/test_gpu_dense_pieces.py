@@ -2,8 +2,10 @@
 of one element to several chunks, odd starts, one layer much wider than the rest, all layers scheduled, every other one, or
 none; whole-model calls and ranges of layers.  Every element against the oracle, bit for bit."""
 import pytest
+import torch
 
 from paper_2502_11058_amd import workloads as W
+from paper_2502_11058_amd.harness import DeviceReplica
 from test_gpu_parity import run_trajectory
 
 pytestmark = pytest.mark.gpu
@@ -24,3 +26,33 @@ def test_pieces(oracle, n_layers, policy, period, optimizer, dtype, n, wire16, l
     w = _workload(n_layers, 400_003, optimizer, dtype, n, policy, period)
     t = run_trajectory(oracle, w, iters=3, fused=True, wire16=wire16, layerwise=layerwise, options={"update_chunk": 1024})
     assert t.frac() == 1.0
+
+
+@pytest.mark.parametrize("n_layers,period,policy", [(20, 1, "every"), (21, 1, "every"), (300, 1, "every"), (41, 2, "round_robin")])
+@pytest.mark.parametrize("optimizer,dtype,n,wire16", [("sgdm", "f32", 4, False), ("adamw", "bf16", 3, True)])
+def test_more_segments_than_a_launch_takes(oracle, n_layers, period, policy, optimizer, dtype, n, wire16):
+    """Small models on both sides of the number of segments from which their slots take the table: layers of several tensors,
+    whole-model calls and ranges of layers, every element against the oracle and the same statistics whatever the ranges."""
+    ts = [W.TensorSpec(f"l{l}.{j}", l, SIZES[(l + j) % len(SIZES)]) for l in range(n_layers) for j in range(1 + l % 3)]
+    w = W.Workload(f"segments{n_layers}", ts, n_replicas=n, period=period, optimizer=optimizer, param_dtype=dtype, lr=1e-3, sigma_drift=1e-3,
+                   iterations=2, policy=policy)
+    for layerwise in (0, 1, 7):
+        assert run_trajectory(oracle, w, iters=2, fused=True, wire16=wire16, layerwise=layerwise, options={"update_chunk": 1024}).frac() == 1.0
+    rep = DeviceReplica(w, 0, options={"update_chunk": 1024}, wire16=wire16)
+    rep.init_params()
+    rep.fill_grads(0)
+    flat = torch.cat([t for l in rep.sets[0] for t, k in zip(rep.sync, rep.layer_of) if k == l])
+    (rep.fill_peers16_from if wire16 else rep.fill_peers_from)(flat, 0, flat.numel())
+    streams = [a for a in (rep.a_sync, rep.a_s0, rep.a_s1, rep.a_model) if a is not None]
+    saved = [a.clone() for a in streams]
+    seen = []
+    for layers in (n_layers, 1, 7):
+        for a, b in zip(streams, saved):
+            a.copy_(b)
+        rep.stats.fill_(-1.0)
+        for lo in range(0, n_layers, layers):
+            rep.ctx.ddp_fused_sync_update_layers(0, lo, min(layers, n_layers - lo), rep.peers16 if wire16 else rep.peers, int(wire16), 0, n, 0,
+                                                 rep.stats, rep.opt_struct(1))
+        seen.append([rep.stats.clone()] + [a.clone() for a in streams])
+    assert all(torch.equal(a, b) for got in seen[1:] for a, b in zip(got, seen[0]))
+    rep.close()
