@@ -127,12 +127,6 @@ static int residency_pad(const ddp_ctx *c, int wg_per_cu) {
     return pad > 0 ? pad : 0;
 }
 
-// Whether the workgroups of a launch put the layers' statistics together themselves.  That saves a launch (3 us of host time;
-// fused step over 8 layers of 256^2: 8.4 -> 7.9 us on the GPU as well), but every workgroup then makes its partials visible
-// to the other XCDs before it ends, which writes its L2 back: with 257 workgroups nothing is lost, with 514 an average of
-// 7.3 us takes 10.7, with 3500 one of 48 takes 178.  Hence: not much more than one workgroup per CU.
-static bool fold_stats(const ddp_ctx *ctx, int64_t workgroups) { return 4 * workgroups <= 5 * (int64_t)ctx->cus; }
-
 // First element of layer l in registration order (l = L: the number of elements).
 static int64_t layer_elem0(const ddp_ctx *ctx, int l) { return ctx->tensor_elem_off[(size_t)ctx->layer_first_tensor[(size_t)l]]; }
 
@@ -363,7 +357,7 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
             st.layer_pos.assign((size_t)ctx->L, -1);
             std::vector<CopyChunk> cc;
             std::vector<MeanChunk> mc;
-            std::vector<int32_t> lcp, fused_ranges;
+            std::vector<int32_t> lcp;
             std::vector<TensorSlot> tslot((size_t)ctx->T, TensorSlot{-1, -1, -1});
             int64_t off = 0;
             for (int j = set_ptr[s]; j < set_ptr[s + 1]; ++j) {
@@ -371,8 +365,8 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
                 st.layers.push_back(l);
                 st.layer_begin.push_back(off);
                 lcp.push_back((int32_t)mc.size());
-                fused_ranges.push_back(ctx->tensor_chunk_base[(size_t)ctx->layer_first_tensor[(size_t)l]]);
-                fused_ranges.push_back(ctx->tensor_chunk_base[(size_t)ctx->layer_first_tensor[(size_t)l + 1]]);
+                st.fused_ranges.push_back(ctx->tensor_chunk_base[(size_t)ctx->layer_first_tensor[(size_t)l]]);
+                st.fused_ranges.push_back(ctx->tensor_chunk_base[(size_t)ctx->layer_first_tensor[(size_t)l + 1]]);
                 st.layer_pos[(size_t)l] = (int32_t)st.layers.size() - 1;
                 st.dense_ranges.push_back((int32_t)dense_wg_base[(size_t)l]);
                 st.dense_ranges.push_back((int32_t)dense_wg_base[(size_t)l + 1]);
@@ -416,15 +410,15 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
                 mean_ranges.push_back(lcp[i + 1]);
                 st.max_mean_partials = std::max<int64_t>(st.max_mean_partials, lcp[i + 1] - lcp[i]);
             }
-            for (size_t i = 0; i + 1 < fused_ranges.size(); i += 2) {
-                st.max_fused_partials = std::max<int64_t>(st.max_fused_partials, fused_ranges[i + 1] - fused_ranges[i]);
+            for (size_t i = 0; i + 1 < st.fused_ranges.size(); i += 2) {
+                st.max_fused_partials = std::max<int64_t>(st.max_fused_partials, st.fused_ranges[i + 1] - st.fused_ranges[i]);
                 st.max_dense_partials = std::max<int64_t>(st.max_dense_partials, st.dense_ranges[i + 1] - st.dense_ranges[i]);
             }
-            if (fold_stats(ctx, st.n_mean))
+            if (fold_stats(ctx->cus, st.n_mean, st.n_mean))
                 for (size_t i = 0; i + 1 < lcp.size(); ++i) mean_ranges.insert(mean_ranges.end(), (size_t)(lcp[i + 1] - lcp[i]), (int32_t)i);
             if (rc == DDP_OK) rc = upload(ctx, mean_ranges, &st.d_layer_ranges);
             if (rc == DDP_OK) rc = upload(ctx, tslot, &st.d_tensor_slot);
-            if (rc == DDP_OK) rc = upload(ctx, fused_ranges, &st.d_fused_ranges);
+            if (rc == DDP_OK) rc = upload(ctx, st.fused_ranges, &st.d_fused_ranges);
             if (rc == DDP_OK) rc = upload(ctx, st.dense_ranges, &st.d_dense_ranges);
             if (ctx->dense) st.dense_passes = plan_dense(st, ctx->L, [&](int l) { return layer_elem0(ctx, l); }, ctx->update_chunk);
             if (rc != DDP_OK) {
@@ -594,7 +588,7 @@ int ddp::partial_average_impl(ddp_ctx *ctx, const char *who, bool wire16, int sl
     a.out = flat_out;
     a.chunks = s->d_mean;
     a.n_chunks = s->n_mean;
-    const bool fold = layer_stats && !scratch && fold_stats(ctx, s->n_mean);
+    const bool fold = layer_stats && !scratch && fold_stats(ctx->cus, s->n_mean, s->n_mean);
     a.st = {layer_stats ? partials : nullptr, s->d_layer_ranges, layer_stats, fold ? ctx->d_counters : nullptr};
     a.chunk_pos = s->d_layer_ranges + 2 * s->layers.size();
     a.nontemporal = ctx->nontemporal;
@@ -787,12 +781,21 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
         first = 0;
         count = ctx->L;
     }
+    const bool dense = ctx->dense_path && !st->dense_passes.empty();
+    const int32_t *ranges = dense ? st->d_dense_ranges : st->d_fused_ranges;
+    const std::vector<int32_t> &parts = dense ? st->dense_ranges : st->fused_ranges;
+    const int64_t max_partials = dense ? st->max_dense_partials : st->max_fused_partials;
     // Statistics: one reduction per run of consecutive slot positions inside the range (a schedule in backward order gives a
     // single run).
     const int nl = (int)st->layers.size();
     auto inside = [&](int i) { return i < nl && st->layers[(size_t)i] >= first && st->layers[(size_t)i] < first + count; };
-    bool any = false;
-    for (int i = 0; layer_stats && i < nl && !any; ++i) any = inside(i);
+    int64_t partials = 0;
+    for (int i = 0; layer_stats && i < nl; ++i)
+        if (inside(i)) partials += parts[2 * (size_t)i + 1] - parts[2 * (size_t)i];
+    const bool any = partials > 0;
+    // One order of summation for a slot, whatever range the call has: the workgroups add a layer's partials up in the order of
+    // the one-launch reduction, so they do it only in slots that this reduction serves.
+    const bool fold = any && max_partials <= kStatSingleMax && fold_stats(ctx->cus, c1 - c0, partials);
     f.wire16 = wire16;
     f.update_first = update_first;
     f.n_replicas = N;
@@ -803,12 +806,6 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     f.with_model = ctx->param_dtype == DDP_BF16;
     f.s = s;
     f.lds_pad = ctx->update_lds;
-    const bool dense = ctx->dense_path && !st->dense_passes.empty();
-    const int32_t *ranges = dense ? st->d_dense_ranges : st->d_fused_ranges;
-    const int64_t max_partials = dense ? st->max_dense_partials : st->max_fused_partials;
-    // One order of summation for a slot, whatever range the call has: the workgroups add a layer's partials up in the order of
-    // the one-launch reduction, so they do it only in slots that this reduction serves.
-    const bool fold = any && max_partials <= kStatSingleMax && fold_stats(ctx, c1 - c0);
     f.st = {any ? ctx->d_partials : nullptr, ranges, layer_stats, fold ? ctx->d_counters : nullptr};
     if (dense) {
         rc = fused_dense(ctx, *st, first, count, f, stream);

@@ -106,7 +106,8 @@ struct SlotTables {
     int32_t *d_layer_ranges = nullptr;     // per layer of the slot: [first, last) mean chunk; behind them, in a slot whose
                                            // statistics are folded (fold_stats), the layer position of every mean chunk
     TensorSlot *d_tensor_slot = nullptr;   // per registered tensor
-    int32_t *d_fused_ranges = nullptr;     // per layer of the slot: [first, last) update chunk (registration order)
+    std::vector<int32_t> fused_ranges;     // per layer of the slot: [first, last) update chunk (registration order)
+    int32_t *d_fused_ranges = nullptr;
     // dense arenas: per layer of the slot [first, last) index of its workgroups' partials (layers numbered in
     // registration order)
     std::vector<int32_t> dense_ranges;

@@ -1,5 +1,5 @@
-// The launches of the fused step over dense arenas: how the model is cut into pieces, once per slot, and what of them a call
-// on a range of layers runs.  Arithmetic on the host only.
+// Which launches a call takes: where the statistics are put together, and, for the fused step over dense arenas, how the model
+// is cut into pieces, once per slot, and what of them a call on a range of layers runs.  Arithmetic on the host only.
 #ifndef DDP_PLAN_H
 #define DDP_PLAN_H
 
@@ -8,6 +8,18 @@
 #include "ddp_internal.h"
 
 namespace ddp {
+
+// Whether the workgroups of a launch put the layers' statistics together themselves: `partials` of its `workgroups` have a pair
+// of partial sums.  That saves a launch (3 us of host time), but each of these workgroups makes its pair visible to the other
+// XCDs before it ends, which writes its L2 back.  Launch of their own / folded in us, fused SGD, N = 4, 256 CUs:
+//                  behind other work    back to back    waited for
+//     32 pairs        6.7 / 6.2          7.6 / 5.8      19.3 / 18.4
+//     64 pairs        6.8 / 6.9          7.5 / 6.5      19.0 / 19.1
+//    128 pairs        6.9 / 8.2          7.5 / 7.7      19.1 / 20.3
+//    256 pairs        7.3 / 10.7         9.1 / 10.1     19.5 / 22.5
+// (the average alone: 128 pairs 7.9 / 7.3 back to back, 256 pairs 8.2 / 9.6).  Hence half a workgroup per CU, where calls back
+// to back break even, in launches of not much more than one (the others hide the second launch's host time).
+inline bool fold_stats(int cus, int64_t workgroups, int64_t partials) { return 2 * partials <= cus && 4 * workgroups <= 5 * (int64_t)cus; }
 
 // Workgroups of the table-free fused kernel over elements [e0, e1) of the arenas: chunks counted from the multiple of four at
 // or below e0, where every stream is vector-aligned.

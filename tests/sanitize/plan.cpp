@@ -151,6 +151,8 @@ int main(int argc, char **argv) {
         for (int first = 0; first < 9; ++first)
             for (int count = 1; first + count <= 9; ++count) check_call(u, first, count);
     }
+    // statistics folded into the launch: the line in pairs of partial sums, and the one in workgroups
+    CHECK(fold_stats(256, 128, 128) && !fold_stats(256, 129, 129) && fold_stats(256, 320, 128) && !fold_stats(256, 321, 1));
     // the number of launches, on both sides of each line; 0: the table's single one
     auto launches = [&](std::vector<int64_t> sizes) {
         std::vector<int> order;

@@ -1,6 +1,7 @@
-"""Statistics that the workgroups put together themselves (launches of about one workgroup per CU) and those of a launch of
-their own, on both sides of the rule's line: against the oracle, the same bits on every repetition, the same bits for the
-allocation-free entry point (which never folds), and through a captured graph that is replayed between eager calls."""
+"""Statistics that the workgroups put together themselves (launches of about one workgroup per CU, half of which have a
+share) and those of a launch of their own, on both sides of the rule's lines: against the oracle, the same bits on every
+repetition, the same bits for the allocation-free entry point (which never folds), and through a captured graph that is
+replayed between eager calls."""
 import numpy as np
 import pytest
 import torch
@@ -11,7 +12,8 @@ from paper_2502_11058_amd.harness import DeviceReplica
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("per_layer", [[1], [3, 5], [64] * 4, [319], [320], [321], [200, 1, 119], [1] * 40, [900, 2]])
+@pytest.mark.parametrize("per_layer", [[1], [3, 5], [64] * 4, [319], [320], [321], [200, 1, 119], [1] * 40, [900, 2],
+                                       [127], [128], [129], [70, 1, 57], [70, 1, 58], [33] * 3, [2] * 64, [2] * 65])
 def test_both_sides_of_the_line(oracle, per_layer):
     assert torch.cuda.is_available(), "no GPU visible"
     n = 4
