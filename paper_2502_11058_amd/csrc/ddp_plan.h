@@ -128,6 +128,7 @@ inline void clip_pass(const DensePass &p, int64_t e0, int64_t e1, int64_t chunk,
         add_pieces(part, part.begin, part.end, -1, 0, -1, -1, part.width, chunk);
         return;
     }
+    bool scheduled = false;
     for (int i = 0; i < p.n_pieces; ++i) {
         const Piece &whole = p.pieces[i];
         const int64_t b = std::max(whole.begin, e0), e = std::min(whole.begin + whole.count, e1);
@@ -137,7 +138,9 @@ inline void clip_pass(const DensePass &p, int64_t e0, int64_t e1, int64_t chunk,
         q.begin = b;  // (moves in unscheduled pieces only: a scheduled one is part of one layer)
         q.count = (int32_t)(e - b);
         part.width = std::max(part.width, (int)dense_workgroups(b, e, chunk));
+        scheduled = scheduled || q.flat0 >= 0;
     }
+    if (!scheduled && part.begin % 4 == 0) part.width = part.n_pieces = 0;  // a plain update, whose workgroups start sooner
 }
 
 }  // namespace ddp

@@ -150,6 +150,18 @@ int main(int argc, char **argv) {
         CHECK(u.passes.size() == 2 && u.passes[0].width == 0);
         for (int first = 0; first < 9; ++first)
             for (int count = 1; first + count <= 9; ++count) check_call(u, first, count);
+        const Model v = make({8, 1000, 1001, 4000, 6, 12}, {2, 4}, 2048);  // one launch; unscheduled ranges are plain updates
+        CHECK(v.passes.size() == 1);
+        static DensePass part;
+        auto range = [&](int first, int last) { clip_pass(v.passes[0], v.e[(size_t)first], v.e[(size_t)last], 2048, part); };
+        range(0, 2);
+        CHECK(part.width == 0);
+        range(1, 2);
+        CHECK(part.width == 0);
+        range(3, 4);  // begins at element 2009
+        CHECK(part.width > 0 && part.pieces[0].begin == 2009);
+        range(0, 3);
+        CHECK(part.width == 1 && part.n_pieces == 2 && part.pieces[1].flat0 == 0);
     }
     // statistics folded into the launch: the line in pairs of partial sums, and the one in workgroups
     CHECK(fold_stats(256, 128, 128) && !fold_stats(256, 129, 129) && fold_stats(256, 320, 128) && !fold_stats(256, 321, 1));
