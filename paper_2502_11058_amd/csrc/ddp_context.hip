@@ -45,15 +45,13 @@ static void free_slot(SlotTables &s) {
     if (s.d_copy) (void)hipFree(s.d_copy);
     if (s.d_mean) (void)hipFree(s.d_mean);
     if (s.d_layer_ranges) (void)hipFree(s.d_layer_ranges);
-    if (s.d_tensor_slot) (void)hipFree(s.d_tensor_slot);
-    if (s.d_fused_ranges) (void)hipFree(s.d_fused_ranges);
-    if (s.d_dense_ranges) (void)hipFree(s.d_dense_ranges);
-    s.d_dense_ranges = nullptr;
+    if (s.d_run_slot) (void)hipFree(s.d_run_slot);
+    if (s.d_update_ranges) (void)hipFree(s.d_update_ranges);
     s.d_copy = nullptr;
     s.d_mean = nullptr;
     s.d_layer_ranges = nullptr;
-    s.d_tensor_slot = nullptr;
-    s.d_fused_ranges = nullptr;
+    s.d_run_slot = nullptr;
+    s.d_update_ranges = nullptr;
 }
 
 static void drop_schedule(ddp_ctx *c) {
@@ -70,9 +68,11 @@ static void drop_schedule(ddp_ctx *c) {
 static void drop_model(ddp_ctx *c) {
     drop_schedule(c);
     if (c->d_tensors) (void)hipFree(c->d_tensors);
+    if (c->d_runs) (void)hipFree(c->d_runs);
     if (c->d_update) (void)hipFree(c->d_update);
-    if (c->d_tensor_chunk_base) (void)hipFree(c->d_tensor_chunk_base);
-    c->d_tensor_chunk_base = nullptr;
+    if (c->d_run_chunk_base) (void)hipFree(c->d_run_chunk_base);
+    c->d_run_chunk_base = nullptr;
+    c->d_runs = nullptr;
     c->d_tensors = nullptr;
     c->d_update = nullptr;
     c->n_update = 0;
@@ -290,28 +290,41 @@ extern "C" int ddp_register_model(ddp_ctx *ctx, int L, int T, const int32_t *lay
         }
         ctx->dense = dense;
 
-        // update table: every tensor cut into runs of update_chunk elements that end on the parameters' 16-byte boundaries, so
-        // that only a tensor's first and last chunk have elements outside a whole vector
+        // Update table: every run cut into chunks of update_chunk elements that end on the parameters' 16-byte boundaries, so
+        // that only a run's first and last chunk have elements outside a whole vector.  A run is a tensor; over dense arenas it
+        // is a whole layer, so that the table's chunks, and the partial sums that they give, are those of the table-free kernels.
+        std::vector<TensorDesc> runs = ts;
+        ctx->layer_first_run = first;
+        if (dense) {
+            runs.clear();
+            for (int l = 0; l < L; ++l) {
+                runs.push_back(ts[(size_t)first[(size_t)l]]);
+                runs.back().numel = ctx->tensor_elem_off[(size_t)first[(size_t)l + 1]] - ctx->tensor_elem_off[(size_t)first[(size_t)l]];
+                ctx->layer_first_run[(size_t)l] = l;
+            }
+            ctx->layer_first_run[(size_t)L] = L;
+        }
         std::vector<UpdateChunk> uc;
-        ctx->tensor_chunk_base.assign((size_t)T + 1, 0);
-        for (int t = 0; t < T; ++t) {
-            ctx->tensor_chunk_base[(size_t)t] = (int32_t)uc.size();
-            const int64_t past = (int64_t)((reinterpret_cast<uintptr_t>(ts[(size_t)t].sync) >> 2) & 3u);  // elements past such a boundary
-            for (int64_t b = 0, e; b < numel[t]; b = e) {
-                e = std::min<int64_t>(numel[t], (b + past) / ctx->update_chunk * ctx->update_chunk + ctx->update_chunk - past);
-                uc.push_back({b, t, (int32_t)(e - b)});
+        ctx->run_chunk_base.clear();
+        for (size_t t = 0; t < runs.size(); ++t) {
+            ctx->run_chunk_base.push_back((int32_t)uc.size());
+            const int64_t past = (int64_t)((reinterpret_cast<uintptr_t>(runs[t].sync) >> 2) & 3u);  // elements past such a boundary
+            for (int64_t b = 0, e; b < runs[t].numel; b = e) {
+                e = std::min<int64_t>(runs[t].numel, (b + past) / ctx->update_chunk * ctx->update_chunk + ctx->update_chunk - past);
+                uc.push_back({b, (int32_t)t, (int32_t)(e - b)});
             }
         }
         if (uc.size() > (size_t)0x7fffffff) {
             drop_model(ctx);
             return fail(ctx, DDP_ESHAPE, "ddp_register_model: more than 2^31-1 update chunks; raise update_chunk");
         }
-        ctx->tensor_chunk_base[(size_t)T] = (int32_t)uc.size();
+        ctx->run_chunk_base.push_back((int32_t)uc.size());
         ctx->n_update = (int64_t)uc.size();
         interleave_segments(uc, ctx->dispatch_ways);
         rc = upload(ctx, ts, &ctx->d_tensors);
+        if (rc == DDP_OK) rc = upload(ctx, runs, &ctx->d_runs);
         if (rc == DDP_OK) rc = upload(ctx, uc, &ctx->d_update);
-        if (rc == DDP_OK) rc = upload(ctx, ctx->tensor_chunk_base, &ctx->d_tensor_chunk_base);
+        if (rc == DDP_OK) rc = upload(ctx, ctx->run_chunk_base, &ctx->d_run_chunk_base);
         if (rc != DDP_OK) {
             drop_model(ctx);
             return rc;
@@ -345,12 +358,6 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
 
         drop_schedule(ctx);
         std::vector<SlotTables> slots((size_t)H);
-        // workgroups of the table-free fused kernel, layer by layer in registration order (never more than the update
-        // table has chunks, so the reduction scratch sized for the table covers them)
-        std::vector<int64_t> dense_wg_base((size_t)ctx->L + 1, 0);
-        for (int l = 0; l < ctx->L; ++l) {
-            dense_wg_base[(size_t)l + 1] = dense_wg_base[(size_t)l] + dense_workgroups(layer_elem0(ctx, l), layer_elem0(ctx, l + 1), ctx->update_chunk);
-        }
         int64_t max_mean_chunks = 0;
         for (int s = 0; s < H; ++s) {
             SlotTables &st = slots[(size_t)s];
@@ -358,23 +365,21 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
             std::vector<CopyChunk> cc;
             std::vector<MeanChunk> mc;
             std::vector<int32_t> lcp;
-            std::vector<TensorSlot> tslot((size_t)ctx->T, TensorSlot{-1, -1, -1});
+            std::vector<RunSlot> run_slot(ctx->run_chunk_base.size() - 1, RunSlot{-1, -1, -1});
             int64_t off = 0;
             for (int j = set_ptr[s]; j < set_ptr[s + 1]; ++j) {
                 const int l = set_layers[j];
                 st.layers.push_back(l);
                 st.layer_begin.push_back(off);
                 lcp.push_back((int32_t)mc.size());
-                st.fused_ranges.push_back(ctx->tensor_chunk_base[(size_t)ctx->layer_first_tensor[(size_t)l]]);
-                st.fused_ranges.push_back(ctx->tensor_chunk_base[(size_t)ctx->layer_first_tensor[(size_t)l + 1]]);
+                st.update_ranges.push_back(ctx->run_chunk_base[(size_t)ctx->layer_first_run[(size_t)l]]);
+                st.update_ranges.push_back(ctx->run_chunk_base[(size_t)ctx->layer_first_run[(size_t)l + 1]]);
                 st.layer_pos[(size_t)l] = (int32_t)st.layers.size() - 1;
-                st.dense_ranges.push_back((int32_t)dense_wg_base[(size_t)l]);
-                st.dense_ranges.push_back((int32_t)dense_wg_base[(size_t)l + 1]);
                 const int64_t layer_start = off;
                 for (int t = ctx->layer_first_tensor[(size_t)l]; t < ctx->layer_first_tensor[(size_t)l + 1]; ++t) {
                     st.tensors.push_back(t);
                     st.tensor_off.push_back(off);
-                    tslot[(size_t)t] = {off, st.layer_pos[(size_t)l], l};
+                    if (!ctx->dense || off == layer_start) run_slot[(size_t)(ctx->dense ? l : t)] = {off, st.layer_pos[(size_t)l], l};
                     for (int64_t b = 0; b < ctx->numel[(size_t)t]; b += ctx->copy_chunk) {
                         int64_t n = std::min<int64_t>(ctx->copy_chunk, ctx->numel[(size_t)t] - b);
                         cc.push_back({b, off + b, t, (int32_t)n});
@@ -410,17 +415,14 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
                 mean_ranges.push_back(lcp[i + 1]);
                 st.max_mean_partials = std::max<int64_t>(st.max_mean_partials, lcp[i + 1] - lcp[i]);
             }
-            for (size_t i = 0; i + 1 < st.fused_ranges.size(); i += 2) {
-                st.max_fused_partials = std::max<int64_t>(st.max_fused_partials, st.fused_ranges[i + 1] - st.fused_ranges[i]);
-                st.max_dense_partials = std::max<int64_t>(st.max_dense_partials, st.dense_ranges[i + 1] - st.dense_ranges[i]);
-            }
+            for (size_t i = 0; i + 1 < st.update_ranges.size(); i += 2)
+                st.max_update_partials = std::max<int64_t>(st.max_update_partials, st.update_ranges[i + 1] - st.update_ranges[i]);
             if (fold_stats(ctx->cus, st.n_mean, st.n_mean))
                 for (size_t i = 0; i + 1 < lcp.size(); ++i) mean_ranges.insert(mean_ranges.end(), (size_t)(lcp[i + 1] - lcp[i]), (int32_t)i);
             if (rc == DDP_OK) rc = upload(ctx, mean_ranges, &st.d_layer_ranges);
-            if (rc == DDP_OK) rc = upload(ctx, tslot, &st.d_tensor_slot);
-            if (rc == DDP_OK) rc = upload(ctx, st.fused_ranges, &st.d_fused_ranges);
-            if (rc == DDP_OK) rc = upload(ctx, st.dense_ranges, &st.d_dense_ranges);
-            if (ctx->dense) st.dense_passes = plan_dense(st, ctx->L, [&](int l) { return layer_elem0(ctx, l); }, ctx->update_chunk);
+            if (rc == DDP_OK) rc = upload(ctx, run_slot, &st.d_run_slot);
+            if (rc == DDP_OK) rc = upload(ctx, st.update_ranges, &st.d_update_ranges);
+            if (ctx->dense) plan_dense(st, ctx->L, [&](int l) { return layer_elem0(ctx, l); }, ctx->update_chunk);
             if (rc != DDP_OK) {
                 for (auto &x : slots) free_slot(x);
                 return rc;
@@ -668,8 +670,8 @@ static int layer_chunk_range(ddp_ctx *ctx, const char *who, int first, int count
         return fail(ctx, DDP_EINVAL, std::string(who) + ": layer range outside [0, " + std::to_string(ctx->L) + ")");
     if (ctx->dispatch_ways != 1 && !(first == 0 && count == ctx->L))
         return fail(ctx, DDP_ESTATE, std::string(who) + ": a layer range needs the update table in registration order (option dispatch_ways = 1)");
-    *c0 = ctx->tensor_chunk_base[(size_t)ctx->layer_first_tensor[(size_t)first]];
-    *c1 = ctx->tensor_chunk_base[(size_t)ctx->layer_first_tensor[(size_t)(first + count)]];
+    *c0 = ctx->run_chunk_base[(size_t)ctx->layer_first_run[(size_t)first]];
+    *c1 = ctx->run_chunk_base[(size_t)ctx->layer_first_run[(size_t)(first + count)]];
     return DDP_OK;
 }
 
@@ -705,7 +707,7 @@ static int local_update_impl(ddp_ctx *ctx, const char *who, bool whole, int firs
         rc = launch_update_dense(opt->kind, ctx->grad_dtype, ctx->param_dtype == DDP_BF16, d, s, ctx->nontemporal, ctx->update_lds, stream);
         return after_launch(ctx, who, rc);
     }
-    rc = launch_update(opt->kind, ctx->grad_dtype, ctx->param_dtype == DDP_BF16, ctx->d_tensors, ctx->d_update + c0, c1 - c0, s,
+    rc = launch_update(opt->kind, ctx->grad_dtype, ctx->param_dtype == DDP_BF16, ctx->d_runs, ctx->d_update + c0, c1 - c0, s,
                        ctx->nontemporal, ctx->update_lds, stream);
     return after_launch(ctx, who, rc);
 }
@@ -730,8 +732,7 @@ static int fused_dense(const ddp_ctx *ctx, const SlotTables &st, int first, int 
     const TensorDesc &t0 = ctx->tensors[0];
     f.d = {t0.grad, t0.sync, t0.state0, t0.state1, t0.model, 0, (int)ctx->update_chunk};
     int rc = 0;
-    auto at = std::upper_bound(st.dense_passes.begin(), st.dense_passes.end(), e0, [](int64_t e, const DensePass &p) { return e < p.end; });
-    for (; at != st.dense_passes.end() && at->begin < e1 && rc == 0; ++at) {
+    for (auto at = first_pass(st, e0); at != st.dense_passes.end() && at->begin < e1 && rc == 0; ++at) {
         DensePass part;
         f.pass = &*at;
         if (at->begin < e0 || at->end > e1) {
@@ -781,21 +782,17 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
         first = 0;
         count = ctx->L;
     }
-    const bool dense = ctx->dense_path && !st->dense_passes.empty();
-    const int32_t *ranges = dense ? st->d_dense_ranges : st->d_fused_ranges;
-    const std::vector<int32_t> &parts = dense ? st->dense_ranges : st->fused_ranges;
-    const int64_t max_partials = dense ? st->max_dense_partials : st->max_fused_partials;
     // Statistics: one reduction per run of consecutive slot positions inside the range (a schedule in backward order gives a
     // single run).
     const int nl = (int)st->layers.size();
     auto inside = [&](int i) { return i < nl && st->layers[(size_t)i] >= first && st->layers[(size_t)i] < first + count; };
     int64_t partials = 0;
     for (int i = 0; layer_stats && i < nl; ++i)
-        if (inside(i)) partials += parts[2 * (size_t)i + 1] - parts[2 * (size_t)i];
+        if (inside(i)) partials += st->update_ranges[2 * (size_t)i + 1] - st->update_ranges[2 * (size_t)i];
     const bool any = partials > 0;
     // One order of summation for a slot, whatever range the call has: the workgroups add a layer's partials up in the order of
     // the one-launch reduction, so they do it only in slots that this reduction serves.
-    const bool fold = any && max_partials <= kStatSingleMax && fold_stats(ctx->cus, c1 - c0, partials);
+    const bool fold = any && st->max_update_partials <= kStatSingleMax && fold_stats(ctx->cus, c1 - c0, partials);
     f.wire16 = wire16;
     f.update_first = update_first;
     f.n_replicas = N;
@@ -806,15 +803,15 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     f.with_model = ctx->param_dtype == DDP_BF16;
     f.s = s;
     f.lds_pad = ctx->update_lds;
-    f.st = {any ? ctx->d_partials : nullptr, ranges, layer_stats, fold ? ctx->d_counters : nullptr};
-    if (dense) {
+    f.st = {any ? ctx->d_partials : nullptr, st->d_update_ranges, layer_stats, fold ? ctx->d_counters : nullptr};
+    if (ctx->dense_path && takes_pieces(*st, layer_elem0(ctx, first), layer_elem0(ctx, first + count))) {
         rc = fused_dense(ctx, *st, first, count, f, stream);
     } else {
-        f.tensors = ctx->d_tensors;
+        f.runs = ctx->d_runs;
         f.chunks = ctx->d_update + c0;
         f.n_chunks = c1 - c0;
-        f.tensor_slot = st->d_tensor_slot;
-        f.tensor_chunk_base = ctx->d_tensor_chunk_base;
+        f.run_slot = st->d_run_slot;
+        f.run_chunk_base = ctx->d_run_chunk_base;
         f.chunk_elems = (int)ctx->update_chunk;
         rc = launch_fused(f, stream);
     }
@@ -822,8 +819,8 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
         int j = i;
         while (inside(j)) ++j;
         if (j > i)
-            rc = launch_stats(f.st.partials, ctx->d_slice_sums + (int64_t)i * 2 * kStatSlices, ranges + 2 * i, j - i, N, layer_stats + 2 * i, max_partials,
-                              stream);
+            rc = launch_stats(f.st.partials, ctx->d_slice_sums + (int64_t)i * 2 * kStatSlices, st->d_update_ranges + 2 * i, j - i, N,
+                              layer_stats + 2 * i, st->max_update_partials, stream);
         i = j + 1;
     }
     return after_launch(ctx, who, rc);

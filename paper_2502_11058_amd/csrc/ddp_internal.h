@@ -48,9 +48,9 @@ struct TensorDesc {   // one registered tensor
     int64_t numel;
 };
 
-struct UpdateChunk {  // local_update: elements [begin, begin+count) of tensor `tensor`
+struct UpdateChunk {  // local_update: elements [begin, begin+count) of run `run` (a tensor; over dense arenas a whole layer)
     int64_t begin;
-    int32_t tensor;
+    int32_t run;
     int32_t count;
 };
 
@@ -67,8 +67,8 @@ struct MeanChunk {  // partial_average: flat elements [begin, +count), all insid
     int32_t partial;  // where this chunk's partial sums go: its index in flat order, whatever the dispatch order
 };
 
-struct TensorSlot {  // a registered tensor in one slot
-    int64_t flat0;   // first flat index, -1 if it is not scheduled
+struct RunSlot {    // a run of the update table in one slot
+    int64_t flat0;  // first flat index, -1 if it is not scheduled
     int32_t pos;     // position of its layer in the slot
     int32_t layer;
 };
@@ -105,16 +105,13 @@ struct SlotTables {
     int64_t n_mean = 0;
     int32_t *d_layer_ranges = nullptr;     // per layer of the slot: [first, last) mean chunk; behind them, in a slot whose
                                            // statistics are folded (fold_stats), the layer position of every mean chunk
-    TensorSlot *d_tensor_slot = nullptr;   // per registered tensor
-    std::vector<int32_t> fused_ranges;     // per layer of the slot: [first, last) update chunk (registration order)
-    int32_t *d_fused_ranges = nullptr;
-    // dense arenas: per layer of the slot [first, last) index of its workgroups' partials (layers numbered in
-    // registration order)
-    std::vector<int32_t> dense_ranges;
-    int64_t max_mean_partials = 0, max_fused_partials = 0, max_dense_partials = 0;  // largest per-layer count of each range table
+    RunSlot *d_run_slot = nullptr;         // per run of the update table
+    std::vector<int32_t> update_ranges;    // per layer of the slot: [first, last) update chunk (registration order), whose places
+    int32_t *d_update_ranges = nullptr;    // the partials of the fused step have, table-driven or table-free
+    int64_t max_mean_partials = 0, max_update_partials = 0;  // largest per-layer count of each range table
     std::vector<int32_t> layer_pos;  // [L] layer -> position in this slot, -1 if not scheduled
-    int32_t *d_dense_ranges = nullptr;
     std::vector<DensePass> dense_passes;  // dense arenas: the launches of the fused step over the whole model
+    bool table_first = false;             // ... for which the table's single launch is the better one
 };
 
 // How the per-layer statistics of a launch are put together from its workgroups' partial pairs.
@@ -174,11 +171,11 @@ struct FusedLaunch {
 };
 // ... the table-driven one, over chunks of the update table ...
 struct FusedTable : FusedLaunch {
-    const TensorDesc *tensors;
+    const TensorDesc *runs;
     const UpdateChunk *chunks;
     int64_t n_chunks;
-    const TensorSlot *tensor_slot;
-    const int32_t *tensor_chunk_base;
+    const RunSlot *run_slot;
+    const int32_t *run_chunk_base;
     int chunk_elems;
 };
 int launch_fused(const FusedTable &f, void *stream);
@@ -199,7 +196,7 @@ struct FusedDense : FusedLaunch {
     const DensePass *pass;
 };
 int launch_fused_dense(const FusedDense &f, void *stream);
-int launch_update(int kind, int grad_dtype, bool with_model, const TensorDesc *tensors, const UpdateChunk *chunks,
+int launch_update(int kind, int grad_dtype, bool with_model, const TensorDesc *runs, const UpdateChunk *chunks,
                   int64_t n_chunks, const UpdateScalars &s, bool nontemporal, int lds_pad, void *stream);
 
 // Shared body of the averaging entry points (ddp_context.hip).  scratch == nullptr: the context's reduction scratch.
@@ -235,10 +232,12 @@ struct ddp_ctx {
     bool dense = false;      // tensors lie back to back in every stream and the streams' starts are vector-aligned
     bool dense_path = true;  // option: use the table-free kernels where `dense` allows it
     ddp::TensorDesc *d_tensors = nullptr;
+    std::vector<int32_t> layer_first_run;  // L + 1: runs of the update table
+    ddp::TensorDesc *d_runs = nullptr;
     ddp::UpdateChunk *d_update = nullptr;
     int64_t n_update = 0;
-    std::vector<int32_t> tensor_chunk_base;  // T + 1: first update chunk of each tensor, registration order
-    int32_t *d_tensor_chunk_base = nullptr;
+    std::vector<int32_t> run_chunk_base;  // first update chunk of each run, registration order, and their number
+    int32_t *d_run_chunk_base = nullptr;
     // schedule
     int H = 0;
     std::vector<ddp::SlotTables> slots;

@@ -13,23 +13,23 @@ namespace {
 
 struct FusedArgs {
     Peers peers;
-    const TensorDesc *tensors;
+    const TensorDesc *runs;
     const UpdateChunk *chunks;
-    const TensorSlot *tensor_slot;
-    const int32_t *tensor_chunk_base;   // per tensor: index of its first chunk in registration order
+    const RunSlot *run_slot;
+    const int32_t *run_chunk_base;      // per run: index of its first chunk in registration order
     StatsLaunch st;                     // partials: [n_chunks][2], only touched for scheduled chunks
     UpdateScalars s;
     int chunk_elems;
 };
 
-// A chunk of a scheduled tensor takes fused_body, every other chunk the optimizer step only.  At least two wavefronts per
+// A chunk of a scheduled run takes fused_body, every other chunk the optimizer step only.  At least two wavefronts per
 // SIMD (the launch bounds): the residency that the launch asks for.
 template <bool ADAM, bool GBF16, bool MODEL, int NREP, bool EXACT, bool STATS, bool W16, bool UTS>
 __global__ __launch_bounds__(kThreads, 2) void fused_kernel(const FusedArgs a) {
     __shared__ double lds[2][kThreads / kWave];
     const UpdateChunk ch = a.chunks[blockIdx.x];
-    const TensorDesc td = a.tensors[ch.tensor];
-    const TensorSlot ts = a.tensor_slot[ch.tensor];
+    const TensorDesc td = a.runs[ch.run];
+    const RunSlot ts = a.run_slot[ch.run];
     const Streams<GBF16> c = chunk_streams<GBF16>(td, ch);
     if (ts.flat0 < 0) {  // uniform for the workgroup
         update_body<ADAM, GBF16, MODEL, true, false>(c, a.s);
@@ -40,8 +40,8 @@ __global__ __launch_bounds__(kThreads, 2) void fused_kernel(const FusedArgs a) {
     if constexpr (STATS) {
         const double gt = block_sum(gsum, lds[0]);
         const double mt = block_sum(msum, lds[1]);
-        // chunks end at the parameters' 16-byte boundaries: chunk c of a tensor begins 0..3 elements before c * chunk_elems
-        put_partial(a.st, (int64_t)a.tensor_chunk_base[ch.tensor] + (ch.begin + 3) / a.chunk_elems, ts.pos, ts.layer, a.peers.n, gt, mt, lds);
+        // chunks end at the parameters' 16-byte boundaries: chunk c of a run begins 0..3 elements before c * chunk_elems
+        put_partial(a.st, (int64_t)a.run_chunk_base[ch.run] + (ch.begin + 3) / a.chunk_elems, ts.pos, ts.layer, a.peers.n, gt, mt, lds);
     }
 }
 
@@ -71,10 +71,10 @@ struct LaunchTable {
 int DDP_FUSED_HALF(const FusedTable &f, void *stream) {
     FusedArgs a;
     fill_peers(a.peers, f);
-    a.tensors = f.tensors;
+    a.runs = f.runs;
     a.chunks = f.chunks;
-    a.tensor_slot = f.tensor_slot;
-    a.tensor_chunk_base = f.tensor_chunk_base;
+    a.run_slot = f.run_slot;
+    a.run_chunk_base = f.run_chunk_base;
     a.st = f.st;
     a.s = f.s;
     a.chunk_elems = f.chunk_elems;

@@ -5,10 +5,10 @@ namespace ddp {
 namespace {
 
 template <bool ADAM, bool GBF16, bool MODEL, bool NT>
-__global__ __launch_bounds__(kThreads) void update_kernel(const TensorDesc *__restrict__ tensors, const UpdateChunk *__restrict__ chunks,
+__global__ __launch_bounds__(kThreads) void update_kernel(const TensorDesc *__restrict__ runs, const UpdateChunk *__restrict__ chunks,
                                                           const UpdateScalars s) {
     const UpdateChunk ch = chunks[blockIdx.x];
-    const TensorDesc td = tensors[ch.tensor];
+    const TensorDesc td = runs[ch.run];
     update_body<ADAM, GBF16, MODEL, NT, false>(chunk_streams<GBF16>(td, ch), s);
 }
 
@@ -27,13 +27,13 @@ __global__ __launch_bounds__(kThreads) void update_dense_kernel(const DenseArgs 
 
 }  // namespace
 
-int launch_update(int kind, int grad_dtype, bool with_model, const TensorDesc *tensors, const UpdateChunk *chunks, int64_t n_chunks,
+int launch_update(int kind, int grad_dtype, bool with_model, const TensorDesc *runs, const UpdateChunk *chunks, int64_t n_chunks,
                   const UpdateScalars &s, bool nontemporal, int lds_pad, void *stream) {
     const bool adam = kind == DDP_OPT_ADAMW, gb = grad_dtype == DDP_BF16;
 #define DDP_UPD(A, G, M)                                                                               \
     if (adam == A && gb == G && with_model == M)                                                       \
-        return nontemporal ? launch(update_kernel<A, G, M, true>, n_chunks, stream, lds_pad, tensors, chunks, s) \
-                           : launch(update_kernel<A, G, M, false>, n_chunks, stream, lds_pad, tensors, chunks, s);
+        return nontemporal ? launch(update_kernel<A, G, M, true>, n_chunks, stream, lds_pad, runs, chunks, s) \
+                           : launch(update_kernel<A, G, M, false>, n_chunks, stream, lds_pad, runs, chunks, s);
     DDP_UPD(false, false, false)
     DDP_UPD(false, false, true)
     DDP_UPD(false, true, false)

@@ -46,13 +46,12 @@ inline void add_pieces(DensePass &p, int64_t begin, int64_t end, int64_t flat0, 
 // some 3 us of ramp.  Shared against own launches, N = 2 / 4 / 8: 20 layers of 10 M 0.94 / 0.95 / 0.92 of the time, of 20 M
 // 0.99 / 1.00 / 0.99 (8 of them 0.98 / 0.98 / 0.96, 40 of them 0.99 / 1.02 / 1.02), of 25 M 1.00 / 1.01 / 1.00, of 30 M
 // 1.00 / 1.03 / 1.03: the line is where it breaks even.
-// A launch takes kMaxSegments; where that makes several and the model is small, the slot takes the table, whose single launch
-// starts its workgroups later but is one (no plan is made; ranges of layers take the table too, so that the statistics of a slot
-// have one grouping).  Pieces against the table in us, N = 4: 400 layers of 1000 elements 83 / 8, 21 of 64 K 17.0 / 12.5, of
-// 256 K 37.9 / 34.3, of 1 M 117 / 115; N = 2: 21 of 1 M 126 / 129, 40 of 4 M 836 / 868.
-// No plan either where a launch would need more than kMaxPieces pieces.
+// A launch takes kMaxSegments; where that makes several and the model is small, the table is the better one (table_first): its
+// workgroups start later but all in one launch.  Pieces against the table in us, N = 4: 400 layers of 1000 elements 83 / 8, 21 of
+// 64 K 17.0 / 12.5, of 256 K 37.9 / 34.3, of 1 M 117 / 115; N = 2: 21 of 1 M 126 / 129, 40 of 4 M 836 / 868.
+// No passes where a launch would need more than kMaxPieces pieces: such a slot always takes the table.
 template <class Elem0>
-std::vector<DensePass> plan_dense(const SlotTables &st, int L, Elem0 &&elem0, int64_t chunk) {
+void plan_dense(SlotTables &st, int L, Elem0 &&elem0, int64_t chunk) {
     constexpr int kMaxSegments = 20;
     struct Segment {
         int64_t begin, end, flat0, pbase, wg;
@@ -63,12 +62,11 @@ std::vector<DensePass> plan_dense(const SlotTables &st, int L, Elem0 &&elem0, in
         const int i = st.layer_pos[(size_t)l];
         int m = l + 1;
         while (i < 0 && m < L && st.layer_pos[(size_t)m] < 0) ++m;
-        all.push_back({elem0(l), elem0(m), i < 0 ? -1 : st.layer_begin[(size_t)i], i < 0 ? 0 : st.dense_ranges[2 * (size_t)i],
+        all.push_back({elem0(l), elem0(m), i < 0 ? -1 : st.layer_begin[(size_t)i], i < 0 ? 0 : st.update_ranges[2 * (size_t)i],
                        dense_workgroups(elem0(l), elem0(m), chunk), i, l});
         l = m;
     }
-    std::vector<DensePass> passes;
-    if (all.empty()) return passes;
+    std::vector<DensePass> &passes = st.dense_passes;
     constexpr int64_t kAlone = (int64_t)3 << 23, kPerLaunch = (int64_t)1 << 24;  // 25 M; elements that a launch more is worth
     auto group = [&](size_t k) {  // segments that share the launch of segment k, the first one of it
         size_t n = 1;
@@ -78,7 +76,7 @@ std::vector<DensePass> plan_dense(const SlotTables &st, int L, Elem0 &&elem0, in
     };
     int64_t shared = 0;
     for (size_t k = 0; k < all.size(); k += group(k)) shared += all[k].end - all[k].begin < kAlone;
-    if (all.back().end - all[0].begin < (shared - 1) * kPerLaunch) return passes;
+    st.table_first = all.back().end - all[0].begin < (shared - 1) * kPerLaunch;
     const int64_t widest = widest_piece(chunk);
     for (size_t i = 0; i < all.size();) {
         const Segment *seg = &all[i];
@@ -86,7 +84,10 @@ std::vector<DensePass> plan_dense(const SlotTables &st, int L, Elem0 &&elem0, in
         i += (size_t)n;
         int64_t least = 0;
         for (int k = 0; k < n; ++k) least += (seg[k].wg + widest - 1) / widest;
-        if (least > kMaxPieces) return {};
+        if (least > kMaxPieces) {
+            passes.clear();
+            return;
+        }
         passes.emplace_back();
         DensePass &p = passes.back();
         p.width = p.n_pieces = 0;
@@ -110,7 +111,16 @@ std::vector<DensePass> plan_dense(const SlotTables &st, int L, Elem0 &&elem0, in
         for (int k = 0; k < n; ++k)
             add_pieces(p, seg[k].begin, seg[k].end, seg[k].flat0, seg[k].pbase, seg[k].pos, seg[k].layer, width, chunk);
     }
-    return passes;
+}
+
+// The first launch that has elements from e0 on.
+inline std::vector<DensePass>::const_iterator first_pass(const SlotTables &st, int64_t e0) {
+    return std::upper_bound(st.dense_passes.begin(), st.dense_passes.end(), e0, [](int64_t e, const DensePass &p) { return e < p.end; });
+}
+
+// Whether a call on elements [e0, e1), e0 < e1, runs pieces: where the table is better for the slot, if one launch does it.
+inline bool takes_pieces(const SlotTables &st, int64_t e0, int64_t e1) {
+    return !st.dense_passes.empty() && (!st.table_first || first_pass(st, e0)->end >= e1);
 }
 
 // What a call on elements [e0, e1), whole layers, runs of launch p: the pieces inside, runs of unscheduled layers cut at the

@@ -32,7 +32,6 @@ struct Model {
     std::vector<int64_t> e;  // first element of every layer, and the end
     SlotTables st;
     int64_t chunk;
-    std::vector<DensePass> passes;
     int L() const { return (int)e.size() - 1; }
 };
 
@@ -49,12 +48,12 @@ static Model make(const std::vector<int64_t> &sizes, const std::vector<int> &ord
         m.st.layer_pos[(size_t)l] = (int32_t)m.st.layers.size();
         m.st.layers.push_back(l);
         m.st.layer_begin.push_back(off);
-        m.st.dense_ranges.push_back((int32_t)wg[(size_t)l]);
-        m.st.dense_ranges.push_back((int32_t)wg[(size_t)l + 1]);
+        m.st.update_ranges.push_back((int32_t)wg[(size_t)l]);
+        m.st.update_ranges.push_back((int32_t)wg[(size_t)l + 1]);
         off += sizes[(size_t)l];
     }
     m.st.layer_begin.push_back(off);
-    m.passes = plan_dense(m.st, m.L(), [&](int l) { return m.e[(size_t)l]; }, chunk);
+    plan_dense(m.st, m.L(), [&](int l) { return m.e[(size_t)l]; }, chunk);
     return m;
 }
 
@@ -63,8 +62,8 @@ static int check_call(const Model &m, int first, int count) {
     const int64_t e0 = m.e[(size_t)first], e1 = m.e[(size_t)(first + count)];
     int64_t at = e0;
     int launches = 0;
-    for (const DensePass &whole : m.passes) {
-        if (whole.end <= e0 || whole.begin >= e1) continue;
+    for (auto pass = first_pass(m.st, e0); pass != m.st.dense_passes.end() && pass->begin < e1; ++pass) {
+        const DensePass &whole = *pass;
         static DensePass part;
         const long before = g_allocations;
         clip_pass(whole, e0, e1, m.chunk, part);
@@ -101,13 +100,14 @@ static int check_call(const Model &m, int first, int count) {
             CHECK(q.begin >= l0 && at <= l1 && q.flat0 == m.st.layer_begin[(size_t)q.pos] + (q.begin - l0));
             // its workgroups follow each other in the layer's partials: the first one's place, and the last one's
             CHECK(q.begin == l0 || q.begin % 4 == 0);
-            CHECK(q.pbase == m.st.dense_ranges[2 * (size_t)q.pos] + (q.begin / 4 * 4 - l0 / 4 * 4) / m.chunk);
+            CHECK(q.pbase == m.st.update_ranges[2 * (size_t)q.pos] + (q.begin / 4 * 4 - l0 / 4 * 4) / m.chunk);
             CHECK((q.begin / 4 * 4 - l0 / 4 * 4) % m.chunk == 0);
-            CHECK(at == l1 ? q.pbase + wg == m.st.dense_ranges[2 * (size_t)q.pos + 1] : at % 4 == 0 && wg == (at - q.begin / 4 * 4) / m.chunk);
+            CHECK(at == l1 ? q.pbase + wg == m.st.update_ranges[2 * (size_t)q.pos + 1] : at % 4 == 0 && wg == (at - q.begin / 4 * 4) / m.chunk);
         }
         CHECK(at == part.end && widest == part.width);
     }
     CHECK(at == e1);
+    CHECK(takes_pieces(m.st, e0, e1) == (!m.st.table_first || launches == 1));
     return launches;
 }
 
@@ -132,7 +132,7 @@ int main(int argc, char **argv) {
         for (int64_t n : sizes) total += (n + chunk - 1) / chunk + 1;
         if (total > INT32_MAX) continue;  // registration refuses it
         const Model m = make(sizes, order, chunk);
-        if (m.passes.empty()) continue;
+        if (m.st.dense_passes.empty()) continue;
         ++planned;
         check_call(m, 0, L);
         for (int k = 0; k < 40; ++k, ++ranges) {
@@ -147,13 +147,13 @@ int main(int argc, char **argv) {
         const Model m = make(sizes, {20, 19, 18, 17, 16, 15, 14, 13, 12, 11, 10, 9, 8, 7, 6, 5, 4, 3, 2, 1, 0}, 2048);
         CHECK(check_call(m, 0, 21) == 2 && check_call(m, 1, 20) == 1 && check_call(m, 5, 7) == 1);
         const Model u = make(std::vector<int64_t>(9, ((int64_t)1 << 25) + 1), {8}, 2048);
-        CHECK(u.passes.size() == 2 && u.passes[0].width == 0);
+        CHECK(u.st.dense_passes.size() == 2 && u.st.dense_passes[0].width == 0);
         for (int first = 0; first < 9; ++first)
             for (int count = 1; first + count <= 9; ++count) check_call(u, first, count);
         const Model v = make({8, 1000, 1001, 4000, 6, 12}, {2, 4}, 2048);  // one launch; unscheduled ranges are plain updates
-        CHECK(v.passes.size() == 1);
+        CHECK(v.st.dense_passes.size() == 1);
         static DensePass part;
-        auto range = [&](int first, int last) { clip_pass(v.passes[0], v.e[(size_t)first], v.e[(size_t)last], 2048, part); };
+        auto range = [&](int first, int last) { clip_pass(v.st.dense_passes[0], v.e[(size_t)first], v.e[(size_t)last], 2048, part); };
         range(0, 2);
         CHECK(part.width == 0);
         range(1, 2);
@@ -169,7 +169,8 @@ int main(int argc, char **argv) {
     auto launches = [&](std::vector<int64_t> sizes) {
         std::vector<int> order;
         for (int l = (int)sizes.size() - 1; l >= 0; --l) order.push_back(l);
-        return (int)make(sizes, order, 2048).passes.size();
+        const Model m = make(sizes, order, 2048);
+        return m.st.table_first ? 0 : (int)m.st.dense_passes.size();
     };
     auto layers = [](size_t n, int64_t size) { return std::vector<int64_t>(n, size); };
     const int64_t large = (int64_t)3 << 23;
@@ -178,8 +179,8 @@ int main(int argc, char **argv) {
     CHECK(launches(layers(20, large - 1)) == 1 && launches(layers(20, large)) == 20);
     CHECK(launches({large, 5, 7, large, 9}) == 4 && launches({5, large, 7}) == 3 && launches({5, large - 1, 7, large - 1, 9}) == 1);
     // more pieces of 2^31 elements than a launch takes: no plan (the slot takes the table), and nothing written out of range
-    CHECK(make({(int64_t)1 << 37, 5}, {1, 0}, 2048 * 64).passes.empty());
-    CHECK(make({5, (int64_t)1 << 37}, {0}, 2048 * 64).passes.empty());
+    CHECK(make({(int64_t)1 << 37, 5}, {1, 0}, 2048 * 64).st.dense_passes.empty());
+    CHECK(make({5, (int64_t)1 << 37}, {0}, 2048 * 64).st.dense_passes.empty());
     std::printf("plan sweep ok: %ld slots, %ld ranges\n", planned, ranges);
     return 0;
 }

@@ -38,21 +38,22 @@ def test_more_segments_than_a_launch_takes(oracle, n_layers, period, policy, opt
                    iterations=2, policy=policy)
     for layerwise in (0, 1, 7):
         assert run_trajectory(oracle, w, iters=2, fused=True, wire16=wire16, layerwise=layerwise, options={"update_chunk": 1024}).frac() == 1.0
-    rep = DeviceReplica(w, 0, options={"update_chunk": 1024}, wire16=wire16)
-    rep.init_params()
-    rep.fill_grads(0)
-    flat = torch.cat([t for l in rep.sets[0] for t, k in zip(rep.sync, rep.layer_of) if k == l])
-    (rep.fill_peers16_from if wire16 else rep.fill_peers_from)(flat, 0, flat.numel())
-    streams = [a for a in (rep.a_sync, rep.a_s0, rep.a_s1, rep.a_model) if a is not None]
-    saved = [a.clone() for a in streams]
     seen = []
-    for layers in (n_layers, 1, 7):
-        for a, b in zip(streams, saved):
-            a.copy_(b)
-        rep.stats.fill_(-1.0)
-        for lo in range(0, n_layers, layers):
-            rep.ctx.ddp_fused_sync_update_layers(0, lo, min(layers, n_layers - lo), rep.peers16 if wire16 else rep.peers, int(wire16), 0, n, 0,
-                                                 rep.stats, rep.opt_struct(1))
-        seen.append([rep.stats.clone()] + [a.clone() for a in streams])
+    for dense_path in (1, 0):
+        rep = DeviceReplica(w, 0, options={"update_chunk": 1024, "dense_path": dense_path}, wire16=wire16)
+        rep.init_params()
+        rep.fill_grads(0)
+        flat = torch.cat([t for l in rep.sets[0] for t, k in zip(rep.sync, rep.layer_of) if k == l])
+        (rep.fill_peers16_from if wire16 else rep.fill_peers_from)(flat, 0, flat.numel())
+        streams = [a for a in (rep.a_sync, rep.a_s0, rep.a_s1, rep.a_model) if a is not None]
+        saved = [a.clone() for a in streams]
+        for layers in (n_layers, 1, 7):
+            for a, b in zip(streams, saved):
+                a.copy_(b)
+            rep.stats.fill_(-1.0)
+            for lo in range(0, n_layers, layers):
+                rep.ctx.ddp_fused_sync_update_layers(0, lo, min(layers, n_layers - lo), rep.peers16 if wire16 else rep.peers, int(wire16), 0, n, 0,
+                                                     rep.stats, rep.opt_struct(1))
+            seen.append([rep.stats.cpu()] + [a.cpu() for a in streams])
+        rep.close()
     assert all(torch.equal(a, b) for got in seen[1:] for a, b in zip(got, seen[0]))
-    rep.close()
