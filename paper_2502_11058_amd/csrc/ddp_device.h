@@ -554,19 +554,21 @@ __device__ __forceinline__ void fused_math4(const typename WireVec<W16>::type (&
     x = m;
 }
 
-// Run-time replica counts (the kernels compiled for a fixed count keep all replicas in registers): a thread parks
-// each vector it loads in LDS while it forms the rank-order sum, and reads the vectors back for the statistics, so every
-// replica is fetched from memory once (the averaging kernel keeps the first kRegReps replicas in registers and parks only
-// the rest).  The staging area is dynamic LDS laid out [replica][thread] (each thread only
-// ever touches its own column: no barrier needed, no bank conflicts); with kStageBytes of it, stage_threads(N) threads
-// of the workgroup (whole wavefronts) take part in the vector loop.
+// Run-time replica counts, those above kFixedReps (the kernels up to there keep all replicas in registers): the first kRegReps
+// replicas of a vector stay in registers; a thread parks the rest in LDS while it forms the rank-order sum and reads them back
+// for the statistics, so every replica is fetched from memory once.  The staging area is dynamic LDS laid out
+// [replica][thread] (each thread only ever touches its own column: no barrier needed, no bank conflicts); with kStageBytes of
+// it, stage_threads(staged replicas) threads of the workgroup (whole wavefronts) take part in the vector loop.
 constexpr int kStageBytes = 65536;
-constexpr int kRegReps = 16;  // averaging kernel, run-time count: replicas of a vector that stay in registers
-inline int stage_threads(int n_replicas) {
-    int t = kStageBytes / 16 / (n_replicas > 0 ? n_replicas : 1) / kWave * kWave;
-    return t > kThreads ? kThreads : t;  // at least one wavefront up to DDP_MAX_REPLICAS = 64
+constexpr int kFixedReps = 32;
+constexpr int kRegReps = 16;
+inline int stage_threads(int staged) {
+    const int t = kStageBytes / 16 / (staged > 0 ? staged : 1) / kWave * kWave;
+    return t > kThreads ? kThreads : t;  // at least one wavefront up to DDP_MAX_REPLICAS
 }
-static_assert(kStageBytes / 16 / DDP_MAX_REPLICAS >= kWave, "the staging area must hold one wavefront at the largest replica count");
+inline int stage_bytes(int staged) { return staged * stage_threads(staged) * 16; }
+static_assert(kStageBytes / 16 / (DDP_MAX_REPLICAS - kRegReps) >= kWave, "the staging area must hold one wavefront at the largest replica count");
+static_assert(kRegReps <= kFixedReps, "the run-time loop takes its register replicas without a condition");
 
 // lds_pad: bytes of dynamic LDS requested per workgroup although no kernel uses them.  A CU has 160 KiB, so the pad
 // caps how many workgroups are resident per CU, i.e. how wide the window of addresses in flight is.

@@ -23,7 +23,7 @@ inline void fill_peers(Peers &p, const FusedLaunch &f) {
     p.inv_n = f.inv_n;
     p.n = f.n_replicas;
     p.local_rank = f.local_rank;
-    p.stage_threads = stage_threads(f.n_replicas > kRegReps ? f.n_replicas - kRegReps : 0);  // only the terms beyond the registers are staged
+    p.stage_threads = stage_threads(f.n_replicas - kRegReps);  // only the terms beyond the registers are staged
 }
 
 // Both cases of Eq. (5) in one pass over the run c, whose peers' values start at flat index fo: the average over the N
@@ -34,7 +34,7 @@ inline void fill_peers(Peers &p, const FusedLaunch &f) {
 //                replicas that are averaged have taken this iteration's step; the bits of local update -> pack ->
 //                partial average -> unpack).
 // W16: peers are bf16 and the local replica contributes its bf16 rounding.  NREP > 0: the replica count (EXACT), or the
-// largest one that the registers are laid out for; 0: run-time loop.  gsum, msum: this thread's statistics (STATS).
+// largest one that the registers are laid out for; 0: run-time loop, for more than kFixedReps.  gsum, msum: this thread's statistics (STATS).
 template <bool ADAM, bool GBF16, bool MODEL, int NREP, bool EXACT, bool STATS, bool W16, bool UTS, bool BUF>
 __device__ __forceinline__ void fused_body(const Streams<GBF16> c, int64_t fo, const Peers &a, const UpdateScalars &s, double &gsum, double &msum) {
     typedef GradVec<GBF16> G;
@@ -115,9 +115,8 @@ __device__ __forceinline__ void fused_body(const Streams<GBF16> c, int64_t fo, c
             store4(i, pl, av, bv);
         }
     } else {
-        // run-time replica count; with statistics the terms beyond the first kRegReps are parked in LDS (see
-        // stage_threads) so that the peers are fetched once; only the first `vt` threads take part (all of them
-        // up to 32 replicas)
+        // run-time replica count, above kFixedReps; with statistics the terms beyond the first kRegReps are parked in LDS (see
+        // stage_threads) so that the peers are fetched once; only the first `vt` threads take part (192 at N = 33, 64 at 64)
         extern __shared__ __align__(16) unsigned char dyn_lds[];
         f32x4 *stage = reinterpret_cast<f32x4 *>(dyn_lds);
         const int vt = STATS ? a.stage_threads : kThreads;
@@ -135,12 +134,10 @@ __device__ __forceinline__ void fused_body(const Streams<GBF16> c, int64_t fo, c
             // the first kRegReps terms of the rank-order sum stay in registers, the rest are parked in LDS
             f32x4 r[kRegReps];
 #pragma unroll
-            for (int k = 0; k < kRegReps; ++k)
-                if (k < nrep) r[k] = term(k);
+            for (int k = 0; k < kRegReps; ++k) r[k] = term(k);
             f32x4 acc = r[0];
 #pragma unroll
-            for (int k = 1; k < kRegReps; ++k)
-                if (k < nrep) acc = acc + r[k];
+            for (int k = 1; k < kRegReps; ++k) acc = acc + r[k];
             for (int k0 = kRegReps; k0 < nrep; k0 += 8) {  // eight more peers in flight, then park and add them in rank order
                 f32x4 x[8];
 #pragma unroll
@@ -156,8 +153,7 @@ __device__ __forceinline__ void fused_body(const Streams<GBF16> c, int64_t fo, c
             f32x4 m = acc * inv_n;
             if constexpr (STATS) {
 #pragma unroll
-                for (int k = 0; k < kRegReps; ++k)
-                    if (k < nrep) stats4(m, r[k]);
+                for (int k = 0; k < kRegReps; ++k) stats4(m, r[k]);
                 for (int k = kRegReps; k < nrep; ++k) stats4(m, stage[(k - kRegReps) * vt + tid]);
                 msq4(m);
             }
@@ -197,8 +193,7 @@ __device__ __forceinline__ void fused_body(const Streams<GBF16> c, int64_t fo, c
 // (the residency pad, or the staging area of the run-time replica count if that is larger).
 template <bool A, bool G, bool M, int NR, bool EXACT, class K>
 int dispatch_fused_n(const FusedLaunch &f, const K &k) {
-    const int staged = f.n_replicas > kRegReps ? f.n_replicas - kRegReps : 0;
-    const int need = NR == 0 && f.st.partials ? staged * stage_threads(staged) * 16 : 0;
+    const int need = NR == 0 && f.st.partials ? stage_bytes(f.n_replicas - kRegReps) : 0;
     const int lds = f.lds_pad > need ? f.lds_pad : need;
     if (f.wire16) {
         if (f.update_first) return f.st.partials ? k.template go<A, G, M, NR, EXACT, true, true, true>(lds) : k.template go<A, G, M, NR, EXACT, false, true, true>(lds);
@@ -216,7 +211,7 @@ int dispatch_fused_t(const FusedLaunch &f, const K &k) {
         case 4: return dispatch_fused_n<A, G, M, 4, true>(f, k);
         case 8: return dispatch_fused_n<A, G, M, 8, true>(f, k);
         case 16: return dispatch_fused_n<A, G, M, 16, true>(f, k);
-        case 32: return dispatch_fused_n<A, G, M, 32, true>(f, k);
+        case kFixedReps: return dispatch_fused_n<A, G, M, kFixedReps, true>(f, k);
     }
     // Other counts up to 31 take the kernel laid out for the next power of two, whose upper loads are conditional: within 3 %
     // of the rate of the exact kernels beside them (28 M parameters, SGD-m, bf16 peers, N = 12: 130 us; 192 us with the
@@ -224,7 +219,7 @@ int dispatch_fused_t(const FusedLaunch &f, const K &k) {
     if (n < 4) return dispatch_fused_n<A, G, M, 4, false>(f, k);
     if (n < 8) return dispatch_fused_n<A, G, M, 8, false>(f, k);
     if (n < 16) return dispatch_fused_n<A, G, M, 16, false>(f, k);
-    if (n < 32) return dispatch_fused_n<A, G, M, 32, false>(f, k);
+    if (n < kFixedReps) return dispatch_fused_n<A, G, M, kFixedReps, false>(f, k);
     return dispatch_fused_n<A, G, M, 0, false>(f, k);
 }
 

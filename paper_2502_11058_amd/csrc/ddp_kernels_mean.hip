@@ -112,9 +112,9 @@ __global__ __launch_bounds__(kThreads) void mean_kernel(const MeanArgs a) {
         if constexpr (B > 1)
             for (; v < nv; v += kThreads) groups(v, std::integral_constant<int, 1>());
     } else if constexpr (STATS) {
-        // Run-time replica count with statistics: the first kRegReps replicas of a vector stay in registers, the rest are
-        // parked in LDS (one column per thread), so every replica is fetched from memory once and, up to 32 replicas,
-        // every thread takes part.
+        // Run-time replica count (above kFixedReps) with statistics: the first kRegReps replicas of a vector stay in registers,
+        // the rest are parked in LDS (one column per thread), so every replica is fetched from memory once; 192 threads take
+        // part at N = 33, 64 at N = 64.
         extern __shared__ __align__(16) unsigned char dyn_lds[];
         f32x4 *stage = reinterpret_cast<f32x4 *>(dyn_lds);
         const int vt = a.stage_threads;
@@ -122,12 +122,10 @@ __global__ __launch_bounds__(kThreads) void mean_kernel(const MeanArgs a) {
             for (int v = tid; v < nv; v += vt) {
                 f32x4 r[kRegReps];
 #pragma unroll
-                for (int k = 0; k < kRegReps; ++k)
-                    if (k < nrep) r[k] = wire4<W16, NT>(a.x[k], vbase + v);
+                for (int k = 0; k < kRegReps; ++k) r[k] = wire4<W16, NT>(a.x[k], vbase + v);
                 f32x4 acc = r[0];
 #pragma unroll
-                for (int k = 1; k < kRegReps; ++k)
-                    if (k < nrep) acc = acc + r[k];
+                for (int k = 1; k < kRegReps; ++k) acc = acc + r[k];
                 for (int k0 = kRegReps; k0 < nrep; k0 += 4) {  // four more loads in flight, then park and add them in rank order
                     f32x4 x[4];
 #pragma unroll
@@ -142,8 +140,7 @@ __global__ __launch_bounds__(kThreads) void mean_kernel(const MeanArgs a) {
                 }
                 const f32x4 m = acc * inv_n;
 #pragma unroll
-                for (int k = 0; k < kRegReps; ++k)
-                    if (k < nrep) stats4(m, r[k]);
+                for (int k = 0; k < kRegReps; ++k) stats4(m, r[k]);
                 for (int k = kRegReps; k < nrep; ++k) stats4(m, stage[(k - kRegReps) * vt + tid]);
                 msq4(m);
                 st<NT>(o4 + v, m);
@@ -214,8 +211,7 @@ __global__ __launch_bounds__(kThreads) void stats_single_kernel(const double *__
 // Dynamic LDS of a launch: the residency pad, or the staging area of the run-time replica count if that is larger.
 template <int NREP>
 int mean_lds(const MeanLaunch &a) {
-    const int staged = a.n_replicas > kRegReps ? a.n_replicas - kRegReps : 0;
-    const int need = NREP == 0 && a.st.partials ? staged * stage_threads(staged) * 16 : 0;
+    const int need = NREP == 0 && a.st.partials ? stage_bytes(a.n_replicas - kRegReps) : 0;
     return a.lds_pad > need ? a.lds_pad : need;
 }
 
@@ -259,7 +255,7 @@ int launch_mean(const MeanLaunch &a, void *stream) {
     ma.chunk_pos = a.chunk_pos;
     ma.inv_n = a.inv_n;
     ma.n = a.n_replicas;
-    ma.stage_threads = stage_threads(a.n_replicas > kRegReps ? a.n_replicas - kRegReps : 0);   // the replicas beyond the registers are staged
+    ma.stage_threads = stage_threads(a.n_replicas - kRegReps);  // the replicas beyond the registers are staged
     int rc;
     switch (a.n_replicas) {
         case 1: rc = launch_mean_n<1, true>(ma, a, stream); break;
@@ -278,8 +274,8 @@ int launch_mean(const MeanLaunch &a, void *stream) {
         case 14: rc = launch_mean_n<14, true>(ma, a, stream); break;
         case 15: rc = launch_mean_n<15, true>(ma, a, stream); break;
         case 16: rc = launch_mean_n<16, true>(ma, a, stream); break;
-        case 32: rc = launch_mean_n<32, true>(ma, a, stream); break;
-        default: rc = a.n_replicas < 32 ? launch_mean_n<32, false>(ma, a, stream) : launch_mean_n<0, false>(ma, a, stream); break;
+        case kFixedReps: rc = launch_mean_n<kFixedReps, true>(ma, a, stream); break;
+        default: rc = a.n_replicas < kFixedReps ? launch_mean_n<kFixedReps, false>(ma, a, stream) : launch_mean_n<0, false>(ma, a, stream); break;
     }
     return rc;
 }
