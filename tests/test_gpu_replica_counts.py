@@ -49,12 +49,15 @@ def test_counts_and_ranks(oracle, n, wire16):
                 rep.ctx.ddp_partial_average(r % 2, rep.flat, rep.peers, n, rank, rep.flat, rep.stats)
             assert np.array_equal(_host(rep.flat[:total]).view(np.int32), want.view(np.int32)), (n, rank)
             by_average = rep.stats.cpu().numpy().copy()
+            rep.stats.fill_(-1.0)                              # whatever the fused step leaves out stays visible
             _, ref = wk.sync(S, host_peers, rank, wire16=wire16)
             wk.local_update([_host(g) for g in rep.grad], r + 1)
             rep.fused_step(r, rank, with_stats=r != 1, wire16=wire16)          # without statistics in between
             by_fused = rep.stats.cpu().numpy()
+            if r == 1:
+                assert (by_fused == -1.0).all(), (n, rank)
             for i, (gam, msq) in enumerate(ref):
-                for got in (by_average, by_fused):
+                for got in (by_average,) if r == 1 else (by_average, by_fused):
                     assert got[2 * i] == pytest.approx(gam, rel=1e-10, abs=1e-300) and got[2 * i + 1] == pytest.approx(msq, rel=1e-10)
             for a, b in zip(rep.sync, wk.p):
                 assert np.array_equal(_host(a).view(np.int32), b.view(np.int32)), (optimizer, n, rank)
