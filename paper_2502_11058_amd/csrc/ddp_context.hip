@@ -1,5 +1,5 @@
 // Host side of the library: context, model registration, per-slot offset tables, argument checks and the four
-// per-iteration entry points (Algorithm 1 of the paper, one worker).  Kernels live in ddp_kernels.hip.
+// per-iteration entry points (Algorithm 1 of the paper, one worker).  The kernels are in ddp_kernels_*.hip.
 #include <hip/hip_runtime.h>
 
 #include <cmath>

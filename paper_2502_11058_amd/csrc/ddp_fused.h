@@ -17,7 +17,7 @@ struct Peers {
     int stage_threads;  // run-time replica count with statistics: threads that take part in the vector loop
 };
 
-// (entries from N-1 on are never read and stay as they are)
+// (entries from N-1 on are never read)
 inline void fill_peers(Peers &p, const FusedLaunch &f) {
     for (int k = 0; k + 1 < f.n_replicas; ++k) p.x[k] = f.x[k];
     p.inv_n = f.inv_n;

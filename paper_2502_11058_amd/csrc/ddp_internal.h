@@ -123,7 +123,7 @@ struct StatsLaunch {
                                   // itself; nullptr: a launch of its own follows (launch_stats)
 };
 
-// ---- launchers (ddp_kernels.hip) -------------------------------------------------------------------------------
+// ---- launchers (ddp_kernels_*.hip) -------------------------------------------------------------------------------
 struct MeanLaunch {
     const void *x[DDP_MAX_REPLICAS];  // replicas in rank order (fp32, or bf16 when wire16)
     bool wire16;

@@ -108,3 +108,35 @@ def test_small_layers_beside_a_large_one(per_layer, dense_path):
         assert (seen[-1] >= 0.0).all()
         assert np.array_equal(seen[-1], seen[0]), layers
     rep.close()
+
+
+@pytest.mark.parametrize("dense_path", [1, 0])
+@pytest.mark.parametrize("per_layer", [[30] * 12, [128, 1, 127, 64, 3, 100]])
+def test_ranges_in_flight_on_two_streams(per_layer, dense_path):
+    """Range calls that put their statistics together themselves, disjoint ones in flight at the same time on two streams (each
+    layer has its own counter and partials): the bits of the calls one after the other, on every repetition."""
+    assert torch.cuda.is_available(), "no GPU visible"
+    L = len(per_layer)
+    ts = [W.TensorSpec(f"l{l}", l, 1024 * k - (l % 3)) for l, k in enumerate(per_layer)]
+    w = W.Workload(f"streams{L}", ts, n_replicas=4, period=1, optimizer="sgdm", param_dtype="f32", lr=1e-2, sigma_drift=1e-3, policy="every")
+    rep = DeviceReplica(w, 0, options={"update_chunk": 1024, "mean_chunk": 1024, "dense_path": dense_path})
+    rep.init_params()
+    rep.fill_grads(0)
+    flat = torch.cat([rep.sync[l] for l in rep.sets[0]])
+    rep.fill_peers_from(flat, 0, flat.numel())
+    saved = [a.clone() for a in (rep.a_sync, rep.a_s0)]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    opt = rep.opt_struct(1)
+    seen = []
+    for turn in range(12):
+        rep.a_sync.copy_(saved[0])
+        rep.a_s0.copy_(saved[1])
+        rep.stats.fill_(-1.0)
+        torch.cuda.synchronize()
+        for l in range(L):
+            s = streams[l % 2] if turn else streams[0]
+            rep.ctx.ddp_fused_sync_update_layers(0, l, 1, rep._peers_arr, 0, 0, 4, 0, rep.stats, opt, s)
+        torch.cuda.synchronize()
+        seen.append([rep.stats.clone(), rep.a_sync.clone(), rep.a_s0.clone()])
+        assert all(torch.equal(a, b) for a, b in zip(seen[-1], seen[0])), turn
+    rep.close()
