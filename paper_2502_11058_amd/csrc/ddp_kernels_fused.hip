@@ -27,12 +27,13 @@ struct FusedArgs {
 template <bool ADAM, bool GBF16, bool MODEL, int NREP, bool EXACT, bool STATS, bool W16, bool UTS>
 __global__ __launch_bounds__(kThreads, 2) void fused_kernel(const FusedArgs a) {
     __shared__ double lds[2][kThreads / kWave];
+    const bool paced = ADAM && long_launch();
     const UpdateChunk ch = a.chunks[blockIdx.x];
     const TensorDesc td = a.runs[ch.run];
     const RunSlot ts = a.run_slot[ch.run];
     const Streams<GBF16> c = chunk_streams<GBF16>(td, ch);
     if (ts.flat0 < 0) {  // uniform for the workgroup
-        update_body<ADAM, GBF16, MODEL, true, false>(c, a.s);
+        update_body<ADAM, GBF16, MODEL, true, false>(c, a.s, paced);
         return;
     }
     double gsum = 0.0, msum = 0.0;

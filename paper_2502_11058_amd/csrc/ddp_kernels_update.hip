@@ -7,9 +7,10 @@ namespace {
 template <bool ADAM, bool GBF16, bool MODEL, bool NT>
 __global__ __launch_bounds__(kThreads) void update_kernel(const TensorDesc *__restrict__ runs, const UpdateChunk *__restrict__ chunks,
                                                           const UpdateScalars s) {
+    const bool paced = ADAM && long_launch();
     const UpdateChunk ch = chunks[blockIdx.x];
     const TensorDesc td = runs[ch.run];
-    update_body<ADAM, GBF16, MODEL, NT, false>(chunk_streams<GBF16>(td, ch), s);
+    update_body<ADAM, GBF16, MODEL, NT, false>(chunk_streams<GBF16>(td, ch), s, paced);
 }
 
 // The update when the registered tensors lie back to back in every stream (one arena per stream): workgroup b takes

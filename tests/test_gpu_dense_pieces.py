@@ -57,3 +57,24 @@ def test_more_segments_than_a_launch_takes(oracle, n_layers, period, policy, opt
             seen.append([rep.stats.cpu()] + [a.cpu() for a in streams])
         rep.close()
     assert all(torch.equal(a, b) for got in seen[1:] for a, b in zip(got, seen[0]))
+
+
+@pytest.mark.parametrize("chunks", [16383, 16385])
+def test_long_table_launches(chunks):
+    """AdamW launches of the table-driven kernels on both sides of the length from which they ask for less at a time: the bits of
+    the table-free kernels, for the update alone and for the fused step."""
+    w = W.Workload(f"long{chunks}", [W.TensorSpec("a", 0, 1024 * (chunks - 3) + 5), W.TensorSpec("b", 1, 2051)], n_replicas=2, period=2,
+                   optimizer="adamw", param_dtype="bf16", lr=1e-3, sigma_drift=1e-3, policy="round_robin")
+    got = []
+    for dense_path in (1, 0):
+        rep = DeviceReplica(w, 0, options={"update_chunk": 1024, "dense_path": dense_path})
+        rep.init_params()
+        for r in (0, 1):                                # the long layer scheduled, then the short one
+            rep.fill_grads(r)
+            rep.ctx.ddp_pack(r, rep.flat)
+            rep.fill_peers_from(rep.flat, r, rep.slot_numel[r])
+            rep.fused_step(r)
+            rep.ctx.ddp_local_update(rep.opt_struct(r + 2))
+        got.append([a.cpu() for a in (rep.a_sync, rep.a_s0, rep.a_s1, rep.a_model, rep.stats)])
+        rep.close()
+    assert all(torch.equal(a, b) for a, b in zip(*got))
