@@ -724,15 +724,15 @@ extern "C" int ddp_local_update_layers(ddp_ctx *ctx, int layer_first, int layer_
     });
 }
 
-// The kernels of the fused step over layers [first, first + count) of a model registered as dense arenas.
-static int fused_dense(const ddp_ctx *ctx, const SlotTables &st, int first, int count, const FusedLaunch &common, void *stream) {
-    const int64_t e0 = layer_elem0(ctx, first), e1 = layer_elem0(ctx, first + count);
+// The kernels of the fused step over elements [e0, e1), whole layers, of a model registered as dense arenas; `at`: the first launch.
+static int fused_dense(const ddp_ctx *ctx, const SlotTables &st, std::vector<DensePass>::const_iterator at, int64_t e0, int64_t e1,
+                       const FusedLaunch &common, void *stream) {
     FusedDense f;
     static_cast<FusedLaunch &>(f) = common;
     const TensorDesc &t0 = ctx->tensors[0];
     f.d = {t0.grad, t0.sync, t0.state0, t0.state1, t0.model, 0, (int)ctx->update_chunk};
     int rc = 0;
-    for (auto at = first_pass(st, e0); at != st.dense_passes.end() && at->begin < e1 && rc == 0; ++at) {
+    for (; at != st.dense_passes.end() && at->begin < e1 && rc == 0; ++at) {
         DensePass part;
         f.pass = &*at;
         if (at->begin < e0 || at->end > e1) {
@@ -804,8 +804,10 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     f.s = s;
     f.lds_pad = ctx->update_lds;
     f.st = {any ? ctx->d_partials : nullptr, st->d_update_ranges, layer_stats, fold ? ctx->d_counters : nullptr};
-    if (ctx->dense_path && takes_pieces(*st, layer_elem0(ctx, first), layer_elem0(ctx, first + count))) {
-        rc = fused_dense(ctx, *st, first, count, f, stream);
+    const int64_t e0 = layer_elem0(ctx, first), e1 = layer_elem0(ctx, first + count);
+    const auto at = first_pass(*st, e0);
+    if (ctx->dense_path && takes_pieces(*st, at, e1)) {
+        rc = fused_dense(ctx, *st, at, e0, e1, f, stream);
     } else {
         f.runs = ctx->d_runs;
         f.chunks = ctx->d_update + c0;

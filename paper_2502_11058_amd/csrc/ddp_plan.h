@@ -118,9 +118,10 @@ inline std::vector<DensePass>::const_iterator first_pass(const SlotTables &st, i
     return std::upper_bound(st.dense_passes.begin(), st.dense_passes.end(), e0, [](int64_t e, const DensePass &p) { return e < p.end; });
 }
 
-// Whether a call on elements [e0, e1), e0 < e1, runs pieces: where the table is better for the slot, if one launch does it.
-inline bool takes_pieces(const SlotTables &st, int64_t e0, int64_t e1) {
-    return !st.dense_passes.empty() && (!st.table_first || first_pass(st, e0)->end >= e1);
+// Whether a call on elements up to e1 whose first launch is `at` runs pieces: where the table is better for the slot, if one
+// launch does it.
+inline bool takes_pieces(const SlotTables &st, std::vector<DensePass>::const_iterator at, int64_t e1) {
+    return at != st.dense_passes.end() && (!st.table_first || at->end >= e1);
 }
 
 // What a call on elements [e0, e1), whole layers, runs of launch p: the pieces inside, runs of unscheduled layers cut at the
@@ -141,6 +142,7 @@ inline void clip_pass(const DensePass &p, int64_t e0, int64_t e1, int64_t chunk,
     bool scheduled = false;
     for (int i = 0; i < p.n_pieces; ++i) {
         const Piece &whole = p.pieces[i];
+        if (whole.begin >= e1) break;
         const int64_t b = std::max(whole.begin, e0), e = std::min(whole.begin + whole.count, e1);
         if (b >= e) continue;
         Piece &q = part.pieces[part.n_pieces++];

@@ -107,7 +107,7 @@ static int check_call(const Model &m, int first, int count) {
         CHECK(at == part.end && widest == part.width);
     }
     CHECK(at == e1);
-    CHECK(takes_pieces(m.st, e0, e1) == (!m.st.table_first || launches == 1));
+    CHECK(takes_pieces(m.st, first_pass(m.st, e0), e1) == (!m.st.table_first || launches == 1));
     return launches;
 }
 
