@@ -417,7 +417,7 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
             }
             for (size_t i = 0; i + 1 < st.update_ranges.size(); i += 2)
                 st.max_update_partials = std::max<int64_t>(st.max_update_partials, st.update_ranges[i + 1] - st.update_ranges[i]);
-            if (fold_stats(ctx->cus, st.n_mean, st.n_mean))
+            if (folds(ctx->cus, st.n_mean, st.n_mean, st.max_mean_partials))
                 for (size_t i = 0; i + 1 < lcp.size(); ++i) mean_ranges.insert(mean_ranges.end(), (size_t)(lcp[i + 1] - lcp[i]), (int32_t)i);
             if (rc == DDP_OK) rc = upload(ctx, mean_ranges, &st.d_layer_ranges);
             if (rc == DDP_OK) rc = upload(ctx, run_slot, &st.d_run_slot);
@@ -430,8 +430,9 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
         }
         max_mean_chunks = std::max(max_mean_chunks, ctx->n_update);  // the fused step keeps one partial per update chunk
         if (max_mean_chunks > 0) {
-            const size_t sums = ((size_t)max_mean_chunks + (size_t)ctx->L * kStatSlices) * 2;
-            const std::vector<int32_t> zeros((size_t)ctx->L, 0);
+            const size_t line = kFoldLine * sizeof(int32_t) / sizeof(double);  // the counters start on a cache line
+            const size_t sums = (((size_t)max_mean_chunks + (size_t)ctx->L * kStatSlices) * 2 + line - 1) / line * line;
+            const std::vector<int32_t> zeros((size_t)ctx->L * kFoldStride, 0);
             hipError_t e = hipMalloc((void **)&ctx->d_partials, sums * sizeof(double) + zeros.size() * sizeof(int32_t));
             if (e != hipSuccess) {
                 ctx->d_partials = nullptr;
@@ -590,7 +591,7 @@ int ddp::partial_average_impl(ddp_ctx *ctx, const char *who, bool wire16, int sl
     a.out = flat_out;
     a.chunks = s->d_mean;
     a.n_chunks = s->n_mean;
-    const bool fold = layer_stats && !scratch && fold_stats(ctx->cus, s->n_mean, s->n_mean);
+    const bool fold = layer_stats && !scratch && folds(ctx->cus, s->n_mean, s->n_mean, s->max_mean_partials);
     a.st = {layer_stats ? partials : nullptr, s->d_layer_ranges, layer_stats, fold ? ctx->d_counters : nullptr};
     a.chunk_pos = s->d_layer_ranges + 2 * s->layers.size();
     a.nontemporal = ctx->nontemporal;
@@ -786,13 +787,17 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     // single run).
     const int nl = (int)st->layers.size();
     auto inside = [&](int i) { return i < nl && st->layers[(size_t)i] >= first && st->layers[(size_t)i] < first + count; };
-    int64_t partials = 0;
+    int64_t partials = 0, most = 0;
     for (int i = 0; layer_stats && i < nl; ++i)
-        if (inside(i)) partials += st->update_ranges[2 * (size_t)i + 1] - st->update_ranges[2 * (size_t)i];
+        if (inside(i)) {
+            const int64_t n = st->update_ranges[2 * (size_t)i + 1] - st->update_ranges[2 * (size_t)i];
+            partials += n;
+            most = std::max(most, n);
+        }
     const bool any = partials > 0;
     // One order of summation for a slot, whatever range the call has: the workgroups add a layer's partials up in the order of
     // the one-launch reduction, so they do it only in slots that this reduction serves.
-    const bool fold = any && st->max_update_partials <= kStatSingleMax && fold_stats(ctx->cus, c1 - c0, partials);
+    const bool fold = any && st->max_update_partials <= kStatSingleMax && folds(ctx->cus, c1 - c0, partials, most);
     f.wire16 = wire16;
     f.update_first = update_first;
     f.n_replicas = N;

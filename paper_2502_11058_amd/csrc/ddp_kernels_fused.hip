@@ -39,10 +39,9 @@ __global__ __launch_bounds__(kThreads, 2) void fused_kernel(const FusedArgs a) {
     double gsum = 0.0, msum = 0.0;
     fused_body<ADAM, GBF16, MODEL, NREP, EXACT, STATS, W16, UTS, false>(c, ts.flat0 + ch.begin, a.peers, a.s, gsum, msum);
     if constexpr (STATS) {
-        const double gt = block_sum(gsum, lds[0]);
-        const double mt = block_sum(msum, lds[1]);
+        block_sum2(gsum, msum, lds);
         // chunks end at the parameters' 16-byte boundaries: chunk c of a run begins 0..3 elements before c * chunk_elems
-        put_partial(a.st, (int64_t)a.run_chunk_base[ch.run] + (ch.begin + 3) / a.chunk_elems, ts.pos, ts.layer, a.peers.n, gt, mt, lds);
+        put_partial(a.st, (int64_t)a.run_chunk_base[ch.run] + (ch.begin + 3) / a.chunk_elems, ts.pos, ts.layer, a.peers.n, gsum, msum, lds);
     }
 }
 

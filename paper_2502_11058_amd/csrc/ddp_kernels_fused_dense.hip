@@ -47,9 +47,8 @@ __global__ __launch_bounds__(kThreads, 2) void fused_dense_kernel(const FusedDen
     double gsum = 0.0, msum = 0.0;
     fused_body<ADAM, GBF16, MODEL, NREP, EXACT, STATS, W16, UTS, true>(c, t.flat0 + at, a.peers, a.s, gsum, msum);
     if constexpr (STATS) {
-        const double gt = block_sum(gsum, lds[0]);
-        const double mt = block_sum(msum, lds[1]);
-        put_partial(a.st, (int64_t)t.pbase + blockIdx.x, t.pos, t.layer, a.peers.n, gt, mt, lds);
+        block_sum2(gsum, msum, lds);
+        put_partial(a.st, (int64_t)t.pbase + blockIdx.x, t.pos, t.layer, a.peers.n, gsum, msum, lds);
     }
 }
 

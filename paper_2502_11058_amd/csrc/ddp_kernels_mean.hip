@@ -155,10 +155,9 @@ __global__ __launch_bounds__(kThreads) void mean_kernel(const MeanArgs a) {
     }
 
     if constexpr (STATS) {
-        const double g = block_sum(gsum, lds[0]);
-        const double m = block_sum(msum, lds[1]);
+        block_sum2(gsum, msum, lds);
         const int pos = a.st.counters ? a.chunk_pos[ch.partial] : 0;
-        put_partial(a.st, ch.partial, pos, pos, nrep, g, m, lds);
+        put_partial(a.st, ch.partial, pos, pos, nrep, gsum, msum, lds);
     }
 }
 
@@ -177,8 +176,7 @@ __global__ __launch_bounds__(kThreads) void stats_slices_kernel(const double *__
         g += partials[2 * c];
         m += partials[2 * c + 1];
     }
-    g = block_sum(g, lds[0]);
-    m = block_sum(m, lds[1]);
+    block_sum2(g, m, lds);
     if (threadIdx.x == 0) {
         slice_sums[2 * ((int64_t)l * kStatSlices + j)] = g;
         slice_sums[2 * ((int64_t)l * kStatSlices + j) + 1] = m;

@@ -10,16 +10,26 @@
 namespace ddp {
 
 // Whether the workgroups of a launch put the layers' statistics together themselves: `partials` of its `workgroups` have a pair
-// of partial sums.  That saves a launch (3 us of host time), but each of these workgroups makes its pair visible to the other
-// XCDs before it ends, which writes its L2 back.  Launch of their own / folded in us, fused SGD, N = 4, 256 CUs:
-//                  behind other work    back to back    waited for
-//     32 pairs        6.7 / 6.2          7.6 / 5.8      19.3 / 18.4
-//     64 pairs        6.8 / 6.9          7.5 / 6.5      19.0 / 19.1
-//    128 pairs        6.9 / 8.2          7.5 / 7.7      19.1 / 20.3
-//    256 pairs        7.3 / 10.7         9.1 / 10.1     19.5 / 22.5
-// (the average alone: 128 pairs 7.9 / 7.3 back to back, 256 pairs 8.2 / 9.6).  Hence half a workgroup per CU, where calls back
-// to back break even, in launches of not much more than one (the others hide the second launch's host time).
+// of partial sums, at most `most` in one layer.  That saves a launch (3 us of host time), but each of these workgroups waits for
+// its pair and its counter to be where all XCDs see them before it ends.  Half a workgroup per CU with a share, in launches of
+// not much more than one, was the line while every pair cost a write-back of an L2 and a layer had one counter ...
 inline bool fold_stats(int cus, int64_t workgroups, int64_t partials) { return 2 * partials <= cus && 4 * workgroups <= 5 * (int64_t)cus; }
+// ... and counted in groups (kFoldGroup) it pays up to 5/4 workgroups per CU with a share, whatever the launch has besides.  Launch
+// of their own / folded in us, 256 CUs, two layers (four at 396 and 513 pairs):
+//                             back to back    waited for    behind other work
+//     fused SGD, N = 4  128   8.19 /  7.74   20.9 / 20.3      8.4 /  8.1
+//                       198  10.51 / 10.22   23.4 / 22.9     10.7 / 10.4
+//                       352  15.19 / 14.22   27.6 / 26.7     15.2 / 14.4
+//     average, N = 4    128   6.84 /  5.72   17.9 / 17.8      6.1 /  6.0
+//                       256   6.75 /  5.53   17.5 / 17.4      5.9 /  5.9
+//     average, N = 12   256   9.27 /  9.11   20.7 / 20.5      9.8 /  9.6
+//                       352  11.03 / 11.27   23.1 / 23.1     11.4 / 11.5
+//     average, N = 8    396   9.05 /  8.88   21.2 / 21.2      9.5 /  9.3
+//                       513  10.98 / 11.41   22.5 / 22.9     11.8 / 12.2
+inline bool fold_grouped(int cus, int64_t partials, int64_t most) { return 4 * partials <= 5 * (int64_t)cus && most <= kFoldGroup * kFoldGroups; }
+inline bool folds(int cus, int64_t workgroups, int64_t partials, int64_t most) {
+    return fold_stats(cus, workgroups, partials) || fold_grouped(cus, partials, most);
+}
 
 // Workgroups of the table-free fused kernel over elements [e0, e1) of the arenas: chunks counted from the multiple of four at
 // or below e0, where every stream is vector-aligned.
