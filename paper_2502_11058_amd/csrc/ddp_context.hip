@@ -290,9 +290,9 @@ extern "C" int ddp_register_model(ddp_ctx *ctx, int L, int T, const int32_t *lay
         }
         ctx->dense = dense;
 
-        // Update table: every run cut into chunks of update_chunk elements that end on the parameters' 16-byte boundaries, so
-        // that only a run's first and last chunk have elements outside a whole vector.  A run is a tensor; over dense arenas it
-        // is a whole layer, so that the table's chunks, and the partial sums that they give, are those of the table-free kernels.
+        // Update table: every run cut into chunks of update_chunk elements that end on cache lines (kLine), so that only a run's
+        // first and last chunk have elements outside a whole vector.  A run is a tensor; over dense arenas it is a whole layer,
+        // so that the table's chunks, and the partial sums that they give, are those of the table-free kernels.
         std::vector<TensorDesc> runs = ts;
         ctx->layer_first_run = first;
         if (dense) {
@@ -308,7 +308,8 @@ extern "C" int ddp_register_model(ddp_ctx *ctx, int L, int T, const int32_t *lay
         ctx->run_chunk_base.clear();
         for (size_t t = 0; t < runs.size(); ++t) {
             ctx->run_chunk_base.push_back((int32_t)uc.size());
-            const int64_t past = (int64_t)((reinterpret_cast<uintptr_t>(runs[t].sync) >> 2) & 3u);  // elements past such a boundary
+            // elements past such a boundary
+            const int64_t past = dense ? (runs[t].sync - ts[0].sync) % kLine : (int64_t)((reinterpret_cast<uintptr_t>(runs[t].sync) >> 2) % kLine);
             for (int64_t b = 0, e; b < runs[t].numel; b = e) {
                 e = std::min<int64_t>(runs[t].numel, (b + past) / ctx->update_chunk * ctx->update_chunk + ctx->update_chunk - past);
                 uc.push_back({b, (int32_t)t, (int32_t)(e - b)});
@@ -386,11 +387,13 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
                     }
                     off += ctx->numel[(size_t)t];
                 }
-                // mean chunks: cut the layer's flat range at multiples of mean_chunk measured from a 4-element
-                // boundary, so that every chunk but the first starts 16-byte aligned
+                // mean chunks: the layer's flat range cut at multiples of mean_chunk measured from a cache line (kLine), so that
+                // every chunk but the first starts on one in all buffers.  As many as from a 4-element boundary, so that a slot
+                // needs no more scratch: what would be one more, less than a line, goes with the last.
+                const int64_t n = (off - layer_start / 4 * 4 + ctx->mean_chunk - 1) / ctx->mean_chunk;
                 int64_t b = layer_start;
-                while (b < off) {
-                    int64_t e = std::min<int64_t>(off, (b / 4) * 4 + ctx->mean_chunk);
+                for (int64_t c = 1; b < off; ++c) {
+                    const int64_t e = c >= n ? off : std::min<int64_t>(off, layer_start / kLine * kLine + c * ctx->mean_chunk);
                     mc.push_back({b, (int32_t)(e - b), (int32_t)mc.size()});
                     b = e;
                 }
@@ -422,7 +425,7 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
             if (rc == DDP_OK) rc = upload(ctx, mean_ranges, &st.d_layer_ranges);
             if (rc == DDP_OK) rc = upload(ctx, run_slot, &st.d_run_slot);
             if (rc == DDP_OK) rc = upload(ctx, st.update_ranges, &st.d_update_ranges);
-            if (ctx->dense) plan_dense(st, ctx->L, [&](int l) { return layer_elem0(ctx, l); }, ctx->update_chunk);
+            if (ctx->dense) plan_dense(st, ctx->L, [&](int l) { return layer_elem0(ctx, l); }, ctx->update_chunk, kLine);
             if (rc != DDP_OK) {
                 for (auto &x : slots) free_slot(x);
                 return rc;
@@ -690,6 +693,7 @@ static bool dense_range(const ddp_ctx *ctx, int first, int count, DenseLaunch &d
     d.mdl = ctx->param_dtype == DDP_BF16 ? t0.model + e0 : nullptr;
     d.n = e1 - e0;
     d.chunk = (int)ctx->update_chunk;
+    d.past = (int)(e0 % kLine);
     return true;
 }
 
@@ -731,13 +735,13 @@ static int fused_dense(const ddp_ctx *ctx, const SlotTables &st, std::vector<Den
     FusedDense f;
     static_cast<FusedLaunch &>(f) = common;
     const TensorDesc &t0 = ctx->tensors[0];
-    f.d = {t0.grad, t0.sync, t0.state0, t0.state1, t0.model, 0, (int)ctx->update_chunk};
+    f.d = {t0.grad, t0.sync, t0.state0, t0.state1, t0.model, 0, (int)ctx->update_chunk, 0};
     int rc = 0;
     for (; at != st.dense_passes.end() && at->begin < e1 && rc == 0; ++at) {
         DensePass part;
         f.pass = &*at;
         if (at->begin < e0 || at->end > e1) {
-            clip_pass(*at, e0, e1, ctx->update_chunk, part);
+            clip_pass(*at, e0, e1, ctx->update_chunk, part, kLine);
             f.pass = &part;
         }
         if (f.pass->width > 0) {
@@ -752,6 +756,7 @@ static int fused_dense(const ddp_ctx *ctx, const SlotTables &st, std::vector<Den
         d.s1 = d.s1 ? d.s1 + e : nullptr;
         d.mdl = d.mdl ? d.mdl + e : nullptr;
         d.n = f.pass->end - e;
+        d.past = (int)(e % kLine);
         rc = launch_update_dense(f.kind, f.grad_dtype, f.with_model, d, f.s, true, f.lds_pad, stream);
     }
     return rc;

@@ -505,6 +505,7 @@ struct DenseArgs {
     unsigned short *mdl;
     int64_t n;  // elements in the range
     int chunk;  // elements per workgroup, a multiple of 1024
+    int past;   // elements of the first workgroup's chunk that lie before the range (kLine)
     UpdateScalars s;
 };
 

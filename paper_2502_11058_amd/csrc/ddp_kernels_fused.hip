@@ -40,8 +40,8 @@ __global__ __launch_bounds__(kThreads, 2) void fused_kernel(const FusedArgs a) {
     fused_body<ADAM, GBF16, MODEL, NREP, EXACT, STATS, W16, UTS, false>(c, ts.flat0 + ch.begin, a.peers, a.s, gsum, msum);
     if constexpr (STATS) {
         block_sum2(gsum, msum, lds);
-        // chunks end at the parameters' 16-byte boundaries: chunk c of a run begins 0..3 elements before c * chunk_elems
-        put_partial(a.st, (int64_t)a.run_chunk_base[ch.run] + (ch.begin + 3) / a.chunk_elems, ts.pos, ts.layer, a.peers.n, gsum, msum, lds);
+        // chunks end on cache lines: chunk c of a run begins less than kLine elements before c * chunk_elems
+        put_partial(a.st, (int64_t)a.run_chunk_base[ch.run] + (ch.begin + kLine - 1) / a.chunk_elems, ts.pos, ts.layer, a.peers.n, gsum, msum, lds);
     }
 }
 

@@ -31,7 +31,7 @@ __global__ __launch_bounds__(kThreads, 2) void fused_dense_kernel(const FusedDen
     asm volatile("" ::"s"(a.d.g), "s"(a.d.p), "s"(a.d.s0), "s"(a.d.s1), "s"(a.d.mdl));
 #pragma unroll
     for (int j = 0; j < (NREP < 16 ? NREP : 16) - 1; ++j) asm volatile("" ::"s"(a.peers.x[j]));
-    const int past = (int)t.begin & 3;                       // chunks end at multiples of four
+    const int past = (int)t.begin & (kLine - 1);             // chunks end at multiples of kLine
     const int hi = ((int)blockIdx.x + 1) * a.d.chunk - past;
     int at = hi - a.d.chunk;
     at = at > 0 ? at : 0;

@@ -14,14 +14,19 @@ __global__ __launch_bounds__(kThreads) void update_kernel(const TensorDesc *__re
 }
 
 // The update when the registered tensors lie back to back in every stream (one arena per stream): workgroup b takes
-// elements [b * chunk, (b + 1) * chunk) of the range, addresses follow from the block index alone (no table), and
-// every chunk starts aligned, so there is no head; only the last workgroup has a tail of fewer than four elements.
+// elements [b * chunk, (b + 1) * chunk) of the arenas, counted from the cache line (kLine) that the range starts in, addresses
+// follow from the block index alone (no table), and every chunk starts aligned, so there is no head; only the last workgroup
+// has a tail of fewer than four elements.
 // Same operations per element as update_kernel, hence the same bits.
 template <bool ADAM, bool GBF16, bool MODEL, int AUX>
 __global__ __launch_bounds__(kThreads) void update_dense_kernel(const DenseArgs a) {
-    const int64_t b = (int64_t)blockIdx.x * a.chunk;
+    int64_t b = (int64_t)blockIdx.x * a.chunk - a.past;
     const int64_t left = a.n - b;
-    const int count = left < (int64_t)a.chunk ? (int)left : a.chunk;
+    int count = left < (int64_t)a.chunk ? (int)left : a.chunk;
+    if (b < 0) {
+        count -= a.past;
+        b = 0;
+    }
     const Streams<GBF16> c{reinterpret_cast<const typename GradVec<GBF16>::elem *>(a.g) + b, a.p + b, a.s0 + b, a.s1 + b, a.mdl + b, count};
     update_body<ADAM, GBF16, MODEL, AUX != 0, true>(c, a.s);
 }
@@ -58,8 +63,9 @@ int launch_update_dense(int kind, int grad_dtype, bool with_model, const DenseLa
     a.mdl = d.mdl;
     a.n = d.n;
     a.chunk = d.chunk;
+    a.past = d.past;
     a.s = s;
-    const int64_t grid = (d.n + d.chunk - 1) / d.chunk;
+    const int64_t grid = (d.n + d.past + d.chunk - 1) / d.chunk;
     const bool adam = kind == DDP_OPT_ADAMW, gb = grad_dtype == DDP_BF16;
 #define DDP_UPD(A, G, M)                                                                                \
     if (adam == A && gb == G && with_model == M)                                                        \

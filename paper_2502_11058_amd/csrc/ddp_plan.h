@@ -31,9 +31,9 @@ inline bool folds(int cus, int64_t workgroups, int64_t partials, int64_t most) {
     return fold_stats(cus, workgroups, partials) || fold_grouped(cus, partials, most);
 }
 
-// Workgroups of the table-free fused kernel over elements [e0, e1) of the arenas: chunks counted from the multiple of four at
-// or below e0, where every stream is vector-aligned.
-inline int64_t dense_workgroups(int64_t e0, int64_t e1, int64_t chunk) { return (e1 - e0 / 4 * 4 + chunk - 1) / chunk; }
+// Workgroups of the table-free fused kernel over elements [e0, e1) of the arenas: chunks counted from the multiple of `line` at
+// or below e0 (kLine in the library; of four at least, where every stream is vector-aligned).
+inline int64_t dense_workgroups(int64_t e0, int64_t e1, int64_t chunk, int64_t line = 4) { return (e1 - e0 / line * line + chunk - 1) / chunk; }
 
 // Chunks of the widest piece that the kernel's 32-bit indexes allow.
 inline int64_t widest_piece(int64_t chunk) { return INT32_MAX / chunk - 1; }
@@ -41,8 +41,8 @@ inline int64_t widest_piece(int64_t chunk) { return INT32_MAX / chunk - 1; }
 // Elements [begin, end), all of one scheduled layer (flat0 >= 0) or all unscheduled, as pieces of at most `width` chunks behind
 // those that p has.
 inline void add_pieces(DensePass &p, int64_t begin, int64_t end, int64_t flat0, int64_t pbase, int32_t pos, int32_t layer, int64_t width,
-                       int64_t chunk) {
-    const int64_t base = begin / 4 * 4, wg = dense_workgroups(begin, end, chunk);
+                       int64_t chunk, int64_t line = 4) {
+    const int64_t base = begin / line * line, wg = dense_workgroups(begin, end, chunk, line);
     for (int64_t b = 0; b < wg; b += width) {
         const int64_t at = b == 0 ? begin : base + b * chunk, to = std::min(end, base + (b + width) * chunk);
         p.pieces[p.n_pieces++] = {at, flat0 < 0 ? -1 : flat0 + (at - begin), (int32_t)(to - at), (int32_t)(pbase + b), pos, layer};
@@ -61,7 +61,7 @@ inline void add_pieces(DensePass &p, int64_t begin, int64_t end, int64_t flat0, 
 // 64 K 17.0 / 12.5, of 256 K 37.9 / 34.3, of 1 M 117 / 115; N = 2: 21 of 1 M 126 / 129, 40 of 4 M 836 / 868.
 // No passes where a launch would need more than kMaxPieces pieces: such a slot always takes the table.
 template <class Elem0>
-void plan_dense(SlotTables &st, int L, Elem0 &&elem0, int64_t chunk) {
+void plan_dense(SlotTables &st, int L, Elem0 &&elem0, int64_t chunk, int64_t line = 4) {
     constexpr int kMaxSegments = 20;
     struct Segment {
         int64_t begin, end, flat0, pbase, wg;
@@ -73,7 +73,7 @@ void plan_dense(SlotTables &st, int L, Elem0 &&elem0, int64_t chunk) {
         int m = l + 1;
         while (i < 0 && m < L && st.layer_pos[(size_t)m] < 0) ++m;
         all.push_back({elem0(l), elem0(m), i < 0 ? -1 : st.layer_begin[(size_t)i], i < 0 ? 0 : st.update_ranges[2 * (size_t)i],
-                       dense_workgroups(elem0(l), elem0(m), chunk), i, l});
+                       dense_workgroups(elem0(l), elem0(m), chunk, line), i, l});
         l = m;
     }
     std::vector<DensePass> &passes = st.dense_passes;
@@ -119,7 +119,7 @@ void plan_dense(SlotTables &st, int L, Elem0 &&elem0, int64_t chunk) {
             }
         p.width = (int)width;
         for (int k = 0; k < n; ++k)
-            add_pieces(p, seg[k].begin, seg[k].end, seg[k].flat0, seg[k].pbase, seg[k].pos, seg[k].layer, width, chunk);
+            add_pieces(p, seg[k].begin, seg[k].end, seg[k].flat0, seg[k].pbase, seg[k].pos, seg[k].layer, width, chunk, line);
     }
 }
 
@@ -136,7 +136,7 @@ inline bool takes_pieces(const SlotTables &st, std::vector<DensePass>::const_ite
 
 // What a call on elements [e0, e1), whole layers, runs of launch p: the pieces inside, runs of unscheduled layers cut at the
 // range's ends.  No search and nothing allocated; part is written only as far as its pieces go.
-inline void clip_pass(const DensePass &p, int64_t e0, int64_t e1, int64_t chunk, DensePass &part) {
+inline void clip_pass(const DensePass &p, int64_t e0, int64_t e1, int64_t chunk, DensePass &part, int64_t line = 4) {
     part.begin = std::max(p.begin, e0);
     part.end = std::min(p.end, e1);
     part.width = part.n_pieces = 0;
@@ -144,9 +144,9 @@ inline void clip_pass(const DensePass &p, int64_t e0, int64_t e1, int64_t chunk,
     if (p.width == 0) {
         if (part.begin % 4 == 0) return;  // a plain update as well
         // (no more pieces than the whole run would have, which plan_dense has counted)
-        const int64_t wg = dense_workgroups(part.begin, part.end, chunk);
+        const int64_t wg = dense_workgroups(part.begin, part.end, chunk, line);
         part.width = (int)std::min(wg, widest_piece(chunk));
-        add_pieces(part, part.begin, part.end, -1, 0, -1, -1, part.width, chunk);
+        add_pieces(part, part.begin, part.end, -1, 0, -1, -1, part.width, chunk, line);
         return;
     }
     bool scheduled = false;
@@ -159,7 +159,7 @@ inline void clip_pass(const DensePass &p, int64_t e0, int64_t e1, int64_t chunk,
         q = whole;
         q.begin = b;  // (moves in unscheduled pieces only: a scheduled one is part of one layer)
         q.count = (int32_t)(e - b);
-        part.width = std::max(part.width, (int)dense_workgroups(b, e, chunk));
+        part.width = std::max(part.width, (int)dense_workgroups(b, e, chunk, line));
         scheduled = scheduled || q.flat0 >= 0;
     }
     if (!scheduled && part.begin % 4 == 0) part.width = part.n_pieces = 0;  // a plain update, whose workgroups start sooner
