@@ -2,6 +2,8 @@
 #ifndef DDP_FUSED_H
 #define DDP_FUSED_H
 
+#include <type_traits>
+
 #include "ddp_device.h"
 
 #pragma clang fp contract(off)
@@ -94,26 +96,46 @@ __device__ __forceinline__ void fused_body(const Streams<GBF16> c, int64_t fo, c
     if constexpr (NREP > 1) {
         // The local contribution may be computed (updated and / or rounded) and a branch on it per replica would serialise
         // the loads: the N-1 peers are loaded by their position among the peers, all in flight before the first use.
-        for (int v = tid; v < nv; v += kThreads) {
-            const unsigned i = 4u * v;
-            typename WireVec<W16>::type pv[NREP - 1];
+        // One vector of all streams in flight per thread, two where many replicas come as bf16: half the bytes a peer, and while
+        // one vector's long sum is formed nothing else would be asked for.  Fused, bf16 peers, us, one / two: GPT-2 small AdamW
+        // N = 12 687 / 677, N = 24 836 / 812, N = 32 889 / 882, SGD N = 24 672 / 642; 134 M parameters, AdamW, N = 24 935 / 900;
+        // N = 8 634 / 634.  With fp32 peers two are slower (GPT-2 small SGD N = 8 528 / 531, N = 2 420 / 427).
+        constexpr bool kPairs = W16 && NREP >= 16;
+        typedef typename WireVec<W16>::type raw4;
+        auto groups = [&](int v, auto count) {
+            constexpr int K = decltype(count)::value;
+            raw4 pv[K][NREP - 1];
+            f32x4 pl[K], av[K], bv[K];
+            gvec gv[K];
 #pragma unroll
-            for (int j = 0; j < NREP - 1; ++j) {
-                pv[j] = typename WireVec<W16>::type{};
-                if (j < kPeersAlways<NREP, EXACT> || j < nrep - 1) {
-                    // (a buffer's base must be dword-aligned, which a bf16 peer's need not be)
-                    const Stream<BUF && !W16, xelem> x(reinterpret_cast<const xelem *>(a.x[j]) + bfo, nv);
-                    pv[j] = __builtin_bit_cast(typename WireVec<W16>::type, x.template ld<NT>(i));
+            for (int k = 0; k < K; ++k) {
+                const unsigned i = 4u * (v + k * kThreads);
+#pragma unroll
+                for (int j = 0; j < NREP - 1; ++j) {
+                    pv[k][j] = raw4{};
+                    if (j < kPeersAlways<NREP, EXACT> || j < nrep - 1) {
+                        // (a buffer's base must be dword-aligned, which a bf16 peer's need not be)
+                        const Stream<BUF && !W16, xelem> x(reinterpret_cast<const xelem *>(a.x[j]) + bfo, nv);
+                        pv[k][j] = __builtin_bit_cast(raw4, x.template ld<NT>(i));
+                    }
                 }
+                pl[k] = b.p.template ld<NT>(i);
+                gv[k] = b.g.template ld<NT>(i);
+                av[k] = b.s0.template ld<NT>(i);
+                bv[k] = f32x4{};
+                if constexpr (ADAM) bv[k] = b.s1.template ld<NT>(i);
             }
-            f32x4 pl = b.p.template ld<NT>(i);
-            const gvec gv = b.g.template ld<NT>(i);
-            f32x4 av = b.s0.template ld<NT>(i);
-            f32x4 bv{};
-            if constexpr (ADAM) bv = b.s1.template ld<NT>(i);
-            fused_math4<ADAM, GBF16, NREP, EXACT, STATS, W16, UTS>(pv, gv, pl, av, bv, nrep, lr, inv_n, s, gsum, msum);
-            store4(i, pl, av, bv);
-        }
+            if constexpr (K > 1) __builtin_amdgcn_sched_barrier(0);  // all requested before the first vector's arithmetic
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                fused_math4<ADAM, GBF16, NREP, EXACT, STATS, W16, UTS>(pv[k], gv[k], pl[k], av[k], bv[k], nrep, lr, inv_n, s, gsum, msum);
+                store4(4u * (v + k * kThreads), pl[k], av[k], bv[k]);
+            }
+        };
+        int v = tid;
+        if constexpr (kPairs)
+            for (; v + kThreads < nv; v += 2 * kThreads) groups(v, std::integral_constant<int, 2>());
+        for (; v < nv; v += kThreads) groups(v, std::integral_constant<int, 1>());
     } else {
         // run-time replica count, above kFixedReps; with statistics the terms beyond the first kRegReps are parked in LDS (see
         // stage_threads) so that the peers are fetched once; only the first `vt` threads take part (192 at N = 33, 64 at 64)
