@@ -431,7 +431,8 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
                 return rc;
             }
         }
-        max_mean_chunks = std::max(max_mean_chunks, ctx->n_update);  // the fused step keeps one partial per update chunk
+        // the fused step keeps one partial per update chunk, the average of many replicas two per chunk (mean_cut)
+        max_mean_chunks = std::max(2 * max_mean_chunks, ctx->n_update);
         if (max_mean_chunks > 0) {
             const size_t line = kFoldLine * sizeof(int32_t) / sizeof(double);  // the counters start on a cache line
             const size_t sums = (((size_t)max_mean_chunks + (size_t)ctx->L * kStatSlices) * 2 + line - 1) / line * line;
@@ -551,14 +552,15 @@ int ddp::partial_average_impl(ddp_ctx *ctx, const char *who, bool wire16, int sl
     const SlotTables *s = slot_of(ctx, slot, who, &rc);
     if (!s) return rc;
     double *partials = ctx->d_partials, *slice_sums = ctx->d_slice_sums;
+    const int cut = mean_cut(ctx->cus, ctx->mean_chunk, s->n_mean, (int64_t)s->layers.size(), N, wire16), pairs = cut ? 2 : 1;
     if (scratch) {
-        const int64_t need = (s->n_mean + (int64_t)s->layers.size() * kStatSlices) * 2 * (int64_t)sizeof(double);
+        const int64_t need = (s->n_mean + (int64_t)s->layers.size() * kStatSlices) * 2 * (int64_t)sizeof(double);  // (cut, it fits)
         if (layer_stats && need > scratch_bytes)
             return fail(ctx, DDP_ESHAPE, std::string(who) + ": slot " + std::to_string(slot) + " needs " + std::to_string(need) +
                                              " bytes of reduction scratch (" + std::to_string(s->n_mean) + " chunks), the fixed scratch holds " +
                                              std::to_string(scratch_bytes) + "; use ddp_partial_average or a larger mean_chunk");
         partials = scratch;
-        slice_sums = scratch + 2 * s->n_mean;
+        slice_sums = scratch + 2 * pairs * s->n_mean;
     }
     if ((rc = check_device(ctx, who)) != DDP_OK) return rc;
     if (N < 1 || N > DDP_MAX_REPLICAS) return fail(ctx, DDP_EINVAL, std::string(who) + ": N must be in [1, " + std::to_string((int)DDP_MAX_REPLICAS) + "]");
@@ -594,8 +596,11 @@ int ddp::partial_average_impl(ddp_ctx *ctx, const char *who, bool wire16, int sl
     a.out = flat_out;
     a.chunks = s->d_mean;
     a.n_chunks = s->n_mean;
-    const bool fold = layer_stats && !scratch && folds(ctx->cus, s->n_mean, s->n_mean, s->max_mean_partials);
-    a.st = {layer_stats ? partials : nullptr, s->d_layer_ranges, layer_stats, fold ? ctx->d_counters : nullptr};
+    a.cut = cut;
+    // (a slot whose chunks would not be folded uncut has no positions of them)
+    const bool fold = layer_stats && !scratch && folds(ctx->cus, s->n_mean, s->n_mean, s->max_mean_partials) &&
+                      folds(ctx->cus, pairs * s->n_mean, pairs * s->n_mean, pairs * s->max_mean_partials);
+    a.st = {layer_stats ? partials : nullptr, s->d_layer_ranges, layer_stats, fold ? ctx->d_counters : nullptr, pairs};
     a.chunk_pos = s->d_layer_ranges + 2 * s->layers.size();
     a.nontemporal = ctx->nontemporal;
     // Two workgroups per CU pace the requests of many replicas best, but few replicas leave too little in flight (TinyLlama-1.1B,
@@ -607,7 +612,7 @@ int ddp::partial_average_impl(ddp_ctx *ctx, const char *who, bool wire16, int sl
     a.lds_pad = wire16 ? pad / 2 : pad;
     rc = launch_mean(a, stream);
     if (rc == 0 && layer_stats && !fold)
-        rc = launch_stats(partials, slice_sums, s->d_layer_ranges, (int)s->layers.size(), N, layer_stats, s->max_mean_partials, stream);
+        rc = launch_stats(partials, slice_sums, s->d_layer_ranges, pairs, (int)s->layers.size(), N, layer_stats, pairs * s->max_mean_partials, stream);
     return after_launch(ctx, who, rc);
 }
 
@@ -813,7 +818,7 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     f.with_model = ctx->param_dtype == DDP_BF16;
     f.s = s;
     f.lds_pad = ctx->update_lds;
-    f.st = {any ? ctx->d_partials : nullptr, st->d_update_ranges, layer_stats, fold ? ctx->d_counters : nullptr};
+    f.st = {any ? ctx->d_partials : nullptr, st->d_update_ranges, layer_stats, fold ? ctx->d_counters : nullptr, 1};
     const int64_t e0 = layer_elem0(ctx, first), e1 = layer_elem0(ctx, first + count);
     const auto at = first_pass(*st, e0);
     if (ctx->dense_path && takes_pieces(*st, at, e1)) {
@@ -831,7 +836,7 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
         int j = i;
         while (inside(j)) ++j;
         if (j > i)
-            rc = launch_stats(f.st.partials, ctx->d_slice_sums + (int64_t)i * 2 * kStatSlices, st->d_update_ranges + 2 * i, j - i, N,
+            rc = launch_stats(f.st.partials, ctx->d_slice_sums + (int64_t)i * 2 * kStatSlices, st->d_update_ranges + 2 * i, 1, j - i, N,
                               layer_stats + 2 * i, st->max_update_partials, stream);
         i = j + 1;
     }

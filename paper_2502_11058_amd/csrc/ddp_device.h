@@ -310,7 +310,7 @@ __device__ __forceinline__ void put_partial(const StatsLaunch &st, int64_t parti
         return;
     }
     __shared__ int is_last;
-    const int64_t c0 = st.layer_ranges[2 * pos], c1 = st.layer_ranges[2 * pos + 1];
+    const int64_t c0 = (int64_t)st.pairs * st.layer_ranges[2 * pos], c1 = (int64_t)st.pairs * st.layer_ranges[2 * pos + 1];
     if (threadIdx.x == 0) {
         const double was_g = __hip_atomic_exchange(st.partials + 2 * partial, g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const double was_m = __hip_atomic_exchange(st.partials + 2 * partial + 1, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -128,10 +128,11 @@ constexpr int kFoldGroup = 16, kFoldGroups = 16, kFoldLine = 32, kFoldStride = (
 // How the per-layer statistics of a launch are put together from its workgroups' partial pairs.
 struct StatsLaunch {
     double *partials;             // nullptr: no statistics
-    const int32_t *layer_ranges;  // per position in the slot [first, last) partial index
+    const int32_t *layer_ranges;  // per position in the slot [first, last) chunk, in chunks of `pairs` partial pairs each
     double *stats;                // [positions][2]
     int32_t *counters;            // kFoldStride per layer, zero between launches: the layer's last workgroup adds the partials up
                                   // in the kernel itself; nullptr: a launch of its own follows (launch_stats)
+    int pairs;
 };
 
 // ---- launchers (ddp_kernels_*.hip) -------------------------------------------------------------------------------
@@ -143,7 +144,8 @@ struct MeanLaunch {
     float *out;
     const MeanChunk *chunks;
     int64_t n_chunks;
-    StatsLaunch st;
+    int cut;                   // elements after which a chunk is cut in two, a workgroup each; 0: not cut
+    StatsLaunch st;            // st.pairs: 2 where chunks are cut
     const int32_t *chunk_pos;  // with st.counters: per chunk, by its partial index, the position of its layer
     bool nontemporal;
     int lds_pad;
@@ -157,13 +159,14 @@ struct UpdateScalars {
 int launch_copy(bool unpack, const TensorDesc *tensors, const CopyChunk *chunks, int64_t n_chunks, float *flat,
                 bool with_model, bool nontemporal, int lds_pad, void *stream);
 int launch_mean(const MeanLaunch &a, void *stream);
-// Per-layer statistics from per-chunk partials: layer l of n_layers adds partials [ranges[2l], ranges[2l+1]) in a fixed
-// order through kStatSlices slice sums (slice_sums: [n_layers][kStatSlices][2]) into stats[2l], stats[2l+1].
+// Per-layer statistics from per-chunk partials: layer l of n_layers adds the `pairs` partials of each of the chunks
+// [ranges[2l], ranges[2l+1]) in a fixed order through kStatSlices slice sums (slice_sums: [n_layers][kStatSlices][2]) into
+// stats[2l], stats[2l+1].
 // With at most kStatSingleMax partials in any of the layers (max_partials_per_layer, an upper bound is enough) one launch
 // does it all; beyond that the two stages.
 constexpr int kStatSlices = 64;
 constexpr int64_t kStatSingleMax = 4096;
-int launch_stats(const double *partials, double *slice_sums, const int32_t *ranges, int n_layers, int n_replicas, double *stats,
+int launch_stats(const double *partials, double *slice_sums, const int32_t *ranges, int pairs, int n_layers, int n_replicas, double *stats,
                  int64_t max_partials_per_layer, void *stream);
 int launch_pack16(const TensorDesc *tensors, const CopyChunk *chunks, int64_t n_chunks, uint16_t *flat16, bool nontemporal, int lds_pad,
                   void *stream);

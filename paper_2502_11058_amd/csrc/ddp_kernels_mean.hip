@@ -14,6 +14,7 @@ struct MeanArgs {
     const int32_t *chunk_pos;
     float inv_n;
     int n;
+    int cut;            // MeanLaunch
     int stage_threads;  // run-time replica count with statistics: threads that take part in the vector loop
 };
 
@@ -26,7 +27,21 @@ struct MeanArgs {
 template <int NREP, bool EXACT, bool STATS, bool NT, bool W16>
 __global__ __launch_bounds__(kThreads) void mean_kernel(const MeanArgs a) {
     __shared__ double lds[2][kThreads / kWave];
-    const MeanChunk ch = a.chunks[blockIdx.x];
+    MeanChunk ch;
+    if constexpr (NREP > 16) {
+        // One vector per thread at a time, and nothing asked for while its sum and squares are formed: with a chunk's second
+        // vectors in a workgroup of their own the other one's loads fill that time (rule and figures: mean_cut).
+        const int half = a.cut ? (int)blockIdx.x & 1 : 0;
+        ch = a.chunks[a.cut ? blockIdx.x >> 1 : blockIdx.x];
+        if (a.cut) {
+            const int first = a.cut - ((int)ch.begin & (kLine - 1)), at = first < ch.count ? first : ch.count;
+            ch.begin += half ? at : 0;
+            ch.count = half ? ch.count - at : at;
+        }
+        ch.partial = ch.partial * a.st.pairs + half;
+    } else {
+        ch = a.chunks[blockIdx.x];
+    }
     const int n = ch.count;
     const int tid = threadIdx.x;
     const int nrep = EXACT ? NREP : a.n;
@@ -156,7 +171,7 @@ __global__ __launch_bounds__(kThreads) void mean_kernel(const MeanArgs a) {
 
     if constexpr (STATS) {
         block_sum2(gsum, msum, lds);
-        const int pos = a.st.counters ? a.chunk_pos[ch.partial] : 0;
+        const int pos = a.st.counters ? a.chunk_pos[NREP > 16 ? ch.partial / a.st.pairs : ch.partial] : 0;
         put_partial(a.st, ch.partial, pos, pos, nrep, gsum, msum, lds);
     }
 }
@@ -166,10 +181,10 @@ __global__ __launch_bounds__(kThreads) void mean_kernel(const MeanArgs a) {
 // slices, one workgroup each (thread-strided sums, then the workgroup tree); stage 2 adds the slice sums of a layer
 // in slice order and scales the divergence by 1/N (Sec. 3.4: Gamma = 1/K sum_k ||wbar - w^k||^2, per layer).
 __global__ __launch_bounds__(kThreads) void stats_slices_kernel(const double *__restrict__ partials,
-                                                                const int32_t *__restrict__ ranges, double *__restrict__ slice_sums) {
+                                                                const int32_t *__restrict__ ranges, int pairs, double *__restrict__ slice_sums) {
     __shared__ double lds[2][kThreads / kWave];
     const int l = blockIdx.y, j = blockIdx.x;
-    const int64_t c0 = ranges[2 * l], c1 = ranges[2 * l + 1];
+    const int64_t c0 = (int64_t)pairs * ranges[2 * l], c1 = (int64_t)pairs * ranges[2 * l + 1];
     const int64_t lo = c0 + (c1 - c0) * j / kStatSlices, hi = c0 + (c1 - c0) * (j + 1) / kStatSlices;
     double g = 0.0, m = 0.0;
     for (int64_t c = lo + (int64_t)threadIdx.x; c < hi; c += kThreads) {
@@ -200,10 +215,10 @@ __global__ __launch_bounds__(kWave) void stats_finalize_kernel(const double *__r
 // The same reduction in one launch, for layers with few partials (launch-bound slots): one workgroup per layer adds the
 // layer's partials thread-strided, then the workgroup tree.  Fixed order as well.
 __global__ __launch_bounds__(kThreads) void stats_single_kernel(const double *__restrict__ partials, const int32_t *__restrict__ ranges,
-                                                                int n_replicas, double *__restrict__ stats) {
+                                                                int pairs, int n_replicas, double *__restrict__ stats) {
     __shared__ double lds[2][kThreads / kWave];
     const int l = blockIdx.x;
-    sum_partials(partials, ranges[2 * l], ranges[2 * l + 1], n_replicas, stats + 2 * l, lds);
+    sum_partials(partials, (int64_t)pairs * ranges[2 * l], (int64_t)pairs * ranges[2 * l + 1], n_replicas, stats + 2 * l, lds);
 }
 
 // Dynamic LDS of a launch: the residency pad, or the staging area of the run-time replica count if that is larger.
@@ -215,28 +230,29 @@ int mean_lds(const MeanLaunch &a) {
 
 template <int NREP, bool EXACT>
 int launch_mean_n(const MeanArgs &ma, const MeanLaunch &a, void *stream) {
+    const int64_t grid = a.cut ? 2 * a.n_chunks : a.n_chunks;
     if (a.wire16) {
-        if (a.st.partials) return launch(mean_kernel<NREP, EXACT, true, true, true>, a.n_chunks, stream, mean_lds<NREP>(a), ma);
-        return launch(mean_kernel<NREP, EXACT, false, true, true>, a.n_chunks, stream, a.lds_pad, ma);
+        if (a.st.partials) return launch(mean_kernel<NREP, EXACT, true, true, true>, grid, stream, mean_lds<NREP>(a), ma);
+        return launch(mean_kernel<NREP, EXACT, false, true, true>, grid, stream, a.lds_pad, ma);
     }
-    if (a.st.partials) return a.nontemporal ? launch(mean_kernel<NREP, EXACT, true, true, false>, a.n_chunks, stream, mean_lds<NREP>(a), ma)
-                                         : launch(mean_kernel<NREP, EXACT, true, false, false>, a.n_chunks, stream, mean_lds<NREP>(a), ma);
-    return a.nontemporal ? launch(mean_kernel<NREP, EXACT, false, true, false>, a.n_chunks, stream, a.lds_pad, ma)
-                         : launch(mean_kernel<NREP, EXACT, false, false, false>, a.n_chunks, stream, a.lds_pad, ma);
+    if (a.st.partials) return a.nontemporal ? launch(mean_kernel<NREP, EXACT, true, true, false>, grid, stream, mean_lds<NREP>(a), ma)
+                                         : launch(mean_kernel<NREP, EXACT, true, false, false>, grid, stream, mean_lds<NREP>(a), ma);
+    return a.nontemporal ? launch(mean_kernel<NREP, EXACT, false, true, false>, grid, stream, a.lds_pad, ma)
+                         : launch(mean_kernel<NREP, EXACT, false, false, false>, grid, stream, a.lds_pad, ma);
 }
 
 }  // namespace
 
-int launch_stats(const double *partials, double *slice_sums, const int32_t *ranges, int n_layers, int n_replicas, double *stats,
+int launch_stats(const double *partials, double *slice_sums, const int32_t *ranges, int pairs, int n_layers, int n_replicas, double *stats,
                  int64_t max_partials_per_layer, void *stream) {
     if (n_layers <= 0) return 0;
     if (max_partials_per_layer <= kStatSingleMax) {
         hipLaunchKernelGGL(stats_single_kernel, dim3((unsigned)n_layers), dim3(kThreads), 0, (hipStream_t)stream, partials, ranges,
-                           n_replicas, stats);
+                           pairs, n_replicas, stats);
         return (int)hipGetLastError();
     }
     hipLaunchKernelGGL(stats_slices_kernel, dim3(kStatSlices, (unsigned)n_layers), dim3(kThreads), 0, (hipStream_t)stream, partials,
-                       ranges, slice_sums);
+                       ranges, pairs, slice_sums);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return (int)e;
     hipLaunchKernelGGL(stats_finalize_kernel, dim3((unsigned)n_layers), dim3(kWave), 0, (hipStream_t)stream,
@@ -253,6 +269,7 @@ int launch_mean(const MeanLaunch &a, void *stream) {
     ma.chunk_pos = a.chunk_pos;
     ma.inv_n = a.inv_n;
     ma.n = a.n_replicas;
+    ma.cut = a.cut;
     ma.stage_threads = stage_threads(a.n_replicas - kRegReps);  // the replicas beyond the registers are staged
     int rc;
     switch (a.n_replicas) {

@@ -31,6 +31,18 @@ inline bool folds(int cus, int64_t workgroups, int64_t partials, int64_t most) {
     return fold_stats(cus, workgroups, partials) || fold_grouped(cus, partials, most);
 }
 
+// Where the average of N replicas cuts its chunks of `chunk` elements in two, a workgroup each (0: not).  The kernel for more than
+// 16 replicas takes the halves of a chunk one after the other; cut, one workgroup asks while another adds.  Not cut / cut in
+// us, average of fp32 replicas, slots of 2 M, 7 M and 34 M elements: N = 18 31.7 / 33.3, 96 / 96, 424 / 424; N = 24 40.3 / 40.9,
+// 124 / 116, 554 / 516; N = 28 45.9 / 47.1, 142 / 134, 643 / 598; N = 32 49.0 / 48.2, 155 / 150, 729 / 694; the four calls of
+// whole models around such slots, bf16 replicas: N = 24 62.8 / 61.1, 179 / 175, 804 / 783; N = 32 68.0 / 65.0, 197 / 191,
+// 894 / 873.  Up to 16 replicas both halves are in flight together (N = 12, 7 M: 62.5 / 66.1).  A cut chunk has two pairs of partial
+// sums, so slots whose pairs would not fit the fixed scratch are not cut, whichever scratch a call has: same bits from both.
+inline int mean_cut(int cus, int64_t chunk, int64_t n_chunks, int64_t n_layers, int N, bool wire16) {
+    if (N <= 16 || N > 32 || !(wire16 || N == 32 || n_chunks >= 8 * (int64_t)cus)) return 0;
+    return (2 * n_chunks + n_layers * kStatSlices) * 2 * (int64_t)sizeof(double) <= (int64_t)DDP_STATIC_SCRATCH_BYTES ? (int)(chunk / 2) : 0;
+}
+
 // Workgroups of the table-free fused kernel over elements [e0, e1) of the arenas: chunks counted from the multiple of `line` at
 // or below e0 (kLine in the library; of four at least, where every stream is vector-aligned).
 inline int64_t dense_workgroups(int64_t e0, int64_t e1, int64_t chunk, int64_t line = 4) { return (e1 - e0 / line * line + chunk - 1) / chunk; }
