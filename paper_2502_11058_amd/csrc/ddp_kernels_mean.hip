@@ -27,20 +27,15 @@ struct MeanArgs {
 template <int NREP, bool EXACT, bool STATS, bool NT, bool W16>
 __global__ __launch_bounds__(kThreads) void mean_kernel(const MeanArgs a) {
     __shared__ double lds[2][kThreads / kWave];
-    MeanChunk ch;
-    if constexpr (NREP > 16) {
-        // One vector per thread at a time, and nothing asked for while its sum and squares are formed: with a chunk's second
-        // vectors in a workgroup of their own the other one's loads fill that time (rule and figures: mean_cut).
-        const int half = a.cut ? (int)blockIdx.x & 1 : 0;
-        ch = a.chunks[a.cut ? blockIdx.x >> 1 : blockIdx.x];
-        if (a.cut) {
-            const int first = a.cut - ((int)ch.begin & (kLine - 1)), at = first < ch.count ? first : ch.count;
-            ch.begin += half ? at : 0;
-            ch.count = half ? ch.count - at : at;
-        }
-        ch.partial = ch.partial * a.st.pairs + half;
-    } else {
-        ch = a.chunks[blockIdx.x];
+    // (a chunk's halves: rule and figures at mean_cut)
+    const int half = NREP > 0 && a.cut ? (int)blockIdx.x & 1 : 0;
+    MeanChunk ch = a.chunks[NREP > 0 && a.cut ? blockIdx.x >> 1 : blockIdx.x];
+    const int entry = ch.partial;
+    if (NREP > 0 && a.cut) {
+        const int first = a.cut - ((int)ch.begin & (kLine - 1)), at = first < ch.count ? first : ch.count;
+        ch.begin += half ? at : 0;
+        ch.count = half ? ch.count - at : at;
+        ch.partial = 2 * entry + half;
     }
     const int n = ch.count;
     const int tid = threadIdx.x;
@@ -171,7 +166,7 @@ __global__ __launch_bounds__(kThreads) void mean_kernel(const MeanArgs a) {
 
     if constexpr (STATS) {
         block_sum2(gsum, msum, lds);
-        const int pos = a.st.counters ? a.chunk_pos[NREP > 16 ? ch.partial / a.st.pairs : ch.partial] : 0;
+        const int pos = a.st.counters ? a.chunk_pos[entry] : 0;
         put_partial(a.st, ch.partial, pos, pos, nrep, gsum, msum, lds);
     }
 }

@@ -32,14 +32,22 @@ inline bool folds(int cus, int64_t workgroups, int64_t partials, int64_t most) {
 }
 
 // Where the average of N replicas cuts its chunks of `chunk` elements in two, a workgroup each (0: not).  The kernel for more than
-// 16 replicas takes the halves of a chunk one after the other; cut, one workgroup asks while another adds.  Not cut / cut in
-// us, average of fp32 replicas, slots of 2 M, 7 M and 34 M elements: N = 18 31.7 / 33.3, 96 / 96, 424 / 424; N = 24 40.3 / 40.9,
-// 124 / 116, 554 / 516; N = 28 45.9 / 47.1, 142 / 134, 643 / 598; N = 32 49.0 / 48.2, 155 / 150, 729 / 694; the four calls of
-// whole models around such slots, bf16 replicas: N = 24 62.8 / 61.1, 179 / 175, 804 / 783; N = 32 68.0 / 65.0, 197 / 191,
-// 894 / 873.  Up to 16 replicas both halves are in flight together (N = 12, 7 M: 62.5 / 66.1).  A cut chunk has two pairs of partial
-// sums, so slots whose pairs would not fit the fixed scratch are not cut, whichever scratch a call has: same bits from both.
+// 16 replicas takes the halves of a chunk one after the other; cut, one workgroup asks while another adds.  Up to 16 replicas both
+// halves are in flight together, and cutting spreads the sums of small slots over more CUs.  Not cut / cut in us:
+//     fp32, slots of      131 K        262 K        524 K        720 K         2 M         7 M        34 M elements
+//     N = 12            6.4 / 6.2    7.0 / 7.1   10.1 / 9.2   11.1 / 11.2             62.5 / 66.1
+//     N = 16            6.9 / 6.5    8.4 / 8.3   12.4 / 10.8  13.6 / 13.5             81.6 / 81.5
+//     N = 18                                                              31.7 / 33.3   96 / 96     424 / 424
+//     N = 24           10.8 / 9.2   17.6 / 14.7  18.6 / 16.1  21.7 / 19.3  40.3 / 40.9  124 / 116   554 / 516
+//     N = 32                                     22.3 / 17.1               49.0 / 48.2  155 / 150   729 / 694
+//     four calls, bf16 N = 24                                              62.8 / 61.1  179 / 175   804 / 783
+//     four calls, bf16 N = 32                                              68.0 / 65.0  197 / 191   894 / 873
+// (N = 8: 131 K 5.8 / 5.5, 262 K 6.1 / 6.4; bf16, N = 12, waited for: 524 K 35.0 / 36.1).  A cut chunk has two pairs of partial sums,
+// so slots whose pairs would not fit the fixed scratch are not cut, whichever scratch a call has: same bits from both.
 inline int mean_cut(int cus, int64_t chunk, int64_t n_chunks, int64_t n_layers, int N, bool wire16) {
-    if (N <= 16 || N > 32 || !(wire16 || N == 32 || n_chunks >= 8 * (int64_t)cus)) return 0;
+    bool cut = N >= 12 && !wire16 && 4 * n_chunks <= 5 * (int64_t)cus;
+    if (N > 16) cut = wire16 || N == 32 || 2 * n_chunks <= 3 * (int64_t)cus || n_chunks >= 8 * (int64_t)cus;
+    if (!cut || N > 32) return 0;
     return (2 * n_chunks + n_layers * kStatSlices) * 2 * (int64_t)sizeof(double) <= (int64_t)DDP_STATIC_SCRATCH_BYTES ? (int)(chunk / 2) : 0;
 }
 

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 SIZES = [1, 511, 512, 513, 449, 575, 1023, 1024, 1025, 3 * 1024 + 7, 64 * 33 - 1, 2]
 
 
-@pytest.mark.parametrize("n,wire16", [(16, True), (17, True), (24, True), (31, False), (32, False), (32, True), (33, True)])
+@pytest.mark.parametrize("n,wire16", [(11, False), (12, False), (16, False), (16, True), (17, True), (24, False), (24, True), (31, False), (32, False), (32, True), (33, True)])
 @pytest.mark.parametrize("wide", [0, 2100 * 1024 + 5])
 def test_cut(oracle, n, wire16, wide):
     sizes = SIZES + ([wide] if wide else [])
