@@ -42,12 +42,14 @@ static int upload(const ddp_ctx *ctx, const std::vector<T> &host, T **dev) {
 }
 
 static void free_slot(SlotTables &s) {
-    if (s.d_copy) (void)hipFree(s.d_copy);
+    if (s.d_unpack && s.d_unpack != s.d_pack) (void)hipFree(s.d_unpack);
+    if (s.d_pack) (void)hipFree(s.d_pack);
     if (s.d_mean) (void)hipFree(s.d_mean);
     if (s.d_layer_ranges) (void)hipFree(s.d_layer_ranges);
     if (s.d_run_slot) (void)hipFree(s.d_run_slot);
     if (s.d_update_ranges) (void)hipFree(s.d_update_ranges);
-    s.d_copy = nullptr;
+    s.d_pack = nullptr;
+    s.d_unpack = nullptr;
     s.d_mean = nullptr;
     s.d_layer_ranges = nullptr;
     s.d_run_slot = nullptr;
@@ -67,13 +69,11 @@ static void drop_schedule(ddp_ctx *c) {
 
 static void drop_model(ddp_ctx *c) {
     drop_schedule(c);
-    if (c->d_tensors) (void)hipFree(c->d_tensors);
     if (c->d_runs) (void)hipFree(c->d_runs);
     if (c->d_update) (void)hipFree(c->d_update);
     if (c->d_run_chunk_base) (void)hipFree(c->d_run_chunk_base);
     c->d_run_chunk_base = nullptr;
     c->d_runs = nullptr;
-    c->d_tensors = nullptr;
     c->d_update = nullptr;
     c->n_update = 0;
     c->registered = false;
@@ -322,8 +322,8 @@ extern "C" int ddp_register_model(ddp_ctx *ctx, int L, int T, const int32_t *lay
         ctx->run_chunk_base.push_back((int32_t)uc.size());
         ctx->n_update = (int64_t)uc.size();
         interleave_segments(uc, ctx->dispatch_ways);
-        rc = upload(ctx, ts, &ctx->d_tensors);
-        if (rc == DDP_OK) rc = upload(ctx, runs, &ctx->d_runs);
+        rc = upload(ctx, runs, &ctx->d_runs);
+        ctx->runs = std::move(runs);
         if (rc == DDP_OK) rc = upload(ctx, uc, &ctx->d_update);
         if (rc == DDP_OK) rc = upload(ctx, ctx->run_chunk_base, &ctx->d_run_chunk_base);
         if (rc != DDP_OK) {
@@ -363,8 +363,20 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
         for (int s = 0; s < H; ++s) {
             SlotTables &st = slots[(size_t)s];
             st.layer_pos.assign((size_t)ctx->L, -1);
-            std::vector<CopyChunk> cc;
             std::vector<MeanChunk> mc;
+            std::vector<CopyChunk> pack, unpack;
+            bool one_table = true;  // both sides lie alike in their lines: unpack's chunks are pack's
+            int64_t total = 0;
+            for (int j = set_ptr[s]; j < set_ptr[s + 1]; ++j) total += layer_elem0(ctx, set_layers[j] + 1) - layer_elem0(ctx, set_layers[j]);
+            pack.reserve((size_t)(total / ctx->copy_chunk) + ctx->runs.size());
+            mc.reserve((size_t)(total / ctx->mean_chunk) + (size_t)ctx->L);
+            auto cut = [&](std::vector<CopyChunk> &to, int r, int64_t f0, int64_t past) {
+                const TensorDesc &run = ctx->runs[(size_t)r];
+                for (int64_t b = 0, e; b < run.numel; b = e) {
+                    e = std::min<int64_t>(run.numel, (b + past) / ctx->copy_chunk * ctx->copy_chunk + ctx->copy_chunk - past);
+                    to.push_back({run.sync + b, f0 + b, r, (int32_t)(e - b)});
+                }
+            };
             std::vector<int32_t> lcp;
             std::vector<RunSlot> run_slot(ctx->run_chunk_base.size() - 1, RunSlot{-1, -1, -1});
             int64_t off = 0;
@@ -381,11 +393,14 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
                     st.tensors.push_back(t);
                     st.tensor_off.push_back(off);
                     if (!ctx->dense || off == layer_start) run_slot[(size_t)(ctx->dense ? l : t)] = {off, st.layer_pos[(size_t)l], l};
-                    for (int64_t b = 0; b < ctx->numel[(size_t)t]; b += ctx->copy_chunk) {
-                        int64_t n = std::min<int64_t>(ctx->copy_chunk, ctx->numel[(size_t)t] - b);
-                        cc.push_back({b, off + b, t, (int32_t)n});
-                    }
                     off += ctx->numel[(size_t)t];
+                }
+                // copy chunks: the layer's runs (over dense arenas the layer is one) cut on the lines of what is written
+                for (int r = ctx->layer_first_run[(size_t)l]; r < ctx->layer_first_run[(size_t)l + 1]; ++r) {
+                    const TensorDesc &run = ctx->runs[(size_t)r];
+                    const int64_t f0 = run_slot[(size_t)r].flat0;
+                    cut(pack, r, f0, f0 % kLine);
+                    one_table = one_table && (f0 - (int64_t)(reinterpret_cast<uintptr_t>(run.sync) >> 2)) % kLine == 0;
                 }
                 // mean chunks: the layer's flat range cut at multiples of mean_chunk measured from a cache line (kLine), so that
                 // every chunk but the first starts on one in all buffers.  As many as from a 4-element boundary, so that a slot
@@ -398,19 +413,26 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
                     b = e;
                 }
             }
+            for (size_t j = 0; !one_table && j < st.layers.size(); ++j)
+                for (int r = ctx->layer_first_run[(size_t)st.layers[j]]; r < ctx->layer_first_run[(size_t)st.layers[j] + 1]; ++r)
+                    cut(unpack, r, run_slot[(size_t)r].flat0, (int64_t)((reinterpret_cast<uintptr_t>(ctx->runs[(size_t)r].sync) >> 2) % kLine));
             st.layer_begin.push_back(off);
             lcp.push_back((int32_t)mc.size());
-            if (mc.size() > (size_t)0x7fffffff || cc.size() > (size_t)0x7fffffff) {
+            if (mc.size() > (size_t)0x7fffffff || pack.size() > (size_t)0x7fffffff || unpack.size() > (size_t)0x7fffffff) {
                 for (auto &x : slots) free_slot(x);
                 return fail(ctx, DDP_ESHAPE, "ddp_set_schedule: more than 2^31-1 chunks in a slot; raise mean_chunk / copy_chunk");
             }
             st.numel = off;
-            st.n_copy = (int64_t)cc.size();
+            st.n_pack = (int64_t)pack.size();
+            st.n_unpack = one_table ? st.n_pack : (int64_t)unpack.size();
             st.n_mean = (int64_t)mc.size();
             max_mean_chunks = std::max(max_mean_chunks, st.n_mean);
-            interleave_segments(cc, ctx->dispatch_ways);
+            interleave_segments(pack, ctx->dispatch_ways);
+            interleave_segments(unpack, ctx->dispatch_ways);
             interleave_segments(mc, ctx->dispatch_ways);
-            rc = upload(ctx, cc, &st.d_copy);
+            rc = upload(ctx, pack, &st.d_pack);
+            if (rc == DDP_OK && !one_table) rc = upload(ctx, unpack, &st.d_unpack);
+            if (one_table) st.d_unpack = st.d_pack;
             if (rc == DDP_OK) rc = upload(ctx, mc, &st.d_mean);
             std::vector<int32_t> mean_ranges;
             for (size_t i = 0; i + 1 < lcp.size(); ++i) {
@@ -522,7 +544,7 @@ extern "C" int ddp_pack(ddp_ctx *ctx, int slot, float *flat_local, void *stream)
         if ((rc = check_device(ctx, "ddp_pack")) != DDP_OK) return rc;
         if (s->numel == 0) return DDP_OK;
         if ((rc = check_flat(ctx, flat_local, "ddp_pack", "flat_local")) != DDP_OK) return rc;
-        rc = launch_copy(false, ctx->d_tensors, s->d_copy, s->n_copy, flat_local, false, ctx->nontemporal, ctx->copy_lds, stream);
+        rc = launch_copy(false, ctx->d_runs, s->d_pack, s->n_pack, flat_local, false, ctx->nontemporal, ctx->copy_lds, stream);
         return after_launch(ctx, "ddp_pack", rc);
     });
 }
@@ -535,7 +557,7 @@ extern "C" int ddp_unpack(ddp_ctx *ctx, int slot, const float *flat, void *strea
         if ((rc = check_device(ctx, "ddp_unpack")) != DDP_OK) return rc;
         if (s->numel == 0) return DDP_OK;
         if ((rc = check_flat(ctx, flat, "ddp_unpack", "flat")) != DDP_OK) return rc;
-        rc = launch_copy(true, ctx->d_tensors, s->d_copy, s->n_copy, const_cast<float *>(flat), ctx->param_dtype == DDP_BF16,
+        rc = launch_copy(true, ctx->d_runs, s->d_unpack, s->n_unpack, const_cast<float *>(flat), ctx->param_dtype == DDP_BF16,
                          ctx->nontemporal, ctx->copy_lds, stream);
         return after_launch(ctx, "ddp_unpack", rc);
     });
@@ -632,7 +654,7 @@ extern "C" int ddp_pack_wire16(ddp_ctx *ctx, int slot, uint16_t *flat_local16, v
         if ((rc = check_device(ctx, "ddp_pack_wire16")) != DDP_OK) return rc;
         if (s->numel == 0) return DDP_OK;
         if ((rc = check_flat(ctx, flat_local16, "ddp_pack_wire16", "flat_local16")) != DDP_OK) return rc;
-        rc = launch_pack16(ctx->d_tensors, s->d_copy, s->n_copy, flat_local16, ctx->nontemporal, ctx->copy_lds, stream);
+        rc = launch_pack16(s->d_pack, s->n_pack, flat_local16, ctx->nontemporal, ctx->copy_lds, stream);
         return after_launch(ctx, "ddp_pack_wire16", rc);
     });
 }

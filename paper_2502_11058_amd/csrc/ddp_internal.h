@@ -60,10 +60,12 @@ struct UpdateChunk {  // local_update: elements [begin, begin+count) of run `run
     int32_t count;
 };
 
-struct CopyChunk {  // pack / unpack: tensor elements [t_begin, +count) <-> flat elements [flat_begin, +count)
-    int64_t t_begin;
+// pack / unpack: `count` elements at `sync`, in run `run` of the update table, <-> flat elements [flat_begin, +count).  The address is
+// in the record: a workgroup's first load waits for one table, not for a chunk and then a tensor.
+struct CopyChunk {
+    float *sync;
     int64_t flat_begin;
-    int32_t tensor;
+    int32_t run;
     int32_t count;
 };
 
@@ -105,8 +107,9 @@ struct SlotTables {
     std::vector<int64_t> tensor_off;
     int64_t numel = 0;
     // device tables
-    CopyChunk *d_copy = nullptr;
-    int64_t n_copy = 0;
+    CopyChunk *d_pack = nullptr, *d_unpack = nullptr;  // each covers the slot in chunks that end on the lines (kLine) of what is written;
+                                                       // one table where those are the same
+    int64_t n_pack = 0, n_unpack = 0;
     MeanChunk *d_mean = nullptr;
     int64_t n_mean = 0;
     int32_t *d_layer_ranges = nullptr;     // per layer of the slot: [first, last) mean chunk; behind them, in a slot whose
@@ -156,8 +159,8 @@ struct UpdateScalars {
     float beta1, beta2, omb1, omb2, decay, step_size, rsqrt_bc2, eps;  // AdamW
 };
 
-int launch_copy(bool unpack, const TensorDesc *tensors, const CopyChunk *chunks, int64_t n_chunks, float *flat,
-                bool with_model, bool nontemporal, int lds_pad, void *stream);
+int launch_copy(bool unpack, const TensorDesc *runs, const CopyChunk *chunks, int64_t n_chunks, float *flat, bool with_model,
+                bool nontemporal, int lds_pad, void *stream);
 int launch_mean(const MeanLaunch &a, void *stream);
 // Per-layer statistics from per-chunk partials: layer l of n_layers adds the `pairs` partials of each of the chunks
 // [ranges[2l], ranges[2l+1]) in a fixed order through kStatSlices slice sums (slice_sums: [n_layers][kStatSlices][2]) into
@@ -168,8 +171,7 @@ constexpr int kStatSlices = 64;
 constexpr int64_t kStatSingleMax = 4096;
 int launch_stats(const double *partials, double *slice_sums, const int32_t *ranges, int pairs, int n_layers, int n_replicas, double *stats,
                  int64_t max_partials_per_layer, void *stream);
-int launch_pack16(const TensorDesc *tensors, const CopyChunk *chunks, int64_t n_chunks, uint16_t *flat16, bool nontemporal, int lds_pad,
-                  void *stream);
+int launch_pack16(const CopyChunk *chunks, int64_t n_chunks, uint16_t *flat16, bool nontemporal, int lds_pad, void *stream);
 // The fused step: what both forms of the kernel take ...
 struct FusedLaunch {
     const void *x[DDP_MAX_REPLICAS - 1];  // the N-1 peers in rank order; fp32, or bf16 when wire16
@@ -245,8 +247,8 @@ struct ddp_ctx {
     std::vector<int64_t> tensor_elem_off;     // T + 1: elements before each tensor, registration order
     bool dense = false;      // tensors lie back to back in every stream and the streams' starts are vector-aligned
     bool dense_path = true;  // option: use the table-free kernels where `dense` allows it
-    ddp::TensorDesc *d_tensors = nullptr;
     std::vector<int32_t> layer_first_run;  // L + 1: runs of the update table
+    std::vector<ddp::TensorDesc> runs;
     ddp::TensorDesc *d_runs = nullptr;
     ddp::UpdateChunk *d_update = nullptr;
     int64_t n_update = 0;

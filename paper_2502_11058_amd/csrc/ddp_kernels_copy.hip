@@ -8,15 +8,15 @@ namespace {
 // UNPACK = true : sync[t_begin + i] = flat[flat_begin + i], and the bf16 model copy = RNE of the same value.
 // The fp32 stores are always 16-byte aligned; loads, and the bf16 stores, start wherever the other side lies.
 template <bool UNPACK, bool MODEL, bool NT>
-__global__ __launch_bounds__(kThreads) void copy_kernel(const TensorDesc *__restrict__ tensors, const CopyChunk *__restrict__ chunks,
+__global__ __launch_bounds__(kThreads) void copy_kernel(const TensorDesc *__restrict__ runs, const CopyChunk *__restrict__ chunks,
                                                         float *__restrict__ flat) {
     const CopyChunk ch = chunks[blockIdx.x];
-    const TensorDesc td = tensors[ch.tensor];
-    float *tptr = td.sync + ch.t_begin;
+    float *tptr = ch.sync;
     float *fptr = flat + ch.flat_begin;
     const float *src = UNPACK ? fptr : tptr;
     float *dst = UNPACK ? tptr : fptr;
-    unsigned short *mdl = MODEL ? td.model + ch.t_begin : reinterpret_cast<unsigned short *>(dst);  // unused without MODEL
+    // (the copy's address is needed after the first loads only; unused without MODEL)
+    unsigned short *mdl = MODEL ? runs[ch.run].model + (tptr - runs[ch.run].sync) : reinterpret_cast<unsigned short *>(dst);
     const int n = ch.count;
     const int tid = threadIdx.x;
 
@@ -51,11 +51,9 @@ __global__ __launch_bounds__(kThreads) void copy_kernel(const TensorDesc *__rest
 // Pack for a bf16 wire: flat16[flat_begin + i] = bf16_rne(sync[t_begin + i]).  Stores are 8-byte aligned groups of
 // four; the loads start wherever the tensor lies.
 template <bool NT>
-__global__ __launch_bounds__(kThreads) void pack16_kernel(const TensorDesc *__restrict__ tensors, const CopyChunk *__restrict__ chunks,
-                                                          unsigned short *__restrict__ flat16) {
+__global__ __launch_bounds__(kThreads) void pack16_kernel(const CopyChunk *__restrict__ chunks, unsigned short *__restrict__ flat16) {
     const CopyChunk ch = chunks[blockIdx.x];
-    const TensorDesc td = tensors[ch.tensor];
-    const float *src = td.sync + ch.t_begin;
+    const float *src = ch.sync;
     unsigned short *dst = flat16 + ch.flat_begin;
     const int n = ch.count;
     const int tid = threadIdx.x;
@@ -80,20 +78,19 @@ __global__ __launch_bounds__(kThreads) void pack16_kernel(const TensorDesc *__re
 
 }  // namespace
 
-int launch_copy(bool unpack, const TensorDesc *tensors, const CopyChunk *chunks, int64_t n_chunks, float *flat, bool with_model,
+int launch_copy(bool unpack, const TensorDesc *runs, const CopyChunk *chunks, int64_t n_chunks, float *flat, bool with_model,
                 bool nontemporal, int lds_pad, void *stream) {
-    if (!unpack) return nontemporal ? launch(copy_kernel<false, false, true>, n_chunks, stream, lds_pad, tensors, chunks, flat)
-                                    : launch(copy_kernel<false, false, false>, n_chunks, stream, lds_pad, tensors, chunks, flat);
-    if (with_model) return nontemporal ? launch(copy_kernel<true, true, true>, n_chunks, stream, lds_pad, tensors, chunks, flat)
-                                       : launch(copy_kernel<true, true, false>, n_chunks, stream, lds_pad, tensors, chunks, flat);
-    return nontemporal ? launch(copy_kernel<true, false, true>, n_chunks, stream, lds_pad, tensors, chunks, flat)
-                       : launch(copy_kernel<true, false, false>, n_chunks, stream, lds_pad, tensors, chunks, flat);
+    if (!unpack) return nontemporal ? launch(copy_kernel<false, false, true>, n_chunks, stream, lds_pad, runs, chunks, flat)
+                                    : launch(copy_kernel<false, false, false>, n_chunks, stream, lds_pad, runs, chunks, flat);
+    if (with_model) return nontemporal ? launch(copy_kernel<true, true, true>, n_chunks, stream, lds_pad, runs, chunks, flat)
+                                       : launch(copy_kernel<true, true, false>, n_chunks, stream, lds_pad, runs, chunks, flat);
+    return nontemporal ? launch(copy_kernel<true, false, true>, n_chunks, stream, lds_pad, runs, chunks, flat)
+                       : launch(copy_kernel<true, false, false>, n_chunks, stream, lds_pad, runs, chunks, flat);
 }
 
-int launch_pack16(const TensorDesc *tensors, const CopyChunk *chunks, int64_t n_chunks, uint16_t *flat16, bool nontemporal, int lds_pad,
-                  void *stream) {
-    return nontemporal ? launch(pack16_kernel<true>, n_chunks, stream, lds_pad, tensors, chunks, flat16)
-                       : launch(pack16_kernel<false>, n_chunks, stream, lds_pad, tensors, chunks, flat16);
+int launch_pack16(const CopyChunk *chunks, int64_t n_chunks, uint16_t *flat16, bool nontemporal, int lds_pad, void *stream) {
+    return nontemporal ? launch(pack16_kernel<true>, n_chunks, stream, lds_pad, chunks, flat16)
+                       : launch(pack16_kernel<false>, n_chunks, stream, lds_pad, chunks, flat16);
 }
 
 }  // namespace ddp
