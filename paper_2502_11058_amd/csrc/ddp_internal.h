@@ -139,6 +139,7 @@ struct StatsLaunch {
 };
 
 // ---- launchers (ddp_kernels_*.hip) -------------------------------------------------------------------------------
+constexpr int kCutReps = 12;  // fewest replicas whose average may cut chunks (mean_cut)
 struct MeanLaunch {
     const void *x[DDP_MAX_REPLICAS];  // replicas in rank order (fp32, or bf16 when wire16)
     bool wire16;

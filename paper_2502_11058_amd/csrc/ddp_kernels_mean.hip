@@ -24,15 +24,14 @@ struct MeanArgs {
 // STATS adds, per chunk, sum_k sum_i (out_i - x_k,i)^2 and sum_i out_i^2 in fp64.
 // Bound by HBM; with bf16 replicas also by how many wavefronts the registers let in, so a group is kept as it was loaded and
 // widened at each use (N = 32: 241 -> 82 VGPRs).
-template <int NREP, bool EXACT, bool STATS, bool NT, bool W16>
+template <int NREP, bool EXACT, bool STATS, bool NT, bool W16, bool CUT>
 __global__ __launch_bounds__(kThreads) void mean_kernel(const MeanArgs a) {
     __shared__ double lds[2][kThreads / kWave];
-    // (a chunk's halves: rule and figures at mean_cut)
-    const int half = NREP > 0 && a.cut ? (int)blockIdx.x & 1 : 0;
-    MeanChunk ch = a.chunks[NREP > 0 && a.cut ? blockIdx.x >> 1 : blockIdx.x];
+    // CUT: two workgroups a chunk (mean_cut).  A kernel of its own: what the others spent on it before their first load was 0.3 %.
+    MeanChunk ch = a.chunks[CUT ? blockIdx.x >> 1 : blockIdx.x];
     const int entry = ch.partial;
-    if (NREP > 0 && a.cut) {
-        const int first = a.cut - ((int)ch.begin & (kLine - 1)), at = first < ch.count ? first : ch.count;
+    if constexpr (CUT) {
+        const int half = (int)blockIdx.x & 1, first = a.cut - ((int)ch.begin & (kLine - 1)), at = first < ch.count ? first : ch.count;
         ch.begin += half ? at : 0;
         ch.count = half ? ch.count - at : at;
         ch.partial = 2 * entry + half;
@@ -223,17 +222,24 @@ int mean_lds(const MeanLaunch &a) {
     return a.lds_pad > need ? a.lds_pad : need;
 }
 
+template <int NREP, bool EXACT, bool CUT>
+int launch_mean_c(const MeanArgs &ma, const MeanLaunch &a, void *stream) {
+    const int64_t grid = CUT ? 2 * a.n_chunks : a.n_chunks;
+    if (a.wire16) {
+        if (a.st.partials) return launch(mean_kernel<NREP, EXACT, true, true, true, CUT>, grid, stream, mean_lds<NREP>(a), ma);
+        return launch(mean_kernel<NREP, EXACT, false, true, true, CUT>, grid, stream, a.lds_pad, ma);
+    }
+    if (a.st.partials) return a.nontemporal ? launch(mean_kernel<NREP, EXACT, true, true, false, CUT>, grid, stream, mean_lds<NREP>(a), ma)
+                                         : launch(mean_kernel<NREP, EXACT, true, false, false, CUT>, grid, stream, mean_lds<NREP>(a), ma);
+    return a.nontemporal ? launch(mean_kernel<NREP, EXACT, false, true, false, CUT>, grid, stream, a.lds_pad, ma)
+                         : launch(mean_kernel<NREP, EXACT, false, false, false, CUT>, grid, stream, a.lds_pad, ma);
+}
+
 template <int NREP, bool EXACT>
 int launch_mean_n(const MeanArgs &ma, const MeanLaunch &a, void *stream) {
-    const int64_t grid = a.cut ? 2 * a.n_chunks : a.n_chunks;
-    if (a.wire16) {
-        if (a.st.partials) return launch(mean_kernel<NREP, EXACT, true, true, true>, grid, stream, mean_lds<NREP>(a), ma);
-        return launch(mean_kernel<NREP, EXACT, false, true, true>, grid, stream, a.lds_pad, ma);
-    }
-    if (a.st.partials) return a.nontemporal ? launch(mean_kernel<NREP, EXACT, true, true, false>, grid, stream, mean_lds<NREP>(a), ma)
-                                         : launch(mean_kernel<NREP, EXACT, true, false, false>, grid, stream, mean_lds<NREP>(a), ma);
-    return a.nontemporal ? launch(mean_kernel<NREP, EXACT, false, true, false>, grid, stream, a.lds_pad, ma)
-                         : launch(mean_kernel<NREP, EXACT, false, false, false>, grid, stream, a.lds_pad, ma);
+    if constexpr (NREP >= kCutReps)
+        if (a.cut) return launch_mean_c<NREP, EXACT, true>(ma, a, stream);
+    return launch_mean_c<NREP, EXACT, false>(ma, a, stream);
 }
 
 }  // namespace

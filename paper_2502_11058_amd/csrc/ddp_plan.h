@@ -45,7 +45,7 @@ inline bool folds(int cus, int64_t workgroups, int64_t partials, int64_t most) {
 // (N = 8: 131 K 5.8 / 5.5, 262 K 6.1 / 6.4; bf16, N = 12, waited for: 524 K 35.0 / 36.1).  A cut chunk has two pairs of partial sums,
 // so slots whose pairs would not fit the fixed scratch are not cut, whichever scratch a call has: same bits from both.
 inline int mean_cut(int cus, int64_t chunk, int64_t n_chunks, int64_t n_layers, int N, bool wire16) {
-    bool cut = N >= 12 && !wire16 && 4 * n_chunks <= 5 * (int64_t)cus;
+    bool cut = N >= kCutReps && !wire16 && 4 * n_chunks <= 5 * (int64_t)cus;
     if (N > 16) cut = wire16 || N == 32 || 2 * n_chunks <= 3 * (int64_t)cus || n_chunks >= 8 * (int64_t)cus;
     if (!cut || N > 32) return 0;
     return (2 * n_chunks + n_layers * kStatSlices) * 2 * (int64_t)sizeof(double) <= (int64_t)DDP_STATIC_SCRATCH_BYTES ? (int)(chunk / 2) : 0;
