@@ -44,6 +44,35 @@ class ddp_opt(C.Structure):
 
 
 _lib = None
+_CALLS = ["ddp_pack", "ddp_unpack", "ddp_pack_wire16", "ddp_partial_average", "ddp_partial_average_wire16", "ddp_local_update",
+          "ddp_local_update_layers", "ddp_fused_sync_update", "ddp_fused_sync_update_wire16", "ddp_fused_sync_update_layers"]
+
+
+class _NoCalls:
+    """Stands for the extension module where it is not built: every call takes the general path."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+_calls = _NoCalls()
+
+
+def _load_calls(l) -> None:
+    """The per-iteration calls marshalled in C (csrc/ddp_calls.c): 0.5-1.3 us less host time a call.  They return the library's
+    status, or None for arguments of a form that the methods' general path has to look at."""
+    global _calls
+    import importlib.machinery
+    import importlib.util
+    for suffix in importlib.machinery.EXTENSION_SUFFIXES:
+        path = os.path.join(_HERE, "lib", "_calls" + suffix)
+        if os.path.exists(path):
+            spec = importlib.util.spec_from_file_location("paper_2502_11058_amd.lib._calls", path)
+            m = importlib.util.module_from_spec(spec)
+            spec.loader.exec_module(m)
+            m.setup(tuple(C.cast(getattr(l, n), C.c_void_p).value for n in _CALLS), C.Array, ddp_opt)
+            _calls = m
+            return
 
 
 def lib():
@@ -89,6 +118,7 @@ def lib():
         l.ddp_schedule_alg2_solutions.argtypes = [C.c_int, C.c_int, C.c_void_p, C.c_void_p, C.c_void_p]
         l.ddp_schedule_fill_bubbles.argtypes = [C.c_int, C.c_int] + [C.c_void_p] * 7
         l.ddp_schedule_time_model.argtypes = [C.c_int, C.c_int] + [C.c_void_p] * 8
+        _load_calls(l)
         _lib = l
     return _lib
 
@@ -198,6 +228,7 @@ def _current_stream() -> int:
         import torch
         handle = torch.cuda.current_stream().cuda_stream      # initialises, or says why it cannot
         _raw_stream = (torch._C._cuda_isInBadFork, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+        _calls.set_stream_query(*_raw_stream)
         return handle
     return _raw_stream[2](_raw_stream[1]())
 
@@ -259,12 +290,14 @@ class Context:
         h = C.c_void_p()
         _check(lib().ddp_create(C.byref(h), device))
         self._h = h
+        self._at = h.value       # the same address for the calls marshalled in C (0 once closed: the library refuses it)
         self._keep = []          # registered tensors, kept alive
 
     def close(self) -> None:
         if self._h:
             lib().ddp_destroy(self._h)
             self._h = None
+            self._at = 0
 
     def __del__(self):
         try:
@@ -320,9 +353,19 @@ class Context:
         return tid[:nt], off[:nt], lid[:nl], lb
 
     def ddp_pack(self, slot: int, flat_local, stream=None) -> None:
+        rc = _calls.pack(self._at, slot, flat_local, stream)
+        if rc == 0:
+            return
+        if rc is not None:
+            _check(rc, self._h)
         _check(lib().ddp_pack(self._h, slot, flat_local.data_ptr(), _stream_handle(stream)), self._h)
 
     def ddp_partial_average(self, slot: int, flat_local, peers, N: int, local_rank: int, flat_out, layer_stats=None, stream=None) -> None:
+        rc = _calls.average(self._at, slot, flat_local, peers, N, local_rank, flat_out, layer_stats, stream)
+        if rc == 0:
+            return
+        if rc is not None:
+            _check(rc, self._h)
         arr = _peers_arg(peers)
         _check(lib().ddp_partial_average(self._h, slot, flat_local.data_ptr(), None if arr is None else C.addressof(arr), N, local_rank,
                                          flat_out.data_ptr(), None if layer_stats is None else layer_stats.data_ptr(),
@@ -336,38 +379,78 @@ class Context:
                                                 None if layer_stats is None else layer_stats.data_ptr(), _stream_handle(stream)), self._h)
 
     def ddp_unpack(self, slot: int, flat, stream=None) -> None:
+        rc = _calls.unpack(self._at, slot, flat, stream)
+        if rc == 0:
+            return
+        if rc is not None:
+            _check(rc, self._h)
         _check(lib().ddp_unpack(self._h, slot, flat.data_ptr(), _stream_handle(stream)), self._h)
 
     def ddp_local_update(self, opt: ddp_opt, stream=None) -> None:
+        rc = _calls.update(self._at, opt, stream)
+        if rc == 0:
+            return
+        if rc is not None:
+            _check(rc, self._h)
         _check(lib().ddp_local_update(self._h, C.byref(opt), _stream_handle(stream)), self._h)
 
     def ddp_fused_sync_update(self, slot: int, peers, N: int, local_rank: int, layer_stats, opt: ddp_opt, stream=None) -> None:
+        rc = _calls.fused(self._at, slot, peers, N, local_rank, layer_stats, opt, stream)
+        if rc == 0:
+            return
+        if rc is not None:
+            _check(rc, self._h)
         arr = _peers_arg(peers)
         _check(lib().ddp_fused_sync_update(self._h, slot, None if arr is None else C.addressof(arr), N, local_rank,
                                            None if layer_stats is None else layer_stats.data_ptr(), C.byref(opt),
                                            _stream_handle(stream)), self._h)
 
     def ddp_pack_wire16(self, slot: int, flat_local16, stream=None) -> None:
+        rc = _calls.pack16(self._at, slot, flat_local16, stream)
+        if rc == 0:
+            return
+        if rc is not None:
+            _check(rc, self._h)
         _check(lib().ddp_pack_wire16(self._h, slot, flat_local16.data_ptr(), _stream_handle(stream)), self._h)
 
     def ddp_partial_average_wire16(self, slot: int, flat_local16, peers16, N: int, local_rank: int, flat_out, layer_stats=None,
                                    stream=None) -> None:
+        rc = _calls.average16(self._at, slot, flat_local16, peers16, N, local_rank, flat_out, layer_stats, stream)
+        if rc == 0:
+            return
+        if rc is not None:
+            _check(rc, self._h)
         arr = _peers_arg(peers16)
         _check(lib().ddp_partial_average_wire16(self._h, slot, flat_local16.data_ptr(), None if arr is None else C.addressof(arr), N,
                                                 local_rank, flat_out.data_ptr(),
                                                 None if layer_stats is None else layer_stats.data_ptr(), _stream_handle(stream)), self._h)
 
     def ddp_fused_sync_update_wire16(self, slot: int, peers16, N: int, local_rank: int, layer_stats, opt: ddp_opt, stream=None) -> None:
+        rc = _calls.fused16(self._at, slot, peers16, N, local_rank, layer_stats, opt, stream)
+        if rc == 0:
+            return
+        if rc is not None:
+            _check(rc, self._h)
         arr = _peers_arg(peers16)
         _check(lib().ddp_fused_sync_update_wire16(self._h, slot, None if arr is None else C.addressof(arr), N, local_rank,
                                                   None if layer_stats is None else layer_stats.data_ptr(), C.byref(opt),
                                                   _stream_handle(stream)), self._h)
 
     def ddp_local_update_layers(self, layer_first: int, layer_count: int, opt: ddp_opt, stream=None) -> None:
+        rc = _calls.update_layers(self._at, layer_first, layer_count, opt, stream)
+        if rc == 0:
+            return
+        if rc is not None:
+            _check(rc, self._h)
         _check(lib().ddp_local_update_layers(self._h, layer_first, layer_count, C.byref(opt), _stream_handle(stream)), self._h)
 
     def ddp_fused_sync_update_layers(self, slot: int, layer_first: int, layer_count: int, peers, wire_dtype: int, order: int, N: int,
                                      local_rank: int, layer_stats, opt: ddp_opt, stream=None) -> None:
+        rc = _calls.fused_layers(self._at, slot, layer_first, layer_count, peers, wire_dtype, order, N, local_rank, layer_stats, opt, stream)
+        if rc == 0:
+            return
+        if rc is not None:
+            _check(rc, self._h)
         arr = _peers_arg(peers)
         _check(lib().ddp_fused_sync_update_layers(self._h, slot, layer_first, layer_count, None if arr is None else C.addressof(arr),
                                                   wire_dtype, order, N, local_rank,

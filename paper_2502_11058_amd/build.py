@@ -7,6 +7,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -15,6 +16,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB_DIR = os.path.join(HERE, "lib")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(LIB_DIR, "libdreamddp.so")
+CALLS = os.path.join(LIB_DIR, "_calls" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))   # the binding's calls, marshalled in C
 # (source, object name, extra flags); the fused kernels have the most instantiations and are built in two halves each
 SOURCES = [("ddp_kernels_fused.hip", "ddp_kernels_fused_adamw", ["-DDDP_FUSED_ADAM=1"]),
            ("ddp_kernels_fused.hip", "ddp_kernels_fused_sgdm", ["-DDDP_FUSED_ADAM=0"]),
@@ -64,7 +66,18 @@ def build(verbose: bool = False, jobs: int = 0) -> str:
     with ThreadPoolExecutor(max_workers=jobs) as ex:
         list(ex.map(lambda c: _run(c, verbose), cmds))
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", LIB], verbose)
+    build_calls(verbose)
     return LIB
+
+
+def build_calls(verbose: bool = False) -> None:
+    """The extension module of the binding's per-iteration calls; without Python's headers the binding marshals in Python."""
+    include = sysconfig.get_path("include")
+    if not os.path.exists(os.path.join(include, "Python.h")):
+        print("no Python.h in " + include + ": calls are marshalled in Python", file=sys.stderr)
+        return
+    _run(["gcc", "-O2", "-std=gnu11", "-Wall", "-Wextra", "-Wno-unused-parameter", "-shared", "-fPIC", "-I" + include, "-I" + os.path.join(ROOT, "include"),
+          os.path.join(CSRC, "ddp_calls.c"), "-o", CALLS], verbose)
 
 
 if __name__ == "__main__":

@@ -1,0 +1,128 @@
+"""The per-iteration calls marshalled in C against the binding's general path, over the forms that arguments come in: the same
+values reach the library, the same exceptions come back, a failing status raises.  The library is a stub that records."""
+import ctypes as C
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2502_11058_amd import binding as B
+
+# entry point -> letters of its arguments behind the context: i int, p pointer, P peers, o options
+ENTRIES = {"ddp_pack": "ipp", "ddp_unpack": "ipp", "ddp_pack_wire16": "ipp", "ddp_partial_average": "ipPiippp",
+           "ddp_partial_average_wire16": "ipPiippp", "ddp_local_update": "op", "ddp_local_update_layers": "iiop",
+           "ddp_fused_sync_update": "iPiipop", "ddp_fused_sync_update_wire16": "iPiipop", "ddp_fused_sync_update_layers": "iiiPiiiipop"}
+
+
+def _stub():
+    c = {"i": "int", "p": "void *", "P": "void **", "o": "void *"}
+    src = "long rec[16], peers[4]; float lr; int status;\n"
+    for name, sig in ENTRIES.items():
+        src += f"int {name}(void *ctx, {', '.join(f'{c[k]} a{j}' for j, k in enumerate(sig))}) {{ rec[0] = (long)ctx;"
+        for j, k in enumerate(sig):
+            if k == "P":
+                src += f" rec[{j + 1}] = a{j} != 0; for (int q = 0; q < 3; ++q) peers[q] = a{j} ? (long)a{j}[q] : 0;"
+            elif k == "o":
+                src += f" lr = ((float *)a{j})[1];"
+            else:
+                src += f" rec[{j + 1}] = (long)a{j};"
+        src += " return status; }\n"
+    src += 'int ddp_create(void **p, int d) { *p = rec; return 0; }\nint ddp_destroy(void *p) { return 0; }\n'
+    src += 'const char *ddp_last_error(void *p) { return "stub"; }\n'
+    done = set(ENTRIES) | {"ddp_create", "ddp_destroy", "ddp_last_error"}
+    return src + "".join(f"int {n}(void) {{ return 0; }}\n" for n in B.EXPORTS if n not in done)
+
+
+class _Stream:
+    cuda_stream = 4096 + 64
+
+
+@pytest.fixture
+def stub(tmp_path, monkeypatch):
+    if not shutil.which("gcc"):
+        pytest.skip("no host compiler")
+    B.lib()
+    if isinstance(B._calls, B._NoCalls):
+        pytest.skip("the extension module is not built")
+    (tmp_path / "s.c").write_text(_stub())
+    subprocess.run(["gcc", "-shared", "-fPIC", "-O1", "-o", str(tmp_path / "s.so"), str(tmp_path / "s.c")], check=True)
+    real = B._lib
+    monkeypatch.setattr(B, "LIB_PATH", str(tmp_path / "s.so"))
+    monkeypatch.setattr(B, "_lib", None)
+    monkeypatch.setattr(B, "_raw_stream", (lambda: False, lambda: 0, lambda d: 77))
+    l = B.lib()
+    B._calls.set_stream_query(*B._raw_stream)
+    yield l
+    B._load_calls(real)
+
+
+def _both(l, monkeypatch, call):
+    """(outcome, what the library saw) of a call, marshalled in C and on the general path."""
+    got = []
+    for calls in (B._calls, B._NoCalls()):
+        with monkeypatch.context() as m:
+            m.setattr(B, "_calls", calls)
+            for name, n in (("rec", 16), ("peers", 4)):
+                C.memset(C.addressof((C.c_long * n).in_dll(l, name)), 0, 8 * n)
+            try:
+                out = ("returns", call())
+            except Exception as e:  # noqa: BLE001  (the two paths are compared, whatever they raise)
+                out = (type(e).__name__, getattr(e, "code", None))
+            got.append((out, list((C.c_long * 16).in_dll(l, "rec")), list((C.c_long * 4).in_dll(l, "peers")), C.c_float.in_dll(l, "lr").value))
+    return got
+
+
+def _forms():
+    t, s = torch.zeros(8), torch.zeros(4, dtype=torch.float64)
+    lists = [torch.zeros(4) for _ in range(3)]
+    opt = B.make_opt("sgdm", 0.25, 3, momentum=0.9)
+    peers = [lists, tuple(lists), B.device_pointer_array(lists), (C.c_void_p * 3)(1, None, 3), [lists[0], None, 12345], [], (), None,
+             [object()], "abc", [t] * 65]
+    for stream in (None, 0, 5, _Stream(), True, 1.5, "x", np.int64(3)):
+        yield "ddp_pack", (2, t, stream)
+        yield "ddp_local_update", (opt, stream)
+    for slot in (0, -1, 2 ** 31 - 1, 2 ** 31, -2 ** 40, 2 ** 70, True, 1.0, None, np.int32(3)):
+        yield "ddp_unpack", (slot, t, 9)
+        yield "ddp_fused_sync_update_layers", (1, slot, 2, lists, 0, 1, 4, 3, s, opt, 9)
+    for buf in (t, t[3:], t.numpy(), None, 64):
+        yield "ddp_pack_wire16", (1, buf, 9)
+        yield "ddp_partial_average", (1, t, lists, 4, 0, buf, None, 9)
+    for p in peers:
+        yield "ddp_partial_average", (1, t, p, 4, 2, t, s, 9)
+        yield "ddp_partial_average_wire16", (1, t, p, 4, 2, t, None, 9)
+        yield "ddp_fused_sync_update", (1, p, 4, 2, s, opt, 9)
+        yield "ddp_fused_sync_update_wire16", (1, p, 4, 2, None, opt, 9)
+        yield "ddp_fused_sync_update_layers", (1, 0, 2, p, 0, 1, 4, 3, s, opt, 9)
+
+    class Own(B.ddp_opt):
+        pass
+
+    for o in (opt, Own(0, 0.5), None, C.create_string_buffer(64), 7):
+        yield "ddp_local_update_layers", (0, 2, o, 9)
+        yield "ddp_fused_sync_update", (1, lists, 4, 2, s, o, None)
+
+
+def test_same_as_the_general_path(stub, monkeypatch):
+    ctx = B.Context(0)
+    for name, args in _forms():
+        fast, general = _both(stub, monkeypatch, lambda: getattr(ctx, name)(*args))
+        assert fast == general, (name, args)
+    t = torch.zeros(8)
+    fast, general = _both(stub, monkeypatch, lambda: ctx.ddp_pack(slot=3, flat_local=t))
+    assert fast == general and fast[0] == ("returns", None) and fast[1][1:4] == [3, t.data_ptr(), 77]
+    C.c_int.in_dll(stub, "status").value = 3
+    for name, args in list(_forms())[:4]:
+        fast, general = _both(stub, monkeypatch, lambda: getattr(ctx, name)(*args))
+        assert fast == general and fast[0] == ("DdpError", 3)
+    C.c_int.in_dll(stub, "status").value = 0
+    ctx.close()
+    fast, general = _both(stub, monkeypatch, lambda: ctx.ddp_pack(1, t, 9))
+    assert fast == general and fast[1][0] == 0
+
+
+def test_forked_child_takes_the_general_path(stub, monkeypatch):
+    ctx, t = B.Context(0), torch.zeros(8)
+    B._calls.set_stream_query(lambda: True, lambda: 0, lambda d: 78)
+    assert B._calls.pack(ctx._at, 1, t, None) is None and B._calls.pack(ctx._at, 1, t, 5) == 0
