@@ -42,7 +42,6 @@ static int upload(const ddp_ctx *ctx, const std::vector<T> &host, T **dev) {
 }
 
 static void free_slot(SlotTables &s) {
-    if (s.d_unpack && s.d_unpack != s.d_pack) (void)hipFree(s.d_unpack);
     if (s.d_pack) (void)hipFree(s.d_pack);
     if (s.d_mean) (void)hipFree(s.d_mean);
     if (s.d_layer_ranges) (void)hipFree(s.d_layer_ranges);
@@ -430,9 +429,9 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
             interleave_segments(pack, ctx->dispatch_ways);
             interleave_segments(unpack, ctx->dispatch_ways);
             interleave_segments(mc, ctx->dispatch_ways);
+            pack.insert(pack.end(), unpack.begin(), unpack.end());  // one allocation, one copy
             rc = upload(ctx, pack, &st.d_pack);
-            if (rc == DDP_OK && !one_table) rc = upload(ctx, unpack, &st.d_unpack);
-            if (one_table) st.d_unpack = st.d_pack;
+            st.d_unpack = st.d_pack && !one_table ? st.d_pack + st.n_pack : st.d_pack;
             if (rc == DDP_OK) rc = upload(ctx, mc, &st.d_mean);
             std::vector<int32_t> mean_ranges;
             for (size_t i = 0; i + 1 < lcp.size(); ++i) {

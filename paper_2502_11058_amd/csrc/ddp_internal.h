@@ -107,8 +107,9 @@ struct SlotTables {
     std::vector<int64_t> tensor_off;
     int64_t numel = 0;
     // device tables
-    CopyChunk *d_pack = nullptr, *d_unpack = nullptr;  // each covers the slot in chunks that end on the lines (kLine) of what is written;
-                                                       // one table where those are the same
+    // each covers the slot in chunks that end on the lines (kLine) of what is written; one table where those are the same, else
+    // one allocation, d_pack's
+    CopyChunk *d_pack = nullptr, *d_unpack = nullptr;
     int64_t n_pack = 0, n_unpack = 0;
     MeanChunk *d_mean = nullptr;
     int64_t n_mean = 0;
