@@ -126,6 +126,9 @@ static int residency_pad(const ddp_ctx *c, int wg_per_cu) {
     return pad > 0 ? pad : 0;
 }
 
+// The residency request of the update and the fused step.
+static int update_lds(const ddp_ctx *c) { return c->small && !c->update_lds_set ? 0 : c->update_lds; }
+
 // First element of layer l in registration order (l = L: the number of elements).
 static int64_t layer_elem0(const ddp_ctx *ctx, int l) { return ctx->tensor_elem_off[(size_t)ctx->layer_first_tensor[(size_t)l]]; }
 
@@ -187,6 +190,7 @@ extern "C" int ddp_set_option(ddp_ctx *ctx, const char *name, int64_t value) {
         if (k == "update_chunk" || k == "mean_chunk" || k == "copy_chunk") {
             if (!chunk_ok(value)) return fail(ctx, DDP_EINVAL, "ddp_set_option: chunk must be a multiple of 1024 in [1024, 1048576]");
             if (ctx->registered) return fail(ctx, DDP_ESTATE, "ddp_set_option: chunk sizes must be set before ddp_register_model");
+            ctx->update_chunk_set = ctx->update_chunk_set || k == "update_chunk";
             (k == "update_chunk" ? ctx->update_chunk : k == "mean_chunk" ? ctx->mean_chunk : ctx->copy_chunk) = value;
             return DDP_OK;
         }
@@ -199,12 +203,14 @@ extern "C" int ddp_set_option(ddp_ctx *ctx, const char *name, int64_t value) {
         if (k == "update_wg_per_cu" || k == "mean_wg_per_cu" || k == "copy_wg_per_cu") {
             if (value < 0 || value > 32) return fail(ctx, DDP_EINVAL, "ddp_set_option: workgroups per CU must be in [0, 32] (0 = no cap)");
             ctx->mean_lds_set = ctx->mean_lds_set || k == "mean_wg_per_cu";
+            ctx->update_lds_set = ctx->update_lds_set || k == "update_wg_per_cu";
             (k == "update_wg_per_cu" ? ctx->update_lds : k == "mean_wg_per_cu" ? ctx->mean_lds : ctx->copy_lds) = residency_pad(ctx, (int)value);
             return DDP_OK;
         }
         if (k == "update_lds" || k == "mean_lds" || k == "copy_lds") {
             if (value < 0 || value > 65536) return fail(ctx, DDP_EINVAL, "ddp_set_option: LDS pad must be in [0, 65536] bytes");
             ctx->mean_lds_set = ctx->mean_lds_set || k == "mean_lds";
+            ctx->update_lds_set = ctx->update_lds_set || k == "update_lds";
             (k == "update_lds" ? ctx->update_lds : k == "mean_lds" ? ctx->mean_lds : ctx->copy_lds) = (int)value;
             return DDP_OK;
         }
@@ -278,6 +284,8 @@ extern "C" int ddp_register_model(ddp_ctx *ctx, int L, int T, const int32_t *lay
         // 128-bit (bf16: 64-bit) boundaries.  The update then needs no table.
         ctx->tensor_elem_off.assign((size_t)T + 1, 0);
         for (int t = 0; t < T; ++t) ctx->tensor_elem_off[(size_t)t + 1] = ctx->tensor_elem_off[(size_t)t] + numel[t];
+        ctx->small = !ctx->update_chunk_set && small_model(ctx->cus, ctx->tensor_elem_off[(size_t)T], has1);
+        ctx->run_chunk = ctx->small ? kSmallChunk : ctx->update_chunk;
         const uintptr_t gsz = grad_dtype == DDP_F32 ? 4 : 2;
         bool dense = aligned(ts[0].sync, 16) && aligned(ts[0].state0, 16) && aligned(ts[0].grad, 4 * gsz) &&
                      (!has1 || aligned(ts[0].state1, 16)) && (param_dtype != DDP_BF16 || aligned(ts[0].model, 8));
@@ -289,7 +297,7 @@ extern "C" int ddp_register_model(ddp_ctx *ctx, int L, int T, const int32_t *lay
         }
         ctx->dense = dense;
 
-        // Update table: every run cut into chunks of update_chunk elements that end on cache lines (kLine), so that only a run's
+        // Update table: every run cut into chunks of run_chunk elements that end on cache lines (kLine), so that only a run's
         // first and last chunk have elements outside a whole vector.  A run is a tensor; over dense arenas it is a whole layer,
         // so that the table's chunks, and the partial sums that they give, are those of the table-free kernels.
         std::vector<TensorDesc> runs = ts;
@@ -310,7 +318,7 @@ extern "C" int ddp_register_model(ddp_ctx *ctx, int L, int T, const int32_t *lay
             // elements past such a boundary
             const int64_t past = dense ? (runs[t].sync - ts[0].sync) % kLine : (int64_t)((reinterpret_cast<uintptr_t>(runs[t].sync) >> 2) % kLine);
             for (int64_t b = 0, e; b < runs[t].numel; b = e) {
-                e = std::min<int64_t>(runs[t].numel, (b + past) / ctx->update_chunk * ctx->update_chunk + ctx->update_chunk - past);
+                e = std::min<int64_t>(runs[t].numel, (b + past) / ctx->run_chunk * ctx->run_chunk + ctx->run_chunk - past);
                 uc.push_back({b, (int32_t)t, (int32_t)(e - b)});
             }
         }
@@ -446,7 +454,7 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
             if (rc == DDP_OK) rc = upload(ctx, mean_ranges, &st.d_layer_ranges);
             if (rc == DDP_OK) rc = upload(ctx, run_slot, &st.d_run_slot);
             if (rc == DDP_OK) rc = upload(ctx, st.update_ranges, &st.d_update_ranges);
-            if (ctx->dense) plan_dense(st, ctx->L, [&](int l) { return layer_elem0(ctx, l); }, ctx->update_chunk, kLine);
+            if (ctx->dense) plan_dense(st, ctx->L, [&](int l) { return layer_elem0(ctx, l); }, ctx->run_chunk, kLine);
             if (rc != DDP_OK) {
                 for (auto &x : slots) free_slot(x);
                 return rc;
@@ -718,7 +726,7 @@ static bool dense_range(const ddp_ctx *ctx, int first, int count, DenseLaunch &d
     d.g = (const char *)t0.grad + (uintptr_t)e0 * (ctx->grad_dtype == DDP_F32 ? 4 : 2);
     d.mdl = ctx->param_dtype == DDP_BF16 ? t0.model + e0 : nullptr;
     d.n = e1 - e0;
-    d.chunk = (int)ctx->update_chunk;
+    d.chunk = (int)ctx->run_chunk;
     d.past = (int)(e0 % kLine);
     return true;
 }
@@ -735,11 +743,11 @@ static int local_update_impl(ddp_ctx *ctx, const char *who, bool whole, int firs
     if (c1 == c0) return DDP_OK;
     DenseLaunch d{};
     if (dense_range(ctx, whole ? 0 : first, whole ? ctx->L : count, d)) {
-        rc = launch_update_dense(opt->kind, ctx->grad_dtype, ctx->param_dtype == DDP_BF16, d, s, ctx->nontemporal, ctx->update_lds, stream);
+        rc = launch_update_dense(opt->kind, ctx->grad_dtype, ctx->param_dtype == DDP_BF16, d, s, ctx->nontemporal, update_lds(ctx), stream);
         return after_launch(ctx, who, rc);
     }
     rc = launch_update(opt->kind, ctx->grad_dtype, ctx->param_dtype == DDP_BF16, ctx->d_runs, ctx->d_update + c0, c1 - c0, s,
-                       ctx->nontemporal, ctx->update_lds, stream);
+                       ctx->nontemporal, update_lds(ctx), stream);
     return after_launch(ctx, who, rc);
 }
 
@@ -761,13 +769,13 @@ static int fused_dense(const ddp_ctx *ctx, const SlotTables &st, std::vector<Den
     FusedDense f;
     static_cast<FusedLaunch &>(f) = common;
     const TensorDesc &t0 = ctx->tensors[0];
-    f.d = {t0.grad, t0.sync, t0.state0, t0.state1, t0.model, 0, (int)ctx->update_chunk, 0};
+    f.d = {t0.grad, t0.sync, t0.state0, t0.state1, t0.model, 0, (int)ctx->run_chunk, 0};
     int rc = 0;
     for (; at != st.dense_passes.end() && at->begin < e1 && rc == 0; ++at) {
         DensePass part;
         f.pass = &*at;
         if (at->begin < e0 || at->end > e1) {
-            clip_pass(*at, e0, e1, ctx->update_chunk, part, kLine);
+            clip_pass(*at, e0, e1, ctx->run_chunk, part, kLine);
             f.pass = &part;
         }
         if (f.pass->width > 0) {
@@ -838,7 +846,7 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     f.grad_dtype = ctx->grad_dtype;
     f.with_model = ctx->param_dtype == DDP_BF16;
     f.s = s;
-    f.lds_pad = ctx->update_lds;
+    f.lds_pad = update_lds(ctx);
     f.st = {any ? ctx->d_partials : nullptr, st->d_update_ranges, layer_stats, fold ? ctx->d_counters : nullptr, 1};
     const int64_t e0 = layer_elem0(ctx, first), e1 = layer_elem0(ctx, first + count);
     const auto at = first_pass(*st, e0);
@@ -850,7 +858,7 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
         f.n_chunks = c1 - c0;
         f.run_slot = st->d_run_slot;
         f.run_chunk_base = ctx->d_run_chunk_base;
-        f.chunk_elems = (int)ctx->update_chunk;
+        f.chunk_elems = (int)ctx->run_chunk;
         rc = launch_fused(f, stream);
     }
     for (int i = 0; any && !fold && i < nl && rc == 0;) {

@@ -127,7 +127,7 @@ struct SlotTables {
 // Counters of a layer whose workgroups add the statistics up themselves, in 32-bit words: one per group of kFoldGroup partials (the
 // last group takes what is left) and one over the groups, each in a cache line of its own.  Arrivals at one counter are served
 // one after the other, 20-25 ns each: 128 of them on one 6.3 us, in groups 5.7 (average, N = 4).
-constexpr int kFoldGroup = 16, kFoldGroups = 16, kFoldLine = 32, kFoldStride = (1 + kFoldGroups) * kFoldLine;
+constexpr int kFoldGroup = 16, kFoldGroups = 20, kFoldLine = 32, kFoldStride = (1 + kFoldGroups) * kFoldLine;
 
 // How the per-layer statistics of a launch are put together from its workgroups' partial pairs.
 struct StatsLaunch {
@@ -236,9 +236,12 @@ struct ddp_ctx {
     int dispatch_ways = 1;
     int lds_per_cu = 163840, lds_per_wg_max = 65536;  // what the device reports (ddp_create); gfx950 values until then
     int update_lds = 64512, mean_lds = 64512, copy_lds = 26112;  // dynamic-LDS pad per workgroup: caps residency per CU (2 / 2 / 6)
+    bool update_chunk_set = false, update_lds_set = false;  // ... given by the caller, whatever the model's size (small_model)
     bool mean_lds_set = false;  // the average's residency was given by the caller, whatever the replica count
     // model
     bool registered = false;
+    int64_t run_chunk = 2048;  // elements per chunk of the update table and the table-free kernels: update_chunk, or small_model's
+    bool small = false;
     int L = 0, T = 0;
     int param_dtype = DDP_F32, grad_dtype = DDP_F32;
     bool has_state1 = false;

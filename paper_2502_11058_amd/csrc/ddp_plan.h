@@ -51,6 +51,21 @@ inline int mean_cut(int cus, int64_t chunk, int64_t n_chunks, int64_t n_layers, 
     return (2 * n_chunks + n_layers * kStatSlices) * 2 * (int64_t)sizeof(double) <= (int64_t)DDP_STATIC_SCRATCH_BYTES ? (int)(chunk / 2) : 0;
 }
 
+// Whether a model is so small that its update and fused step take chunks of kSmallChunk elements and no cap on the workgroups per
+// CU: at two workgroups per CU and 2048 elements each it is one or two rounds of them, the second half empty.  Usual shape /
+// this one in us, 8 layers, fused, back to back:
+//     chunks of 2048           129          257          513         1026         1409         2050
+//     AdamW, N = 8          6.5 / 6.3    8.4 / 7.8   11.1 / 10.4  17.4 / 16.3  22.0 / 22.2  28.7 / 29.0
+//     ... separate tensors  6.8 / 6.5    8.5 / 8.1   11.4 / 10.5  17.9 / 16.9  22.4 / 22.0  29.5 / 29.5
+//     SGD, N = 4            5.3 / 5.7    5.6 / 6.4    7.6 / 7.3   12.1 / 11.1  14.9 / 14.5  19.1 / 19.0
+//     SGD, bf16, N = 12     7.7 / 7.0    8.3 / 7.9   12.4 / 11.2  14.8 / 14.3  17.7 / 17.6  22.4 / 22.7
+// Up to 4.5 chunks per CU, then; below 5/4 only with a second moment, where a workgroup has more to do than its statistics.
+constexpr int64_t kSmallChunk = 1024;
+inline bool small_model(int cus, int64_t numel, bool second_moment) {
+    const int64_t chunks = (numel + 2047) / 2048;
+    return 2 * chunks <= 9 * (int64_t)cus && (second_moment || 4 * chunks > 5 * (int64_t)cus);
+}
+
 // Workgroups of the table-free fused kernel over elements [e0, e1) of the arenas: chunks counted from the multiple of `line` at
 // or below e0 (kLine in the library; of four at least, where every stream is vector-aligned).
 inline int64_t dense_workgroups(int64_t e0, int64_t e1, int64_t chunk, int64_t line = 4) { return (e1 - e0 / line * line + chunk - 1) / chunk; }
