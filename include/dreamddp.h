@@ -134,7 +134,8 @@ int ddp_destroy(ddp_ctx *ctx);
  *   "update_chunk", "mean_chunk", "copy_chunk"  elements per workgroup (multiple of 1024, 1024..1048576;
  *                                               defaults 2048 / 2048 / 2048; update_chunk, unless the caller sets it, 1024
  *                                               for models of up to 4.5 chunks of 2048 per CU: with a second moment all of
- *                                               them, without one those above 5/4)
+ *                                               them, without one those above 5/4), and for AdamW updates of arenas in
+ *                                               launches of up to 7/4
  *   "dispatch_ways"                             1..4096 (default 1): launch order of the workgroups; w > 1 cuts every
  *                                               chunk table into w contiguous segments and visits them round-robin
  *   "update_wg_per_cu", "mean_wg_per_cu",       0..32 (defaults 2 / 2 / 6; 0 = no cap): most workgroups of that kernel family resident per
@@ -146,7 +147,7 @@ int ddp_destroy(ddp_ctx *ctx);
  *                                               average runs at twice mean_wg_per_cu (half the bytes per workgroup in flight).
  *                                               Unless the caller sets it, averages of up to 4 replicas run at 3 and of up to
  *                                               2 at 4: less would be in flight than the memory needs.  Unless the caller sets
- *                                               it, the models that take update chunks of 1024 run the update uncapped
+ *                                               it, what takes update chunks of 1024 by itself runs uncapped
  *   "update_lds", "mean_lds", "copy_lds"        0..65536: the same cap given directly as bytes of LDS per workgroup (for sweeps)
  *   "nontemporal"                               0/1 (default 1): streaming cache hints on loads and stores
  *   "dense_path"                                0/1 (default 1): when the registered tensors lie back to back in every

@@ -713,6 +713,14 @@ static int layer_chunk_range(ddp_ctx *ctx, const char *who, int first, int count
     return DDP_OK;
 }
 
+// The table-free update of d.n elements; a short launch, in a model that is not small, takes the small models' shape (short_update).
+static int update_dense(const ddp_ctx *ctx, int kind, DenseLaunch d, const UpdateScalars &s, bool nontemporal, void *stream) {
+    const bool small = !ctx->update_chunk_set && short_update(ctx->cus, d.n, kind == DDP_OPT_ADAMW);
+    if (small) d.chunk = (int)kSmallChunk;
+    return launch_update_dense(kind, ctx->grad_dtype, ctx->param_dtype == DDP_BF16, d, s, nontemporal,
+                               small && !ctx->update_lds_set ? 0 : update_lds(ctx), stream);
+}
+
 // The streams of layers [first, first + count) as one dense range, if the model is registered that way, the option
 // allows it and the range starts on a vector boundary.
 static bool dense_range(const ddp_ctx *ctx, int first, int count, DenseLaunch &d) {
@@ -743,7 +751,7 @@ static int local_update_impl(ddp_ctx *ctx, const char *who, bool whole, int firs
     if (c1 == c0) return DDP_OK;
     DenseLaunch d{};
     if (dense_range(ctx, whole ? 0 : first, whole ? ctx->L : count, d)) {
-        rc = launch_update_dense(opt->kind, ctx->grad_dtype, ctx->param_dtype == DDP_BF16, d, s, ctx->nontemporal, update_lds(ctx), stream);
+        rc = update_dense(ctx, opt->kind, d, s, ctx->nontemporal, stream);
         return after_launch(ctx, who, rc);
     }
     rc = launch_update(opt->kind, ctx->grad_dtype, ctx->param_dtype == DDP_BF16, ctx->d_runs, ctx->d_update + c0, c1 - c0, s,
@@ -791,7 +799,7 @@ static int fused_dense(const ddp_ctx *ctx, const SlotTables &st, std::vector<Den
         d.mdl = d.mdl ? d.mdl + e : nullptr;
         d.n = f.pass->end - e;
         d.past = (int)(e % kLine);
-        rc = launch_update_dense(f.kind, f.grad_dtype, f.with_model, d, f.s, true, f.lds_pad, stream);
+        rc = update_dense(ctx, f.kind, d, f.s, true, stream);
     }
     return rc;
 }
