@@ -60,10 +60,7 @@ __global__ __launch_bounds__(kThreads) void mean_kernel(const MeanArgs a) {
     // all buffers are 16-byte aligned at element 0, so the flat index decides the alignment
     int h = (int)((4 - (base & 3)) & 3);
     if (h > n) h = n;
-    if (tid < h) one(base + tid);
     const int nv = (n - h) >> 2;
-    const int tail0 = h + 4 * nv;
-    if (tid < n - tail0) one(base + tail0 + tid);
 
     const int64_t vbase = (base + h) >> 2;  // index in 16-byte units
     f32x4 *o4 = reinterpret_cast<f32x4 *>(a.out) + vbase;
@@ -162,6 +159,9 @@ __global__ __launch_bounds__(kThreads) void mean_kernel(const MeanArgs a) {
             st<NT>(o4 + v, acc * inv_n);
         }
     }
+
+    // head and tail together, behind the vectors: only a layer's first and last chunk have any
+    if (tid < n - 4 * nv) one(base + (tid < h ? tid : 4 * nv + tid));
 
     if constexpr (STATS) {
         block_sum2(gsum, msum, lds);
