@@ -240,6 +240,22 @@ __device__ __forceinline__ int head_to_16B(const void *p, int n) {  // fp32 elem
     return h < n ? h : n;
 }
 
+// Sum of a double over the workgroup, in the order of block_sum2.  Result valid in thread 0.
+__device__ __forceinline__ double block_sum(double v, double *lds) {
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_down(v, off, kWave);
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    if (lane == 0) lds[wave] = v;
+    __syncthreads();
+    double r = 0.0;
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int w = 0; w < kThreads / kWave; ++w) r += lds[w];
+    }
+    __syncthreads();
+    return r;
+}
+
 // Sums of two doubles over the workgroup in a fixed order: butterfly-free shuffle-down tree inside each wavefront, then the
 // four wavefront sums added in wavefront order by thread 0.  Results valid in thread 0.  Both trees side by side, one barrier:
 // the chain of shuffles is what a short kernel waits for.

@@ -61,6 +61,15 @@ __global__ __launch_bounds__(kThreads) void mean_kernel(const MeanArgs a) {
     int h = (int)((4 - (base & 3)) & 3);
     if (h > n) h = n;
     const int nv = (n - h) >> 2;
+    // Only a layer's first and last chunk have a head and a tail, which are taken behind the vectors.  Up to four replicas, with
+    // three and four workgroups per CU, the memory serves the requests best a little apart: there the conditions come first, and
+    // the two sums of a long launch one after the other (TinyLlama-1.1B, us, as the others / so: N = 4 853 / 830, N = 2 508 / 502,
+    // N = 3 664 / 656; N = 8 1519 / 1545).
+    constexpr bool kApart = NREP > 0 && NREP <= 4;
+    auto ends = [&]() {
+        if (tid < n - 4 * nv) one(base + (tid < h ? tid : 4 * nv + tid));
+    };
+    if constexpr (kApart) ends();
 
     const int64_t vbase = (base + h) >> 2;  // index in 16-byte units
     f32x4 *o4 = reinterpret_cast<f32x4 *>(a.out) + vbase;
@@ -160,11 +169,15 @@ __global__ __launch_bounds__(kThreads) void mean_kernel(const MeanArgs a) {
         }
     }
 
-    // head and tail together, behind the vectors: only a layer's first and last chunk have any
-    if (tid < n - 4 * nv) one(base + (tid < h ? tid : 4 * nv + tid));
+    if constexpr (!kApart) ends();
 
     if constexpr (STATS) {
-        block_sum2(gsum, msum, lds);
+        if (kApart && !a.st.counters) {
+            gsum = block_sum(gsum, lds[0]);
+            msum = block_sum(msum, lds[1]);
+        } else {
+            block_sum2(gsum, msum, lds);
+        }
         const int pos = a.st.counters ? a.chunk_pos[entry] : 0;
         put_partial(a.st, ch.partial, pos, pos, nrep, gsum, msum, lds);
     }
