@@ -54,7 +54,7 @@ __device__ __forceinline__ void st(T *p, T v) {
 
 // Groups of four elements at any element: gfx950 takes 128- and 64-bit global accesses at any address, so a stream whose
 // start is not a multiple of its vector needs no scalar loop.  A wavefront's 1 KiB then touches one cache line more than an
-// aligned one, mostly out of the cache: a fused step with odd offsets reads 1.028 times and writes 1.016 times its algorithmic
+// aligned one, mostly out of the cache: a fused step with odd offsets reads 1.017 times and writes 1.000 times its algorithmic
 // bytes.  base is wave-uniform and i, an element index, an unsigned 32-bit one: the access takes its base from scalar registers
 // and one offset register serves all streams of a type.  The address space is stated because a pointer that a kernel reads
 // from a table is a generic one, whose accesses (flat) also wait for and occupy the LDS counter.
