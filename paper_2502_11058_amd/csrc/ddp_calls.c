@@ -247,10 +247,16 @@ FN(setup) {
     Py_XSETREF(opt_type, a[2]);
     Py_RETURN_NONE;
 }
-/* set_stream_query(is bad fork, current device, raw handle of a device's current stream) */
+/* set_stream_query(is bad fork, current device, raw handle of a device's current stream), or three times None: not known (again) */
 FN(set_stream_query) {
     (void)self;
     if (n != 3) return PyErr_Format(PyExc_TypeError, "set_stream_query takes three callables");
+    if (a[2] == Py_None) {
+        Py_CLEAR(bad_fork);
+        Py_CLEAR(get_device);
+        Py_CLEAR(raw_stream);
+        Py_RETURN_NONE;
+    }
     Py_INCREF(a[0]);
     Py_XSETREF(bad_fork, a[0]);
     Py_INCREF(a[1]);

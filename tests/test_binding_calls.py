@@ -1,5 +1,6 @@
 """The per-iteration calls marshalled in C against the binding's general path, over the forms that arguments come in: the same
 values reach the library, the same exceptions come back, a failing status raises.  The library is a stub that records."""
+import contextlib
 import ctypes as C
 import shutil
 import subprocess
@@ -39,23 +40,42 @@ class _Stream:
     cuda_stream = 4096 + 64
 
 
-@pytest.fixture
-def stub(tmp_path, monkeypatch):
+@contextlib.contextmanager
+def _stubbed(tmp_path, monkeypatch):
+    """The binding on a recording library and a stream query of its own; what was there before is back afterwards, in the
+    extension module as well."""
     if not shutil.which("gcc"):
         pytest.skip("no host compiler")
-    B.lib()
+    real, query = B.lib(), B._raw_stream
     if isinstance(B._calls, B._NoCalls):
         pytest.skip("the extension module is not built")
     (tmp_path / "s.c").write_text(_stub())
     subprocess.run(["gcc", "-shared", "-fPIC", "-O1", "-o", str(tmp_path / "s.so"), str(tmp_path / "s.c")], check=True)
-    real = B._lib
     monkeypatch.setattr(B, "LIB_PATH", str(tmp_path / "s.so"))
     monkeypatch.setattr(B, "_lib", None)
     monkeypatch.setattr(B, "_raw_stream", (lambda: False, lambda: 0, lambda d: 77))
-    l = B.lib()
-    B._calls.set_stream_query(*B._raw_stream)
-    yield l
-    B._load_calls(real)
+    try:
+        l = B.lib()
+        B._calls.set_stream_query(*B._raw_stream)
+        yield l
+    finally:
+        B._load_calls(real)
+        B._calls.set_stream_query(*(query or (None, None, None)))
+
+
+@pytest.fixture
+def stub(tmp_path, monkeypatch):
+    with _stubbed(tmp_path, monkeypatch) as l:
+        yield l
+
+
+def test_nothing_of_the_stub_is_left(tmp_path, monkeypatch):
+    t = torch.zeros(8)
+    with monkeypatch.context() as m, _stubbed(tmp_path, m):
+        assert B._calls.pack(0, 1, t, None) == 0
+    # (the library refuses a null context; without a stream query the call is the general path's)
+    assert B._calls.pack(0, 1, t, 9) == 1
+    assert (B._calls.pack(0, 1, t, None) is None) == (B._raw_stream is None)
 
 
 def _both(l, monkeypatch, call):
@@ -120,6 +140,20 @@ def test_same_as_the_general_path(stub, monkeypatch):
     ctx.close()
     fast, general = _both(stub, monkeypatch, lambda: ctx.ddp_pack(1, t, 9))
     assert fast == general and fast[1][0] == 0
+
+
+def test_the_calls_are_taken(stub):
+    """Arguments as programs pass them every iteration do not fall back to the general path, which the comparison would not see."""
+    at, t, s = B.Context(0)._at, torch.zeros(8), torch.zeros(4, dtype=torch.float64)
+    lists, opt, calls = [torch.zeros(4) for _ in range(3)], B.make_opt("sgdm", 0.25, 3), B._calls
+    for stream in (None, 0, 5, _Stream()):
+        assert [c(at, 1, t, stream) for c in (calls.pack, calls.unpack, calls.pack16)] == [0] * 3
+        assert calls.update(at, opt, stream) == 0 and calls.update_layers(at, 0, 2, opt, stream) == 0
+        for peers in (lists, tuple(lists), B.device_pointer_array(lists)):
+            for stats in (s, None):
+                assert [c(at, 1, t, peers, 4, 0, t, stats, stream) for c in (calls.average, calls.average16)] == [0] * 2
+                assert [c(at, 1, peers, 4, 0, stats, opt, stream) for c in (calls.fused, calls.fused16)] == [0] * 2
+                assert calls.fused_layers(at, 1, 0, 2, peers, 0, 1, 4, 0, stats, opt, stream) == 0
 
 
 def test_forked_child_takes_the_general_path(stub, monkeypatch):
