@@ -251,10 +251,20 @@ def device_pointer_array(tensors) -> "C.Array":
     return _dev_ptrs(list(tensors))
 
 
-def _peers_arg(peers):
+def _peers_arg(peers, N):
+    """The array of the peers' pointers.  The library reads N - 1 of them: those that the caller left out are null, which it refuses."""
     if not peers:
         return None
-    return peers if isinstance(peers, C.Array) else _dev_ptrs(list(peers))
+    arr = peers if isinstance(peers, C.Array) else _dev_ptrs(list(peers))
+    try:
+        need = C.c_int(N).value - 1
+    except TypeError:        # (the call itself says so)
+        return arr
+    if C.sizeof(arr) >= need * C.sizeof(C.c_void_p) or need >= DDP_MAX_REPLICAS:    # (as many replicas are refused)
+        return arr
+    full = (C.c_void_p * need)()
+    C.memmove(full, arr, C.sizeof(arr))
+    return full
 
 
 def ddp_stream_probe(read_tensors, write_tensors, nbytes: int, chunk_bytes: int = 8192, lds_pad: int = 65536, stream=None) -> None:
@@ -366,14 +376,14 @@ class Context:
             return
         if rc is not None:
             _check(rc, self._h)
-        arr = _peers_arg(peers)
+        arr = _peers_arg(peers, N)
         _check(lib().ddp_partial_average(self._h, slot, flat_local.data_ptr(), None if arr is None else C.addressof(arr), N, local_rank,
                                          flat_out.data_ptr(), None if layer_stats is None else layer_stats.data_ptr(),
                                          _stream_handle(stream)), self._h)
 
     def ddp_partial_average_static(self, slot: int, flat_local, peers, N: int, local_rank: int, flat_out, layer_stats=None,
                                    stream=None) -> None:
-        arr = _peers_arg(peers)
+        arr = _peers_arg(peers, N)
         _check(lib().ddp_partial_average_static(self._h, slot, flat_local.data_ptr(), None if arr is None else C.addressof(arr), N,
                                                 local_rank, flat_out.data_ptr(),
                                                 None if layer_stats is None else layer_stats.data_ptr(), _stream_handle(stream)), self._h)
@@ -400,7 +410,7 @@ class Context:
             return
         if rc is not None:
             _check(rc, self._h)
-        arr = _peers_arg(peers)
+        arr = _peers_arg(peers, N)
         _check(lib().ddp_fused_sync_update(self._h, slot, None if arr is None else C.addressof(arr), N, local_rank,
                                            None if layer_stats is None else layer_stats.data_ptr(), C.byref(opt),
                                            _stream_handle(stream)), self._h)
@@ -420,7 +430,7 @@ class Context:
             return
         if rc is not None:
             _check(rc, self._h)
-        arr = _peers_arg(peers16)
+        arr = _peers_arg(peers16, N)
         _check(lib().ddp_partial_average_wire16(self._h, slot, flat_local16.data_ptr(), None if arr is None else C.addressof(arr), N,
                                                 local_rank, flat_out.data_ptr(),
                                                 None if layer_stats is None else layer_stats.data_ptr(), _stream_handle(stream)), self._h)
@@ -431,7 +441,7 @@ class Context:
             return
         if rc is not None:
             _check(rc, self._h)
-        arr = _peers_arg(peers16)
+        arr = _peers_arg(peers16, N)
         _check(lib().ddp_fused_sync_update_wire16(self._h, slot, None if arr is None else C.addressof(arr), N, local_rank,
                                                   None if layer_stats is None else layer_stats.data_ptr(), C.byref(opt),
                                                   _stream_handle(stream)), self._h)
@@ -451,7 +461,7 @@ class Context:
             return
         if rc is not None:
             _check(rc, self._h)
-        arr = _peers_arg(peers)
+        arr = _peers_arg(peers, N)
         _check(lib().ddp_fused_sync_update_layers(self._h, slot, layer_first, layer_count, None if arr is None else C.addressof(arr),
                                                   wire_dtype, order, N, local_rank,
                                                   None if layer_stats is None else layer_stats.data_ptr(), C.byref(opt),

@@ -84,7 +84,9 @@ typedef struct {
 static void peers_done(Peers *p) {
     if (p->view.obj) PyBuffer_Release(&p->view);
 }
-static int get_peers(PyObject *o, Peers *p) {
+/* The library reads N - 1 pointers: those that a list leaves out are null, which it refuses; a shorter array is not taken. */
+static int get_peers(PyObject *o, int N, Peers *p) {
+    const int need = N > 1 && N <= DDP_MAX_REPLICAS ? N - 1 : 0;  /* (more replicas are refused before any peer is looked at) */
     p->view.obj = NULL;
     p->at = NULL;
     if (o == Py_None) return 1;
@@ -101,12 +103,17 @@ static int get_peers(PyObject *o, Peers *p) {
             if (!ok) return 0;
         }
         if (i < n) return 0;
+        for (; i < need; ++i) p->own[i] = NULL;
         if (n) p->at = p->own;
         return 1;
     }
     if (PyObject_IsInstance(o, array_type) != 1 || PyObject_GetBuffer(o, &p->view, PyBUF_SIMPLE) != 0) {
         p->view.obj = NULL;
         return no();
+    }
+    if (p->view.len && p->view.len < need * (Py_ssize_t)sizeof(void *)) {
+        peers_done(p);
+        return 0;
     }
     if (p->view.len) p->at = p->view.buf;
     return 1;
@@ -153,8 +160,8 @@ COPY_CALL(pack16, uint16_t *)
         int slot, N, rank, rc;                                                                                                  \
         Peers p;                                                                                                                \
         (void)self;                                                                                                             \
-        if (!lib.name || n != 9 || !get_peers(a[3], &p)) Py_RETURN_NONE;                                                        \
-        if (!get_address(a[0], &ctx) || !get_int(a[1], &slot) || !get_tensor(a[2], &local) || !get_int(a[4], &N) || !get_int(a[5], &rank) || \
+        if (!lib.name || n != 9 || !get_int(a[4], &N) || !get_peers(a[3], N, &p)) Py_RETURN_NONE;                               \
+        if (!get_address(a[0], &ctx) || !get_int(a[1], &slot) || !get_tensor(a[2], &local) || !get_int(a[5], &rank) || \
             !get_tensor(a[6], &out) || !get_optional(a[7], &stats) || !get_stream(a[8], &stream)) {                             \
             peers_done(&p);                                                                                                     \
             Py_RETURN_NONE;                                                                                                     \
@@ -198,8 +205,8 @@ FN(update_layers) {
         Py_buffer opt;                                                                                                        \
         Peers p;                                                                                                              \
         (void)self;                                                                                                           \
-        if (!lib.name || n != 8 || !get_peers(a[2], &p)) Py_RETURN_NONE;                                                      \
-        if (!get_address(a[0], &ctx) || !get_int(a[1], &slot) || !get_int(a[3], &N) || !get_int(a[4], &rank) || !get_optional(a[5], &stats) || \
+        if (!lib.name || n != 8 || !get_int(a[3], &N) || !get_peers(a[2], N, &p)) Py_RETURN_NONE;                             \
+        if (!get_address(a[0], &ctx) || !get_int(a[1], &slot) || !get_int(a[4], &rank) || !get_optional(a[5], &stats) || \
             !get_stream(a[7], &stream) || !get_opt(a[6], &opt)) {                                                             \
             peers_done(&p);                                                                                                   \
             Py_RETURN_NONE;                                                                                                   \
@@ -219,10 +226,11 @@ FN(fused_layers) {
     Py_buffer opt;
     Peers p;
     (void)self;
-    if (!lib.fused_layers || n != 12 || !get_peers(a[4], &p)) Py_RETURN_NONE;
+    if (!lib.fused_layers || n != 12) Py_RETURN_NONE;
     for (i = 0; i < 3 && ok; ++i) ok = get_int(a[1 + i], &v[i]);
     for (i = 0; i < 4 && ok; ++i) ok = get_int(a[5 + i], &w[i]);
-    if (!ok || !get_address(a[0], &ctx) || !get_optional(a[9], &stats) || !get_stream(a[11], &stream) || !get_opt(a[10], &opt)) {
+    if (!ok || !get_peers(a[4], w[2], &p)) Py_RETURN_NONE;
+    if (!get_address(a[0], &ctx) || !get_optional(a[9], &stats) || !get_stream(a[11], &stream) || !get_opt(a[10], &opt)) {
         peers_done(&p);
         Py_RETURN_NONE;
     }

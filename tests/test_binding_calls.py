@@ -156,6 +156,37 @@ def test_the_calls_are_taken(stub):
                 assert calls.fused_layers(at, 1, 0, 2, peers, 0, 1, 4, 0, stats, opt, stream) == 0
 
 
+def _short_forms(n):
+    """Fewer than N - 1 peers, in every form that peers come in."""
+    few = [torch.zeros(4) for _ in range(n)]
+    return [few, tuple(few), iter(few), B.device_pointer_array(few), (C.c_char * (8 * n)).from_buffer_copy(B.device_pointer_array(few))], few
+
+
+@pytest.mark.parametrize("n", [1, 2])
+def test_missing_peers_are_null(stub, monkeypatch, n):
+    """The library reads N - 1 pointers: those that a caller left out arrive as null, which it refuses, not as whatever lies behind
+    the last one (the previous call's peers).  The same on both paths, and where N is none that the library takes."""
+    ctx, t, s, opt = B.Context(0), torch.zeros(8), torch.zeros(4, dtype=torch.float64), B.make_opt("sgdm", 0.25, 3)
+    full = [torch.zeros(4) for _ in range(3)]
+    calls = {"ddp_partial_average": lambda p, N: (1, t, p, N, 0, t, s, 9), "ddp_partial_average_wire16": lambda p, N: (1, t, p, N, 0, t, None, 9),
+             "ddp_fused_sync_update": lambda p, N: (1, p, N, 0, s, opt, 9), "ddp_fused_sync_update_wire16": lambda p, N: (1, p, N, 0, s, opt, 9),
+             "ddp_fused_sync_update_layers": lambda p, N: (1, 0, 2, p, 0, 1, N, 0, s, opt, 9)}
+    for name, args in calls.items():
+        for i in range(5):
+            for fast in (True, False):
+                with monkeypatch.context() as m:
+                    if not fast:
+                        m.setattr(B, "_calls", B._NoCalls())
+                    getattr(ctx, name)(*args(full, 4))
+                    forms, few = _short_forms(n)
+                    getattr(ctx, name)(*args(forms[i], 4))
+                    seen = list((C.c_long * 4).in_dll(stub, "peers"))[:3]
+                    assert seen == [q.data_ptr() for q in few] + [0] * (3 - n), (name, i, fast)
+        for N in (0, -5, -2 ** 31, 65, 2 ** 31, 2 ** 32 + 4, 2 ** 70, True, np.int32(4), 4.0, None):
+            fast, general = _both(stub, monkeypatch, lambda: getattr(ctx, name)(*args(full, N)))
+            assert fast[0] == general[0] and fast[1] == general[1], (name, N)
+
+
 def test_forked_child_takes_the_general_path(stub, monkeypatch):
     ctx, t = B.Context(0), torch.zeros(8)
     B._calls.set_stream_query(lambda: True, lambda: 0, lambda d: 78)
