@@ -26,10 +26,15 @@ static PyObject *array_type, *opt_type;                /* ctypes.Array, the bind
 static PyObject *bad_fork, *get_device, *raw_stream;   /* torch's raw queries of the current stream */
 static PyObject *s_data_ptr, *s_cuda_stream;
 
-/* Each returns 1, or 0 for a form it does not take (no exception left behind). */
+/* Each returns 1, or 0 for a form it does not take, without an exception, and where the argument's own code raised one, with it:
+ * arguments are looked at in the order of the general path, which would raise the same.  Then the call returns general(). */
 static int no(void) {
     PyErr_Clear();
     return 0;
+}
+static PyObject *general(void) {
+    if (PyErr_Occurred()) return NULL;
+    Py_RETURN_NONE;
 }
 static int get_int(PyObject *o, int *out) {
     int over;
@@ -41,7 +46,7 @@ static int get_int(PyObject *o, int *out) {
     return 1;
 }
 static int get_address(PyObject *o, void **out) { /* an exact int; a new reference is not taken */
-    if (!o || !PyLong_CheckExact(o)) return o ? 0 : no();
+    if (!o || !PyLong_CheckExact(o)) return 0;
     *out = PyLong_AsVoidPtr(o);
     return *out || !PyErr_Occurred() ? 1 : no();
 }
@@ -58,14 +63,14 @@ static int get_optional(PyObject *o, void **out) {
 static int get_stream(PyObject *o, void **out) {
     PyObject *p, *dev;
     int ok;
-    if (PyLong_CheckExact(o)) return get_address(o, out);
+    if (PyLong_Check(o)) return get_address(o, out);
     if (o == Py_None) {
         if (!raw_stream) return 0;
         p = PyObject_CallNoArgs(bad_fork);
         ok = p == Py_False;
         Py_XDECREF(p);
-        if (!ok) return no();
-        if (!(dev = PyObject_CallNoArgs(get_device))) return no();
+        if (!ok) return 0;
+        if (!(dev = PyObject_CallNoArgs(get_device))) return 0;
         p = PyObject_CallOneArg(raw_stream, dev);
         Py_DECREF(dev);
     } else {
@@ -98,7 +103,7 @@ static int get_peers(PyObject *o, int N, Peers *p) {
             int ok;
             Py_INCREF(x);
             p->own[i] = NULL;
-            ok = x == Py_None || (PyLong_CheckExact(x) ? get_address(x, &p->own[i]) : get_tensor(x, &p->own[i]));
+            ok = x == Py_None || (PyLong_Check(x) ? get_address(x, &p->own[i]) : get_tensor(x, &p->own[i]));
             Py_DECREF(x);
             if (!ok) return 0;
         }
@@ -118,36 +123,39 @@ static int get_peers(PyObject *o, int N, Peers *p) {
     if (p->view.len) p->at = p->view.buf;
     return 1;
 }
+static void opt_done(Py_buffer *view) {
+    if (view->obj) PyBuffer_Release(view);
+}
 static int get_opt(PyObject *o, Py_buffer *view) {
     view->obj = NULL;
     if ((PyObject *)Py_TYPE(o) != opt_type) return 0;
     if (PyObject_GetBuffer(o, view, PyBUF_SIMPLE) != 0 || view->len < (Py_ssize_t)sizeof(ddp_opt)) {
-        if (view->obj) PyBuffer_Release(view);
+        opt_done(view);
         view->obj = NULL;
         return no();
     }
     return 1;
 }
 
-#define CALL(expr)               \
-    do {                         \
-        Py_BEGIN_ALLOW_THREADS;  \
-        rc = (expr);             \
-        Py_END_ALLOW_THREADS;    \
+#define CALL(expr)              \
+    do {                        \
+        Py_BEGIN_ALLOW_THREADS; \
+        rc = (expr);            \
+        Py_END_ALLOW_THREADS;   \
     } while (0)
 #define CTX ((ddp_ctx *)ctx)
 #define FN(name) static PyObject *name(PyObject *self, PyObject *const *a, Py_ssize_t n)
 
 /* (ctx, slot, buffer, stream) */
-#define COPY_CALL(name, type)                                                                                                \
-    FN(name) {                                                                                                               \
-        void *ctx, *buf, *stream;                                                                                            \
-        int slot, rc;                                                                                                        \
-        (void)self;                                                                                                          \
+#define COPY_CALL(name, type)                                                                                                   \
+    FN(name) {                                                                                                                  \
+        void *ctx, *buf, *stream;                                                                                               \
+        int slot, rc;                                                                                                           \
+        (void)self;                                                                                                             \
         if (!lib.name || n != 4 || !get_address(a[0], &ctx) || !get_int(a[1], &slot) || !get_tensor(a[2], &buf) || !get_stream(a[3], &stream)) \
-            Py_RETURN_NONE;                                                                                                  \
-        CALL(lib.name(CTX, slot, (type)buf, stream));                                                                        \
-        return PyLong_FromLong(rc);                                                                                          \
+            return general();                                                                                                   \
+        CALL(lib.name(CTX, slot, (type)buf, stream));                                                                           \
+        return PyLong_FromLong(rc);                                                                                             \
     }
 COPY_CALL(pack, float *)
 COPY_CALL(unpack, const float *)
@@ -160,11 +168,11 @@ COPY_CALL(pack16, uint16_t *)
         int slot, N, rank, rc;                                                                                                  \
         Peers p;                                                                                                                \
         (void)self;                                                                                                             \
-        if (!lib.name || n != 9 || !get_int(a[4], &N) || !get_peers(a[3], N, &p)) Py_RETURN_NONE;                               \
-        if (!get_address(a[0], &ctx) || !get_int(a[1], &slot) || !get_tensor(a[2], &local) || !get_int(a[5], &rank) || \
+        if (!lib.name || n != 9 || !get_int(a[4], &N) || !get_peers(a[3], N, &p)) return general();                             \
+        if (!get_address(a[0], &ctx) || !get_int(a[1], &slot) || !get_int(a[5], &rank) || !get_tensor(a[2], &local) ||          \
             !get_tensor(a[6], &out) || !get_optional(a[7], &stats) || !get_stream(a[8], &stream)) {                             \
             peers_done(&p);                                                                                                     \
-            Py_RETURN_NONE;                                                                                                     \
+            return general();                                                                                                   \
         }                                                                                                                       \
         CALL(lib.name(CTX, slot, (const type *)local, (const type *const *)p.at, N, rank, (float *)out, (double *)stats, stream)); \
         peers_done(&p);                                                                                                         \
@@ -179,9 +187,13 @@ FN(update) {
     Py_buffer opt;
     int rc;
     (void)self;
-    if (!lib.update || n != 3 || !get_address(a[0], &ctx) || !get_stream(a[2], &stream) || !get_opt(a[1], &opt)) Py_RETURN_NONE;
+    if (!lib.update || n != 3 || !get_address(a[0], &ctx) || !get_opt(a[1], &opt)) return general();
+    if (!get_stream(a[2], &stream)) {
+        opt_done(&opt);
+        return general();
+    }
     CALL(lib.update(CTX, (const ddp_opt *)opt.buf, stream));
-    PyBuffer_Release(&opt);
+    opt_done(&opt);
     return PyLong_FromLong(rc);
 }
 FN(update_layers) {
@@ -189,32 +201,37 @@ FN(update_layers) {
     Py_buffer opt;
     int first, count, rc;
     (void)self;
-    if (!lib.update_layers || n != 5 || !get_address(a[0], &ctx) || !get_int(a[1], &first) || !get_int(a[2], &count) || !get_stream(a[4], &stream) ||
-        !get_opt(a[3], &opt))
-        Py_RETURN_NONE;
+    if (!lib.update_layers || n != 5 || !get_address(a[0], &ctx) || !get_int(a[1], &first) || !get_int(a[2], &count) || !get_opt(a[3], &opt))
+        return general();
+    if (!get_stream(a[4], &stream)) {
+        opt_done(&opt);
+        return general();
+    }
     CALL(lib.update_layers(CTX, first, count, (const ddp_opt *)opt.buf, stream));
-    PyBuffer_Release(&opt);
+    opt_done(&opt);
     return PyLong_FromLong(rc);
 }
 
 /* (ctx, slot, peers, N, local_rank, layer_stats, opt, stream) */
-#define FUSED_CALL(name, type)                                                                                                \
-    FN(name) {                                                                                                                \
-        void *ctx, *stats, *stream;                                                                                           \
-        int slot, N, rank, rc;                                                                                                \
-        Py_buffer opt;                                                                                                        \
-        Peers p;                                                                                                              \
-        (void)self;                                                                                                           \
-        if (!lib.name || n != 8 || !get_int(a[3], &N) || !get_peers(a[2], N, &p)) Py_RETURN_NONE;                             \
+#define FUSED_CALL(name, type)                                                                                           \
+    FN(name) {                                                                                                           \
+        void *ctx, *stats, *stream;                                                                                      \
+        int slot, N, rank, rc;                                                                                           \
+        Py_buffer opt;                                                                                                   \
+        Peers p;                                                                                                         \
+        (void)self;                                                                                                      \
+        opt.obj = NULL;                                                                                                  \
+        if (!lib.name || n != 8 || !get_int(a[3], &N) || !get_peers(a[2], N, &p)) return general();                      \
         if (!get_address(a[0], &ctx) || !get_int(a[1], &slot) || !get_int(a[4], &rank) || !get_optional(a[5], &stats) || \
-            !get_stream(a[7], &stream) || !get_opt(a[6], &opt)) {                                                             \
-            peers_done(&p);                                                                                                   \
-            Py_RETURN_NONE;                                                                                                   \
-        }                                                                                                                     \
-        CALL(lib.name(CTX, slot, (const type *const *)p.at, N, rank, (double *)stats, (const ddp_opt *)opt.buf, stream));     \
-        PyBuffer_Release(&opt);                                                                                               \
-        peers_done(&p);                                                                                                       \
-        return PyLong_FromLong(rc);                                                                                           \
+            !get_opt(a[6], &opt) || !get_stream(a[7], &stream)) {                                                        \
+            opt_done(&opt);                                                                                               \
+            peers_done(&p);                                                                                               \
+            return general();                                                                                             \
+        }                                                                                                                 \
+        CALL(lib.name(CTX, slot, (const type *const *)p.at, N, rank, (double *)stats, (const ddp_opt *)opt.buf, stream)); \
+        opt_done(&opt);                                                                                                   \
+        peers_done(&p);                                                                                                   \
+        return PyLong_FromLong(rc);                                                                                       \
     }
 FUSED_CALL(fused, float)
 FUSED_CALL(fused16, uint16_t)
@@ -226,16 +243,18 @@ FN(fused_layers) {
     Py_buffer opt;
     Peers p;
     (void)self;
-    if (!lib.fused_layers || n != 12) Py_RETURN_NONE;
+    opt.obj = NULL;
+    if (!lib.fused_layers || n != 12) return general();
     for (i = 0; i < 3 && ok; ++i) ok = get_int(a[1 + i], &v[i]);
     for (i = 0; i < 4 && ok; ++i) ok = get_int(a[5 + i], &w[i]);
-    if (!ok || !get_peers(a[4], w[2], &p)) Py_RETURN_NONE;
-    if (!get_address(a[0], &ctx) || !get_optional(a[9], &stats) || !get_stream(a[11], &stream) || !get_opt(a[10], &opt)) {
+    if (!ok || !get_peers(a[4], w[2], &p)) return general();
+    if (!get_address(a[0], &ctx) || !get_optional(a[9], &stats) || !get_opt(a[10], &opt) || !get_stream(a[11], &stream)) {
+        opt_done(&opt);
         peers_done(&p);
-        Py_RETURN_NONE;
+        return general();
     }
     CALL(lib.fused_layers(CTX, v[0], v[1], v[2], (const void *const *)p.at, w[0], w[1], w[2], w[3], (double *)stats, (const ddp_opt *)opt.buf, stream));
-    PyBuffer_Release(&opt);
+    opt_done(&opt);
     peers_done(&p);
     return PyLong_FromLong(rc);
 }

@@ -98,7 +98,7 @@ def _forms():
     t, s = torch.zeros(8), torch.zeros(4, dtype=torch.float64)
     lists = [torch.zeros(4) for _ in range(3)]
     opt = B.make_opt("sgdm", 0.25, 3, momentum=0.9)
-    peers = [lists, tuple(lists), B.device_pointer_array(lists), (C.c_void_p * 3)(1, None, 3), [lists[0], None, 12345], [], (), None,
+    peers = [lists, tuple(lists), B.device_pointer_array(lists), (C.c_void_p * 3)(1, None, 3), [lists[0], None, 12345], [lists[0], True, 7], [], (), None,
              [object()], "abc", [t] * 65]
     for stream in (None, 0, 5, _Stream(), True, 1.5, "x", np.int64(3)):
         yield "ddp_pack", (2, t, stream)
@@ -185,6 +185,50 @@ def test_missing_peers_are_null(stub, monkeypatch, n):
         for N in (0, -5, -2 ** 31, 65, 2 ** 31, 2 ** 32 + 4, 2 ** 70, True, np.int32(4), 4.0, None):
             fast, general = _both(stub, monkeypatch, lambda: getattr(ctx, name)(*args(full, N)))
             assert fast[0] == general[0] and fast[1] == general[1], (name, N)
+
+
+class _Once:
+    """A tensor (or a stream) whose address cannot be had the first time."""
+
+    def __init__(self, error, value=64):
+        self.error, self.value = error, value
+
+    def _get(self):
+        error, self.error = self.error, None
+        if error:
+            raise error("first")
+        return self.value
+
+    data_ptr = _get
+    cuda_stream = property(_get)
+
+
+@pytest.mark.parametrize("error", [KeyboardInterrupt, RuntimeError, AttributeError])
+def test_an_argument_s_own_exception_comes_back(stub, monkeypatch, error):
+    """What an argument raises when it is asked for its address ends the call, as on the general path; it is not asked again."""
+    ctx, t, opt = B.Context(0), torch.zeros(8), B.make_opt("sgdm", 0.25, 3)
+    once = lambda: _Once(error)  # noqa: E731
+    calls = [lambda: ctx.ddp_pack(1, once(), 9), lambda: ctx.ddp_unpack(1, t, once()), lambda: ctx.ddp_pack_wire16(1, once(), once()),
+             lambda: ctx.ddp_partial_average(1, once(), [t] * 3, 4, 0, t, t, 9), lambda: ctx.ddp_partial_average(1, t, [t, once(), t], 4, 0, t, t, 9),
+             lambda: ctx.ddp_partial_average_wire16(1, t, (once(), t, t), 4, 0, once(), t, 9),
+             lambda: ctx.ddp_partial_average(1, t, [t] * 3, 4, 0, once(), None, 9), lambda: ctx.ddp_partial_average(1, t, [t] * 3, 4, 0, t, once(), 9),
+             lambda: ctx.ddp_local_update(opt, once()), lambda: ctx.ddp_local_update_layers(0, 2, opt, once()),
+             lambda: ctx.ddp_fused_sync_update(1, [t] * 3, 4, 0, once(), opt, 9), lambda: ctx.ddp_fused_sync_update_wire16(1, [once()] * 3, 4, 0, None, opt, 9),
+             lambda: ctx.ddp_fused_sync_update_layers(1, 0, 2, [t] * 3, 0, 1, 4, 0, None, opt, once()),
+             # (two that cannot be used: the one that the general path looks at first decides)
+             lambda: ctx.ddp_local_update(None, once()), lambda: ctx.ddp_fused_sync_update(1, [t] * 3, 4, 0, None, 7, once()),
+             lambda: ctx.ddp_partial_average(1, once(), [t] * 3, 4, 2 ** 40, t, None, "x"), lambda: ctx.ddp_pack(None, once(), 9)]
+    for k, call in enumerate(calls):
+        got = []
+        for path in (B._calls, B._NoCalls()):
+            with monkeypatch.context() as m:
+                m.setattr(B, "_calls", path)
+                try:
+                    got.append(("returns", call()))
+                except BaseException as e:  # noqa: BLE001
+                    got.append((type(e), str(e)))
+        assert got[0] == got[1], k
+        assert got[0] == (error, "first") or k in (13, 14), k
 
 
 def test_forked_child_takes_the_general_path(stub, monkeypatch):
