@@ -5,6 +5,7 @@ Every source is compiled to an object of its own (in parallel) and the objects a
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -51,7 +52,7 @@ def _run(cmd, verbose):
     diag = _diagnostics(r.stdout + r.stderr)
     if r.returncode != 0:
         sys.stderr.write(diag + "\n")
-        raise RuntimeError("hipcc failed: " + " ".join(cmd[-3:]))
+        raise RuntimeError(os.path.basename(cmd[0]) + " failed: " + " ".join(cmd[-3:]))
     if verbose and diag:
         print(diag, flush=True)
 
@@ -71,12 +72,16 @@ def build(verbose: bool = False, jobs: int = 0) -> str:
 
 
 def build_calls(verbose: bool = False) -> None:
-    """The extension module of the binding's per-iteration calls; without Python's headers the binding marshals in Python."""
+    """The extension module of the binding's per-iteration calls; without Python's headers or a C compiler the binding marshals in
+    Python, and a module built from an earlier source goes."""
     include = sysconfig.get_path("include")
-    if not os.path.exists(os.path.join(include, "Python.h")):
-        print("no Python.h in " + include + ": calls are marshalled in Python", file=sys.stderr)
+    cc = shutil.which("gcc") or shutil.which("cc")
+    if not cc or not os.path.exists(os.path.join(include, "Python.h")):
+        print(("no C compiler" if not cc else "no Python.h in " + include) + ": calls are marshalled in Python", file=sys.stderr)
+        if os.path.exists(CALLS):
+            os.remove(CALLS)
         return
-    _run(["gcc", "-O2", "-std=gnu11", "-Wall", "-Wextra", "-Wno-unused-parameter", "-shared", "-fPIC", "-I" + include, "-I" + os.path.join(ROOT, "include"),
+    _run([cc, "-O2", "-std=gnu11", "-Wall", "-Wextra", "-Wno-unused-parameter", "-shared", "-fPIC", "-I" + include, "-I" + os.path.join(ROOT, "include"),
           os.path.join(CSRC, "ddp_calls.c"), "-o", CALLS], verbose)
 
 

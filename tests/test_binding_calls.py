@@ -235,3 +235,19 @@ def test_forked_child_takes_the_general_path(stub, monkeypatch):
     ctx, t = B.Context(0), torch.zeros(8)
     B._calls.set_stream_query(lambda: True, lambda: 0, lambda d: 78)
     assert B._calls.pack(ctx._at, 1, t, None) is None and B._calls.pack(ctx._at, 1, t, 5) == 0
+
+
+@pytest.mark.parametrize("missing", ["compiler", "headers"])
+def test_build_without_compiler_or_headers(tmp_path, monkeypatch, capfd, missing):
+    """hipcc alone builds the library: without the module the calls take the general path, and no stale module stays behind."""
+    from paper_2502_11058_amd import build
+    stale = tmp_path / "_calls.so"
+    stale.write_bytes(b"stale")
+    monkeypatch.setattr(build, "CALLS", str(stale))
+    monkeypatch.setattr(build, "_run", lambda cmd, verbose: pytest.fail("nothing to run"))
+    if missing == "compiler":
+        monkeypatch.setenv("PATH", str(tmp_path))
+    else:
+        monkeypatch.setattr(build.sysconfig, "get_path", lambda name: str(tmp_path))
+    build.build_calls()
+    assert not stale.exists() and "marshalled in Python" in capfd.readouterr().err
