@@ -61,15 +61,11 @@ __global__ __launch_bounds__(kThreads) void mean_kernel(const MeanArgs a) {
     int h = (int)((4 - (base & 3)) & 3);
     if (h > n) h = n;
     const int nv = (n - h) >> 2;
-    // Only a layer's first and last chunk have a head and a tail, which are taken behind the vectors.  Up to four replicas, with
-    // three and four workgroups per CU, the memory serves the requests best a little apart: there the conditions come first, and
-    // the two sums of a long launch one after the other (TinyLlama-1.1B, us, as the others / so: N = 4 853 / 830, N = 2 508 / 502,
-    // N = 3 664 / 656; N = 8 1519 / 1545).
-    constexpr bool kApart = NREP > 0 && NREP <= 4;
-    auto ends = [&]() {
-        if (tid < n - 4 * nv) one(base + (tid < h ? tid : 4 * nv + tid));
-    };
-    if constexpr (kApart) ends();
+    // Head and tail, which only a layer's first and last chunk have, come before the vectors: behind them all replica pointers stay
+    // live across the loop, and the kernel for 32 replicas spilled 54 scalar registers into 36 bytes of scratch per lane (none so).
+    // No time either way, alternating builds: TinyLlama-1.1B, us, first / behind, N = 5 1066 / 1059, N = 6 1193 / 1203, N = 8
+    // 1536 / 1533, N = 24 4344 / 4397, N = 32 5812 / 5791 (runs of one build differ by 2 %).
+    if (tid < n - 4 * nv) one(base + (tid < h ? tid : 4 * nv + tid));
 
     const int64_t vbase = (base + h) >> 2;  // index in 16-byte units
     f32x4 *o4 = reinterpret_cast<f32x4 *>(a.out) + vbase;
@@ -169,9 +165,10 @@ __global__ __launch_bounds__(kThreads) void mean_kernel(const MeanArgs a) {
         }
     }
 
-    if constexpr (!kApart) ends();
-
     if constexpr (STATS) {
+        // Up to four replicas, with three and four workgroups per CU, the two sums of a long launch come one after the other
+        // (TinyLlama-1.1B, us, side by side / so: N = 4 860 / 831, N = 2 508 / 501, N = 3 661 / 653).
+        constexpr bool kApart = NREP > 0 && NREP <= 4;
         if (kApart && !a.st.counters) {
             gsum = block_sum(gsum, lds[0]);
             msum = block_sum(msum, lds[1]);
