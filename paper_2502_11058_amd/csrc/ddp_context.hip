@@ -834,18 +834,19 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     // single run).
     const int nl = (int)st->layers.size();
     auto inside = [&](int i) { return i < nl && st->layers[(size_t)i] >= first && st->layers[(size_t)i] < first + count; };
-    int64_t partials = 0, most = 0;
-    for (int i = 0; layer_stats && i < nl; ++i)
+    int64_t scheduled = 0, most = 0;  // chunks of the slot's layers in the range, each of which has a pair of partial sums
+    for (int i = 0; (layer_stats || wire16) && i < nl; ++i)
         if (inside(i)) {
             const int64_t n = st->update_ranges[2 * (size_t)i + 1] - st->update_ranges[2 * (size_t)i];
-            partials += n;
+            scheduled += n;
             most = std::max(most, n);
         }
-    const bool any = partials > 0;
+    const bool any = layer_stats && scheduled > 0;
     // One order of summation for a slot, whatever range the call has: the workgroups add a layer's partials up in the order of
     // the one-launch reduction, so they do it only in slots that this reduction serves.
-    const bool fold = any && st->max_update_partials <= kStatSingleMax && folds(ctx->cus, c1 - c0, partials, most);
+    const bool fold = any && st->max_update_partials <= kStatSingleMax && folds(ctx->cus, c1 - c0, scheduled, most);
     f.wire16 = wire16;
+    f.pairs = takes_pairs(ctx->cus, ctx->run_chunk, c1 - c0, scheduled, N, wire16);
     f.update_first = update_first;
     f.n_replicas = N;
     f.local_rank = local_rank;

@@ -37,7 +37,7 @@ inline void fill_peers(Peers &p, const FusedLaunch &f) {
 //                partial average -> unpack).
 // W16: peers are bf16 and the local replica contributes its bf16 rounding.  NREP > 0: the replica count (EXACT), or the
 // largest one that the registers are laid out for; 0: run-time loop, for more than kFixedReps.  gsum, msum: this thread's statistics (STATS).
-template <bool ADAM, bool GBF16, bool MODEL, int NREP, bool EXACT, bool STATS, bool W16, bool UTS, bool BUF>
+template <bool ADAM, bool GBF16, bool MODEL, int NREP, bool EXACT, bool STATS, bool W16, bool UTS, bool PAIRS, bool BUF>
 __device__ __forceinline__ void fused_body(const Streams<GBF16> c, int64_t fo, const Peers &a, const UpdateScalars &s, double &gsum, double &msum) {
     typedef GradVec<GBF16> G;
     typedef typename G::vec gvec;
@@ -96,11 +96,8 @@ __device__ __forceinline__ void fused_body(const Streams<GBF16> c, int64_t fo, c
     if constexpr (NREP > 1) {
         // The local contribution may be computed (updated and / or rounded) and a branch on it per replica would serialise
         // the loads: the N-1 peers are loaded by their position among the peers, all in flight before the first use.
-        // One vector of all streams in flight per thread, two where many replicas come as bf16: half the bytes a peer, and while
-        // one vector's long sum is formed nothing else would be asked for.  Fused, bf16 peers, us, one / two: GPT-2 small AdamW
-        // N = 12 687 / 677, N = 24 836 / 812, N = 32 889 / 882, SGD N = 24 672 / 642; 134 M parameters, AdamW, N = 24 935 / 900;
-        // N = 8 634 / 634.  With fp32 peers two are slower (GPT-2 small SGD N = 8 528 / 531, N = 2 420 / 427).
-        constexpr bool kPairs = W16 && NREP >= 16;
+        // One vector of all streams in flight per thread, or two (PAIRS, a kernel of its own: takes_pairs): with many bf16 peers, half
+        // the bytes a peer, nothing else would be asked for while one vector's long sum is formed.
         typedef typename WireVec<W16>::type raw4;
         auto groups = [&](int v, auto count) {
             constexpr int K = decltype(count)::value;
@@ -133,7 +130,7 @@ __device__ __forceinline__ void fused_body(const Streams<GBF16> c, int64_t fo, c
             }
         };
         int v = tid;
-        if constexpr (kPairs)
+        if constexpr (PAIRS)
             for (; v + kThreads < nv; v += 2 * kThreads) groups(v, std::integral_constant<int, 2>());
         for (; v < nv; v += kThreads) groups(v, std::integral_constant<int, 1>());
     } else {
@@ -211,18 +208,22 @@ __device__ __forceinline__ void fused_body(const Streams<GBF16> c, int64_t fo, c
     }
 }
 
-// The instantiation for a launch: K::go<ADAM, GBF16, MODEL, NREP, EXACT, STATS, W16, UTS>(lds), lds = the dynamic LDS it needs
+// The instantiation for a launch: K::go<ADAM, GBF16, MODEL, NREP, EXACT, STATS, W16, UTS, PAIRS>(lds), lds = the dynamic LDS it needs
 // (the residency pad, or the staging area of the run-time replica count if that is larger).
+template <bool A, bool G, bool M, int NR, bool EXACT, bool W, bool PAIRS, class K>
+int dispatch_fused_w(const FusedLaunch &f, const K &k, int lds) {
+    if (f.update_first) return f.st.partials ? k.template go<A, G, M, NR, EXACT, true, W, true, PAIRS>(lds) : k.template go<A, G, M, NR, EXACT, false, W, true, PAIRS>(lds);
+    return f.st.partials ? k.template go<A, G, M, NR, EXACT, true, W, false, PAIRS>(lds) : k.template go<A, G, M, NR, EXACT, false, W, false, PAIRS>(lds);
+}
+
 template <bool A, bool G, bool M, int NR, bool EXACT, class K>
 int dispatch_fused_n(const FusedLaunch &f, const K &k) {
     const int need = NR == 0 && f.st.partials ? stage_bytes(f.n_replicas - kRegReps) : 0;
     const int lds = f.lds_pad > need ? f.lds_pad : need;
-    if (f.wire16) {
-        if (f.update_first) return f.st.partials ? k.template go<A, G, M, NR, EXACT, true, true, true>(lds) : k.template go<A, G, M, NR, EXACT, false, true, true>(lds);
-        return f.st.partials ? k.template go<A, G, M, NR, EXACT, true, true, false>(lds) : k.template go<A, G, M, NR, EXACT, false, true, false>(lds);
-    }
-    if (f.update_first) return f.st.partials ? k.template go<A, G, M, NR, EXACT, true, false, true>(lds) : k.template go<A, G, M, NR, EXACT, false, false, true>(lds);
-    return f.st.partials ? k.template go<A, G, M, NR, EXACT, true, false, false>(lds) : k.template go<A, G, M, NR, EXACT, false, false, false>(lds);
+    if (!f.wire16) return dispatch_fused_w<A, G, M, NR, EXACT, false, false>(f, k, lds);
+    if constexpr (NR >= 16)
+        if (f.pairs) return dispatch_fused_w<A, G, M, NR, EXACT, true, true>(f, k, lds);
+    return dispatch_fused_w<A, G, M, NR, EXACT, true, false>(f, k, lds);
 }
 
 template <bool A, bool G, bool M, class K>

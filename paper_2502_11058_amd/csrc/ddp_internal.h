@@ -186,6 +186,7 @@ struct FusedLaunch {
     UpdateScalars s;
     StatsLaunch st;
     int lds_pad;
+    bool pairs;  // two vectors of all streams in flight per thread (takes_pairs)
 };
 // ... the table-driven one, over chunks of the update table ...
 struct FusedTable : FusedLaunch {

@@ -24,7 +24,7 @@ struct FusedArgs {
 
 // A chunk of a scheduled run takes fused_body, every other chunk the optimizer step only.  At least two wavefronts per
 // SIMD (the launch bounds): the residency that the launch asks for.
-template <bool ADAM, bool GBF16, bool MODEL, int NREP, bool EXACT, bool STATS, bool W16, bool UTS>
+template <bool ADAM, bool GBF16, bool MODEL, int NREP, bool EXACT, bool STATS, bool W16, bool UTS, bool PAIRS>
 __global__ __launch_bounds__(kThreads, 2) void fused_kernel(const FusedArgs a) {
     __shared__ double lds[2][kThreads / kWave];
     const bool paced = ADAM && long_launch();
@@ -37,7 +37,7 @@ __global__ __launch_bounds__(kThreads, 2) void fused_kernel(const FusedArgs a) {
         return;
     }
     double gsum = 0.0, msum = 0.0;
-    fused_body<ADAM, GBF16, MODEL, NREP, EXACT, STATS, W16, UTS, false>(c, ts.flat0 + ch.begin, a.peers, a.s, gsum, msum);
+    fused_body<ADAM, GBF16, MODEL, NREP, EXACT, STATS, W16, UTS, PAIRS, false>(c, ts.flat0 + ch.begin, a.peers, a.s, gsum, msum);
     if constexpr (STATS) {
         block_sum2(gsum, msum, lds);
         // chunks end on cache lines: chunk c of a run begins less than kLine elements before c * chunk_elems
@@ -53,9 +53,9 @@ struct LaunchTable {
     const FusedTable &f;
     const FusedArgs &a;
     void *stream;
-    template <bool A, bool G, bool M, int NR, bool EXACT, bool STATS, bool W, bool U>
+    template <bool A, bool G, bool M, int NR, bool EXACT, bool STATS, bool W, bool U, bool PAIRS>
     int go(int lds) const {
-        return launch(fused_kernel<A, G, M, NR, EXACT, STATS, W, U>, f.n_chunks, stream, lds, a);
+        return launch(fused_kernel<A, G, M, NR, EXACT, STATS, W, U, PAIRS>, f.n_chunks, stream, lds, a);
     }
 };
 

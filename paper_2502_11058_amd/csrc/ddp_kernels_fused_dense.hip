@@ -22,7 +22,7 @@ struct FusedDenseArgs {
 // part of the launch's arguments.  Bound by HBM with two workgroups per CU, so what a workgroup spends before its first load
 // counts: with the pieces searched by workgroup index instead of indexed (about 0.2 us) TinyLlama-1.1B at N = 2 took 5450 us,
 // so 5220.
-template <bool ADAM, bool GBF16, bool MODEL, int NREP, bool EXACT, bool STATS, bool W16, bool UTS>
+template <bool ADAM, bool GBF16, bool MODEL, int NREP, bool EXACT, bool STATS, bool W16, bool UTS, bool PAIRS>
 __global__ __launch_bounds__(kThreads, 2) void fused_dense_kernel(const FusedDenseArgs a) {
     __shared__ double lds[2][kThreads / kWave];
     const Piece t = a.pieces[blockIdx.y];
@@ -45,7 +45,7 @@ __global__ __launch_bounds__(kThreads, 2) void fused_dense_kernel(const FusedDen
         return;
     }
     double gsum = 0.0, msum = 0.0;
-    fused_body<ADAM, GBF16, MODEL, NREP, EXACT, STATS, W16, UTS, true>(c, t.flat0 + at, a.peers, a.s, gsum, msum);
+    fused_body<ADAM, GBF16, MODEL, NREP, EXACT, STATS, W16, UTS, PAIRS, true>(c, t.flat0 + at, a.peers, a.s, gsum, msum);
     if constexpr (STATS) {
         block_sum2(gsum, msum, lds);
         put_partial(a.st, (int64_t)t.pbase + blockIdx.x, t.pos, t.layer, a.peers.n, gsum, msum, lds);
@@ -56,9 +56,9 @@ struct LaunchDense {
     const FusedDense &f;
     const FusedDenseArgs &a;
     void *stream;
-    template <bool A, bool G, bool M, int NR, bool EXACT, bool STATS, bool W, bool U>
+    template <bool A, bool G, bool M, int NR, bool EXACT, bool STATS, bool W, bool U, bool PAIRS>
     int go(int lds) const {
-        return launch2(fused_dense_kernel<A, G, M, NR, EXACT, STATS, W, U>, f.pass->width, f.pass->n_pieces, stream, lds, a);
+        return launch2(fused_dense_kernel<A, G, M, NR, EXACT, STATS, W, U, PAIRS>, f.pass->width, f.pass->n_pieces, stream, lds, a);
     }
 };
 

@@ -71,6 +71,27 @@ inline bool small_model(int cus, int64_t numel, bool second_moment) {
 // just one round, 72.3 / 73.2; SGD 886^2 47.1 / 47.0.
 inline bool short_update(int cus, int64_t numel, bool adamw) { return adamw && 4 * ((numel + 2047) / 2048) <= 7 * (int64_t)cus; }
 
+// Whether the fused step of N bf16 replicas has two vectors of all streams in flight per thread (fused_body), in a call on `all`
+// chunks, `scheduled` of them of the slot's layers: in kernels laid out for 16 and 32 replicas, where a chunk has a second vector for
+// each thread.  That takes up to twice the registers and makes every workgroup's ramp longer, which a call of a few rounds of
+// workgroups does not hide.  One vector / two in us (scheduled of all chunks per CU):
+//     8 layers, fused       N = 24, SGD       N = 24, AdamW     N = 32, AdamW
+//     543^2  (1.1 of 4.5)   21.3 /  23.5      24.4 /  26.8      27.2 /  30.4
+//     640^2  (1.6 of 6.3)   24.0 /  25.4      29.5 /  30.1      31.2 /  33.0
+//     724^2  (2 of 8)       31.0 /  30.5      36.4 /  36.3      39.5 /  40.4
+//     886^2  (3 of 12)      43.3 /  42.6      52.0 /  51.2      56.7 /  56.3
+//     1533^2 (9 of 36)     111.7 / 107.3     138.1 / 134.7     149.6 / 152.3
+//     GPT-2 small          674   / 641       836   / 808       879   / 877       (N = 12, AdamW 687 / 677, N = 16 722 / 709)
+//     4, layer by layer, all scheduled
+//     800^2  (1.2 of 1.2)   71.2 /  86.6      79.0 /  96.0      86.0 / 102.4
+//     1448^2 (4 of 4)      148.0 / 152.2     167.8 / 168.8     184.0 / 196.0
+//     1773^2 (6 of 6)      212.8 / 206.6     239.1 / 232.1     275.0 / 278.7
+// 800^2 at N = 12 and 16, SGD: 47.2 / 51.7, 49.6 / 57.7.  Fewer replicas: GPT-2 small N = 8 634 / 634; fp32 peers are slower so (N = 8 528 /
+// 531, N = 2 420 / 427).
+inline bool takes_pairs(int cus, int64_t chunk, int64_t all, int64_t scheduled, int N, bool wire16) {
+    return wire16 && N > 8 && N <= 32 && chunk >= 2048 && scheduled >= 3 * (int64_t)cus && 2 * all >= 9 * (int64_t)cus;
+}
+
 // Workgroups of the table-free fused kernel over elements [e0, e1) of the arenas: chunks counted from the multiple of `line` at
 // or below e0 (kLine in the library; of four at least, where every stream is vector-aligned).
 inline int64_t dense_workgroups(int64_t e0, int64_t e1, int64_t chunk, int64_t line = 4) { return (e1 - e0 / line * line + chunk - 1) / chunk; }
