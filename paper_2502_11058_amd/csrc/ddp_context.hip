@@ -366,7 +366,7 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
 
         drop_schedule(ctx);
         std::vector<SlotTables> slots((size_t)H);
-        int64_t max_mean_chunks = 0;
+        int64_t max_mean_pairs = 0;
         for (int s = 0; s < H; ++s) {
             SlotTables &st = slots[(size_t)s];
             st.layer_pos.assign((size_t)ctx->L, -1);
@@ -433,7 +433,7 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
             st.n_pack = (int64_t)pack.size();
             st.n_unpack = one_table ? st.n_pack : (int64_t)unpack.size();
             st.n_mean = (int64_t)mc.size();
-            max_mean_chunks = std::max(max_mean_chunks, st.n_mean);
+            max_mean_pairs = std::max(max_mean_pairs, st.n_mean * mean_pairs(ctx->cus, ctx->mean_chunk, st.n_mean, (int64_t)st.layers.size()));
             interleave_segments(pack, ctx->dispatch_ways);
             interleave_segments(unpack, ctx->dispatch_ways);
             interleave_segments(mc, ctx->dispatch_ways);
@@ -460,11 +460,10 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
                 return rc;
             }
         }
-        // the fused step keeps one partial per update chunk, the average of many replicas two per chunk (mean_cut)
-        max_mean_chunks = std::max(2 * max_mean_chunks, ctx->n_update);
-        if (max_mean_chunks > 0) {
+        const int64_t max_pairs = std::max(max_mean_pairs, ctx->n_update);  // the fused step keeps one per update chunk
+        if (max_pairs > 0) {
             const size_t line = kFoldLine * sizeof(int32_t) / sizeof(double);  // the counters start on a cache line
-            const size_t sums = (((size_t)max_mean_chunks + (size_t)ctx->L * kStatSlices) * 2 + line - 1) / line * line;
+            const size_t sums = (((size_t)max_pairs + (size_t)ctx->L * kStatSlices) * 2 + line - 1) / line * line;
             const std::vector<int32_t> zeros((size_t)ctx->L * kFoldStride, 0);
             hipError_t e = hipMalloc((void **)&ctx->d_partials, sums * sizeof(double) + zeros.size() * sizeof(int32_t));
             if (e != hipSuccess) {
@@ -479,8 +478,8 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
                 drop_schedule(ctx);
                 return hip_fail(ctx, e, "hipMemcpy of the counters");
             }
-            ctx->partials_cap = max_mean_chunks;
-            ctx->d_slice_sums = ctx->d_partials + 2 * max_mean_chunks;
+            ctx->partials_cap = max_pairs;
+            ctx->d_slice_sums = ctx->d_partials + 2 * max_pairs;
         }
         ctx->slots = std::move(slots);
         ctx->H = H;

@@ -50,6 +50,10 @@ inline int mean_cut(int cus, int64_t chunk, int64_t n_chunks, int64_t n_layers, 
     if (!cut || N > 32) return 0;
     return (2 * n_chunks + n_layers * kStatSlices) * 2 * (int64_t)sizeof(double) <= (int64_t)DDP_STATIC_SCRATCH_BYTES ? (int)(chunk / 2) : 0;
 }
+// Pairs of partial sums per chunk that a slot's averages may need, whatever the call: two if any is cut.
+inline int mean_pairs(int cus, int64_t chunk, int64_t n_chunks, int64_t n_layers) {
+    return mean_cut(cus, chunk, n_chunks, n_layers, 32, true) ? 2 : 1;
+}
 
 // Whether a model is so small that its update and fused step take chunks of kSmallChunk elements and no cap on the workgroups per
 // CU: at two workgroups per CU and 2048 elements each it is one or two rounds of them, the second half empty.  Usual shape /

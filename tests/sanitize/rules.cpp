@@ -23,6 +23,12 @@ int main() {
         CHECK(!takes_pairs(256, 2048, 1151, 768, N, true) && !takes_pairs(256, 2048, many, 767, N, true));
         CHECK(!takes_pairs(256, 1024, many, many, N, true) && !takes_pairs(256, 2048, many, many, N, false));
     }
+    // every average that is cut finds two pairs a chunk in its context's scratch; slots that are never cut have one
+    for (int64_t n : {1, 100, 319, 320, 321, 384, 385, 2048, 100000, 520000, 524288, 600000})
+        for (int64_t layers : {1, 32, 100})
+            for (int N = 1; N <= DDP_MAX_REPLICAS; ++N)
+                for (bool wire16 : {false, true}) CHECK(!mean_cut(256, 2048, n, layers, N, wire16) || mean_pairs(256, 2048, n, layers) == 2);
+    CHECK(mean_pairs(256, 2048, 524288 - 32, 1) == 2 && mean_pairs(256, 2048, 524288 - 31, 1) == 1);
     std::printf("rules ok\n");
     return 0;
 }
