@@ -449,7 +449,7 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
             }
             for (size_t i = 0; i + 1 < st.update_ranges.size(); i += 2)
                 st.max_update_partials = std::max<int64_t>(st.max_update_partials, st.update_ranges[i + 1] - st.update_ranges[i]);
-            if (folds(ctx->cus, st.n_mean, st.n_mean, st.max_mean_partials))
+            if (folds(ctx->cus, st.n_mean, st.max_mean_partials))
                 for (size_t i = 0; i + 1 < lcp.size(); ++i) mean_ranges.insert(mean_ranges.end(), (size_t)(lcp[i + 1] - lcp[i]), (int32_t)i);
             if (rc == DDP_OK) rc = upload(ctx, mean_ranges, &st.d_layer_ranges);
             if (rc == DDP_OK) rc = upload(ctx, run_slot, &st.d_run_slot);
@@ -626,8 +626,8 @@ int ddp::partial_average_impl(ddp_ctx *ctx, const char *who, bool wire16, int sl
     a.n_chunks = s->n_mean;
     a.cut = cut;
     // (a slot whose chunks would not be folded uncut has no positions of them)
-    const bool fold = layer_stats && !scratch && folds(ctx->cus, s->n_mean, s->n_mean, s->max_mean_partials) &&
-                      folds(ctx->cus, pairs * s->n_mean, pairs * s->n_mean, pairs * s->max_mean_partials);
+    const bool fold = layer_stats && !scratch && folds(ctx->cus, s->n_mean, s->max_mean_partials) &&
+                      folds(ctx->cus, pairs * s->n_mean, pairs * s->max_mean_partials);
     a.st = {layer_stats ? partials : nullptr, s->d_layer_ranges, layer_stats, fold ? ctx->d_counters : nullptr, pairs};
     a.chunk_pos = s->d_layer_ranges + 2 * s->layers.size();
     a.nontemporal = ctx->nontemporal;
@@ -843,7 +843,7 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     const bool any = layer_stats && scheduled > 0;
     // One order of summation for a slot, whatever range the call has: the workgroups add a layer's partials up in the order of
     // the one-launch reduction, so they do it only in slots that this reduction serves.
-    const bool fold = any && st->max_update_partials <= kStatSingleMax && folds(ctx->cus, c1 - c0, scheduled, most);
+    const bool fold = any && st->max_update_partials <= kStatSingleMax && folds(ctx->cus, scheduled, most);
     f.wire16 = wire16;
     f.pairs = takes_pairs(ctx->cus, ctx->run_chunk, c1 - c0, scheduled, N, wire16);
     f.update_first = update_first;

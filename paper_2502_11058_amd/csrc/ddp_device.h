@@ -337,10 +337,8 @@ __device__ __forceinline__ void put_partial(const StatsLaunch &st, int64_t parti
             if (yes) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
             return yes;
         };
-        const int n = (int)(c1 - c0), at = (int)(partial - c0), full = n / kFoldGroup;
-        const int groups = full < kFoldGroups ? (n + kFoldGroup - 1) / kFoldGroup : kFoldGroups;
-        const int group = at / kFoldGroup < groups ? at / kFoldGroup : groups - 1;
-        const int members = group == groups - 1 ? n - group * kFoldGroup : kFoldGroup;
+        const int n = (int)(c1 - c0), group = (int)(partial - c0) / kFoldGroup, groups = (n + kFoldGroup - 1) / kFoldGroup;
+        const int left = n - group * kFoldGroup, members = left < kFoldGroup ? left : kFoldGroup;
         is_last = last(of_layer + (1 + group) * kFoldLine, members) && (groups == 1 || last(of_layer, groups));
     }
     __syncthreads();

@@ -124,8 +124,8 @@ struct SlotTables {
     bool table_first = false;             // ... for which the table's single launch is the better one
 };
 
-// Counters of a layer whose workgroups add the statistics up themselves, in 32-bit words: one per group of kFoldGroup partials (the
-// last group takes what is left) and one over the groups, each in a cache line of its own.  Arrivals at one counter are served
+// Counters of a layer whose workgroups add the statistics up themselves, in 32-bit words: one per group of kFoldGroup partials
+// and one over the groups, each in a cache line of its own.  Arrivals at one counter are served
 // one after the other, 20-25 ns each: 128 of them on one 6.3 us, in groups 5.7 (average, N = 4).
 constexpr int kFoldGroup = 16, kFoldGroups = 20, kFoldLine = 32, kFoldStride = (1 + kFoldGroups) * kFoldLine;
 
@@ -140,7 +140,7 @@ struct StatsLaunch {
 };
 
 // ---- launchers (ddp_kernels_*.hip) -------------------------------------------------------------------------------
-constexpr int kCutReps = 12;  // fewest replicas whose average may cut chunks (mean_cut)
+constexpr int kCutReps = 12, kCutReps16 = 17;  // fewest replicas, fp32 and bf16, whose average may cut chunks (mean_cut)
 struct MeanLaunch {
     const void *x[DDP_MAX_REPLICAS];  // replicas in rank order (fp32, or bf16 when wire16)
     bool wire16;

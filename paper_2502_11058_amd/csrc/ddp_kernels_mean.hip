@@ -235,9 +235,11 @@ int mean_lds(const MeanLaunch &a) {
 template <int NREP, bool EXACT, bool CUT>
 int launch_mean_c(const MeanArgs &ma, const MeanLaunch &a, void *stream) {
     const int64_t grid = CUT ? 2 * a.n_chunks : a.n_chunks;
-    if (a.wire16) {
-        if (a.st.partials) return launch(mean_kernel<NREP, EXACT, true, true, true, CUT>, grid, stream, mean_lds<NREP>(a), ma);
-        return launch(mean_kernel<NREP, EXACT, false, true, true, CUT>, grid, stream, a.lds_pad, ma);
+    if constexpr (!CUT || NREP >= kCutReps16) {
+        if (a.wire16) {
+            if (a.st.partials) return launch(mean_kernel<NREP, EXACT, true, true, true, CUT>, grid, stream, mean_lds<NREP>(a), ma);
+            return launch(mean_kernel<NREP, EXACT, false, true, true, CUT>, grid, stream, a.lds_pad, ma);
+        }
     }
     if (a.st.partials) return a.nontemporal ? launch(mean_kernel<NREP, EXACT, true, true, false, CUT>, grid, stream, mean_lds<NREP>(a), ma)
                                          : launch(mean_kernel<NREP, EXACT, true, false, false, CUT>, grid, stream, mean_lds<NREP>(a), ma);

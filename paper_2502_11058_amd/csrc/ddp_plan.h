@@ -9,13 +9,10 @@
 
 namespace ddp {
 
-// Whether the workgroups of a launch put the layers' statistics together themselves: `partials` of its `workgroups` have a pair
-// of partial sums, at most `most` in one layer.  That saves a launch (3 us of host time), but each of these workgroups waits for
-// its pair and its counter to be where all XCDs see them before it ends.  Half a workgroup per CU with a share, in launches of
-// not much more than one, was the line while every pair cost a write-back of an L2 and a layer had one counter ...
-inline bool fold_stats(int cus, int64_t workgroups, int64_t partials) { return 2 * partials <= cus && 4 * workgroups <= 5 * (int64_t)cus; }
-// ... and counted in groups (kFoldGroup) it pays up to 5/4 workgroups per CU with a share, whatever the launch has besides.  Launch
-// of their own / folded in us, 256 CUs, two layers (four at 396 and 513 pairs):
+// Whether the workgroups of a launch put the layers' statistics together themselves: `partials` of them have a pair of partial
+// sums, at most `most` in one layer (counted in kFoldGroups groups of kFoldGroup).  That saves a launch (3 us of host time), but each
+// of these workgroups waits for its pair and its counter to be where all XCDs see them before it ends.  Up to 5/4 workgroups per CU
+// with a share, whatever the launch has besides.  Launch of their own / folded in us, 256 CUs, two layers (four at 396 and 513 pairs):
 //                             back to back    waited for    behind other work
 //     fused SGD, N = 4  128   8.19 /  7.74   20.9 / 20.3      8.4 /  8.1
 //                       198  10.51 / 10.22   23.4 / 22.9     10.7 / 10.4
@@ -26,10 +23,8 @@ inline bool fold_stats(int cus, int64_t workgroups, int64_t partials) { return 2
 //                       352  11.03 / 11.27   23.1 / 23.1     11.4 / 11.5
 //     average, N = 8    396   9.05 /  8.88   21.2 / 21.2      9.5 /  9.3
 //                       513  10.98 / 11.41   22.5 / 22.9     11.8 / 12.2
-inline bool fold_grouped(int cus, int64_t partials, int64_t most) { return 4 * partials <= 5 * (int64_t)cus && most <= kFoldGroup * kFoldGroups; }
-inline bool folds(int cus, int64_t workgroups, int64_t partials, int64_t most) {
-    return fold_stats(cus, workgroups, partials) || fold_grouped(cus, partials, most);
-}
+// One line for both kernels, drawn where the average crosses; the fused step, whose workgroups have more to do, still gains at 352.
+inline bool folds(int cus, int64_t partials, int64_t most) { return 4 * partials <= 5 * (int64_t)cus && most <= kFoldGroup * kFoldGroups; }
 
 // Where the average of N replicas cuts its chunks of `chunk` elements in two, a workgroup each (0: not).  The kernel for more than
 // 16 replicas takes the halves of a chunk one after the other; cut, one workgroup asks while another adds.  Up to 16 replicas both
@@ -45,10 +40,10 @@ inline bool folds(int cus, int64_t workgroups, int64_t partials, int64_t most) {
 // (N = 8: 131 K 5.8 / 5.5, 262 K 6.1 / 6.4; bf16, N = 12, waited for: 524 K 35.0 / 36.1).  A cut chunk has two pairs of partial sums,
 // so slots whose pairs would not fit the fixed scratch are not cut, whichever scratch a call has: same bits from both.
 inline int mean_cut(int cus, int64_t chunk, int64_t n_chunks, int64_t n_layers, int N, bool wire16) {
-    bool cut = N >= kCutReps && !wire16 && 4 * n_chunks <= 5 * (int64_t)cus;
-    if (N > 16) cut = wire16 || N == 32 || 2 * n_chunks <= 3 * (int64_t)cus || n_chunks >= 8 * (int64_t)cus;
-    if (!cut || N > 32) return 0;
-    return (2 * n_chunks + n_layers * kStatSlices) * 2 * (int64_t)sizeof(double) <= (int64_t)DDP_STATIC_SCRATCH_BYTES ? (int)(chunk / 2) : 0;
+    if (N < (wire16 ? kCutReps16 : kCutReps) || N > 32) return 0;
+    const bool cut = N <= 16 ? 4 * n_chunks <= 5 * (int64_t)cus
+                             : wire16 || N == 32 || 2 * n_chunks <= 3 * (int64_t)cus || n_chunks >= 8 * (int64_t)cus;
+    return cut && (2 * n_chunks + n_layers * kStatSlices) * 2 * (int64_t)sizeof(double) <= (int64_t)DDP_STATIC_SCRATCH_BYTES ? (int)(chunk / 2) : 0;
 }
 // Pairs of partial sums per chunk that a slot's averages may need, whatever the call: two if any is cut.
 inline int mean_pairs(int cus, int64_t chunk, int64_t n_chunks, int64_t n_layers) {
@@ -63,7 +58,8 @@ inline int mean_pairs(int cus, int64_t chunk, int64_t n_chunks, int64_t n_layers
 //     ... separate tensors  6.8 / 6.5    8.5 / 8.1   11.4 / 10.5  17.9 / 16.9  22.4 / 22.0  29.5 / 29.5
 //     SGD, N = 4            5.3 / 5.7    5.6 / 6.4    7.6 / 7.3   12.1 / 11.1  14.9 / 14.5  19.1 / 19.0
 //     SGD, bf16, N = 12     7.7 / 7.0    8.3 / 7.9   12.4 / 11.2  14.8 / 14.3  17.7 / 17.6  22.4 / 22.7
-// Up to 4.5 chunks per CU, then; below 5/4 only with a second moment, where a workgroup has more to do than its statistics.
+// Up to 4.5 chunks per CU, then; below 5/4 only with a second moment.  SGD with many bf16 peers gains there too, but replica count and
+// wire come with each call, when the tables are long made, and with few replicas SGD loses more than that.
 constexpr int64_t kSmallChunk = 1024;
 inline bool small_model(int cus, int64_t numel, bool second_moment) {
     const int64_t chunks = (numel + 2047) / 2048;
@@ -96,9 +92,9 @@ inline bool takes_pairs(int cus, int64_t chunk, int64_t all, int64_t scheduled, 
     return wire16 && N > 8 && N <= 32 && chunk >= 2048 && scheduled >= 3 * (int64_t)cus && 2 * all >= 9 * (int64_t)cus;
 }
 
-// Workgroups of the table-free fused kernel over elements [e0, e1) of the arenas: chunks counted from the multiple of `line` at
-// or below e0 (kLine in the library; of four at least, where every stream is vector-aligned).
-inline int64_t dense_workgroups(int64_t e0, int64_t e1, int64_t chunk, int64_t line = 4) { return (e1 - e0 / line * line + chunk - 1) / chunk; }
+// Workgroups of the table-free fused kernel over elements [e0, e1) of the arenas: chunks counted from the multiple of `line`
+// (kLine) at or below e0.
+inline int64_t dense_workgroups(int64_t e0, int64_t e1, int64_t chunk, int64_t line) { return (e1 - e0 / line * line + chunk - 1) / chunk; }
 
 // Chunks of the widest piece that the kernel's 32-bit indexes allow.
 inline int64_t widest_piece(int64_t chunk) { return INT32_MAX / chunk - 1; }
@@ -106,7 +102,7 @@ inline int64_t widest_piece(int64_t chunk) { return INT32_MAX / chunk - 1; }
 // Elements [begin, end), all of one scheduled layer (flat0 >= 0) or all unscheduled, as pieces of at most `width` chunks behind
 // those that p has.
 inline void add_pieces(DensePass &p, int64_t begin, int64_t end, int64_t flat0, int64_t pbase, int32_t pos, int32_t layer, int64_t width,
-                       int64_t chunk, int64_t line = 4) {
+                       int64_t chunk, int64_t line) {
     const int64_t base = begin / line * line, wg = dense_workgroups(begin, end, chunk, line);
     for (int64_t b = 0; b < wg; b += width) {
         const int64_t at = b == 0 ? begin : base + b * chunk, to = std::min(end, base + (b + width) * chunk);
@@ -126,7 +122,7 @@ inline void add_pieces(DensePass &p, int64_t begin, int64_t end, int64_t flat0, 
 // 64 K 17.0 / 12.5, of 256 K 37.9 / 34.3, of 1 M 117 / 115; N = 2: 21 of 1 M 126 / 129, 40 of 4 M 836 / 868.
 // No passes where a launch would need more than kMaxPieces pieces: such a slot always takes the table.
 template <class Elem0>
-void plan_dense(SlotTables &st, int L, Elem0 &&elem0, int64_t chunk, int64_t line = 4) {
+void plan_dense(SlotTables &st, int L, Elem0 &&elem0, int64_t chunk, int64_t line) {
     constexpr int kMaxSegments = 20;
     struct Segment {
         int64_t begin, end, flat0, pbase, wg;
@@ -201,7 +197,7 @@ inline bool takes_pieces(const SlotTables &st, std::vector<DensePass>::const_ite
 
 // What a call on elements [e0, e1), whole layers, runs of launch p: the pieces inside, runs of unscheduled layers cut at the
 // range's ends.  No search and nothing allocated; part is written only as far as its pieces go.
-inline void clip_pass(const DensePass &p, int64_t e0, int64_t e1, int64_t chunk, DensePass &part, int64_t line = 4) {
+inline void clip_pass(const DensePass &p, int64_t e0, int64_t e1, int64_t chunk, DensePass &part, int64_t line) {
     part.begin = std::max(p.begin, e0);
     part.end = std::min(p.end, e1);
     part.width = part.n_pieces = 0;

@@ -41,7 +41,7 @@ static Model make(const std::vector<int64_t> &sizes, const std::vector<int> &ord
     m.e.push_back(0);
     for (int64_t n : sizes) m.e.push_back(m.e.back() + n);
     std::vector<int64_t> wg(1, 0);
-    for (size_t l = 0; l < sizes.size(); ++l) wg.push_back(wg.back() + dense_workgroups(m.e[l], m.e[l + 1], chunk));
+    for (size_t l = 0; l < sizes.size(); ++l) wg.push_back(wg.back() + dense_workgroups(m.e[l], m.e[l + 1], chunk, kLine));
     m.st.layer_pos.assign(sizes.size(), -1);
     int64_t off = 0;
     for (int l : order) {
@@ -53,7 +53,7 @@ static Model make(const std::vector<int64_t> &sizes, const std::vector<int> &ord
         off += sizes[(size_t)l];
     }
     m.st.layer_begin.push_back(off);
-    plan_dense(m.st, m.L(), [&](int l) { return m.e[(size_t)l]; }, chunk);
+    plan_dense(m.st, m.L(), [&](int l) { return m.e[(size_t)l]; }, chunk, kLine);
     return m;
 }
 
@@ -66,7 +66,7 @@ static int check_call(const Model &m, int first, int count) {
         const DensePass &whole = *pass;
         static DensePass part;
         const long before = g_allocations;
-        clip_pass(whole, e0, e1, m.chunk, part);
+        clip_pass(whole, e0, e1, m.chunk, part, kLine);
         CHECK(g_allocations == before);
         if (whole.begin >= e0 && whole.end <= e1) {  // inside: the clipped form is the launch itself
             CHECK(part.width == whole.width && part.n_pieces == whole.n_pieces && part.begin == whole.begin && part.end == whole.end);
@@ -87,7 +87,7 @@ static int check_call(const Model &m, int first, int count) {
             const Piece &q = part.pieces[i];
             CHECK(q.begin == at && q.count > 0);
             at += q.count;
-            const int64_t wg = dense_workgroups(q.begin, at, m.chunk);
+            const int64_t wg = dense_workgroups(q.begin, at, m.chunk, kLine);
             CHECK(wg <= part.width);
             widest = std::max(widest, wg);
             if (q.flat0 < 0) {
@@ -99,10 +99,10 @@ static int check_call(const Model &m, int first, int count) {
             const int64_t l0 = m.e[(size_t)q.layer], l1 = m.e[(size_t)q.layer + 1];
             CHECK(q.begin >= l0 && at <= l1 && q.flat0 == m.st.layer_begin[(size_t)q.pos] + (q.begin - l0));
             // its workgroups follow each other in the layer's partials: the first one's place, and the last one's
-            CHECK(q.begin == l0 || q.begin % 4 == 0);
-            CHECK(q.pbase == m.st.update_ranges[2 * (size_t)q.pos] + (q.begin / 4 * 4 - l0 / 4 * 4) / m.chunk);
-            CHECK((q.begin / 4 * 4 - l0 / 4 * 4) % m.chunk == 0);
-            CHECK(at == l1 ? q.pbase + wg == m.st.update_ranges[2 * (size_t)q.pos + 1] : at % 4 == 0 && wg == (at - q.begin / 4 * 4) / m.chunk);
+            CHECK(q.begin == l0 || q.begin % kLine == 0);
+            CHECK(q.pbase == m.st.update_ranges[2 * (size_t)q.pos] + (q.begin / kLine * kLine - l0 / kLine * kLine) / m.chunk);
+            CHECK((q.begin / kLine * kLine - l0 / kLine * kLine) % m.chunk == 0);
+            CHECK(at == l1 ? q.pbase + wg == m.st.update_ranges[2 * (size_t)q.pos + 1] : at % kLine == 0 && wg == (at - q.begin / kLine * kLine) / m.chunk);
         }
         CHECK(at == part.end && widest == part.width);
     }
@@ -153,7 +153,7 @@ int main(int argc, char **argv) {
         const Model v = make({8, 1000, 1001, 4000, 6, 12}, {2, 4}, 2048);  // one launch; unscheduled ranges are plain updates
         CHECK(v.st.dense_passes.size() == 1);
         static DensePass part;
-        auto range = [&](int first, int last) { clip_pass(v.st.dense_passes[0], v.e[(size_t)first], v.e[(size_t)last], 2048, part); };
+        auto range = [&](int first, int last) { clip_pass(v.st.dense_passes[0], v.e[(size_t)first], v.e[(size_t)last], 2048, part, kLine); };
         range(0, 2);
         CHECK(part.width == 0);
         range(1, 2);
@@ -163,8 +163,6 @@ int main(int argc, char **argv) {
         range(0, 3);
         CHECK(part.width == 1 && part.n_pieces == 2 && part.pieces[1].flat0 == 0);
     }
-    // statistics folded into the launch: the line in pairs of partial sums, and the one in workgroups
-    CHECK(fold_stats(256, 128, 128) && !fold_stats(256, 129, 129) && fold_stats(256, 320, 128) && !fold_stats(256, 321, 1));
     // the number of launches, on both sides of each line; 0: the table's single one
     auto launches = [&](std::vector<int64_t> sizes) {
         std::vector<int> order;

@@ -29,6 +29,24 @@ int main() {
             for (int N = 1; N <= DDP_MAX_REPLICAS; ++N)
                 for (bool wire16 : {false, true}) CHECK(!mean_cut(256, 2048, n, layers, N, wire16) || mean_pairs(256, 2048, n, layers) == 2);
     CHECK(mean_pairs(256, 2048, 524288 - 32, 1) == 2 && mean_pairs(256, 2048, 524288 - 31, 1) == 1);
+    // statistics folded into the launch: 5/4 workgroups per CU with a pair, as many pairs in a layer as it has counters for
+    CHECK(folds(256, 1, 1) && folds(256, 320, 1) && folds(256, 320, 320) && !folds(256, 321, 1) && folds(304, 380, 320) && !folds(304, 321, 321));
+    // chunks of the average cut in two: 12 to 16 fp32 replicas over small slots; 17 to 31 over small and large ones, with a bf16 wire
+    // and from 32 replicas over all; none above 32
+    for (int N = 1; N <= DDP_MAX_REPLICAS; ++N) {
+        const bool few = N >= 12 && N <= 16, many = N >= 17 && N <= 32;
+        for (int64_t n : {1, 320, 321, 384, 385, 2047, 2048}) {
+            CHECK(mean_cut(256, 2048, n, 4, N, true) == (many ? 1024 : 0));
+            const bool line = few ? n <= 320 : many && (N == 32 || n <= 384 || n >= 2048);
+            CHECK(mean_cut(256, 2048, n, 4, N, false) == (line ? 1024 : 0));
+        }
+    }
+    CHECK(mean_cut(256, 4096, 1, 4, 16, false) == 2048);
+    // small models: 4.5 chunks of 2048 per CU, without a second moment more than 5/4; short AdamW updates: 7/4
+    const int64_t lo = 320 * 2048, hi = 1152 * 2048, sh = 448 * 2048;
+    CHECK(small_model(256, 1, true) && small_model(256, hi, true) && !small_model(256, hi + 1, true));
+    CHECK(!small_model(256, 1, false) && !small_model(256, lo, false) && small_model(256, lo + 1, false) && small_model(256, hi, false) && !small_model(256, hi + 1, false));
+    CHECK(short_update(256, 1, true) && short_update(256, sh, true) && !short_update(256, sh + 1, true) && !short_update(256, 1, false));
     std::printf("rules ok\n");
     return 0;
 }

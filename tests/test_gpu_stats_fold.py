@@ -1,4 +1,4 @@
-"""Statistics that the workgroups put together themselves (launches of about one workgroup per CU, half of which have a
+"""Statistics that the workgroups put together themselves (launches in which up to 5/4 workgroups per CU have a
 share) and those of a launch of their own, on both sides of the rule's lines: against the oracle, the same bits on every
 repetition, the same bits for the allocation-free entry point (which never folds), and through a captured graph that is
 replayed between eager calls."""
