@@ -315,7 +315,11 @@ __device__ __forceinline__ void sum_partials(const double *partials, int64_t c0,
 // agent scope: the workgroups of a layer run on several XCDs, each with an L2 of its own.  The pair is exchanged, not stored: the
 // old values come back from where all XCDs see the new ones, so once they have arrived the counter may be raised without the
 // release that would write the XCD's whole L2 back, and the last workgroup reads the pairs past its own L2 without an acquire
-// that would empty it (8 layers of 256^2, N = 4, us a call: fused step 6.9 -> 6.3, average 6.1 -> 5.3).
+// that would empty it (8 layers of 256^2, N = 4, us a call: fused step 6.9 -> 6.3, average 6.1 -> 5.3).  The language orders none of
+// this, every access is relaxed; gfx950 does: an agent-scope atomic that has returned was performed where the agent-scope accesses
+// of all XCDs meet, the wave waits for the returned values (s_waitcnt, which the empty asm that uses them forces) before it issues
+// the counter's atomic, each further atomic depends on the value of the one before, and the loads, of agent scope too, are issued
+// behind the barrier that follows the last.  Any other target needs release and acquire at the counters.
 __device__ __forceinline__ void put_partial(const StatsLaunch &st, int64_t partial, int pos, int layer, int n_replicas, double g, double m,
                                             double (*lds)[kThreads / kWave]) {
     if (st.counters == nullptr) {
