@@ -19,7 +19,8 @@
  *   - The four per-iteration calls only enqueue kernels on the caller's stream (a hipStream_t passed as
  *     void*, NULL = the default stream).  They never allocate, free, copy to the host or synchronise.
  *   - A context holds nothing of the training state: only tables derived from the registration and the schedule, and a
- *     reduction scratch that every call writes before it reads (and a counter per layer that is zero between calls).  Parameters, optimizer state, model copy and the step
+ *     reduction scratch that every call writes before it reads (and 21 counters per layer, 2.7 KB, each in a cache line of its
+ *     own, that are zero between calls).  Parameters, optimizer state, model copy and the step
  *     counter (ddp_opt.step) are the caller's: a checkpoint is those tensors plus the iteration number, and a new
  *     context registered over the restored tensors continues with the bits of the uninterrupted run.
  *   - A context is not thread-safe; calls that share a context or device buffers must be ordered by the caller
@@ -237,7 +238,8 @@ int ddp_local_update(ddp_ctx *ctx, const ddp_opt *opt, void *stream);
  * ddp_unpack -> ddp_local_update with the same arguments (the statistics agree to fp64 rounding: their partial sums are
  * grouped differently), but the local flat buffer is never written or read: HBM traffic is 4(N-1) bytes per scheduled element
  * plus the update's bytes per parameter.  peers, N, local_rank, layer_stats as in ddp_partial_average; opt as in
- * ddp_local_update.  No flat_local / flat_out: the result lives in the model tensors only. */
+ * ddp_local_update.  No flat_local / flat_out: the result lives in the model tensors only.  Over separately allocated tensors
+ * the statistics' grouping, and so their last bits, depends on where in a 256-byte line each of them starts. */
 int ddp_fused_sync_update(ddp_ctx *ctx, int slot, const float *const *peers, int N, int local_rank, double *layer_stats,
                           const ddp_opt *opt, void *stream);
 
