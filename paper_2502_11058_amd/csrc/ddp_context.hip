@@ -834,7 +834,7 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     const int nl = (int)st->layers.size();
     auto inside = [&](int i) { return i < nl && st->layers[(size_t)i] >= first && st->layers[(size_t)i] < first + count; };
     int64_t scheduled = 0, most = 0;  // chunks of the slot's layers in the range, each of which has a pair of partial sums
-    for (int i = 0; (layer_stats || wire16) && i < nl; ++i)
+    for (int i = 0; (layer_stats || (wire16 && N > 8)) && i < nl; ++i)
         if (inside(i)) {
             const int64_t n = st->update_ranges[2 * (size_t)i + 1] - st->update_ranges[2 * (size_t)i];
             scheduled += n;

@@ -52,6 +52,8 @@ struct TensorDesc {   // one registered tensor
 // dense arenas from the arenas' first element): a cache line of any stream, 128 bytes of 16-bit elements too, then belongs to one
 // chunk.  Lines that two workgroups shared were read twice and written in parts, by two XCDs' L2s: 16 layers of 1533^2, AdamW
 // with bf16 gradients and copy, N = 8, fused: 226 us with chunks that end at multiples of four elements, 218 so; average of N = 16 over layers of 3001^2: 207 and 200.
+// Where flat element 0 meets a layer that starts inside a line, the peers' lines are shared instead, most of the bytes from about 24
+// replicas on: 4 layers of 1448^2, layer by layer, fp32, N = 4 69.3 and 65.3, N = 32 84.0 and 86.3.
 constexpr int kLine = 64;
 
 struct UpdateChunk {  // local_update: elements [begin, begin+count) of run `run` (a tensor; over dense arenas a whole layer)
