@@ -385,21 +385,23 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
                 }
             };
             std::vector<int32_t> lcp;
-            std::vector<RunSlot> run_slot(ctx->run_chunk_base.size() - 1, RunSlot{-1, -1, -1});
+            std::vector<RunSlot> run_slot(ctx->run_chunk_base.size() - 1, RunSlot{-1, -1, {-1, 0, 0}});
             int64_t off = 0;
             for (int j = set_ptr[s]; j < set_ptr[s + 1]; ++j) {
                 const int l = set_layers[j];
                 st.layers.push_back(l);
                 st.layer_begin.push_back(off);
                 lcp.push_back((int32_t)mc.size());
-                st.update_ranges.push_back(ctx->run_chunk_base[(size_t)ctx->layer_first_run[(size_t)l]]);
-                st.update_ranges.push_back(ctx->run_chunk_base[(size_t)ctx->layer_first_run[(size_t)l + 1]]);
+                const int32_t c0 = ctx->run_chunk_base[(size_t)ctx->layer_first_run[(size_t)l]];
+                const int32_t c1 = ctx->run_chunk_base[(size_t)ctx->layer_first_run[(size_t)l + 1]];
+                st.update_ranges.push_back(c0);
+                st.update_ranges.push_back(c1);
                 st.layer_pos[(size_t)l] = (int32_t)st.layers.size() - 1;
                 const int64_t layer_start = off;
                 for (int t = ctx->layer_first_tensor[(size_t)l]; t < ctx->layer_first_tensor[(size_t)l + 1]; ++t) {
                     st.tensors.push_back(t);
                     st.tensor_off.push_back(off);
-                    if (!ctx->dense || off == layer_start) run_slot[(size_t)(ctx->dense ? l : t)] = {off, st.layer_pos[(size_t)l], l};
+                    if (!ctx->dense || off == layer_start) run_slot[(size_t)(ctx->dense ? l : t)] = {off, l, {st.layer_pos[(size_t)l], c0, c1 - c0}};
                     off += ctx->numel[(size_t)t];
                 }
                 // copy chunks: the layer's runs (over dense arenas the layer is one) cut on the lines of what is written
@@ -416,9 +418,10 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
                 int64_t b = layer_start;
                 for (int64_t c = 1; b < off; ++c) {
                     const int64_t e = c >= n ? off : std::min<int64_t>(off, layer_start / kLine * kLine + c * ctx->mean_chunk);
-                    mc.push_back({b, (int32_t)(e - b), (int32_t)mc.size()});
+                    mc.push_back({b, (int32_t)(e - b), (int32_t)mc.size(), {j - set_ptr[s], lcp.back(), 0}});
                     b = e;
                 }
+                for (size_t c = (size_t)lcp.back(); c < mc.size(); ++c) mc[c].of.n = (int32_t)mc.size() - lcp.back();
             }
             for (size_t j = 0; !one_table && j < st.layers.size(); ++j)
                 for (int r = ctx->layer_first_run[(size_t)st.layers[j]]; r < ctx->layer_first_run[(size_t)st.layers[j] + 1]; ++r)
@@ -449,8 +452,6 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
             }
             for (size_t i = 0; i + 1 < st.update_ranges.size(); i += 2)
                 st.max_update_partials = std::max<int64_t>(st.max_update_partials, st.update_ranges[i + 1] - st.update_ranges[i]);
-            if (folds(ctx->cus, st.n_mean, st.max_mean_partials))
-                for (size_t i = 0; i + 1 < lcp.size(); ++i) mean_ranges.insert(mean_ranges.end(), (size_t)(lcp[i + 1] - lcp[i]), (int32_t)i);
             if (rc == DDP_OK) rc = upload(ctx, mean_ranges, &st.d_layer_ranges);
             if (rc == DDP_OK) rc = upload(ctx, run_slot, &st.d_run_slot);
             if (rc == DDP_OK) rc = upload(ctx, st.update_ranges, &st.d_update_ranges);
@@ -625,11 +626,8 @@ int ddp::partial_average_impl(ddp_ctx *ctx, const char *who, bool wire16, int sl
     a.chunks = s->d_mean;
     a.n_chunks = s->n_mean;
     a.cut = cut;
-    // (a slot whose chunks would not be folded uncut has no positions of them)
-    const bool fold = layer_stats && !scratch && folds(ctx->cus, s->n_mean, s->max_mean_partials) &&
-                      folds(ctx->cus, pairs * s->n_mean, pairs * s->max_mean_partials);
-    a.st = {layer_stats ? partials : nullptr, s->d_layer_ranges, layer_stats, fold ? ctx->d_counters : nullptr, pairs};
-    a.chunk_pos = s->d_layer_ranges + 2 * s->layers.size();
+    const bool fold = layer_stats && !scratch && folds(ctx->cus, pairs * s->n_mean, pairs * s->max_mean_partials);
+    a.st = {layer_stats ? partials : nullptr, layer_stats, fold ? ctx->d_counters : nullptr};
     a.nontemporal = ctx->nontemporal;
     // Two workgroups per CU pace the requests of many replicas best, but few replicas leave too little in flight (TinyLlama-1.1B,
     // us with 2 / 3 / 4 per CU: N = 2 662 / 539 / 502, N = 4 964 / 837 / 895, N = 6 1207 / 1256 / 1280; GPT-2 small N = 2
@@ -855,7 +853,7 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     f.with_model = ctx->param_dtype == DDP_BF16;
     f.s = s;
     f.lds_pad = update_lds(ctx);
-    f.st = {any ? ctx->d_partials : nullptr, st->d_update_ranges, layer_stats, fold ? ctx->d_counters : nullptr, 1};
+    f.st = {any ? ctx->d_partials : nullptr, layer_stats, fold ? ctx->d_counters : nullptr};
     const int64_t e0 = layer_elem0(ctx, first), e1 = layer_elem0(ctx, first + count);
     const auto at = first_pass(*st, e0);
     if (ctx->dense_path && takes_pieces(*st, at, e1)) {

@@ -240,10 +240,36 @@ __device__ __forceinline__ int head_to_16B(const void *p, int n) {  // fp32 elem
     return h < n ? h : n;
 }
 
+// Sum of a double over the wavefront, valid in lane 0: lane i and lane i + 32, then 16, 8, 4, 2, 1, the order of a shuffle-down tree.
+// The halves come by lane swaps and row shifts of the vector unit; through the LDS crossbar (ds_bpermute, __shfl_down) each of the
+// six steps waits some 100 cycles, and a short kernel waits for the whole chain, twice where its workgroups put the layers'
+// sums together.  With that, the layer's range in the chunk's record and one wavefront behind the counters, us a call: fused step, 8
+// layers of 256^2, N = 4 6.44 -> 5.95, 13 of 172^2, AdamW 6.97 -> 6.44; average, 9 layers of 145^2, N = 32 8.29 -> 7.62.
+template <int CTRL>
+__device__ __forceinline__ double row_shifted(double v) {
+    const u32x2 w = __builtin_bit_cast(u32x2, v);
+    return __builtin_bit_cast(double, u32x2{(unsigned)__builtin_amdgcn_update_dpp(0, (int)w.x, CTRL, 0xf, 0xf, true),
+                                            (unsigned)__builtin_amdgcn_update_dpp(0, (int)w.y, CTRL, 0xf, 0xf, true)});
+}
+__device__ __forceinline__ double wave_sum(double v) {
+    u32x2 w = __builtin_bit_cast(u32x2, v);
+    auto lo = __builtin_amdgcn_permlane32_swap(w.x, w.x, false, false), hi = __builtin_amdgcn_permlane32_swap(w.y, w.y, false, false);
+    v = __builtin_bit_cast(double, u32x2{lo[0], hi[0]}) + __builtin_bit_cast(double, u32x2{lo[1], hi[1]});
+    w = __builtin_bit_cast(u32x2, v);
+    lo = __builtin_amdgcn_permlane16_swap(w.x, w.x, false, false);
+    hi = __builtin_amdgcn_permlane16_swap(w.y, w.y, false, false);
+    v = __builtin_bit_cast(double, u32x2{lo[0], hi[0]}) + __builtin_bit_cast(double, u32x2{lo[1], hi[1]});
+    constexpr int kRowShl = 0x100;  // lane i takes lane i + n of its row of 16
+    v += row_shifted<kRowShl + 8>(v);
+    v += row_shifted<kRowShl + 4>(v);
+    v += row_shifted<kRowShl + 2>(v);
+    v += row_shifted<kRowShl + 1>(v);
+    return v;
+}
+
 // Sum of a double over the workgroup, in the order of block_sum2.  Result valid in thread 0.
 __device__ __forceinline__ double block_sum(double v, double *lds) {
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_down(v, off, kWave);
+    v = wave_sum(v);
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     if (lane == 0) lds[wave] = v;
     __syncthreads();
@@ -256,16 +282,11 @@ __device__ __forceinline__ double block_sum(double v, double *lds) {
     return r;
 }
 
-// Sums of two doubles over the workgroup in a fixed order: butterfly-free shuffle-down tree inside each wavefront, then the
-// four wavefront sums added in wavefront order by thread 0.  Results valid in thread 0.  Both trees side by side, one barrier:
-// the chain of shuffles is what a short kernel waits for.
+// Sums of two doubles over the workgroup in a fixed order: a tree inside each wavefront (wave_sum), then the four wavefront sums
+// added in wavefront order by thread 0.  Results valid in thread 0.  Both trees side by side, one barrier.
 __device__ __forceinline__ void block_sum2(double &g, double &m, double (*lds)[kThreads / kWave]) {
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-        const double x = __shfl_down(g, off, kWave), y = __shfl_down(m, off, kWave);
-        g += x;
-        m += y;
-    }
+    g = wave_sum(g);
+    m = wave_sum(m);
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     if (lane == 0) {
         lds[0][wave] = g;
@@ -282,29 +303,58 @@ __device__ __forceinline__ void block_sum2(double &g, double &m, double (*lds)[k
     }
 }
 
-// The sums of a layer from its partials, in a fixed order: thread-strided, then the workgroup tree.  Eight pairs in flight
-// per thread: the loop is bound by latency (3456 partials: 4.4 us one pair at a time, 3.2 us so).
+// The sums of a layer from its partials, in a fixed order: thread-strided, then the workgroup tree.  Sixteen pairs in flight per
+// thread, all that a layer summed in one launch has: the loop is bound by latency.
 __device__ __forceinline__ void sum_partials(const double *partials, int64_t c0, int64_t c1, int n_replicas, double *stats, double (*lds)[kThreads / kWave]) {
     double g = 0.0, m = 0.0;
-    constexpr int U = 8;  // pairs in flight per thread
+    typedef double f64x2 __attribute__((ext_vector_type(2)));
+    constexpr int U = (int)(kStatSingleMax / kThreads);  // pairs in flight per thread
     for (int64_t c = c0 + (int64_t)threadIdx.x; c < c1; c += U * kThreads) {
-        double x[U], y[U];
+        f64x2 x[U];
 #pragma unroll
         for (int j = 0; j < U; ++j) {
-            x[j] = y[j] = 0.0;
-            if (c + j * kThreads < c1) {
-                x[j] = __hip_atomic_load(partials + 2 * (c + j * kThreads), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                y[j] = __hip_atomic_load(partials + 2 * (c + j * kThreads) + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+            x[j] = f64x2{};
+            if (c + j * kThreads < c1) x[j] = reinterpret_cast<const f64x2 *>(partials)[c + j * kThreads];
         }
 #pragma unroll
         for (int j = 0; j < U; ++j) {  // (both sums are of squares: adding zero changes nothing)
-            g += x[j];
-            m += y[j];
+            g += x[j].x;
+            m += x[j].y;
         }
     }
     block_sum2(g, m, lds);
     if (threadIdx.x == 0) {
+        stats[0] = g / (double)n_replicas;
+        stats[1] = m;
+    }
+}
+
+// The same sums, of up to kFoldGroup * kFoldGroups partials and in the same order, by one wavefront: its lane stands for the
+// threads lane, lane + 64, lane + 128 and lane + 192 of sum_partials, whose trees have no barrier between them here.
+__device__ __forceinline__ void sum_partials_wave(const double *partials, int n, int n_replicas, double *stats) {
+    constexpr int kWaves = kThreads / kWave;
+    static_assert(kFoldGroup * kFoldGroups <= kThreads + kWave, "one more partial per lane than sum_partials' threads have");
+    const int lane = (int)threadIdx.x;
+    double x[kWaves + 1], y[kWaves + 1];
+#pragma unroll
+    for (int w = 0; w <= kWaves; ++w) {
+        const int c = w * kWave + lane;
+        x[w] = y[w] = 0.0;
+        if (c < n) {
+            x[w] = __hip_atomic_load(partials + 2 * c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            y[w] = __hip_atomic_load(partials + 2 * c + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    x[0] += x[kWaves];
+    y[0] += y[kWaves];
+    double g = 0.0, m = 0.0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w)
+        if (w * kWave < n) {
+            g += wave_sum(x[w]);
+            m += wave_sum(y[w]);
+        }
+    if (lane == 0) {
         stats[0] = g / (double)n_replicas;
         stats[1] = m;
     }
@@ -319,9 +369,12 @@ __device__ __forceinline__ void sum_partials(const double *partials, int64_t c0,
 // this, every access is relaxed; gfx950 does: an agent-scope atomic that has returned was performed where the agent-scope accesses
 // of all XCDs meet, the wave waits for the returned values (s_waitcnt, which the empty asm that uses them forces) before it issues
 // the counter's atomic, each further atomic depends on the value of the one before, and the loads, of agent scope too, are issued
-// behind the barrier that follows the last.  Any other target needs release and acquire at the counters.
-__device__ __forceinline__ void put_partial(const StatsLaunch &st, int64_t partial, int pos, int layer, int n_replicas, double g, double m,
-                                            double (*lds)[kThreads / kWave]) {
+// behind the branch on the last one's value.  Any other target needs release and acquire at the counters.
+// All of it is the first wavefront's, which has the pair: no barrier behind the counters, and the others are done.  PAIRS: partial
+// pairs per chunk.
+template <int PAIRS>
+__device__ __forceinline__ void put_partial(const StatsLaunch &st, int64_t partial, const LayerSums &of, int layer, int n_replicas, double g, double m) {
+    if (threadIdx.x >= kWave) return;
     if (st.counters == nullptr) {
         if (threadIdx.x == 0) {
             st.partials[2 * partial] = g;
@@ -329,8 +382,9 @@ __device__ __forceinline__ void put_partial(const StatsLaunch &st, int64_t parti
         }
         return;
     }
-    __shared__ int is_last;
-    const int64_t c0 = (int64_t)st.pairs * st.layer_ranges[2 * pos], c1 = (int64_t)st.pairs * st.layer_ranges[2 * pos + 1];
+    const int n = PAIRS * of.n;
+    const int64_t c0 = (int64_t)PAIRS * of.first;
+    int is_last = 0;
     if (threadIdx.x == 0) {
         const double was_g = __hip_atomic_exchange(st.partials + 2 * partial, g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const double was_m = __hip_atomic_exchange(st.partials + 2 * partial + 1, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -341,13 +395,14 @@ __device__ __forceinline__ void put_partial(const StatsLaunch &st, int64_t parti
             if (yes) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
             return yes;
         };
-        const int n = (int)(c1 - c0), group = (int)(partial - c0) / kFoldGroup, groups = (n + kFoldGroup - 1) / kFoldGroup;
+        const int group = (int)(partial - c0) / kFoldGroup, groups = (n + kFoldGroup - 1) / kFoldGroup;
         const int left = n - group * kFoldGroup, members = left < kFoldGroup ? left : kFoldGroup;
         is_last = last(of_layer + (1 + group) * kFoldLine, members) && (groups == 1 || last(of_layer, groups));
     }
-    __syncthreads();
+    is_last = __builtin_amdgcn_readfirstlane(is_last);
+    asm volatile("" ::: "memory");  // (the loads stay behind the branch)
     if (!is_last) return;
-    sum_partials(st.partials, c0, c1, n_replicas, st.stats + 2 * pos, lds);
+    sum_partials_wave(st.partials + 2 * c0, n, n_replicas, st.stats + 2 * of.pos);
 }
 
 // ---------------------------------------------------------------------------------------------------------------

@@ -71,16 +71,24 @@ struct CopyChunk {
     int32_t count;
 };
 
-struct MeanChunk {  // partial_average: flat elements [begin, +count), all inside one layer of the slot
+// A layer of the slot as its statistics are put together: `n` chunks from `first` on, each with its partial sums.  Every chunk's
+// record has it, so that a workgroup has it at hand with its first load and not, behind its last store, from a table of its own.
+struct LayerSums {
+    int32_t pos;  // position of the layer in the slot
+    int32_t first, n;
+};
+
+struct alignas(32) MeanChunk {  // partial_average: flat elements [begin, +count), all inside one layer of the slot
     int64_t begin;
     int32_t count;
     int32_t partial;  // where this chunk's partial sums go: its index in flat order, whatever the dispatch order
+    LayerSums of;
 };
 
-struct RunSlot {    // a run of the update table in one slot
-    int64_t flat0;  // first flat index, -1 if it is not scheduled
-    int32_t pos;     // position of its layer in the slot
+struct alignas(32) RunSlot {  // a run of the update table in one slot
+    int64_t flat0;            // first flat index, -1 if it is not scheduled
     int32_t layer;
+    LayerSums of;  // chunks of the update table
 };
 
 // One launch of the fused step over dense arenas: consecutive pieces of the model, each part of a scheduled layer or of a run
@@ -93,6 +101,7 @@ struct Piece {
     int32_t count;  // elements
     int32_t pbase;
     int32_t pos, layer;  // position of the layer in the slot, and the layer
+    int32_t first, n;    // LayerSums, in chunks of the update table
 };
 struct DensePass {
     int width;          // chunks of the widest piece; 0: a plain update of elements [begin, end)
@@ -115,8 +124,7 @@ struct SlotTables {
     int64_t n_pack = 0, n_unpack = 0;
     MeanChunk *d_mean = nullptr;
     int64_t n_mean = 0;
-    int32_t *d_layer_ranges = nullptr;     // per layer of the slot: [first, last) mean chunk; behind them, in a slot whose
-                                           // statistics are folded (folds), the layer position of every mean chunk
+    int32_t *d_layer_ranges = nullptr;     // per layer of the slot: [first, last) mean chunk
     RunSlot *d_run_slot = nullptr;         // per run of the update table
     std::vector<int32_t> update_ranges;    // per layer of the slot: [first, last) update chunk (registration order), whose places
     int32_t *d_update_ranges = nullptr;    // the partials of the fused step have, table-driven or table-free
@@ -133,12 +141,10 @@ constexpr int kFoldGroup = 16, kFoldGroups = 20, kFoldLine = 32, kFoldStride = (
 
 // How the per-layer statistics of a launch are put together from its workgroups' partial pairs.
 struct StatsLaunch {
-    double *partials;             // nullptr: no statistics
-    const int32_t *layer_ranges;  // per position in the slot [first, last) chunk, in chunks of `pairs` partial pairs each
-    double *stats;                // [positions][2]
-    int32_t *counters;            // kFoldStride per layer, zero between launches: the layer's last workgroup adds the partials up
-                                  // in the kernel itself; nullptr: a launch of its own follows (launch_stats)
-    int pairs;
+    double *partials;   // nullptr: no statistics
+    double *stats;      // [positions][2]
+    int32_t *counters;  // kFoldStride per layer, zero between launches: the layer's last workgroup adds the partials up
+                        // in the kernel itself; nullptr: a launch of its own follows (launch_stats)
 };
 
 // ---- launchers (ddp_kernels_*.hip) -------------------------------------------------------------------------------
@@ -152,8 +158,7 @@ struct MeanLaunch {
     const MeanChunk *chunks;
     int64_t n_chunks;
     int cut;                   // elements after which a chunk is cut in two, a workgroup each; 0: not cut
-    StatsLaunch st;            // st.pairs: 2 where chunks are cut
-    const int32_t *chunk_pos;  // with st.counters: per chunk, by its partial index, the position of its layer
+    StatsLaunch st;            // two partial pairs per chunk where chunks are cut
     bool nontemporal;
     int lds_pad;
 };

@@ -41,7 +41,7 @@ __global__ __launch_bounds__(kThreads, 2) void fused_kernel(const FusedArgs a) {
     if constexpr (STATS) {
         block_sum2(gsum, msum, lds);
         // chunks end on cache lines: chunk c of a run begins less than kLine elements before c * chunk_elems
-        put_partial(a.st, (int64_t)a.run_chunk_base[ch.run] + (ch.begin + kLine - 1) / a.chunk_elems, ts.pos, ts.layer, a.peers.n, gsum, msum, lds);
+        put_partial<1>(a.st, (int64_t)a.run_chunk_base[ch.run] + (ch.begin + kLine - 1) / a.chunk_elems, ts.of, ts.layer, a.peers.n, gsum, msum);
     }
 }
 

@@ -48,7 +48,7 @@ __global__ __launch_bounds__(kThreads, 2) void fused_dense_kernel(const FusedDen
     fused_body<ADAM, GBF16, MODEL, NREP, EXACT, STATS, W16, UTS, PAIRS, true>(c, t.flat0 + at, a.peers, a.s, gsum, msum);
     if constexpr (STATS) {
         block_sum2(gsum, msum, lds);
-        put_partial(a.st, (int64_t)t.pbase + blockIdx.x, t.pos, t.layer, a.peers.n, gsum, msum, lds);
+        put_partial<1>(a.st, (int64_t)t.pbase + blockIdx.x, LayerSums{t.pos, t.first, t.n}, t.layer, a.peers.n, gsum, msum);
     }
 }
 

@@ -11,7 +11,6 @@ struct MeanArgs {
     float *out;
     const MeanChunk *chunks;
     StatsLaunch st;
-    const int32_t *chunk_pos;
     float inv_n;
     int n;
     int cut;            // MeanLaunch
@@ -29,13 +28,14 @@ __global__ __launch_bounds__(kThreads) void mean_kernel(const MeanArgs a) {
     __shared__ double lds[2][kThreads / kWave];
     // CUT: two workgroups a chunk (mean_cut).  A kernel of its own: what the others spent on it before their first load was 0.3 %.
     MeanChunk ch = a.chunks[CUT ? blockIdx.x >> 1 : blockIdx.x];
-    const int entry = ch.partial;
     if constexpr (CUT) {
         const int half = (int)blockIdx.x & 1, first = a.cut - ((int)ch.begin & (kLine - 1)), at = first < ch.count ? first : ch.count;
         ch.begin += half ? at : 0;
         ch.count = half ? ch.count - at : at;
-        ch.partial = 2 * entry + half;
+        ch.partial = 2 * ch.partial + half;
     }
+    // (in a vector register until the end: the kernels with conditions have no scalar one to spare)
+    if constexpr (STATS && !EXACT && NREP > 0) asm("" : "+v"(ch.of.n));
     const int n = ch.count;
     const int tid = threadIdx.x;
     const int nrep = EXACT ? NREP : a.n;
@@ -175,8 +175,8 @@ __global__ __launch_bounds__(kThreads) void mean_kernel(const MeanArgs a) {
         } else {
             block_sum2(gsum, msum, lds);
         }
-        const int pos = a.st.counters ? a.chunk_pos[entry] : 0;
-        put_partial(a.st, ch.partial, pos, pos, nrep, gsum, msum, lds);
+        if constexpr (!EXACT && NREP > 0) ch.of.n = __builtin_amdgcn_readfirstlane(ch.of.n);
+        put_partial<CUT ? 2 : 1>(a.st, ch.partial, ch.of, ch.of.pos, nrep, gsum, msum);
     }
 }
 
@@ -279,7 +279,6 @@ int launch_mean(const MeanLaunch &a, void *stream) {
     ma.out = a.out;
     ma.chunks = a.chunks;
     ma.st = a.st;
-    ma.chunk_pos = a.chunk_pos;
     ma.inv_n = a.inv_n;
     ma.n = a.n_replicas;
     ma.cut = a.cut;

@@ -101,12 +101,12 @@ inline int64_t widest_piece(int64_t chunk) { return INT32_MAX / chunk - 1; }
 
 // Elements [begin, end), all of one scheduled layer (flat0 >= 0) or all unscheduled, as pieces of at most `width` chunks behind
 // those that p has.
-inline void add_pieces(DensePass &p, int64_t begin, int64_t end, int64_t flat0, int64_t pbase, int32_t pos, int32_t layer, int64_t width,
+inline void add_pieces(DensePass &p, int64_t begin, int64_t end, int64_t flat0, int64_t pbase, int32_t layer, const LayerSums &of, int64_t width,
                        int64_t chunk, int64_t line) {
     const int64_t base = begin / line * line, wg = dense_workgroups(begin, end, chunk, line);
     for (int64_t b = 0; b < wg; b += width) {
         const int64_t at = b == 0 ? begin : base + b * chunk, to = std::min(end, base + (b + width) * chunk);
-        p.pieces[p.n_pieces++] = {at, flat0 < 0 ? -1 : flat0 + (at - begin), (int32_t)(to - at), (int32_t)(pbase + b), pos, layer};
+        p.pieces[p.n_pieces++] = {at, flat0 < 0 ? -1 : flat0 + (at - begin), (int32_t)(to - at), (int32_t)(pbase + b), of.pos, layer, of.first, of.n};
     }
 }
 
@@ -126,7 +126,8 @@ void plan_dense(SlotTables &st, int L, Elem0 &&elem0, int64_t chunk, int64_t lin
     constexpr int kMaxSegments = 20;
     struct Segment {
         int64_t begin, end, flat0, pbase, wg;
-        int32_t pos, layer;
+        int32_t layer;
+        LayerSums of;
     };
     std::vector<Segment> all;
     for (int l = 0; l < L;) {
@@ -134,7 +135,8 @@ void plan_dense(SlotTables &st, int L, Elem0 &&elem0, int64_t chunk, int64_t lin
         int m = l + 1;
         while (i < 0 && m < L && st.layer_pos[(size_t)m] < 0) ++m;
         all.push_back({elem0(l), elem0(m), i < 0 ? -1 : st.layer_begin[(size_t)i], i < 0 ? 0 : st.update_ranges[2 * (size_t)i],
-                       dense_workgroups(elem0(l), elem0(m), chunk, line), i, l});
+                       dense_workgroups(elem0(l), elem0(m), chunk, line), l, {i, 0, 0}});
+        if (i >= 0) all.back().of = {i, st.update_ranges[2 * (size_t)i], st.update_ranges[2 * (size_t)i + 1] - st.update_ranges[2 * (size_t)i]};
         l = m;
     }
     std::vector<DensePass> &passes = st.dense_passes;
@@ -180,7 +182,7 @@ void plan_dense(SlotTables &st, int L, Elem0 &&elem0, int64_t chunk, int64_t lin
             }
         p.width = (int)width;
         for (int k = 0; k < n; ++k)
-            add_pieces(p, seg[k].begin, seg[k].end, seg[k].flat0, seg[k].pbase, seg[k].pos, seg[k].layer, width, chunk, line);
+            add_pieces(p, seg[k].begin, seg[k].end, seg[k].flat0, seg[k].pbase, seg[k].layer, seg[k].of, width, chunk, line);
     }
 }
 
@@ -207,7 +209,7 @@ inline void clip_pass(const DensePass &p, int64_t e0, int64_t e1, int64_t chunk,
         // (no more pieces than the whole run would have, which plan_dense has counted)
         const int64_t wg = dense_workgroups(part.begin, part.end, chunk, line);
         part.width = (int)std::min(wg, widest_piece(chunk));
-        add_pieces(part, part.begin, part.end, -1, 0, -1, -1, part.width, chunk, line);
+        add_pieces(part, part.begin, part.end, -1, 0, -1, {-1, 0, 0}, part.width, chunk, line);
         return;
     }
     bool scheduled = false;
