@@ -126,8 +126,20 @@ static int residency_pad(const ddp_ctx *c, int wg_per_cu) {
     return pad > 0 ? pad : 0;
 }
 
-// The residency request of the update and the fused step.
+// The residency request of the update, and of the fused step (fused_wg_per_cu).
 static int update_lds(const ddp_ctx *c) { return c->small && !c->update_lds_set ? 0 : c->update_lds; }
+static int fused_lds(const ddp_ctx *c, int N, bool wire16, bool adamw, int64_t elements) {
+    if (!c->halved || c->update_lds_set) return update_lds(c);
+    return residency_pad(c, fused_wg_per_cu(N, wire16, adamw, c->grad_dtype == DDP_BF16, elements));
+}
+
+// Elements per workgroup of the fused step.
+static int64_t fused_chunk(const ddp_ctx *c) { return c->halved ? c->run_chunk / 2 : c->run_chunk; }
+
+// Chunks that a workgroup of the fused step takes of unscheduled layers, at its three or four workgroups per CU: with SGD, a third less
+// bytes an element, two (us, two against one: GPT-2, 5 blocks of 384, N = 6 bf16 47.0 / 49.9, 12 layers of 817^2, N = 3 32.5 / 33.2); with AdamW that would
+// be too much in flight (14 layers of 1490^2, N = 6 157.4 / 148.9, 16 of 1533^2, N = 8 220.1 / 212.3).
+static int64_t plain_chunks(const ddp_ctx *c) { return c->halved && !c->has_state1 ? 2 : 1; }
 
 // First element of layer l in registration order (l = L: the number of elements).
 static int64_t layer_elem0(const ddp_ctx *ctx, int l) { return ctx->tensor_elem_off[(size_t)ctx->layer_first_tensor[(size_t)l]]; }
@@ -263,6 +275,7 @@ extern "C" int ddp_register_model(ddp_ctx *ctx, int L, int T, const int32_t *lay
             d.state0 = (float *)state0_ptr[t];
             d.state1 = state1_ptr ? (float *)state1_ptr[t] : nullptr;
             d.numel = numel[t];
+            d.past = 0;
             first[(size_t)layer_of[t] + 1] = t + 1;
         }
         if (layer_of[T - 1] != L - 1) return fail(ctx, DDP_EINVAL, "ddp_register_model: layer_of does not reach L-1");
@@ -296,6 +309,9 @@ extern "C" int ddp_register_model(ddp_ctx *ctx, int L, int T, const int32_t *lay
                     (param_dtype != DDP_BF16 || b.model == a.model + a.numel);
         }
         ctx->dense = dense;
+        int64_t largest = 0;
+        for (int l = 0; l < L; ++l) largest = std::max(largest, layer_elem0(ctx, l + 1) - layer_elem0(ctx, l));
+        ctx->halved = !ctx->update_chunk_set && ctx->run_chunk == 2 * kSmallChunk && takes_halves(ctx->tensor_elem_off[(size_t)T], largest, dense, has1);
 
         // Update table: every run cut into chunks of run_chunk elements that end on cache lines (kLine), so that only a run's
         // first and last chunk have elements outside a whole vector.  A run is a tensor; over dense arenas it is a whole layer,
@@ -317,6 +333,7 @@ extern "C" int ddp_register_model(ddp_ctx *ctx, int L, int T, const int32_t *lay
             ctx->run_chunk_base.push_back((int32_t)uc.size());
             // elements past such a boundary
             const int64_t past = dense ? (runs[t].sync - ts[0].sync) % kLine : (int64_t)((reinterpret_cast<uintptr_t>(runs[t].sync) >> 2) % kLine);
+            runs[t].past = (int32_t)past;
             for (int64_t b = 0, e; b < runs[t].numel; b = e) {
                 e = std::min<int64_t>(runs[t].numel, (b + past) / ctx->run_chunk * ctx->run_chunk + ctx->run_chunk - past);
                 uc.push_back({b, (int32_t)t, (int32_t)(e - b)});
@@ -392,8 +409,11 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
                 st.layers.push_back(l);
                 st.layer_begin.push_back(off);
                 lcp.push_back((int32_t)mc.size());
-                const int32_t c0 = ctx->run_chunk_base[(size_t)ctx->layer_first_run[(size_t)l]];
-                const int32_t c1 = ctx->run_chunk_base[(size_t)ctx->layer_first_run[(size_t)l + 1]];
+                // the layer's partials in the fused step: two per chunk of the update table where that is halved, but not for what
+                // lies behind a dense layer's last half
+                const int32_t k = ctx->halved ? 2 : 1, c0 = k * ctx->run_chunk_base[(size_t)ctx->layer_first_run[(size_t)l]];
+                const int32_t c1 = ctx->dense ? c0 + (int32_t)dense_workgroups(layer_elem0(ctx, l), layer_elem0(ctx, l + 1), fused_chunk(ctx), kLine)
+                                              : k * ctx->run_chunk_base[(size_t)ctx->layer_first_run[(size_t)l + 1]];
                 st.update_ranges.push_back(c0);
                 st.update_ranges.push_back(c1);
                 st.layer_pos[(size_t)l] = (int32_t)st.layers.size() - 1;
@@ -455,13 +475,13 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
             if (rc == DDP_OK) rc = upload(ctx, mean_ranges, &st.d_layer_ranges);
             if (rc == DDP_OK) rc = upload(ctx, run_slot, &st.d_run_slot);
             if (rc == DDP_OK) rc = upload(ctx, st.update_ranges, &st.d_update_ranges);
-            if (ctx->dense) plan_dense(st, ctx->L, [&](int l) { return layer_elem0(ctx, l); }, ctx->run_chunk, kLine);
+            if (ctx->dense) plan_dense(st, ctx->L, [&](int l) { return layer_elem0(ctx, l); }, fused_chunk(ctx), kLine, plain_chunks(ctx));
             if (rc != DDP_OK) {
                 for (auto &x : slots) free_slot(x);
                 return rc;
             }
         }
-        const int64_t max_pairs = std::max(max_mean_pairs, ctx->n_update);  // the fused step keeps one per update chunk
+        const int64_t max_pairs = std::max(max_mean_pairs, (ctx->halved ? 2 : 1) * ctx->n_update);  // the fused step keeps one per workgroup
         if (max_pairs > 0) {
             const size_t line = kFoldLine * sizeof(int32_t) / sizeof(double);  // the counters start on a cache line
             const size_t sums = (((size_t)max_pairs + (size_t)ctx->L * kStatSlices) * 2 + line - 1) / line * line;
@@ -774,13 +794,14 @@ static int fused_dense(const ddp_ctx *ctx, const SlotTables &st, std::vector<Den
     FusedDense f;
     static_cast<FusedLaunch &>(f) = common;
     const TensorDesc &t0 = ctx->tensors[0];
-    f.d = {t0.grad, t0.sync, t0.state0, t0.state1, t0.model, 0, (int)ctx->run_chunk, 0};
+    f.d = {t0.grad, t0.sync, t0.state0, t0.state1, t0.model, 0, (int)fused_chunk(ctx), 0};
+    f.plain = (int)(plain_chunks(ctx) * fused_chunk(ctx));
     int rc = 0;
     for (; at != st.dense_passes.end() && at->begin < e1 && rc == 0; ++at) {
         DensePass part;
         f.pass = &*at;
         if (at->begin < e0 || at->end > e1) {
-            clip_pass(*at, e0, e1, ctx->run_chunk, part, kLine);
+            clip_pass(*at, e0, e1, fused_chunk(ctx), part, kLine, plain_chunks(ctx));
             f.pass = &part;
         }
         if (f.pass->width > 0) {
@@ -796,6 +817,7 @@ static int fused_dense(const ddp_ctx *ctx, const SlotTables &st, std::vector<Den
         d.mdl = d.mdl ? d.mdl + e : nullptr;
         d.n = f.pass->end - e;
         d.past = (int)(e % kLine);
+        d.chunk = (int)ctx->run_chunk;
         rc = update_dense(ctx, f.kind, d, f.s, true, stream);
     }
     return rc;
@@ -832,7 +854,7 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     const int nl = (int)st->layers.size();
     auto inside = [&](int i) { return i < nl && st->layers[(size_t)i] >= first && st->layers[(size_t)i] < first + count; };
     int64_t scheduled = 0, most = 0;  // chunks of the slot's layers in the range, each of which has a pair of partial sums
-    for (int i = 0; (layer_stats || (wire16 && N > 8)) && i < nl; ++i)
+    for (int i = 0; i < nl; ++i)
         if (inside(i)) {
             const int64_t n = st->update_ranges[2 * (size_t)i + 1] - st->update_ranges[2 * (size_t)i];
             scheduled += n;
@@ -841,9 +863,9 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     const bool any = layer_stats && scheduled > 0;
     // One order of summation for a slot, whatever range the call has: the workgroups add a layer's partials up in the order of
     // the one-launch reduction, so they do it only in slots that this reduction serves.
-    const bool fold = any && st->max_update_partials <= kStatSingleMax && folds(ctx->cus, scheduled, most);
+    const bool fold = any && st->max_update_partials <= kStatSingleMax && folds_fused(ctx->cus, scheduled, most);
     f.wire16 = wire16;
-    f.pairs = takes_pairs(ctx->cus, ctx->run_chunk, c1 - c0, scheduled, N, wire16);
+    f.pairs = takes_pairs(ctx->cus, fused_chunk(ctx), c1 - c0, scheduled, N, wire16);
     f.update_first = update_first;
     f.n_replicas = N;
     f.local_rank = local_rank;
@@ -852,12 +874,14 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     f.grad_dtype = ctx->grad_dtype;
     f.with_model = ctx->param_dtype == DDP_BF16;
     f.s = s;
-    f.lds_pad = update_lds(ctx);
     f.st = {any ? ctx->d_partials : nullptr, layer_stats, fold ? ctx->d_counters : nullptr};
     const int64_t e0 = layer_elem0(ctx, first), e1 = layer_elem0(ctx, first + count);
+    f.lds_pad = fused_lds(ctx, N, wire16, opt->kind == DDP_OPT_ADAMW, e1 - e0);
     const auto at = first_pass(*st, e0);
     if (ctx->dense_path && takes_pieces(*st, at, e1)) {
         rc = fused_dense(ctx, *st, at, e0, e1, f, stream);
+    } else if (scheduled == 0) {
+        rc = launch_update(f.kind, ctx->grad_dtype, f.with_model, ctx->d_runs, ctx->d_update + c0, c1 - c0, s, true, update_lds(ctx), stream);
     } else {
         f.runs = ctx->d_runs;
         f.chunks = ctx->d_update + c0;
@@ -865,6 +889,7 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
         f.run_slot = st->d_run_slot;
         f.run_chunk_base = ctx->d_run_chunk_base;
         f.chunk_elems = (int)ctx->run_chunk;
+        f.halved = ctx->halved;
         rc = launch_fused(f, stream);
     }
     for (int i = 0; any && !fold && i < nl && rc == 0;) {

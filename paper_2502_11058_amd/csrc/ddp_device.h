@@ -282,9 +282,10 @@ __device__ __forceinline__ double block_sum(double v, double *lds) {
     return r;
 }
 
-// Sums of two doubles over the workgroup in a fixed order: a tree inside each wavefront (wave_sum), then the four wavefront sums
+// Sums of two doubles over the workgroup in a fixed order: a tree inside each wavefront (wave_sum), then the wavefronts' sums
 // added in wavefront order by thread 0.  Results valid in thread 0.  Both trees side by side, one barrier.
-__device__ __forceinline__ void block_sum2(double &g, double &m, double (*lds)[kThreads / kWave]) {
+template <int WAVES = kThreads / kWave>
+__device__ __forceinline__ void block_sum2(double &g, double &m, double (*lds)[WAVES]) {
     g = wave_sum(g);
     m = wave_sum(m);
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
@@ -296,25 +297,26 @@ __device__ __forceinline__ void block_sum2(double &g, double &m, double (*lds)[k
     if (threadIdx.x == 0) {
         g = m = 0.0;
 #pragma unroll
-        for (int w = 0; w < kThreads / kWave; ++w) {
+        for (int w = 0; w < WAVES; ++w) {
             g += lds[0][w];
             m += lds[1][w];
         }
     }
 }
 
-// The sums of a layer from its partials, in a fixed order: thread-strided, then the workgroup tree.  Sixteen pairs in flight per
-// thread, all that a layer summed in one launch has: the loop is bound by latency.
-__device__ __forceinline__ void sum_partials(const double *partials, int64_t c0, int64_t c1, int n_replicas, double *stats, double (*lds)[kThreads / kWave]) {
+// The sums of a layer from its partials by a workgroup of kSumThreads, in a fixed order: thread-strided, then the workgroup tree.
+// Eight pairs in flight per thread, all that a layer summed in one launch has: the loop is bound by latency.
+constexpr int kSumThreads = 1024;
+__device__ __forceinline__ void sum_partials(const double *partials, int64_t c0, int64_t c1, int n_replicas, double *stats, double (*lds)[kSumThreads / kWave]) {
     double g = 0.0, m = 0.0;
     typedef double f64x2 __attribute__((ext_vector_type(2)));
-    constexpr int U = (int)(kStatSingleMax / kThreads);  // pairs in flight per thread
-    for (int64_t c = c0 + (int64_t)threadIdx.x; c < c1; c += U * kThreads) {
+    constexpr int U = (int)(kStatSingleMax / kSumThreads);  // pairs in flight per thread
+    for (int64_t c = c0 + (int64_t)threadIdx.x; c < c1; c += U * kSumThreads) {
         f64x2 x[U];
 #pragma unroll
         for (int j = 0; j < U; ++j) {
             x[j] = f64x2{};
-            if (c + j * kThreads < c1) x[j] = reinterpret_cast<const f64x2 *>(partials)[c + j * kThreads];
+            if (c + j * kSumThreads < c1) x[j] = reinterpret_cast<const f64x2 *>(partials)[c + j * kSumThreads];
         }
 #pragma unroll
         for (int j = 0; j < U; ++j) {  // (both sums are of squares: adding zero changes nothing)
@@ -322,7 +324,7 @@ __device__ __forceinline__ void sum_partials(const double *partials, int64_t c0,
             m += x[j].y;
         }
     }
-    block_sum2(g, m, lds);
+    block_sum2<kSumThreads / kWave>(g, m, lds);
     if (threadIdx.x == 0) {
         stats[0] = g / (double)n_replicas;
         stats[1] = m;
@@ -330,14 +332,14 @@ __device__ __forceinline__ void sum_partials(const double *partials, int64_t c0,
 }
 
 // The same sums, of up to kFoldGroup * kFoldGroups partials and in the same order, by one wavefront: its lane stands for the
-// threads lane, lane + 64, lane + 128 and lane + 192 of sum_partials, whose trees have no barrier between them here.
+// threads lane, lane + 64, .. of sum_partials, whose trees have no barrier between them here.
 __device__ __forceinline__ void sum_partials_wave(const double *partials, int n, int n_replicas, double *stats) {
-    constexpr int kWaves = kThreads / kWave;
-    static_assert(kFoldGroup * kFoldGroups <= kThreads + kWave, "one more partial per lane than sum_partials' threads have");
+    constexpr int kParts = kFoldGroup * kFoldGroups / kWave;
+    static_assert(kParts * kWave == kFoldGroup * kFoldGroups && kParts * kWave <= kSumThreads, "a thread of sum_partials has one of these partials");
     const int lane = (int)threadIdx.x;
-    double x[kWaves + 1], y[kWaves + 1];
+    double x[kParts], y[kParts];
 #pragma unroll
-    for (int w = 0; w <= kWaves; ++w) {
+    for (int w = 0; w < kParts; ++w) {
         const int c = w * kWave + lane;
         x[w] = y[w] = 0.0;
         if (c < n) {
@@ -345,11 +347,9 @@ __device__ __forceinline__ void sum_partials_wave(const double *partials, int n,
             y[w] = __hip_atomic_load(partials + 2 * c + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
-    x[0] += x[kWaves];
-    y[0] += y[kWaves];
     double g = 0.0, m = 0.0;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w)
+    for (int w = 0; w < kParts; ++w)
         if (w * kWave < n) {
             g += wave_sum(x[w]);
             m += wave_sum(y[w]);
@@ -484,7 +484,7 @@ __device__ __forceinline__ Streams<GBF16> chunk_streams(const TensorDesc &td, co
             td.state1 + ch.begin, td.model + ch.begin, ch.count};
 }
 
-// Table-driven AdamW launches from 34 M elements on (in chunks of the default size) ask for less at a time, so that the memory
+// Table-driven AdamW updates from 34 M elements on (in workgroups of the default size) ask for less at a time, so that the memory
 // serves fewer rows at once.  Update over separate tensors, us, all in flight / paced: TinyLlama-1.1B 5305 / 5065, Llama blocks
 // of 340 M 1254 / 1214, 200 M 977 / 909, GPT-2 small 563 / 553, 28 M 127 / 127, 3 M 16.6 / 17.5.
 __device__ __forceinline__ bool long_launch() { return gridDim.x >= 16384; }

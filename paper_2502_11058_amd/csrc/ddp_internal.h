@@ -46,6 +46,7 @@ struct TensorDesc {   // one registered tensor
     float *state0;    // momentum / first moment
     float *state1;    // second moment or nullptr
     int64_t numel;
+    int32_t past;     // elements of its first cache line (kLine) before it
 };
 
 // Inside a run, chunks end at multiples of kLine elements, counted where the run's fp32 streams have a 256-byte boundary (over
@@ -88,7 +89,7 @@ struct alignas(32) MeanChunk {  // partial_average: flat elements [begin, +count
 struct alignas(32) RunSlot {  // a run of the update table in one slot
     int64_t flat0;            // first flat index, -1 if it is not scheduled
     int32_t layer;
-    LayerSums of;  // chunks of the update table
+    LayerSums of;  // chunks of the fused step
 };
 
 // One launch of the fused step over dense arenas: consecutive pieces of the model, each part of a scheduled layer or of a run
@@ -101,7 +102,7 @@ struct Piece {
     int32_t count;  // elements
     int32_t pbase;
     int32_t pos, layer;  // position of the layer in the slot, and the layer
-    int32_t first, n;    // LayerSums, in chunks of the update table
+    int32_t first, n;    // LayerSums
 };
 struct DensePass {
     int width;          // chunks of the widest piece; 0: a plain update of elements [begin, end)
@@ -126,8 +127,8 @@ struct SlotTables {
     int64_t n_mean = 0;
     int32_t *d_layer_ranges = nullptr;     // per layer of the slot: [first, last) mean chunk
     RunSlot *d_run_slot = nullptr;         // per run of the update table
-    std::vector<int32_t> update_ranges;    // per layer of the slot: [first, last) update chunk (registration order), whose places
-    int32_t *d_update_ranges = nullptr;    // the partials of the fused step have, table-driven or table-free
+    std::vector<int32_t> update_ranges;    // per layer of the slot: [first, last) chunk of the fused step (registration order), whose
+    int32_t *d_update_ranges = nullptr;    // places its partials have, table-driven or table-free
     int64_t max_mean_partials = 0, max_update_partials = 0;  // largest per-layer count of each range table
     std::vector<int32_t> layer_pos;  // [L] layer -> position in this slot, -1 if not scheduled
     std::vector<DensePass> dense_passes;  // dense arenas: the launches of the fused step over the whole model
@@ -137,7 +138,7 @@ struct SlotTables {
 // Counters of a layer whose workgroups add the statistics up themselves, in 32-bit words: one per group of kFoldGroup partials
 // and one over the groups, each in a cache line of its own.  Arrivals at one counter are served
 // one after the other, 20-25 ns each: 128 of them on one 6.3 us, in groups 5.7 (average, N = 4).
-constexpr int kFoldGroup = 16, kFoldGroups = 20, kFoldLine = 32, kFoldStride = (1 + kFoldGroups) * kFoldLine;
+constexpr int kFoldGroup = 32, kFoldGroups = 20, kFoldLine = 32, kFoldStride = (1 + kFoldGroups) * kFoldLine;
 
 // How the per-layer statistics of a launch are put together from its workgroups' partial pairs.
 struct StatsLaunch {
@@ -177,7 +178,7 @@ int launch_mean(const MeanLaunch &a, void *stream);
 // With at most kStatSingleMax partials in any of the layers (max_partials_per_layer, an upper bound is enough) one launch
 // does it all; beyond that the two stages.
 constexpr int kStatSlices = 64;
-constexpr int64_t kStatSingleMax = 4096;
+constexpr int64_t kStatSingleMax = 8192;
 int launch_stats(const double *partials, double *slice_sums, const int32_t *ranges, int pairs, int n_layers, int n_replicas, double *stats,
                  int64_t max_partials_per_layer, void *stream);
 int launch_pack16(const CopyChunk *chunks, int64_t n_chunks, uint16_t *flat16, bool nontemporal, int lds_pad, void *stream);
@@ -203,6 +204,7 @@ struct FusedTable : FusedLaunch {
     const RunSlot *run_slot;
     const int32_t *run_chunk_base;
     int chunk_elems;
+    bool halved;  // two workgroups a chunk
 };
 int launch_fused(const FusedTable &f, void *stream);
 // The update over tensors that lie back to back in every stream: the range's first element in each stream (aligned
@@ -219,6 +221,7 @@ int launch_update_dense(int kind, int grad_dtype, bool with_model, const DenseLa
 // ... and the one over dense arenas (d: the arenas' first elements; d.n is not used).
 struct FusedDense : FusedLaunch {
     DenseLaunch d;
+    int plain;  // elements per workgroup of an unscheduled piece
     const DensePass *pass;
 };
 int launch_fused_dense(const FusedDense &f, void *stream);
@@ -249,6 +252,7 @@ struct ddp_ctx {
     // model
     bool registered = false;
     int64_t run_chunk = 2048;  // elements per chunk of the update table and the table-free kernels: update_chunk, or small_model's
+    bool halved = false;       // the fused step has a workgroup for each half of such a chunk (takes_halves)
     bool small = false;
     int L = 0, T = 0;
     int param_dtype = DDP_F32, grad_dtype = DDP_F32;

@@ -20,6 +20,7 @@ struct FusedArgs {
     StatsLaunch st;                     // partials: [n_chunks][2], only touched for scheduled chunks
     UpdateScalars s;
     int chunk_elems;
+    int halved;  // 1: two workgroups a chunk
 };
 
 // A chunk of a scheduled run takes fused_body, every other chunk the optimizer step only.  At least two wavefronts per
@@ -28,9 +29,23 @@ template <bool ADAM, bool GBF16, bool MODEL, int NREP, bool EXACT, bool STATS, b
 __global__ __launch_bounds__(kThreads, 2) void fused_kernel(const FusedArgs a) {
     __shared__ double lds[2][kThreads / kWave];
     const bool paced = ADAM && long_launch();
-    const UpdateChunk ch = a.chunks[blockIdx.x];
+    UpdateChunk ch = a.chunks[blockIdx.x >> a.halved];
     const TensorDesc td = a.runs[ch.run];
     const RunSlot ts = a.run_slot[ch.run];
+    // Where this chunk's partial pair goes: chunks end on cache lines, chunk c of a run begins less than kLine elements before
+    // c * chunk_elems.  (A division: behind the loads.)
+    const int64_t chunk_begin = ch.begin;
+    auto partial = [&] {
+        const int64_t p = (int64_t)a.run_chunk_base[ch.run] + (chunk_begin + kLine - 1) / a.chunk_elems;
+        return a.halved ? 2 * p + (blockIdx.x & 1) : p;
+    };
+    if (a.halved) {
+        const int half = (int)blockIdx.x & 1, first = a.chunk_elems / 2 - ((int)(ch.begin + td.past) & (kLine - 1)), at = first < ch.count ? first : ch.count;
+        ch.begin += half ? at : 0;
+        ch.count = half ? ch.count - at : at;
+        // an empty half has its place among the partials only where another run of the layer lies behind it
+        if (ch.count == 0 && (ts.flat0 < 0 || partial() >= ts.of.first + ts.of.n)) return;
+    }
     const Streams<GBF16> c = chunk_streams<GBF16>(td, ch);
     if (ts.flat0 < 0) {  // uniform for the workgroup
         update_body<ADAM, GBF16, MODEL, true, false>(c, a.s, paced);
@@ -40,8 +55,7 @@ __global__ __launch_bounds__(kThreads, 2) void fused_kernel(const FusedArgs a) {
     fused_body<ADAM, GBF16, MODEL, NREP, EXACT, STATS, W16, UTS, PAIRS, false>(c, ts.flat0 + ch.begin, a.peers, a.s, gsum, msum);
     if constexpr (STATS) {
         block_sum2(gsum, msum, lds);
-        // chunks end on cache lines: chunk c of a run begins less than kLine elements before c * chunk_elems
-        put_partial<1>(a.st, (int64_t)a.run_chunk_base[ch.run] + (ch.begin + kLine - 1) / a.chunk_elems, ts.of, ts.layer, a.peers.n, gsum, msum);
+        put_partial<1>(a.st, partial(), ts.of, ts.layer, a.peers.n, gsum, msum);
     }
 }
 
@@ -55,7 +69,7 @@ struct LaunchTable {
     void *stream;
     template <bool A, bool G, bool M, int NR, bool EXACT, bool STATS, bool W, bool U, bool PAIRS>
     int go(int lds) const {
-        return launch(fused_kernel<A, G, M, NR, EXACT, STATS, W, U, PAIRS>, f.n_chunks, stream, lds, a);
+        return launch(fused_kernel<A, G, M, NR, EXACT, STATS, W, U, PAIRS>, f.halved ? 2 * f.n_chunks : f.n_chunks, stream, lds, a);
     }
 };
 
@@ -78,6 +92,7 @@ int DDP_FUSED_HALF(const FusedTable &f, void *stream) {
     a.st = f.st;
     a.s = f.s;
     a.chunk_elems = f.chunk_elems;
+    a.halved = f.halved;
     return dispatch_fused<DDP_FUSED_ADAM != 0>(f, LaunchTable{f, a, stream});
 }
 

@@ -15,6 +15,7 @@ struct FusedDenseArgs {
     DenseLaunch d;
     StatsLaunch st;
     UpdateScalars s;
+    int plain;  // elements per workgroup of an unscheduled piece (d.chunk: of a scheduled one)
     Piece pieces[kMaxPieces];
 };
 
@@ -32,8 +33,9 @@ __global__ __launch_bounds__(kThreads, 2) void fused_dense_kernel(const FusedDen
 #pragma unroll
     for (int j = 0; j < (NREP < 16 ? NREP : 16) - 1; ++j) asm volatile("" ::"s"(a.peers.x[j]));
     const int past = (int)t.begin & (kLine - 1);             // chunks end at multiples of kLine
-    const int hi = ((int)blockIdx.x + 1) * a.d.chunk - past;
-    int at = hi - a.d.chunk;
+    const int chunk = t.flat0 < 0 ? a.plain : a.d.chunk;
+    const int hi = ((int)blockIdx.x + 1) * chunk - past;
+    int at = hi - chunk;
     at = at > 0 ? at : 0;
     const int n = (hi < t.count ? hi : t.count) - at;
     if (n <= 0) return;  // a piece narrower than the widest
@@ -74,6 +76,7 @@ int DDP_FUSED_HALF(const FusedDense &f, void *stream) {
     FusedDenseArgs a;
     fill_peers(a.peers, f);
     a.d = f.d;
+    a.plain = f.plain;
     a.st = f.st;
     a.s = f.s;
     for (int i = 0; i < f.pass->n_pieces; ++i) a.pieces[i] = f.pass->pieces[i];

@@ -218,9 +218,9 @@ __global__ __launch_bounds__(kWave) void stats_finalize_kernel(const double *__r
 
 // The same reduction in one launch, for layers with few partials (launch-bound slots): one workgroup per layer adds the
 // layer's partials thread-strided, then the workgroup tree.  Fixed order as well.
-__global__ __launch_bounds__(kThreads) void stats_single_kernel(const double *__restrict__ partials, const int32_t *__restrict__ ranges,
+__global__ __launch_bounds__(kSumThreads) void stats_single_kernel(const double *__restrict__ partials, const int32_t *__restrict__ ranges,
                                                                 int pairs, int n_replicas, double *__restrict__ stats) {
-    __shared__ double lds[2][kThreads / kWave];
+    __shared__ double lds[2][kSumThreads / kWave];
     const int l = blockIdx.x;
     sum_partials(partials, (int64_t)pairs * ranges[2 * l], (int64_t)pairs * ranges[2 * l + 1], n_replicas, stats + 2 * l, lds);
 }
@@ -260,7 +260,7 @@ int launch_stats(const double *partials, double *slice_sums, const int32_t *rang
                  int64_t max_partials_per_layer, void *stream) {
     if (n_layers <= 0) return 0;
     if (max_partials_per_layer <= kStatSingleMax) {
-        hipLaunchKernelGGL(stats_single_kernel, dim3((unsigned)n_layers), dim3(kThreads), 0, (hipStream_t)stream, partials, ranges,
+        hipLaunchKernelGGL(stats_single_kernel, dim3((unsigned)n_layers), dim3(kSumThreads), 0, (hipStream_t)stream, partials, ranges,
                            pairs, n_replicas, stats);
         return (int)hipGetLastError();
     }

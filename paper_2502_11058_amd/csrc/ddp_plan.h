@@ -24,7 +24,16 @@ namespace ddp {
 //     average, N = 8    396   9.05 /  8.88   21.2 / 21.2      9.5 /  9.3
 //                       513  10.98 / 11.41   22.5 / 22.9     11.8 / 12.2
 // One line for both kernels, drawn where the average crosses; the fused step, whose workgroups have more to do, still gains at 352.
-inline bool folds(int cus, int64_t partials, int64_t most) { return 4 * partials <= 5 * (int64_t)cus && most <= kFoldGroup * kFoldGroups; }
+inline bool folds(int cus, int64_t partials, int64_t most) { return 4 * partials <= 5 * (int64_t)cus && most <= 320; }
+// The fused step, whose chunks are half the size (kSmallChunk), up to 5/2 per CU with a pair.  Launch of their own / folded in us:
+//     8 layers, one of them scheduled, pairs      257             401             565             626
+//         SGD, N = 4                         10.6 /  9.8     15.2 / 13.4     19.7 / 18.1     21.4 / 19.6
+//         AdamW, N = 8                       14.8 / 13.7     20.5 / 18.8     28.0 / 26.1     30.6 / 28.8
+//     4 layers, one of them scheduled
+//         SGD, N = 4                          8.9 /  7.1     10.0 /  9.8     12.5 / 12.6     13.6 / 12.5
+//         AdamW, N = 8                       10.4 / 10.5     14.0 / 14.3     18.2 / 18.0     18.8 / 17.1
+//         SGD, N = 16                        10.4 / 10.4     13.8 / 14.1     19.6 / 20.2     19.0 / 18.6
+inline bool folds_fused(int cus, int64_t partials, int64_t most) { return 2 * partials <= 5 * (int64_t)cus && most <= kFoldGroup * kFoldGroups; }
 
 // Where the average of N replicas cuts its chunks of `chunk` elements in two, a workgroup each (0: not).  The kernel for more than
 // 16 replicas takes the halves of a chunk one after the other; cut, one workgroup asks while another adds.  Up to 16 replicas both
@@ -50,16 +59,18 @@ inline int mean_pairs(int cus, int64_t chunk, int64_t n_chunks, int64_t n_layers
     return mean_cut(cus, chunk, n_chunks, n_layers, 32, true) ? 2 : 1;
 }
 
-// Whether a model is so small that its update and fused step take chunks of kSmallChunk elements and no cap on the workgroups per
-// CU: at two workgroups per CU and 2048 elements each it is one or two rounds of them, the second half empty.  Usual shape /
-// this one in us, 8 layers, fused, back to back:
+// Whether a model is so small that its update takes chunks of kSmallChunk elements, as every fused step does, and neither has a cap on
+// the workgroups per CU: at two workgroups per CU and 2048 elements each it is one or two rounds of them, the second half empty.
+// That shape / this one in us, 8 layers, fused, back to back:
 //     chunks of 2048           129          257          513         1026         1409         2050
 //     AdamW, N = 8          6.5 / 6.3    8.4 / 7.8   11.1 / 10.4  17.4 / 16.3  22.0 / 22.2  28.7 / 29.0
 //     ... separate tensors  6.8 / 6.5    8.5 / 8.1   11.4 / 10.5  17.9 / 16.9  22.4 / 22.0  29.5 / 29.5
 //     SGD, N = 4            5.3 / 5.7    5.6 / 6.4    7.6 / 7.3   12.1 / 11.1  14.9 / 14.5  19.1 / 19.0
 //     SGD, bf16, N = 12     7.7 / 7.0    8.3 / 7.9   12.4 / 11.2  14.8 / 14.3  17.7 / 17.6  22.4 / 22.7
 // Up to 4.5 chunks per CU, then; below 5/4 only with a second moment.  SGD with many bf16 peers gains there too, but replica count and
-// wire come with each call, when the tables are long made, and with few replicas SGD loses more than that.
+// wire come with each call, when the tables are long made, and with few replicas SGD loses more than that.  (The smallest models' fused step
+// gains with either: SGD, 13 layers of 142^2, N = 16 9.1 / 7.7, 8 of 187^2, N = 32 bf16 11.4 / 8.9; it has these chunks, under a cap that such a
+// model does not reach.)
 constexpr int64_t kSmallChunk = 1024;
 inline bool small_model(int cus, int64_t numel, bool second_moment) {
     const int64_t chunks = (numel + 2047) / 2048;
@@ -71,7 +82,7 @@ inline bool small_model(int cus, int64_t numel, bool second_moment) {
 // just one round, 72.3 / 73.2; SGD 886^2 47.1 / 47.0.
 inline bool short_update(int cus, int64_t numel, bool adamw) { return adamw && 4 * ((numel + 2047) / 2048) <= 7 * (int64_t)cus; }
 
-// Whether the fused step of N bf16 replicas has two vectors of all streams in flight per thread (fused_body), in a call on `all`
+// Whether, in chunks that were given by the caller and are large enough, the fused step of N bf16 replicas has two vectors of all streams in flight per thread (fused_body), in a call on `all`
 // chunks, `scheduled` of them of the slot's layers: in kernels laid out for 16 and 32 replicas, where a chunk has a second vector for
 // each thread.  That takes up to twice the registers and makes every workgroup's ramp longer, which a call of a few rounds of
 // workgroups does not hide.  One vector / two in us (scheduled of all chunks per CU):
@@ -90,6 +101,39 @@ inline bool short_update(int cus, int64_t numel, bool adamw) { return adamw && 4
 // 531, N = 2 420 / 427).
 inline bool takes_pairs(int cus, int64_t chunk, int64_t all, int64_t scheduled, int N, bool wire16) {
     return wire16 && N > 8 && N <= 32 && chunk >= 2048 && scheduled >= 3 * (int64_t)cus && 2 * all >= 9 * (int64_t)cus;
+}
+
+// Whether the fused step has a workgroup for each half (kSmallChunk elements) of a chunk of the update table.  With whole chunks a
+// thread's second vector of all streams waits for what the first one's sum and step leave behind; see fused_wg_per_cu for what that is
+// worth.  Not in models with layers of 128 M elements and more, whose long launches run best with the fewest rows in flight (whole / halves, us:
+// blocks of 4096, 11008, AdamW, N = 8, fused 11121 / 11277, layer by layer 11165 / 11362, N = 4 9550 / 9709; blocks of 2048, 5632, N = 8 6209 / 6178, bf16 5589 /
+// 5558), nor over separate tensors with SGD from 16 M elements on, where unscheduled layers want whole chunks and a slot's calls one order
+// of summation (GPT-2 small, N = 8 538 / 557, 13 blocks of 1536 1691 / 1746, 12 layers of 1378^2, N = 16 bf16 112 / 117; 11 blocks of 128, N = 6 bf16 15.9 / 15.2).
+inline bool takes_halves(int64_t numel, int64_t largest_layer, bool dense, bool second_moment) {
+    return largest_layer < (int64_t)1 << 27 && (dense || second_moment || numel < (int64_t)1 << 24);
+}
+
+// Workgroups per CU that the fused step of N replicas asks for where each takes half a chunk of the update table, kSmallChunk elements,
+// one vector of all streams a thread: four where that vector is at most 96 bytes, else three.  Whole chunks and two workgroups per CU /
+// halves and three / halves and four, us, 12 layers of 1536^2, a third of them scheduled:
+//     N =  2, bf16, SGD    (56 bytes)     97.4 /  99.6 /  94.1        AdamW   (64)    135.1 / 131.7 / 130.5
+//     N =  3, bf16, SGD    (64)          106.6 / 103.8 /  97.8        AdamW   (72)    145.6 / 137.7 / 135.0
+//     N =  4, fp32, SGD    (96)          109.3 / 109.6 / 109.8        AdamW  (104)    149.5 / 144.9 / 146.5
+//     N =  8, fp32, SGD   (160)          135.5 / 135.0 / 136.6        AdamW  (168)    175.7 / 171.7 / 177.5
+//     N =  8, bf16, SGD   (104)          112.8 / 115.8 / 121.2        AdamW  (112)    152.8 / 150.0 / 154.3
+//     N = 16, fp32, SGD   (288)          189.1 / 187.5 / 188.1        AdamW  (296)    229.3 / 230.0 / 234.0
+//     N = 24, bf16, SGD   (232)          175.5 / 166.8 / 169.7        AdamW  (240)    215.9 / 205.4 / 211.2
+// and with every layer scheduled, layer by layer, N = 8: 1448^2 22.1 / 21.1 / 21.2, 2048^2 41.4 / 39.4 / 39.8, 2500^2 60.6 / 59.0 / 59.3.
+// Two in calls on 64 M elements and more of 16 and more fp32 replicas, whose three would have over 200 KB in flight per CU.  Whole chunks
+// and two / halves and three / halves and two, 10 layers:
+//                    1536^2                3000^2                4096^2
+//     N = 16, SGD    157 / 150 / 151       588 / 585 / 582       1085 / 1090 / 1033
+//     N = 16, AdamW  185 / 187 / 197       709 / 708 / 702       1285 / 1297 / 1258
+//     N = 24, SGD    195 / 192 / 193       759 / 748 / 741       1368 / 1384 / 1318
+//     N = 32, AdamW  278 / 272 / 280      1079 / 1063 / 1055     1933 / 1908 / 1880       (N = 12, AdamW 164 / 164 / 180, 1132 / 1140 / 1157)
+inline int fused_wg_per_cu(int N, bool wire16, bool adamw, bool grad16, int64_t elements) {
+    if (!wire16 && N >= 16 && elements >= (int64_t)1 << 26) return 2;
+    return (wire16 ? 8 : 16) * (N - 1) + (adamw ? 48 : 32) + (grad16 ? 8 : 16) <= 96 ? 4 : 3;
 }
 
 // Workgroups of the table-free fused kernel over elements [e0, e1) of the arenas: chunks counted from the multiple of `line`
@@ -121,11 +165,12 @@ inline void add_pieces(DensePass &p, int64_t begin, int64_t end, int64_t flat0, 
 // workgroups start later but all in one launch.  Pieces against the table in us, N = 4: 400 layers of 1000 elements 83 / 8, 21 of
 // 64 K 17.0 / 12.5, of 256 K 37.9 / 34.3, of 1 M 117 / 115; N = 2: 21 of 1 M 126 / 129, 40 of 4 M 836 / 868.
 // No passes where a launch would need more than kMaxPieces pieces: such a slot always takes the table.
+// `plain`: chunks that a workgroup of an unscheduled piece takes.
 template <class Elem0>
-void plan_dense(SlotTables &st, int L, Elem0 &&elem0, int64_t chunk, int64_t line) {
+void plan_dense(SlotTables &st, int L, Elem0 &&elem0, int64_t chunk, int64_t line, int64_t plain = 1) {
     constexpr int kMaxSegments = 20;
     struct Segment {
-        int64_t begin, end, flat0, pbase, wg;
+        int64_t begin, end, flat0, pbase, chunk, wg;
         int32_t layer;
         LayerSums of;
     };
@@ -135,7 +180,8 @@ void plan_dense(SlotTables &st, int L, Elem0 &&elem0, int64_t chunk, int64_t lin
         int m = l + 1;
         while (i < 0 && m < L && st.layer_pos[(size_t)m] < 0) ++m;
         all.push_back({elem0(l), elem0(m), i < 0 ? -1 : st.layer_begin[(size_t)i], i < 0 ? 0 : st.update_ranges[2 * (size_t)i],
-                       dense_workgroups(elem0(l), elem0(m), chunk, line), l, {i, 0, 0}});
+                       i < 0 ? plain * chunk : chunk, 0, l, {i, 0, 0}});
+        all.back().wg = dense_workgroups(elem0(l), elem0(m), all.back().chunk, line);
         if (i >= 0) all.back().of = {i, st.update_ranges[2 * (size_t)i], st.update_ranges[2 * (size_t)i + 1] - st.update_ranges[2 * (size_t)i]};
         l = m;
     }
@@ -150,7 +196,7 @@ void plan_dense(SlotTables &st, int L, Elem0 &&elem0, int64_t chunk, int64_t lin
     int64_t shared = 0;
     for (size_t k = 0; k < all.size(); k += group(k)) shared += all[k].end - all[k].begin < kAlone;
     st.table_first = all.back().end - all[0].begin < (shared - 1) * kPerLaunch;
-    const int64_t widest = widest_piece(chunk);
+    const int64_t widest = widest_piece(plain * chunk);
     for (size_t i = 0; i < all.size();) {
         const Segment *seg = &all[i];
         const int n = (int)group(i);
@@ -182,7 +228,7 @@ void plan_dense(SlotTables &st, int L, Elem0 &&elem0, int64_t chunk, int64_t lin
             }
         p.width = (int)width;
         for (int k = 0; k < n; ++k)
-            add_pieces(p, seg[k].begin, seg[k].end, seg[k].flat0, seg[k].pbase, seg[k].layer, seg[k].of, width, chunk, line);
+            add_pieces(p, seg[k].begin, seg[k].end, seg[k].flat0, seg[k].pbase, seg[k].layer, seg[k].of, width, seg[k].chunk, line);
     }
 }
 
@@ -199,7 +245,7 @@ inline bool takes_pieces(const SlotTables &st, std::vector<DensePass>::const_ite
 
 // What a call on elements [e0, e1), whole layers, runs of launch p: the pieces inside, runs of unscheduled layers cut at the
 // range's ends.  No search and nothing allocated; part is written only as far as its pieces go.
-inline void clip_pass(const DensePass &p, int64_t e0, int64_t e1, int64_t chunk, DensePass &part, int64_t line) {
+inline void clip_pass(const DensePass &p, int64_t e0, int64_t e1, int64_t chunk, DensePass &part, int64_t line, int64_t plain = 1) {
     part.begin = std::max(p.begin, e0);
     part.end = std::min(p.end, e1);
     part.width = part.n_pieces = 0;
@@ -207,9 +253,9 @@ inline void clip_pass(const DensePass &p, int64_t e0, int64_t e1, int64_t chunk,
     if (p.width == 0) {
         if (part.begin % 4 == 0) return;  // a plain update as well
         // (no more pieces than the whole run would have, which plan_dense has counted)
-        const int64_t wg = dense_workgroups(part.begin, part.end, chunk, line);
-        part.width = (int)std::min(wg, widest_piece(chunk));
-        add_pieces(part, part.begin, part.end, -1, 0, -1, {-1, 0, 0}, part.width, chunk, line);
+        const int64_t wg = dense_workgroups(part.begin, part.end, plain * chunk, line);
+        part.width = (int)std::min(wg, widest_piece(plain * chunk));
+        add_pieces(part, part.begin, part.end, -1, 0, -1, {-1, 0, 0}, part.width, plain * chunk, line);
         return;
     }
     bool scheduled = false;
@@ -222,7 +268,7 @@ inline void clip_pass(const DensePass &p, int64_t e0, int64_t e1, int64_t chunk,
         q = whole;
         q.begin = b;  // (moves in unscheduled pieces only: a scheduled one is part of one layer)
         q.count = (int32_t)(e - b);
-        part.width = std::max(part.width, (int)dense_workgroups(b, e, chunk, line));
+        part.width = std::max(part.width, (int)dense_workgroups(b, e, q.flat0 < 0 ? plain * chunk : chunk, line));
         scheduled = scheduled || q.flat0 >= 0;
     }
     if (!scheduled && part.begin % 4 == 0) part.width = part.n_pieces = 0;  // a plain update, whose workgroups start sooner

@@ -1,0 +1,87 @@
+// The plan of the fused step over dense arenas where a workgroup of an unscheduled piece takes several chunks: random models, whole
+// and clipped to ranges of layers; every element belongs to one piece and every launch is wide enough for what the kernel makes of
+// its pieces.  And the rules of the fused step's shape on both sides of their lines, for 256 compute units.
+#include <cstdio>
+#include <cstdlib>
+#include <random>
+
+#include "ddp_plan.h"
+
+#define CHECK(cond)                                                                       \
+    do {                                                                                  \
+        if (!(cond)) {                                                                    \
+            std::fprintf(stderr, "%s:%d: check failed: %s\n", __FILE__, __LINE__, #cond); \
+            std::exit(1);                                                                 \
+        }                                                                                 \
+    } while (0)
+
+using namespace ddp;
+
+int main() {
+    std::mt19937_64 rng(5);
+    auto pick = [&](int64_t lo, int64_t hi) { return lo + (int64_t)(rng() % (uint64_t)(hi - lo + 1)); };
+    long calls = 0;
+    for (int r = 0; r < 500; ++r) {
+        const int64_t chunk = 1024, plain = pick(1, 3);
+        const int L = (int)pick(1, 30), keep = (int)pick(0, 4);
+        SlotTables st;
+        std::vector<int64_t> e(1, 0), wg(1, 0);
+        for (int l = 0; l < L; ++l) {
+            e.push_back(e.back() + std::max<int64_t>(1, chunk * pick(0, 5) + pick(-70, 70) + (pick(0, 9) ? 0 : (int64_t)1 << pick(10, 33))));
+            wg.push_back(wg.back() + dense_workgroups(e[(size_t)l], e[(size_t)l + 1], chunk, kLine));
+        }
+        st.layer_pos.assign((size_t)L, -1);
+        int64_t off = 0;
+        for (int l = L - 1; l >= 0; --l)
+            if (pick(1, 4) <= keep) {
+                st.layer_pos[(size_t)l] = (int32_t)st.layers.size();
+                st.layers.push_back(l);
+                st.layer_begin.push_back(off);
+                st.update_ranges.push_back((int32_t)wg[(size_t)l]);
+                st.update_ranges.push_back((int32_t)wg[(size_t)l + 1]);
+                off += e[(size_t)l + 1] - e[(size_t)l];
+            }
+        plan_dense(st, L, [&](int l) { return e[(size_t)l]; }, chunk, kLine, plain);
+        for (int k = 0; k < 20; ++k, ++calls) {
+            const int first = k ? (int)pick(0, L - 1) : 0, last = k ? (int)pick(first + 1, L) : L;
+            int64_t at = e[(size_t)first];
+            const int64_t e1 = e[(size_t)last];
+            for (auto pass = first_pass(st, at); pass != st.dense_passes.end() && pass->begin < e1; ++pass) {
+                static DensePass part;
+                clip_pass(*pass, e[(size_t)first], e1, chunk, part, kLine, plain);
+                CHECK(part.begin == at);
+                if (part.width == 0) at = part.end;
+                int64_t widest = 0;
+                for (int i = 0; i < part.n_pieces; ++i) {
+                    const Piece &q = part.pieces[i];
+                    CHECK(q.begin == at && q.count > 0);
+                    at += q.count;
+                    // as the kernel counts: the last workgroup with elements
+                    const int64_t step = q.flat0 < 0 ? plain * chunk : chunk, past = q.begin & (kLine - 1);
+                    const int64_t x = (q.count + past - 1) / step;
+                    CHECK(x < part.width && (part.width + 1) * step <= INT32_MAX);
+                    widest = std::max(widest, x + 1);
+                    if (q.flat0 < 0) continue;
+                    CHECK(q.first == st.update_ranges[2 * (size_t)q.pos] && q.first + q.n == st.update_ranges[2 * (size_t)q.pos + 1]);
+                    CHECK(q.pbase >= q.first && q.pbase + x < q.first + q.n);
+                }
+                CHECK(at == part.end && widest == part.width);
+            }
+            if (!st.dense_passes.empty()) CHECK(at == e1);
+        }
+    }
+    // four workgroups per CU up to 96 bytes per thread, else three; two for 16 and more fp32 replicas from 64 M elements on
+    const int64_t few = 1, large = (int64_t)1 << 26;
+    CHECK(fused_wg_per_cu(3, false, false, false, large) == 4 && fused_wg_per_cu(4, false, false, false, few) == 4 && fused_wg_per_cu(5, false, false, false, few) == 3);
+    CHECK(fused_wg_per_cu(3, false, true, true, few) == 4 && fused_wg_per_cu(4, false, true, true, few) == 3);
+    CHECK(fused_wg_per_cu(6, true, true, true, few) == 4 && fused_wg_per_cu(7, true, true, true, few) == 3 && fused_wg_per_cu(64, true, true, false, large) == 3);
+    CHECK(fused_wg_per_cu(15, false, true, true, large) == 3 && fused_wg_per_cu(16, false, true, true, large) == 2 && fused_wg_per_cu(16, false, true, true, large - 1) == 3);
+    // halves of chunks: no layer of 128 M elements, over separate tensors with one moment fewer than 16 M elements
+    const int64_t layer = (int64_t)1 << 27, model = (int64_t)1 << 24;
+    CHECK(takes_halves(1, 1, true, false) && takes_halves(100 * layer, layer - 1, true, false) && !takes_halves(layer, layer, true, true));
+    CHECK(takes_halves(model - 1, 1, false, false) && !takes_halves(model, 1, false, false) && takes_halves(model, 1, false, true));
+    // statistics put together in the launch: 5/2 pairs per CU
+    CHECK(folds_fused(256, 640, 640) && !folds_fused(256, 641, 1) && !folds_fused(304, 641, 641) && folds_fused(304, 760, 640));
+    std::printf("plain pieces ok: %ld calls\n", calls);
+    return 0;
+}
