@@ -240,6 +240,10 @@ __device__ __forceinline__ int head_to_16B(const void *p, int n) {  // fp32 elem
     return h < n ? h : n;
 }
 
+// sum + d * d in fp64.  The product of two widened fp32 values is exact, so one fused operation gives the bits of the two
+// (average, us: 10 layers of 1536^2, N = 24 124.0 -> 121.7, N = 32 157.3 -> 155.7; 9 of 900^2, N = 12 19.1 -> 18.7, N = 16 23.8 -> 23.3).
+__device__ __forceinline__ void add_square(double &sum, float d) { sum = __builtin_fma((double)d, (double)d, sum); }
+
 // Sum of a double over the wavefront, valid in lane 0: lane i and lane i + 32, then 16, 8, 4, 2, 1, the order of a shuffle-down tree.
 // The halves come by lane swaps and row shifts of the vector unit; through the LDS crossbar (ds_bpermute, __shfl_down) each of the
 // six steps waits some 100 cycles, and a short kernel waits for the whole chain, twice where its workgroups put the layers'
@@ -642,10 +646,10 @@ __device__ __forceinline__ void fused_math4(const typename WireVec<W16>::type (&
     f32x4 m = acc * inv_n;
     if constexpr (STATS) {
         auto add_sq = [](double &sum, f32x4 d) {
-            sum += (double)d.x * (double)d.x;
-            sum += (double)d.y * (double)d.y;
-            sum += (double)d.z * (double)d.z;
-            sum += (double)d.w * (double)d.w;
+            add_square(sum, d.x);
+            add_square(sum, d.y);
+            add_square(sum, d.z);
+            add_square(sum, d.w);
         };
 #pragma unroll
         for (int j = 0; j < NREP - 1; ++j) {

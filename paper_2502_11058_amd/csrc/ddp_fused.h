@@ -61,19 +61,23 @@ __device__ __forceinline__ void fused_body(const Streams<GBF16> c, int64_t fo, c
     const Vectors<GBF16, BUF> b(c, h, nv);
     const int64_t bfo = fo + h;
     typedef typename WireVec<W16>::elem xelem;
+    // A buffer's base must be dword-aligned, which a bf16 peer's need not be; and the kernels for 17 to 31 replicas, whose conditions take
+    // scalar registers too, have none to spare for four per peer (10 layers of 3000^2, N = 24, SGD 738 us with buffers, 724 without, AdamW 868 /
+    // 853; N = 32, all unconditional, 906 / 923 and 1052 / 1064).
+    constexpr bool kPeerBuffers = BUF && !W16 && (EXACT || NREP <= 16);
 
     auto stats4 = [&](f32x4 m, f32x4 x) {
         const f32x4 d = m - x;
-        gsum += (double)d.x * (double)d.x;
-        gsum += (double)d.y * (double)d.y;
-        gsum += (double)d.z * (double)d.z;
-        gsum += (double)d.w * (double)d.w;
+        add_square(gsum, d.x);
+        add_square(gsum, d.y);
+        add_square(gsum, d.z);
+        add_square(gsum, d.w);
     };
     auto msq4 = [&](f32x4 m) {
-        msum += (double)m.x * (double)m.x;
-        msum += (double)m.y * (double)m.y;
-        msum += (double)m.z * (double)m.z;
-        msum += (double)m.w * (double)m.w;
+        add_square(msum, m.x);
+        add_square(msum, m.y);
+        add_square(msum, m.z);
+        add_square(msum, m.w);
     };
     auto step4 = [&](gvec gv, f32x4 &x, f32x4 &av, f32x4 &bv) {
         const f32x4 gw = G::widen(gv);
@@ -111,8 +115,7 @@ __device__ __forceinline__ void fused_body(const Streams<GBF16> c, int64_t fo, c
                 for (int j = 0; j < NREP - 1; ++j) {
                     pv[k][j] = raw4{};
                     if (j < kPeersAlways<NREP, EXACT> || j < nrep - 1) {
-                        // (a buffer's base must be dword-aligned, which a bf16 peer's need not be)
-                        const Stream<BUF && !W16, xelem> x(reinterpret_cast<const xelem *>(a.x[j]) + bfo, nv);
+                        const Stream<kPeerBuffers, xelem> x(reinterpret_cast<const xelem *>(a.x[j]) + bfo, nv);
                         pv[k][j] = __builtin_bit_cast(raw4, x.template ld<NT>(i));
                     }
                 }
@@ -195,9 +198,9 @@ __device__ __forceinline__ void fused_body(const Streams<GBF16> c, int64_t fo, c
         if constexpr (STATS) {
             for (int k = 0; k < nrep; ++k) {
                 const float d = m - term(k);
-                gsum += (double)d * (double)d;
+                add_square(gsum, d);
             }
-            msum += (double)m * (double)m;
+            add_square(msum, m);
         }
         float res = m;
         if constexpr (!UTS) step1(gi, res, av, bv);

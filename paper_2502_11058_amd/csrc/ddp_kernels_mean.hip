@@ -50,9 +50,9 @@ __global__ __launch_bounds__(kThreads) void mean_kernel(const MeanArgs a) {
         if constexpr (STATS) {
             for (int k = 0; k < nrep; ++k) {
                 const float d = m - wire1<W16>(a.x[k], i);
-                gsum += (double)d * (double)d;
+                add_square(gsum, d);
             }
-            msum += (double)m * (double)m;
+            add_square(msum, m);
         }
         a.out[i] = m;
     };
@@ -72,16 +72,16 @@ __global__ __launch_bounds__(kThreads) void mean_kernel(const MeanArgs a) {
 
     auto stats4 = [&](f32x4 m, f32x4 x) {
         const f32x4 d = m - x;
-        gsum += (double)d.x * (double)d.x;
-        gsum += (double)d.y * (double)d.y;
-        gsum += (double)d.z * (double)d.z;
-        gsum += (double)d.w * (double)d.w;
+        add_square(gsum, d.x);
+        add_square(gsum, d.y);
+        add_square(gsum, d.z);
+        add_square(gsum, d.w);
     };
     auto msq4 = [&](f32x4 m) {
-        msum += (double)m.x * (double)m.x;
-        msum += (double)m.y * (double)m.y;
-        msum += (double)m.z * (double)m.z;
-        msum += (double)m.w * (double)m.w;
+        add_square(msum, m.x);
+        add_square(msum, m.y);
+        add_square(msum, m.z);
+        add_square(msum, m.w);
     };
 
     if constexpr (NREP > 0) {
