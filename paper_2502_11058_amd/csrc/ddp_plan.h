@@ -243,6 +243,13 @@ inline bool takes_pieces(const SlotTables &st, std::vector<DensePass>::const_ite
     return at != st.dense_passes.end() && (!st.table_first || at->end >= e1);
 }
 
+// Whether a launch has nothing but unscheduled layers.
+inline bool unscheduled(const DensePass &p) {
+    for (int i = 0; i < p.n_pieces; ++i)
+        if (p.pieces[i].flat0 >= 0) return false;
+    return true;
+}
+
 // What a call on elements [e0, e1), whole layers, runs of launch p: the pieces inside, runs of unscheduled layers cut at the
 // range's ends.  No search and nothing allocated; part is written only as far as its pieces go.
 inline void clip_pass(const DensePass &p, int64_t e0, int64_t e1, int64_t chunk, DensePass &part, int64_t line, int64_t plain = 1) {
