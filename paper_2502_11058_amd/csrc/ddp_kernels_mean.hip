@@ -6,8 +6,9 @@
 namespace ddp {
 namespace {
 
+template <int R>
 struct MeanArgs {
-    const void *x[DDP_MAX_REPLICAS];  // fp32 or bf16 flat buffers, rank order
+    const void *x[R];  // fp32 or bf16 flat buffers, rank order; first, so that they lie where wide scalar loads take them
     float *out;
     const MeanChunk *chunks;
     StatsLaunch st;
@@ -16,6 +17,9 @@ struct MeanArgs {
     int cut;            // MeanLaunch
     int stage_threads;  // run-time replica count with statistics: threads that take part in the vector loop
 };
+// Replica pointers among the arguments of a kernel: as many as it can use, since every launch writes and reads all of them.
+template <int NREP>
+constexpr int kArgReps = NREP > 0 ? NREP : DDP_MAX_REPLICAS;
 
 // Eq. (5), second case.  NREP > 0: the replica count (EXACT), or the largest count that the kernel's registers are laid out
 // for, serving the counts above half of it (loads and sum fully unrolled, wave-uniform conditions on the upper half);
@@ -24,7 +28,7 @@ struct MeanArgs {
 // Bound by HBM; with bf16 replicas also by how many wavefronts the registers let in, so a group is kept as it was loaded and
 // widened at each use (N = 32: 241 -> 82 VGPRs).
 template <int NREP, bool EXACT, bool STATS, bool NT, bool W16, bool CUT>
-__global__ __launch_bounds__(kThreads) void mean_kernel(const MeanArgs a) {
+__global__ __launch_bounds__(kThreads) void mean_kernel(const MeanArgs<kArgReps<NREP>> a) {
     __shared__ double lds[2][kThreads / kWave];
     // CUT: two workgroups a chunk (mean_cut).  A kernel of its own: what the others spent on it before their first load was 0.3 %.
     MeanChunk ch = a.chunks[CUT ? blockIdx.x >> 1 : blockIdx.x];
@@ -167,9 +171,11 @@ __global__ __launch_bounds__(kThreads) void mean_kernel(const MeanArgs a) {
 
     if constexpr (STATS) {
         // Up to four replicas, with three and four workgroups per CU, the two sums of a long launch come one after the other
-        // (TinyLlama-1.1B, us, side by side / so: N = 4 860 / 831, N = 2 508 / 501, N = 3 661 / 653).
-        constexpr bool kApart = NREP > 0 && NREP <= 4;
-        if (kApart && !a.st.counters) {
+        // (TinyLlama-1.1B, us, side by side / so: N = 4 860 / 831, N = 2 508 / 501, N = 3 661 / 653);
+        // with 9 to 16 fp32 replicas from 8192 workgroups on (N = 16, 218 M 2469 / 2454, 67 M 774 / 771, N = 14, 37 M 362 / 361, N = 12, 27 M
+        // 222.0 / 221.4; N = 12, 2.4 M 17.4 / 17.9).  Five to eight (N = 6, 159.3 / 160.0) and bf16 replicas gain nothing.
+        constexpr bool kApart = NREP > 0 && NREP <= 4, kLongApart = NREP > 8 && NREP <= 16 && !W16;
+        if ((kApart && !a.st.counters) || (kLongApart && gridDim.x >= 8192)) {
             gsum = block_sum(gsum, lds[0]);
             msum = block_sum(msum, lds[1]);
         } else {
@@ -233,7 +239,16 @@ int mean_lds(const MeanLaunch &a) {
 }
 
 template <int NREP, bool EXACT, bool CUT>
-int launch_mean_c(const MeanArgs &ma, const MeanLaunch &a, void *stream) {
+int launch_mean_c(const MeanLaunch &a, void *stream) {
+    MeanArgs<kArgReps<NREP>> ma;
+    for (int k = 0; k < kArgReps<NREP>; ++k) ma.x[k] = k < a.n_replicas ? a.x[k] : nullptr;
+    ma.out = a.out;
+    ma.chunks = a.chunks;
+    ma.st = a.st;
+    ma.inv_n = a.inv_n;
+    ma.n = a.n_replicas;
+    ma.cut = a.cut;
+    ma.stage_threads = stage_threads(a.n_replicas - kRegReps);  // the replicas beyond the registers are staged
     const int64_t grid = CUT ? 2 * a.n_chunks : a.n_chunks;
     if constexpr (!CUT || NREP >= kCutReps16) {
         if (a.wire16) {
@@ -248,10 +263,10 @@ int launch_mean_c(const MeanArgs &ma, const MeanLaunch &a, void *stream) {
 }
 
 template <int NREP, bool EXACT>
-int launch_mean_n(const MeanArgs &ma, const MeanLaunch &a, void *stream) {
+int launch_mean_n(const MeanLaunch &a, void *stream) {
     if constexpr (NREP >= kCutReps)
-        if (a.cut) return launch_mean_c<NREP, EXACT, true>(ma, a, stream);
-    return launch_mean_c<NREP, EXACT, false>(ma, a, stream);
+        if (a.cut) return launch_mean_c<NREP, EXACT, true>(a, stream);
+    return launch_mean_c<NREP, EXACT, false>(a, stream);
 }
 
 }  // namespace
@@ -274,35 +289,26 @@ int launch_stats(const double *partials, double *slice_sums, const int32_t *rang
 }
 
 int launch_mean(const MeanLaunch &a, void *stream) {
-    MeanArgs ma{};
-    for (int k = 0; k < a.n_replicas; ++k) ma.x[k] = a.x[k];
-    ma.out = a.out;
-    ma.chunks = a.chunks;
-    ma.st = a.st;
-    ma.inv_n = a.inv_n;
-    ma.n = a.n_replicas;
-    ma.cut = a.cut;
-    ma.stage_threads = stage_threads(a.n_replicas - kRegReps);  // the replicas beyond the registers are staged
     int rc;
     switch (a.n_replicas) {
-        case 1: rc = launch_mean_n<1, true>(ma, a, stream); break;
-        case 2: rc = launch_mean_n<2, true>(ma, a, stream); break;
-        case 3: rc = launch_mean_n<3, true>(ma, a, stream); break;
-        case 4: rc = launch_mean_n<4, true>(ma, a, stream); break;
-        case 5: rc = launch_mean_n<5, true>(ma, a, stream); break;
-        case 6: rc = launch_mean_n<6, true>(ma, a, stream); break;
-        case 7: rc = launch_mean_n<7, true>(ma, a, stream); break;
-        case 8: rc = launch_mean_n<8, true>(ma, a, stream); break;
-        case 9: rc = launch_mean_n<9, true>(ma, a, stream); break;
-        case 10: rc = launch_mean_n<10, true>(ma, a, stream); break;
-        case 11: rc = launch_mean_n<11, true>(ma, a, stream); break;
-        case 12: rc = launch_mean_n<12, true>(ma, a, stream); break;
-        case 13: rc = launch_mean_n<13, true>(ma, a, stream); break;
-        case 14: rc = launch_mean_n<14, true>(ma, a, stream); break;
-        case 15: rc = launch_mean_n<15, true>(ma, a, stream); break;
-        case 16: rc = launch_mean_n<16, true>(ma, a, stream); break;
-        case kFixedReps: rc = launch_mean_n<kFixedReps, true>(ma, a, stream); break;
-        default: rc = a.n_replicas < kFixedReps ? launch_mean_n<kFixedReps, false>(ma, a, stream) : launch_mean_n<0, false>(ma, a, stream); break;
+        case 1: rc = launch_mean_n<1, true>(a, stream); break;
+        case 2: rc = launch_mean_n<2, true>(a, stream); break;
+        case 3: rc = launch_mean_n<3, true>(a, stream); break;
+        case 4: rc = launch_mean_n<4, true>(a, stream); break;
+        case 5: rc = launch_mean_n<5, true>(a, stream); break;
+        case 6: rc = launch_mean_n<6, true>(a, stream); break;
+        case 7: rc = launch_mean_n<7, true>(a, stream); break;
+        case 8: rc = launch_mean_n<8, true>(a, stream); break;
+        case 9: rc = launch_mean_n<9, true>(a, stream); break;
+        case 10: rc = launch_mean_n<10, true>(a, stream); break;
+        case 11: rc = launch_mean_n<11, true>(a, stream); break;
+        case 12: rc = launch_mean_n<12, true>(a, stream); break;
+        case 13: rc = launch_mean_n<13, true>(a, stream); break;
+        case 14: rc = launch_mean_n<14, true>(a, stream); break;
+        case 15: rc = launch_mean_n<15, true>(a, stream); break;
+        case 16: rc = launch_mean_n<16, true>(a, stream); break;
+        case kFixedReps: rc = launch_mean_n<kFixedReps, true>(a, stream); break;
+        default: rc = a.n_replicas < kFixedReps ? launch_mean_n<kFixedReps, false>(a, stream) : launch_mean_n<0, false>(a, stream); break;
     }
     return rc;
 }
