@@ -157,6 +157,7 @@ struct WireVec<false> {
     typedef float elem;
     typedef f32x4 type;
     static __device__ __forceinline__ f32x4 widen(f32x4 v) { return v; }
+    static __device__ __forceinline__ float widen1(float v) { return v; }
 };
 template <>
 struct WireVec<true> {
@@ -165,6 +166,7 @@ struct WireVec<true> {
     static __device__ __forceinline__ f32x4 widen(u32x2 v) {
         return f32x4{__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u)};
     }
+    static __device__ __forceinline__ float widen1(unsigned short v) { return bf16_widen(v); }
 };
 // The group for its second use: bf16 is widened anew, or the compiler keeps the widened form, twice the registers, from the
 // first use on.

@@ -186,21 +186,68 @@ __device__ __forceinline__ void fused_body(const Streams<GBF16> c, int64_t fo, c
     // head and tail together, element by element, behind the vectors: only a tensor's first and last chunk have any
     if (tid < c.n - 4 * nv) {
         const unsigned i = tid < h ? tid : 4 * nv + tid;
+        // Replicas that the registers are laid out for are asked for together, as the vectors are, others eight at a time: one after the other
+        // they are a chain of 2 N trips to memory, which a short launch waits for.  Fused step, us, one after the other / so: 14 layers of
+        // 226^2, N = 32 bf16 16.3 / 9.7, 5 of 282^2, AdamW, N = 6 7.2 / 6.3, 15 of 166^2, AdamW, N = 24 13.7 / 11.2 (all at once 9.8, but the scalar
+        // registers that the kernels for 17 to 31 spill then cost 10 layers of 3000^2 845 / 850), N = 40 27.6 / 23.1.
+        constexpr bool kTogether = NREP > 1 && (EXACT || NREP <= 16);
+        xelem peer[kTogether ? NREP - 1 : 1];
+        if constexpr (kTogether) {
+#pragma unroll
+            for (int j = 0; j < NREP - 1; ++j) {
+                peer[j] = xelem{};
+                if (j < kPeersAlways<NREP, EXACT> || j < nrep - 1) peer[j] = ld1(reinterpret_cast<const xelem *>(a.x[j]) + fo, i);
+            }
+        }
         float pl = ld1(c.p, i), av = ld1(c.s0, i), bv = ADAM ? ld1(c.s1, i) : 0.0f;
         const float gi = G::widen1(ld1(c.g, i));
         if constexpr (UTS) step1(gi, pl, av, bv);
         // what this worker contributes: its value, rounded to bf16 first if that is what its peers received
         const float loc = W16 ? bf16_widen(bf16_rne(pl)) : pl;
-        auto term = [&](int k) -> float { return k == lr ? loc : wire1<W16>(a.x[k - (k > lr ? 1 : 0)], fo + i); };
-        float acc = term(0);
-        for (int k = 1; k < nrep; ++k) acc = acc + term(k);
-        const float m = acc * inv_n;
-        if constexpr (STATS) {
-            for (int k = 0; k < nrep; ++k) {
-                const float d = m - term(k);
-                add_square(gsum, d);
+        float m;
+        if constexpr (kTogether) {
+            constexpr int ALWAYS = kPeersAlways<NREP, EXACT>;
+            const int n = fresh(nrep), at = fresh(lr);
+            float acc = -0.0f;
+#pragma unroll
+            for (int j = 0; j < NREP - 1; ++j) {
+                if (j == at) acc = acc + loc;
+                if (j < ALWAYS || j < n - 1) acc = acc + WireVec<W16>::widen1(peer[j]);
             }
-            add_square(msum, m);
+            if constexpr (EXACT)
+                if (at == NREP - 1) acc = acc + loc;
+            m = acc * inv_n;
+            if constexpr (STATS) {
+#pragma unroll
+                for (int j = 0; j < NREP - 1; ++j) {
+                    if (j == at) add_square(gsum, m - loc);
+                    if (j < ALWAYS || j < n - 1) add_square(gsum, m - WireVec<W16>::widen1(peer[j]));
+                }
+                if constexpr (EXACT)
+                    if (at == NREP - 1) add_square(gsum, m - loc);
+                add_square(msum, m);
+            }
+        } else {
+            auto each = [&](auto &&f) {  // f(value) of every replica, in rank order
+                for (int k0 = 0; k0 < nrep; k0 += 8) {
+                    float x[8];
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {  // (the last peer again where the local replica or none is meant)
+                        const int q = k0 + k - (k0 + k > lr ? 1 : 0);
+                        x[k] = wire1<W16>(a.x[q < nrep - 1 ? q : nrep - 2], fo + i);
+                    }
+#pragma unroll
+                    for (int k = 0; k < 8; ++k)
+                        if (k0 + k < nrep) f(k0 + k == lr ? loc : x[k]);
+                }
+            };
+            float acc = -0.0f;
+            each([&](float x) { acc = acc + x; });
+            m = acc * inv_n;
+            if constexpr (STATS) {
+                each([&](float x) { add_square(gsum, m - x); });
+                add_square(msum, m);
+            }
         }
         float res = m;
         if constexpr (!UTS) step1(gi, res, av, bv);
