@@ -804,12 +804,10 @@ static int fused_dense(const ddp_ctx *ctx, const SlotTables &st, std::vector<Den
             clip_pass(*at, e0, e1, fused_chunk(ctx), part, kLine, plain_chunks(ctx));
             f.pass = &part;
         }
-        if (f.pass->width > 0 && !unscheduled(*f.pass)) {
+        if (f.pass->width > 0) {
             rc = launch_fused_dense(f, stream);
             continue;
         }
-        // unscheduled layers alone are a plain update, wherever in a vector they start: its launch carries 104 bytes of arguments, that
-        // of the pieces 1.8 KB, and takes 0.3-0.5 us less of the host (8 layers of 509^2, N = 5, layer by layer, us 35.6 / 31.4)
         const int64_t e = f.pass->begin;
         DenseLaunch d = f.d;
         d.g = (const char *)d.g + e * (ctx->grad_dtype == DDP_F32 ? 4 : 2);

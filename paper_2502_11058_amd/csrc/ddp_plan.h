@@ -212,7 +212,7 @@ void plan_dense(SlotTables &st, int L, Elem0 &&elem0, int64_t chunk, int64_t lin
         p.width = p.n_pieces = 0;
         p.begin = seg[0].begin;
         p.end = seg[n - 1].end;
-        if (n == 1 && seg[0].flat0 < 0 && seg[0].begin % 4 == 0) continue;
+        if (n == 1 && seg[0].flat0 < 0) continue;  // a plain update, wherever in a vector it starts
         // the width that leaves the fewest workgroups without work among those that cut some segment evenly
         int64_t width = widest, best = INT64_MAX;
         for (int k = 0; k < n; ++k)
@@ -243,28 +243,13 @@ inline bool takes_pieces(const SlotTables &st, std::vector<DensePass>::const_ite
     return at != st.dense_passes.end() && (!st.table_first || at->end >= e1);
 }
 
-// Whether a launch has nothing but unscheduled layers.
-inline bool unscheduled(const DensePass &p) {
-    for (int i = 0; i < p.n_pieces; ++i)
-        if (p.pieces[i].flat0 >= 0) return false;
-    return true;
-}
-
 // What a call on elements [e0, e1), whole layers, runs of launch p: the pieces inside, runs of unscheduled layers cut at the
-// range's ends.  No search and nothing allocated; part is written only as far as its pieces go.
+// range's ends; a plain update (width 0) where no scheduled layer is inside.  No search and nothing allocated; part is written only as far as its pieces go.
 inline void clip_pass(const DensePass &p, int64_t e0, int64_t e1, int64_t chunk, DensePass &part, int64_t line, int64_t plain = 1) {
     part.begin = std::max(p.begin, e0);
     part.end = std::min(p.end, e1);
     part.width = part.n_pieces = 0;
-    if (part.begin >= part.end) return;
-    if (p.width == 0) {
-        if (part.begin % 4 == 0) return;  // a plain update as well
-        // (no more pieces than the whole run would have, which plan_dense has counted)
-        const int64_t wg = dense_workgroups(part.begin, part.end, plain * chunk, line);
-        part.width = (int)std::min(wg, widest_piece(plain * chunk));
-        add_pieces(part, part.begin, part.end, -1, 0, -1, {-1, 0, 0}, part.width, plain * chunk, line);
-        return;
-    }
+    if (part.begin >= part.end || p.width == 0) return;  // (a plain update as well)
     bool scheduled = false;
     for (int i = 0; i < p.n_pieces; ++i) {
         const Piece &whole = p.pieces[i];
@@ -278,7 +263,10 @@ inline void clip_pass(const DensePass &p, int64_t e0, int64_t e1, int64_t chunk,
         part.width = std::max(part.width, (int)dense_workgroups(b, e, q.flat0 < 0 ? plain * chunk : chunk, line));
         scheduled = scheduled || q.flat0 >= 0;
     }
-    if (!scheduled && part.begin % 4 == 0) part.width = part.n_pieces = 0;  // a plain update, whose workgroups start sooner
+    // Unscheduled layers alone are a plain update, wherever in a vector they start: its workgroups start sooner, its launch carries 104
+    // bytes of arguments, that of the pieces 1.8 KB, and takes 0.3-0.5 us less of the host (8 layers of 509^2, N = 5, layer by layer, us
+    // 35.6 / 31.4).
+    if (!scheduled) part.width = part.n_pieces = 0;
 }
 
 }  // namespace ddp
