@@ -345,6 +345,7 @@ extern "C" int ddp_register_model(ddp_ctx *ctx, int L, int T, const int32_t *lay
         }
         ctx->run_chunk_base.push_back((int32_t)uc.size());
         ctx->n_update = (int64_t)uc.size();
+        ctx->halved = ctx->halved && halves_fit(ctx->n_update);
         interleave_segments(uc, ctx->dispatch_ways);
         rc = upload(ctx, runs, &ctx->d_runs);
         ctx->runs = std::move(runs);

@@ -113,6 +113,10 @@ inline bool takes_halves(int64_t numel, int64_t largest_layer, bool dense, bool 
     return largest_layer < (int64_t)1 << 27 && (dense || second_moment || numel < (int64_t)1 << 24);
 }
 
+// A launch has less than 2^32 threads in x (hipErrorInvalidConfiguration from there on, measured: 2^24 - 1 workgroups of 256 run, 2^24 are
+// refused).  The table-driven fused step over all n_update chunks of a model, a workgroup for each half: up to 17 G elements.
+inline bool halves_fit(int64_t n_update) { return 2 * n_update < (int64_t)1 << 24; }
+
 // Workgroups per CU that the fused step of N replicas asks for where each takes half a chunk of the update table, kSmallChunk elements,
 // one vector of all streams a thread: four where that vector is at most 96 bytes, else three.  Whole chunks and two workgroups per CU /
 // halves and three / halves and four, us, 12 layers of 1536^2, a third of them scheduled:

@@ -80,6 +80,8 @@ int main() {
     const int64_t layer = (int64_t)1 << 27, model = (int64_t)1 << 24;
     CHECK(takes_halves(1, 1, true, false) && takes_halves(100 * layer, layer - 1, true, false) && !takes_halves(layer, layer, true, true));
     CHECK(takes_halves(model - 1, 1, false, false) && !takes_halves(model, 1, false, false) && takes_halves(model, 1, false, true));
+    // ... and a grid of less than 2^32 threads
+    CHECK(halves_fit(1) && halves_fit(((int64_t)1 << 23) - 1) && !halves_fit((int64_t)1 << 23) && !halves_fit(INT32_MAX));
     // statistics put together in the launch: 5/2 pairs per CU
     CHECK(folds_fused(256, 640, 640) && !folds_fused(256, 641, 1) && !folds_fused(304, 641, 641) && folds_fused(304, 760, 640));
     std::printf("plain pieces ok: %ld calls\n", calls);
