@@ -864,7 +864,7 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     const bool any = layer_stats && scheduled > 0;
     // One order of summation for a slot, whatever range the call has: the workgroups add a layer's partials up in the order of
     // the one-launch reduction, so they do it only in slots that this reduction serves.
-    const bool fold = any && st->max_update_partials <= kStatSingleMax && folds_fused(ctx->cus, scheduled, most);
+    const bool fold = any && st->max_update_partials <= kStatSingleMax && folds_fused(ctx->cus, scheduled, most, (ctx->halved ? 2 : 1) * (c1 - c0));
     f.wire16 = wire16;
     f.pairs = takes_pairs(ctx->cus, fused_chunk(ctx), c1 - c0, scheduled, N, wire16);
     f.update_first = update_first;

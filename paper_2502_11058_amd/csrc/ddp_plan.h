@@ -25,7 +25,8 @@ namespace ddp {
 //                       513  10.98 / 11.41   22.5 / 22.9     11.8 / 12.2
 // One line for both kernels, drawn where the average crosses; the fused step, whose workgroups have more to do, still gains at 352.
 inline bool folds(int cus, int64_t partials, int64_t most) { return 4 * partials <= 5 * (int64_t)cus && most <= 320; }
-// The fused step, whose chunks are half the size (kSmallChunk), up to 5/2 per CU with a pair.  Launch of their own / folded in us:
+// The fused step, whose chunks are half the size (kSmallChunk), up to 5/2 per CU with a pair where at least as many others hide what the
+// folding ones wait for.  Launch of their own / folded in us:
 //     8 layers, one of them scheduled, pairs      257             401             565             626
 //         SGD, N = 4                         10.6 /  9.8     15.2 / 13.4     19.7 / 18.1     21.4 / 19.6
 //         AdamW, N = 8                       14.8 / 13.7     20.5 / 18.8     28.0 / 26.1     30.6 / 28.8
@@ -33,7 +34,13 @@ inline bool folds(int cus, int64_t partials, int64_t most) { return 4 * partials
 //         SGD, N = 4                          8.9 /  7.1     10.0 /  9.8     12.5 / 12.6     13.6 / 12.5
 //         AdamW, N = 8                       10.4 / 10.5     14.0 / 14.3     18.2 / 18.0     18.8 / 17.1
 //         SGD, N = 16                        10.4 / 10.4     13.8 / 14.1     19.6 / 20.2     19.0 / 18.6
-inline bool folds_fused(int cus, int64_t partials, int64_t most) { return 2 * partials <= 5 * (int64_t)cus && most <= kFoldGroup * kFoldGroups; }
+// Where every chunk of the call has a pair, up to 5/4 as above.  12 layers, layer by layer:
+//                                pairs            479             564             625      whole chunks, 512             634
+//         SGD, N = 4                         51.2 / 52.8     57.1 / 59.5     61.1 / 63.3     77.1 / 79.4     92.5 / 94.5
+//         AdamW, N = 8                       66.7 / 68.2     79.1 / 80.5     80.7 / 83.2    109.0 / 111.2   134.8 / 137.7
+inline bool folds_fused(int cus, int64_t partials, int64_t most, int64_t chunks) {
+    return 2 * partials <= 5 * (int64_t)cus && (4 * partials <= 5 * (int64_t)cus || 2 * partials <= chunks) && most <= kFoldGroup * kFoldGroups;
+}
 
 // Where the average of N replicas cuts its chunks of `chunk` elements in two, a workgroup each (0: not).  The kernel for more than
 // 16 replicas takes the halves of a chunk one after the other; cut, one workgroup asks while another adds.  Up to 16 replicas both

@@ -82,8 +82,11 @@ int main() {
     CHECK(takes_halves(model - 1, 1, false, false) && !takes_halves(model, 1, false, false) && takes_halves(model, 1, false, true));
     // ... and a grid of less than 2^32 threads
     CHECK(halves_fit(1) && halves_fit(((int64_t)1 << 23) - 1) && !halves_fit((int64_t)1 << 23) && !halves_fit(INT32_MAX));
-    // statistics put together in the launch: 5/2 pairs per CU
-    CHECK(folds_fused(256, 640, 640) && !folds_fused(256, 641, 1) && !folds_fused(304, 641, 641) && folds_fused(304, 760, 640));
+    // statistics put together in the launch: 5/2 pairs per CU, 5/4 where less than half the call's chunks have none
+    const int64_t beside = 1 << 20;
+    CHECK(folds_fused(256, 640, 640, beside) && !folds_fused(256, 641, 1, beside) && !folds_fused(304, 641, 641, beside) && folds_fused(304, 760, 640, beside));
+    CHECK(folds_fused(256, 640, 640, 1280) && !folds_fused(256, 640, 640, 1279) && folds_fused(256, 320, 320, 320) && !folds_fused(256, 321, 321, 321));
+    CHECK(folds_fused(256, 321, 321, 642) && !folds_fused(256, 321, 321, 641) && folds_fused(304, 380, 380, 380) && !folds_fused(304, 381, 381, 381));
     std::printf("plain pieces ok: %ld calls\n", calls);
     return 0;
 }
