@@ -128,18 +128,18 @@ static int residency_pad(const ddp_ctx *c, int wg_per_cu) {
 
 // The residency request of the update, and of the fused step (fused_wg_per_cu).
 static int update_lds(const ddp_ctx *c) { return c->small && !c->update_lds_set ? 0 : c->update_lds; }
-static int fused_lds(const ddp_ctx *c, int N, bool wire16, bool adamw, int64_t elements) {
-    if (!c->halved || c->update_lds_set) return update_lds(c);
+static int fused_lds(const ddp_ctx *c, bool halved, int N, bool wire16, bool adamw, int64_t elements) {
+    if (!halved || c->update_lds_set) return update_lds(c);
     return residency_pad(c, fused_wg_per_cu(N, wire16, adamw, c->grad_dtype == DDP_BF16, elements));
 }
 
 // Elements per workgroup of the fused step.
-static int64_t fused_chunk(const ddp_ctx *c) { return c->halved ? c->run_chunk / 2 : c->run_chunk; }
+static int64_t fused_chunk(const ddp_ctx *c, bool halved) { return halved ? c->run_chunk / 2 : c->run_chunk; }
 
 // Chunks that a workgroup of the fused step takes of unscheduled layers, at its three or four workgroups per CU: with SGD, a third less
 // bytes an element, two (us, two against one: GPT-2, 5 blocks of 384, N = 6 bf16 47.0 / 49.9, 12 layers of 817^2, N = 3 32.5 / 33.2); with AdamW that would
 // be too much in flight (14 layers of 1490^2, N = 6 157.4 / 148.9, 16 of 1533^2, N = 8 220.1 / 212.3).
-static int64_t plain_chunks(const ddp_ctx *c) { return c->halved && !c->has_state1 ? 2 : 1; }
+static int64_t plain_chunks(const ddp_ctx *c, bool halved) { return halved && !c->has_state1 ? 2 : 1; }
 
 // First element of layer l in registration order (l = L: the number of elements).
 static int64_t layer_elem0(const ddp_ctx *ctx, int l) { return ctx->tensor_elem_off[(size_t)ctx->layer_first_tensor[(size_t)l]]; }
@@ -311,7 +311,7 @@ extern "C" int ddp_register_model(ddp_ctx *ctx, int L, int T, const int32_t *lay
         ctx->dense = dense;
         int64_t largest = 0;
         for (int l = 0; l < L; ++l) largest = std::max(largest, layer_elem0(ctx, l + 1) - layer_elem0(ctx, l));
-        ctx->halved = !ctx->update_chunk_set && ctx->run_chunk == 2 * kSmallChunk && takes_halves(ctx->tensor_elem_off[(size_t)T], largest, dense, has1);
+        ctx->halves = !ctx->update_chunk_set && ctx->run_chunk == 2 * kSmallChunk && takes_halves(ctx->tensor_elem_off[(size_t)T], largest, dense, has1);
 
         // Update table: every run cut into chunks of run_chunk elements that end on cache lines (kLine), so that only a run's
         // first and last chunk have elements outside a whole vector.  A run is a tensor; over dense arenas it is a whole layer,
@@ -345,7 +345,7 @@ extern "C" int ddp_register_model(ddp_ctx *ctx, int L, int T, const int32_t *lay
         }
         ctx->run_chunk_base.push_back((int32_t)uc.size());
         ctx->n_update = (int64_t)uc.size();
-        ctx->halved = ctx->halved && halves_fit(ctx->n_update);
+        ctx->halves = ctx->halves && halves_fit(ctx->n_update);
         interleave_segments(uc, ctx->dispatch_ways);
         rc = upload(ctx, runs, &ctx->d_runs);
         ctx->runs = std::move(runs);
@@ -403,26 +403,36 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
                 }
             };
             std::vector<int32_t> lcp;
-            std::vector<RunSlot> run_slot(ctx->run_chunk_base.size() - 1, RunSlot{-1, -1, {-1, 0, 0}});
+            // the fused step's plans: whole chunks, and halves behind them
+            FusedPlan *const plans[] = {&st, &st.halves};
+            const int shapes = ctx->halves ? 2 : 1;
+            const size_t n_runs = ctx->run_chunk_base.size() - 1;
+            std::vector<RunSlot> run_slot((size_t)shapes * n_runs, RunSlot{-1, -1, {-1, 0, 0}});
             int64_t off = 0;
             for (int j = set_ptr[s]; j < set_ptr[s + 1]; ++j) {
                 const int l = set_layers[j];
                 st.layers.push_back(l);
                 st.layer_begin.push_back(off);
                 lcp.push_back((int32_t)mc.size());
-                // the layer's partials in the fused step: two per chunk of the update table where that is halved, but not for what
-                // lies behind a dense layer's last half
-                const int32_t k = ctx->halved ? 2 : 1, c0 = k * ctx->run_chunk_base[(size_t)ctx->layer_first_run[(size_t)l]];
-                const int32_t c1 = ctx->dense ? c0 + (int32_t)dense_workgroups(layer_elem0(ctx, l), layer_elem0(ctx, l + 1), fused_chunk(ctx), kLine)
-                                              : k * ctx->run_chunk_base[(size_t)ctx->layer_first_run[(size_t)l + 1]];
-                st.update_ranges.push_back(c0);
-                st.update_ranges.push_back(c1);
                 st.layer_pos[(size_t)l] = (int32_t)st.layers.size() - 1;
+                // the layer's partials in the fused step: one per chunk of the update table or two per halved one, but not for what lies
+                // behind a dense layer's last half
+                LayerSums of[2];
+                for (int h = 0; h < shapes; ++h) {
+                    const int32_t k = h + 1, c0 = k * ctx->run_chunk_base[(size_t)ctx->layer_first_run[(size_t)l]];
+                    const int32_t c1 = ctx->dense ? c0 + (int32_t)dense_workgroups(layer_elem0(ctx, l), layer_elem0(ctx, l + 1), fused_chunk(ctx, h), kLine)
+                                                  : k * ctx->run_chunk_base[(size_t)ctx->layer_first_run[(size_t)l + 1]];
+                    plans[h]->update_ranges.push_back(c0);
+                    plans[h]->update_ranges.push_back(c1);
+                    plans[h]->max_update_partials = std::max<int64_t>(plans[h]->max_update_partials, c1 - c0);
+                    of[h] = {st.layer_pos[(size_t)l], c0, c1 - c0};
+                }
                 const int64_t layer_start = off;
                 for (int t = ctx->layer_first_tensor[(size_t)l]; t < ctx->layer_first_tensor[(size_t)l + 1]; ++t) {
                     st.tensors.push_back(t);
                     st.tensor_off.push_back(off);
-                    if (!ctx->dense || off == layer_start) run_slot[(size_t)(ctx->dense ? l : t)] = {off, l, {st.layer_pos[(size_t)l], c0, c1 - c0}};
+                    for (int h = 0; h < shapes && (!ctx->dense || off == layer_start); ++h)
+                        run_slot[(size_t)h * n_runs + (size_t)(ctx->dense ? l : t)] = {off, l, of[h]};
                     off += ctx->numel[(size_t)t];
                 }
                 // copy chunks: the layer's runs (over dense arenas the layer is one) cut on the lines of what is written
@@ -471,18 +481,23 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
                 mean_ranges.push_back(lcp[i + 1]);
                 st.max_mean_partials = std::max<int64_t>(st.max_mean_partials, lcp[i + 1] - lcp[i]);
             }
-            for (size_t i = 0; i + 1 < st.update_ranges.size(); i += 2)
-                st.max_update_partials = std::max<int64_t>(st.max_update_partials, st.update_ranges[i + 1] - st.update_ranges[i]);
             if (rc == DDP_OK) rc = upload(ctx, mean_ranges, &st.d_layer_ranges);
+            std::vector<int32_t> update_ranges = st.update_ranges;
+            update_ranges.insert(update_ranges.end(), st.halves.update_ranges.begin(), st.halves.update_ranges.end());
             if (rc == DDP_OK) rc = upload(ctx, run_slot, &st.d_run_slot);
-            if (rc == DDP_OK) rc = upload(ctx, st.update_ranges, &st.d_update_ranges);
-            if (ctx->dense) plan_dense(st, ctx->L, [&](int l) { return layer_elem0(ctx, l); }, fused_chunk(ctx), kLine, plain_chunks(ctx));
+            if (rc == DDP_OK) rc = upload(ctx, update_ranges, &st.d_update_ranges);
+            if (rc == DDP_OK && ctx->halves) {
+                st.halves.d_run_slot = st.d_run_slot + n_runs;
+                st.halves.d_update_ranges = st.d_update_ranges ? st.d_update_ranges + st.update_ranges.size() : nullptr;
+            }
+            for (int h = 0; h < shapes && ctx->dense; ++h)
+                plan_dense(*plans[h], st, ctx->L, [&](int l) { return layer_elem0(ctx, l); }, fused_chunk(ctx, h), kLine, plain_chunks(ctx, h));
             if (rc != DDP_OK) {
                 for (auto &x : slots) free_slot(x);
                 return rc;
             }
         }
-        const int64_t max_pairs = std::max(max_mean_pairs, (ctx->halved ? 2 : 1) * ctx->n_update);  // the fused step keeps one per workgroup
+        const int64_t max_pairs = std::max(max_mean_pairs, (ctx->halves ? 2 : 1) * ctx->n_update);  // the fused step keeps one per workgroup
         if (max_pairs > 0) {
             const size_t line = kFoldLine * sizeof(int32_t) / sizeof(double);  // the counters start on a cache line
             const size_t sums = (((size_t)max_pairs + (size_t)ctx->L * kStatSlices) * 2 + line - 1) / line * line;
@@ -790,19 +805,19 @@ extern "C" int ddp_local_update_layers(ddp_ctx *ctx, int layer_first, int layer_
 }
 
 // The kernels of the fused step over elements [e0, e1), whole layers, of a model registered as dense arenas; `at`: the first launch.
-static int fused_dense(const ddp_ctx *ctx, const SlotTables &st, std::vector<DensePass>::const_iterator at, int64_t e0, int64_t e1,
+static int fused_dense(const ddp_ctx *ctx, const FusedPlan &plan, bool halved, std::vector<DensePass>::const_iterator at, int64_t e0, int64_t e1,
                        const FusedLaunch &common, void *stream) {
     FusedDense f;
     static_cast<FusedLaunch &>(f) = common;
     const TensorDesc &t0 = ctx->tensors[0];
-    f.d = {t0.grad, t0.sync, t0.state0, t0.state1, t0.model, 0, (int)fused_chunk(ctx), 0};
-    f.plain = (int)(plain_chunks(ctx) * fused_chunk(ctx));
+    f.d = {t0.grad, t0.sync, t0.state0, t0.state1, t0.model, 0, (int)fused_chunk(ctx, halved), 0};
+    f.plain = (int)(plain_chunks(ctx, halved) * fused_chunk(ctx, halved));
     int rc = 0;
-    for (; at != st.dense_passes.end() && at->begin < e1 && rc == 0; ++at) {
+    for (; at != plan.dense_passes.end() && at->begin < e1 && rc == 0; ++at) {
         DensePass part;
         f.pass = &*at;
         if (at->begin < e0 || at->end > e1) {
-            clip_pass(*at, e0, e1, fused_chunk(ctx), part, kLine, plain_chunks(ctx));
+            clip_pass(*at, e0, e1, fused_chunk(ctx, halved), part, kLine, plain_chunks(ctx, halved));
             f.pass = &part;
         }
         if (f.pass->width > 0) {
@@ -852,21 +867,25 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     }
     // Statistics: one reduction per run of consecutive slot positions inside the range (a schedule in backward order gives a
     // single run).
+    const bool adamw = opt->kind == DDP_OPT_ADAMW;
+    const bool halved = ctx->halves && call_takes_halves(ctx->cus, layer_elem0(ctx, ctx->L), ctx->dense, N, wire16, adamw, ctx->grad_dtype == DDP_BF16);
+    const FusedPlan &plan = halved ? st->halves : *st;
+    const int64_t chunks = (halved ? 2 : 1) * (c1 - c0);
     const int nl = (int)st->layers.size();
     auto inside = [&](int i) { return i < nl && st->layers[(size_t)i] >= first && st->layers[(size_t)i] < first + count; };
     int64_t scheduled = 0, most = 0;  // chunks of the slot's layers in the range, each of which has a pair of partial sums
     for (int i = 0; i < nl; ++i)
         if (inside(i)) {
-            const int64_t n = st->update_ranges[2 * (size_t)i + 1] - st->update_ranges[2 * (size_t)i];
+            const int64_t n = plan.update_ranges[2 * (size_t)i + 1] - plan.update_ranges[2 * (size_t)i];
             scheduled += n;
             most = std::max(most, n);
         }
     const bool any = layer_stats && scheduled > 0;
     // One order of summation for a slot, whatever range the call has: the workgroups add a layer's partials up in the order of
     // the one-launch reduction, so they do it only in slots that this reduction serves.
-    const bool fold = any && st->max_update_partials <= kStatSingleMax && folds_fused(ctx->cus, scheduled, most, (ctx->halved ? 2 : 1) * (c1 - c0));
+    const bool fold = any && plan.max_update_partials <= kStatSingleMax && folds_fused(ctx->cus, scheduled, most, chunks);
     f.wire16 = wire16;
-    f.pairs = takes_pairs(ctx->cus, fused_chunk(ctx), c1 - c0, scheduled, N, wire16);
+    f.pairs = takes_pairs(ctx->cus, fused_chunk(ctx, halved), c1 - c0, scheduled, N, wire16);
     f.update_first = update_first;
     f.n_replicas = N;
     f.local_rank = local_rank;
@@ -877,28 +896,28 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     f.s = s;
     f.st = {any ? ctx->d_partials : nullptr, layer_stats, fold ? ctx->d_counters : nullptr};
     const int64_t e0 = layer_elem0(ctx, first), e1 = layer_elem0(ctx, first + count);
-    f.lds_pad = fused_lds(ctx, N, wire16, opt->kind == DDP_OPT_ADAMW, e1 - e0);
-    const auto at = first_pass(*st, e0);
-    if (ctx->dense_path && takes_pieces(*st, at, e1)) {
-        rc = fused_dense(ctx, *st, at, e0, e1, f, stream);
+    f.lds_pad = fused_lds(ctx, halved, N, wire16, adamw, e1 - e0);
+    const auto at = first_pass(plan, e0);
+    if (ctx->dense_path && takes_pieces(plan, at, e1)) {
+        rc = fused_dense(ctx, plan, halved, at, e0, e1, f, stream);
     } else if (scheduled == 0) {
         rc = launch_update(f.kind, ctx->grad_dtype, f.with_model, ctx->d_runs, ctx->d_update + c0, c1 - c0, s, true, update_lds(ctx), stream);
     } else {
         f.runs = ctx->d_runs;
         f.chunks = ctx->d_update + c0;
         f.n_chunks = c1 - c0;
-        f.run_slot = st->d_run_slot;
+        f.run_slot = plan.d_run_slot;
         f.run_chunk_base = ctx->d_run_chunk_base;
         f.chunk_elems = (int)ctx->run_chunk;
-        f.halved = ctx->halved;
+        f.halved = halved;
         rc = launch_fused(f, stream);
     }
     for (int i = 0; any && !fold && i < nl && rc == 0;) {
         int j = i;
         while (inside(j)) ++j;
         if (j > i)
-            rc = launch_stats(f.st.partials, ctx->d_slice_sums + (int64_t)i * 2 * kStatSlices, st->d_update_ranges + 2 * i, 1, j - i, N,
-                              layer_stats + 2 * i, st->max_update_partials, stream);
+            rc = launch_stats(f.st.partials, ctx->d_slice_sums + (int64_t)i * 2 * kStatSlices, plan.d_update_ranges + 2 * i, 1, j - i, N,
+                              layer_stats + 2 * i, plan.max_update_partials, stream);
         i = j + 1;
     }
     return after_launch(ctx, who, rc);

@@ -111,7 +111,17 @@ struct DensePass {
     Piece pieces[kMaxPieces];
 };
 
-struct SlotTables {
+// A slot as the fused step cuts it, in one of its two sizes of chunk.
+struct FusedPlan {
+    RunSlot *d_run_slot = nullptr;         // per run of the update table
+    std::vector<int32_t> update_ranges;    // per layer of the slot: [first, last) chunk of the fused step (registration order), whose
+    int32_t *d_update_ranges = nullptr;    // places its partials have, table-driven or table-free
+    int64_t max_update_partials = 0;       // largest count of a layer
+    std::vector<DensePass> dense_passes;   // dense arenas: the launches of the fused step over the whole model
+    bool table_first = false;              // ... for which the table's single launch is the better one
+};
+
+struct SlotTables : FusedPlan {  // (the plan in the update table's own chunks)
     // host copies (introspection, validation)
     std::vector<int32_t> layers;       // layer ids in flat order
     std::vector<int64_t> layer_begin;  // n_layers + 1 flat offsets
@@ -126,13 +136,9 @@ struct SlotTables {
     MeanChunk *d_mean = nullptr;
     int64_t n_mean = 0;
     int32_t *d_layer_ranges = nullptr;     // per layer of the slot: [first, last) mean chunk
-    RunSlot *d_run_slot = nullptr;         // per run of the update table
-    std::vector<int32_t> update_ranges;    // per layer of the slot: [first, last) chunk of the fused step (registration order), whose
-    int32_t *d_update_ranges = nullptr;    // places its partials have, table-driven or table-free
-    int64_t max_mean_partials = 0, max_update_partials = 0;  // largest per-layer count of each range table
-    std::vector<int32_t> layer_pos;  // [L] layer -> position in this slot, -1 if not scheduled
-    std::vector<DensePass> dense_passes;  // dense arenas: the launches of the fused step over the whole model
-    bool table_first = false;             // ... for which the table's single launch is the better one
+    int64_t max_mean_partials = 0;         // largest count of a layer
+    std::vector<int32_t> layer_pos;        // [L] layer -> position in this slot, -1 if not scheduled
+    FusedPlan halves;                      // ... and in halves of those chunks (ddp_ctx::halves); its device tables lie behind the others
 };
 
 // Counters of a layer whose workgroups add the statistics up themselves, in 32-bit words: one per group of kFoldGroup partials
@@ -252,7 +258,7 @@ struct ddp_ctx {
     // model
     bool registered = false;
     int64_t run_chunk = 2048;  // elements per chunk of the update table and the table-free kernels: update_chunk, or small_model's
-    bool halved = false;       // the fused step has a workgroup for each half of such a chunk (takes_halves)
+    bool halves = false;       // the fused step may have a workgroup for each half of such a chunk (takes_halves, call_takes_halves)
     bool small = false;
     int L = 0, T = 0;
     int param_dtype = DDP_F32, grad_dtype = DDP_F32;

@@ -110,14 +110,52 @@ inline bool takes_pairs(int cus, int64_t chunk, int64_t all, int64_t scheduled, 
     return wire16 && N > 8 && N <= 32 && chunk >= 2048 && scheduled >= 3 * (int64_t)cus && 2 * all >= 9 * (int64_t)cus;
 }
 
-// Whether the fused step has a workgroup for each half (kSmallChunk elements) of a chunk of the update table.  With whole chunks a
-// thread's second vector of all streams waits for what the first one's sum and step leave behind; see fused_wg_per_cu for what that is
-// worth.  Not in models with layers of 128 M elements and more, whose long launches run best with the fewest rows in flight (whole / halves, us:
-// blocks of 4096, 11008, AdamW, N = 8, fused 11121 / 11277, layer by layer 11165 / 11362, N = 4 9550 / 9709; blocks of 2048, 5632, N = 8 6209 / 6178, bf16 5589 /
-// 5558), nor over separate tensors with SGD from 16 M elements on, where unscheduled layers want whole chunks and a slot's calls one order
-// of summation (GPT-2 small, N = 8 538 / 557, 13 blocks of 1536 1691 / 1746, 12 layers of 1378^2, N = 16 bf16 112 / 117; 11 blocks of 128, N = 6 bf16 15.9 / 15.2).
+// Whether a model's fused step may have a workgroup for each half (kSmallChunk elements) of a chunk of the update table, if the call asks
+// for it (call_takes_halves).  With whole chunks a thread's second vector of all streams waits for what the first one's sum and step leave
+// behind.  Not in models with layers of 128 M elements and more, whose long launches run best with the fewest rows in flight.  The line is
+// flat: whole / halves and three per CU, us, four layers of 81, 100, 130 and 160 M, one scheduled:
+//     AdamW, N = 4       1622 / 1623   2056 / 2044   2628 / 2630   3212 / 3233
+//     AdamW, N = 8       1865 / 1854   2376 / 2395   2987 / 3067   3666 / 3683
+//     SGD, N = 8         1467 / 1462   1809 / 1789   2401 / 2393   2914 / 2882
+// and beyond it: blocks of 4096, 11008 (layers of 202 M and 131 M), AdamW, N = 8 11121 / 11277, layer by layer 11165 / 11362, N = 4 9550 / 9709.
+// One such layer decides for the whole model: eight blocks of 20 M beside an embedding of 150 M, N = 8, SGD 1283 / 1283, AdamW
+// 1650 / 1650, bf16 peers 1511 / 1502, so nothing is to be had from choosing launch by launch.  Nor over separate tensors with SGD from 16 M elements
+// on, where unscheduled layers want whole chunks (GPT-2 small, N = 8 538 / 557, 13 blocks of 1536 1691 / 1746, 12 layers of 1378^2, N = 16 bf16 112 / 117).
 inline bool takes_halves(int64_t numel, int64_t largest_layer, bool dense, bool second_moment) {
     return largest_layer < (int64_t)1 << 27 && (dense || second_moment || numel < (int64_t)1 << 24);
+}
+
+// Bytes that a thread of the fused step asks for with one vector of all streams.
+inline int vector_bytes(int N, bool wire16, bool adamw, bool grad16) { return (wire16 ? 8 : 16) * (N - 1) + (adamw ? 48 : 32) + (grad16 ? 8 : 16); }
+
+// Whether a call on a slot of such a model, or on a range of its layers, takes halves: one answer for all of a worker's calls, whatever the
+// range, so that a slot's statistics have one order of summation.  Halves have more in flight, whole chunks fewer workgroups to start
+// and half the partial sums, which decides in models of a few chunks (2048 elements) per CU as long as a vector is small.
+// Fused step, whole chunks and two workgroups per CU / halves and three, us, dense arenas, a quarter or a fifth of the layers scheduled:
+//         chunks per CU               4.8 (12 x 460^2)   5.4 (5 x 750^2)   7.7 (12 x 580^2)   9.4 (12 x 640^2)  13.2 (12 x 760^2)  18.6 (12 x 900^2)
+//     AdamW, N =  4, fp32 (104 bytes)    14.7 / 14.8       15.4 / 15.1       22.5 / 25.0        26.5 / 28.5        38.1 / 39.3        51.9 / 51.8
+//     AdamW, N =  8, fp32 (168)          18.3 / 16.6       17.8 / 17.1       26.1 / 28.6        32.0 / 32.2        43.3 / 44.6        58.7 / 58.7
+//     AdamW, N =  8, bf16 (112)          15.8 / 15.5       16.4 / 16.1       23.1 / 25.3        27.2 / 29.2        38.8 / 39.3        53.4 / 53.0
+//     AdamW, N = 16, bf16 (176)          19.9 / 18.4       20.7 / 19.1       27.1 / 29.1        32.7 / 33.7        45.0 / 44.9        61.7 / 61.7
+//     AdamW, N = 16, fp32 (296)          23.4 / 21.3       23.7 / 22.2       32.6 / 34.8        41.9 / 39.3        53.6 / 54.6        76.7 / 73.5
+//     SGD,   N =  2, fp32 (64)           10.3 / 10.4       10.8 / 11.1       15.1 / 17.3        18.3 / 19.7        26.2 / 26.1        35.3 / 35.2
+//     SGD,   N =  4, fp32 (96)           10.9 / 10.5       11.3 / 11.5       16.3 / 18.2        19.5 / 20.9        28.0 / 28.0        37.9 / 37.8
+//     SGD,   N =  8, fp32 (160)          13.8 / 12.5       14.1 / 12.9       19.4 / 21.2        24.2 / 24.3        33.5 / 33.0        44.6 / 44.6
+//     SGD,   N = 16, fp32 (288)          18.8 / 17.5       20.0 / 17.8       26.4 / 27.7        34.4 / 31.7        44.6 / 43.6        61.9 / 59.9
+// So whole chunks from 6 to 10 chunks per CU, up to 200 bytes a vector, and with SGD below 6 too up to 120 bytes (in models of less than 5/4
+// chunks per CU halves: 12 layers of 200^2, N = 4 4.9 / 4.9, N = 16 7.3 / 6.4).  Layer by layer the halves would be the better ones with AdamW,
+// 640^2, N = 4 58.8 / 58.1, N = 8 63.8 / 61.9, but what the whole-model call gains is more; beyond 10 it is less, and four workgroups per CU
+// give most of it (fused_wg_per_cu).  Over separate tensors with SGD, where the unscheduled layers come in halves too, whole chunks from
+// 5/4 on: N = 8 5.4 per CU 14.3 / 14.3, 7.2 18.3 / 20.7, 18.6 44.6 / 45.8, bf16 39.6 / 41.2, 27.7 58.2 / 60.8, N = 16 24.8 / 27.7 and 88.0 / 89.7; but
+// halves for the largest vectors (N = 24, 9.4 per CU 45.2 / 41.9, 14.7 63.1 / 60.5) and, from 10 on, the smallest, at four per CU (N = 2, 18.6 35.2 / 35.0,
+// bf16 27.7 50.9 / 50.4).
+inline bool call_takes_halves(int cus, int64_t numel, bool dense, int N, bool wire16, bool adamw, bool grad16) {
+    const int64_t chunks = (numel + 2047) / 2048, bytes = vector_bytes(N, wire16, adamw, grad16);
+    const bool below_6 = chunks < 6 * (int64_t)cus, below_10 = chunks < 10 * (int64_t)cus;
+    if (adamw) return below_6 || !below_10 || bytes >= 200;
+    if (4 * chunks <= 5 * (int64_t)cus || bytes >= 300) return true;
+    if (below_10) return dense && bytes >= (below_6 ? 120 : 200);
+    return dense || bytes < 96;
 }
 
 // A launch has less than 2^32 threads in x (hipErrorInvalidConfiguration from there on, measured: 2^24 - 1 workgroups of 256 run, 2^24 are
@@ -178,7 +216,7 @@ inline void add_pieces(DensePass &p, int64_t begin, int64_t end, int64_t flat0, 
 // No passes where a launch would need more than kMaxPieces pieces: such a slot always takes the table.
 // `plain`: chunks that a workgroup of an unscheduled piece takes.
 template <class Elem0>
-void plan_dense(SlotTables &st, int L, Elem0 &&elem0, int64_t chunk, int64_t line, int64_t plain = 1) {
+void plan_dense(FusedPlan &plan, const SlotTables &st, int L, Elem0 &&elem0, int64_t chunk, int64_t line, int64_t plain = 1) {
     constexpr int kMaxSegments = 20;
     struct Segment {
         int64_t begin, end, flat0, pbase, chunk, wg;
@@ -190,13 +228,13 @@ void plan_dense(SlotTables &st, int L, Elem0 &&elem0, int64_t chunk, int64_t lin
         const int i = st.layer_pos[(size_t)l];
         int m = l + 1;
         while (i < 0 && m < L && st.layer_pos[(size_t)m] < 0) ++m;
-        all.push_back({elem0(l), elem0(m), i < 0 ? -1 : st.layer_begin[(size_t)i], i < 0 ? 0 : st.update_ranges[2 * (size_t)i],
+        all.push_back({elem0(l), elem0(m), i < 0 ? -1 : st.layer_begin[(size_t)i], i < 0 ? 0 : plan.update_ranges[2 * (size_t)i],
                        i < 0 ? plain * chunk : chunk, 0, l, {i, 0, 0}});
         all.back().wg = dense_workgroups(elem0(l), elem0(m), all.back().chunk, line);
-        if (i >= 0) all.back().of = {i, st.update_ranges[2 * (size_t)i], st.update_ranges[2 * (size_t)i + 1] - st.update_ranges[2 * (size_t)i]};
+        if (i >= 0) all.back().of = {i, plan.update_ranges[2 * (size_t)i], plan.update_ranges[2 * (size_t)i + 1] - plan.update_ranges[2 * (size_t)i]};
         l = m;
     }
-    std::vector<DensePass> &passes = st.dense_passes;
+    std::vector<DensePass> &passes = plan.dense_passes;
     constexpr int64_t kAlone = (int64_t)3 << 23, kPerLaunch = (int64_t)1 << 24;  // 25 M; elements that a launch more is worth
     auto group = [&](size_t k) {  // segments that share the launch of segment k, the first one of it
         size_t n = 1;
@@ -206,7 +244,7 @@ void plan_dense(SlotTables &st, int L, Elem0 &&elem0, int64_t chunk, int64_t lin
     };
     int64_t shared = 0;
     for (size_t k = 0; k < all.size(); k += group(k)) shared += all[k].end - all[k].begin < kAlone;
-    st.table_first = all.back().end - all[0].begin < (shared - 1) * kPerLaunch;
+    plan.table_first = all.back().end - all[0].begin < (shared - 1) * kPerLaunch;
     const int64_t widest = widest_piece(plain * chunk);
     for (size_t i = 0; i < all.size();) {
         const Segment *seg = &all[i];
@@ -242,16 +280,20 @@ void plan_dense(SlotTables &st, int L, Elem0 &&elem0, int64_t chunk, int64_t lin
             add_pieces(p, seg[k].begin, seg[k].end, seg[k].flat0, seg[k].pbase, seg[k].layer, seg[k].of, width, seg[k].chunk, line);
     }
 }
+template <class Elem0>
+void plan_dense(SlotTables &st, int L, Elem0 &&elem0, int64_t chunk, int64_t line, int64_t plain = 1) {
+    plan_dense(st, st, L, elem0, chunk, line, plain);
+}
 
 // The first launch that has elements from e0 on.
-inline std::vector<DensePass>::const_iterator first_pass(const SlotTables &st, int64_t e0) {
-    return std::upper_bound(st.dense_passes.begin(), st.dense_passes.end(), e0, [](int64_t e, const DensePass &p) { return e < p.end; });
+inline std::vector<DensePass>::const_iterator first_pass(const FusedPlan &plan, int64_t e0) {
+    return std::upper_bound(plan.dense_passes.begin(), plan.dense_passes.end(), e0, [](int64_t e, const DensePass &p) { return e < p.end; });
 }
 
 // Whether a call on elements up to e1 whose first launch is `at` runs pieces: where the table is better for the slot, if one
 // launch does it.
-inline bool takes_pieces(const SlotTables &st, std::vector<DensePass>::const_iterator at, int64_t e1) {
-    return at != st.dense_passes.end() && (!st.table_first || at->end >= e1);
+inline bool takes_pieces(const FusedPlan &plan, std::vector<DensePass>::const_iterator at, int64_t e1) {
+    return at != plan.dense_passes.end() && (!plan.table_first || at->end >= e1);
 }
 
 // What a call on elements [e0, e1), whole layers, runs of launch p: the pieces inside, runs of unscheduled layers cut at the

@@ -80,6 +80,22 @@ int main() {
     const int64_t layer = (int64_t)1 << 27, model = (int64_t)1 << 24;
     CHECK(takes_halves(1, 1, true, false) && takes_halves(100 * layer, layer - 1, true, false) && !takes_halves(layer, layer, true, true));
     CHECK(takes_halves(model - 1, 1, false, false) && !takes_halves(model, 1, false, false) && takes_halves(model, 1, false, true));
+    // ... in calls as measured: whole chunks from 6 to 10 chunks of 2048 per CU for vectors of less than 200 bytes, with SGD below 6 too for less than
+    // 120; over separate tensors with SGD from 5/4 on, but for vectors of 300 bytes and more and, from 10 on, of less than 96
+    const int64_t per = 256 * 2048;
+    for (bool dense : {true, false}) {
+        CHECK(call_takes_halves(256, 6 * per - 2048, dense, 4, false, true, true) && !call_takes_halves(256, 6 * per, dense, 4, false, true, true));
+        CHECK(!call_takes_halves(256, 10 * per - 2048, dense, 4, false, true, true) && call_takes_halves(256, 10 * per, dense, 4, false, true, true));
+        CHECK(!call_takes_halves(256, 8 * per, dense, 9, false, true, true) && call_takes_halves(256, 8 * per, dense, 10, false, true, true));     // 184, 200 bytes
+        CHECK(!call_takes_halves(256, 8 * per, dense, 18, true, true, true) && call_takes_halves(256, 8 * per, dense, 19, true, true, true));      // 192, 200
+        CHECK(call_takes_halves(256, per * 5 / 4, dense, 4, false, false, false) && !call_takes_halves(256, per * 5, dense, 4, false, false, false));
+        CHECK(!call_takes_halves(256, 10 * per - 2048, dense, 5, false, false, false) && call_takes_halves(256, 10 * per, dense, 4, true, false, false));
+        CHECK(call_takes_halves(256, 5 * per, dense, 32, false, false, false) && call_takes_halves(256, 9 * per, dense, 18, false, false, false));  // 544, 320
+    }
+    CHECK(!call_takes_halves(256, 5 * per, true, 5, false, false, false) && call_takes_halves(256, 5 * per, true, 6, false, false, false));          // 112, 128
+    CHECK(!call_takes_halves(256, 6 * per, true, 10, false, false, false) && call_takes_halves(256, 6 * per, true, 11, false, false, false));       // 192, 208
+    CHECK(call_takes_halves(256, 10 * per, true, 16, false, false, false) && !call_takes_halves(256, 10 * per, false, 16, false, false, false));    // 288
+    CHECK(call_takes_halves(256, 10 * per, false, 3, false, false, false) && !call_takes_halves(256, 10 * per, false, 4, false, false, false));     // 80, 96
     // ... and a grid of less than 2^32 threads
     CHECK(halves_fit(1) && halves_fit(((int64_t)1 << 23) - 1) && !halves_fit((int64_t)1 << 23) && !halves_fit(INT32_MAX));
     // statistics put together in the launch: 5/2 pairs per CU, 5/4 where less than half the call's chunks have none
