@@ -128,9 +128,9 @@ static int residency_pad(const ddp_ctx *c, int wg_per_cu) {
 
 // The residency request of the update, and of the fused step (fused_wg_per_cu).
 static int update_lds(const ddp_ctx *c) { return c->small && !c->update_lds_set ? 0 : c->update_lds; }
-static int fused_lds(const ddp_ctx *c, bool halved, int N, bool wire16, bool adamw, int64_t elements) {
+static int fused_lds(const ddp_ctx *c, bool halved, int N, bool wire16, bool adamw, int64_t elements, int64_t halves) {
     if (!halved || c->update_lds_set) return update_lds(c);
-    return residency_pad(c, fused_wg_per_cu(N, wire16, adamw, c->grad_dtype == DDP_BF16, elements));
+    return residency_pad(c, fused_wg_per_cu(c->cus, c->dense, N, wire16, adamw, c->grad_dtype == DDP_BF16, elements, halves));
 }
 
 // Elements per workgroup of the fused step.
@@ -896,7 +896,7 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     f.s = s;
     f.st = {any ? ctx->d_partials : nullptr, layer_stats, fold ? ctx->d_counters : nullptr};
     const int64_t e0 = layer_elem0(ctx, first), e1 = layer_elem0(ctx, first + count);
-    f.lds_pad = fused_lds(ctx, halved, N, wire16, adamw, e1 - e0);
+    f.lds_pad = fused_lds(ctx, halved, N, wire16, adamw, e1 - e0, chunks);
     const auto at = first_pass(plan, e0);
     if (ctx->dense_path && takes_pieces(plan, at, e1)) {
         rc = fused_dense(ctx, plan, halved, at, e0, e1, f, stream);

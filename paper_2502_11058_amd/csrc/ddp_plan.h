@@ -162,27 +162,42 @@ inline bool call_takes_halves(int cus, int64_t numel, bool dense, int N, bool wi
 // refused).  The table-driven fused step over all n_update chunks of a model, a workgroup for each half: up to 17 G elements.
 inline bool halves_fit(int64_t n_update) { return 2 * n_update < (int64_t)1 << 24; }
 
-// Workgroups per CU that the fused step of N replicas asks for where each takes half a chunk of the update table, kSmallChunk elements,
-// one vector of all streams a thread: four where that vector is at most 96 bytes, else three.  Whole chunks and two workgroups per CU /
-// halves and three / halves and four, us, 12 layers of 1536^2, a third of them scheduled:
-//     N =  2, bf16, SGD    (56 bytes)     97.4 /  99.6 /  94.1        AdamW   (64)    135.1 / 131.7 / 130.5
-//     N =  3, bf16, SGD    (64)          106.6 / 103.8 /  97.8        AdamW   (72)    145.6 / 137.7 / 135.0
-//     N =  4, fp32, SGD    (96)          109.3 / 109.6 / 109.8        AdamW  (104)    149.5 / 144.9 / 146.5
-//     N =  8, fp32, SGD   (160)          135.5 / 135.0 / 136.6        AdamW  (168)    175.7 / 171.7 / 177.5
-//     N =  8, bf16, SGD   (104)          112.8 / 115.8 / 121.2        AdamW  (112)    152.8 / 150.0 / 154.3
-//     N = 16, fp32, SGD   (288)          189.1 / 187.5 / 188.1        AdamW  (296)    229.3 / 230.0 / 234.0
-//     N = 24, bf16, SGD   (232)          175.5 / 166.8 / 169.7        AdamW  (240)    215.9 / 205.4 / 211.2
-// and with every layer scheduled, layer by layer, N = 8: 1448^2 22.1 / 21.1 / 21.2, 2048^2 41.4 / 39.4 / 39.8, 2500^2 60.6 / 59.0 / 59.3.
-// Two in calls on 64 M elements and more of 16 and more fp32 replicas, whose three would have over 200 KB in flight per CU.  Whole chunks
-// and two / halves and three / halves and two, 10 layers:
-//                    1536^2                3000^2                4096^2
-//     N = 16, SGD    157 / 150 / 151       588 / 585 / 582       1085 / 1090 / 1033
-//     N = 16, AdamW  185 / 187 / 197       709 / 708 / 702       1285 / 1297 / 1258
-//     N = 24, SGD    195 / 192 / 193       759 / 748 / 741       1368 / 1384 / 1318
-//     N = 32, AdamW  278 / 272 / 280      1079 / 1063 / 1055     1933 / 1908 / 1880       (N = 12, AdamW 164 / 164 / 180, 1132 / 1140 / 1157)
-inline int fused_wg_per_cu(int N, bool wire16, bool adamw, bool grad16, int64_t elements) {
-    if (!wire16 && N >= 16 && elements >= (int64_t)1 << 26) return 2;
-    return (wire16 ? 8 : 16) * (N - 1) + (adamw ? 48 : 32) + (grad16 ? 8 : 16) <= 96 ? 4 : 3;
+// Workgroups per CU that a fused step on `elements` elements asks for where a workgroup takes half a chunk of the update table, kSmallChunk
+// elements, one vector of all streams a thread, and the call has `halves` of them.  Halves and three / halves and four, us, 12 layers, a quarter of them scheduled,
+// dense arenas:
+//                             bytes    1024^2           1536^2           2304^2           3600^2
+//     SGD,   N =  2, bf16       56    44.2 /  42.8     94.8 /  92.7    210.4 / 205.1    520.7 /  512.8
+//     SGD,   N =  2, fp32       64    44.8 /  44.0     97.5 /  95.4    215.6 / 213.2    527.5 /  523.3
+//     SGD,   N =  3, fp32       80    46.0 /  45.4    100.0 /  99.1    220.6 / 219.3    540.3 /  545.3
+//     SGD,   N =  6, bf16       88    47.4 /  46.8    102.6 / 102.0    227.5 / 225.4    566.6 /  562.0
+//     SGD,   N =  4, fp32       96    47.7 /  47.6    103.6 / 103.8    230.9 / 232.7    563.9 /  574.7
+//     SGD,   N =  8, fp32      160    56.7 /  57.2    124.3 / 124.3    275.0 / 279.1    678.3 /  687.2
+//     AdamW, N =  2, bf16       64    60.0 /  60.3    129.0 / 130.0    291.5 / 291.5    717.8 /  725.8
+//     AdamW, N =  3, bf16       64    62.7 /  62.0    135.5 / 133.9    299.5 / 295.1    734.1 /  728.0
+//     AdamW, N =  2, fp32       72    61.2 /  61.9    131.0 / 132.1    293.7 / 294.9    725.4 /  729.1
+//     AdamW, N =  4, bf16       72    62.5 /  62.7    133.2 / 134.7    298.8 / 299.8    743.5 /  746.5
+//     AdamW, N =  8, fp32      168    74.7 /  75.5    159.5 / 165.0    356.1 / 360.4    878.5 /  887.3
+// So four with SGD and less than 96 bytes a vector, with AdamW, a third more bytes to write, for three bf16 replicas; else three.
+// Four also in short AdamW calls, of 6 to 24 chunks (2048 elements) per CU, which are too few rounds of workgroups for three:
+//     580^2 (7.7), N = 24, bf16 33.6 / 33.4, 640^2 (9.4), N = 12 36.0 / 35.6, N = 24, bf16 38.7 / 37.1, 760^2 (13.2), N = 4 39.3 / 38.9, N = 8 44.6 / 44.1,
+//     N = 16, bf16 44.9 / 44.4, 900^2 (18.6), N = 8, bf16 53.0 / 52.6, 5 layers of 1100^2 (11.6), N = 8, bf16 34.4 / 33.6; below, 460^2 (4.8), N = 8
+//     16.6 / 17.6, 5 of 750^2 (5.4), N = 6 16.5 / 17.1
+// and where the call is then one round: layer by layer, 1024^2, SGD, N = 8 86.5 / 84.9, bf16, N = 12 90.3 / 87.7, AdamW, N = 8 109.9 / 108.3.
+// Two over dense arenas in calls on 64 M elements and more of 16 to 32 fp32 replicas, whose three would have over 200 KB in flight per CU.
+// Halves and three / halves and two, 10 layers:
+//                    1536^2          3000^2          4096^2
+//     N = 16, SGD    150 / 151       585 / 582      1090 / 1033
+//     N = 16, AdamW  187 / 197       708 / 702      1297 / 1258
+//     N = 24, SGD    192 / 193       748 / 741      1384 / 1318
+//     N = 32, AdamW  272 / 280      1063 / 1055     1908 / 1880       (N = 12, AdamW 164 / 180, 1140 / 1157)
+// (more replicas, through LDS: 12 of 3600^2, N = 40, SGD 1579 / 1769, N = 64 2953 / 3920; separate tensors, N = 16, AdamW, 12 of 3000^2 775 / 798, 12 of
+// 6500^2 3728 / 3819).
+inline int fused_wg_per_cu(int cus, bool dense, int N, bool wire16, bool adamw, bool grad16, int64_t elements, int64_t halves) {
+    if (dense && !wire16 && N >= 16 && N <= 32 && elements >= (int64_t)1 << 26) return 2;
+    if (halves > 3 * (int64_t)cus && halves <= 4 * (int64_t)cus) return 4;
+    const int64_t chunks = (elements + 2047) / 2048;
+    if (adamw) return (N == 3 && wire16) || (chunks >= 6 * (int64_t)cus && chunks < 24 * (int64_t)cus) ? 4 : 3;
+    return vector_bytes(N, wire16, adamw, grad16) < 96 ? 4 : 3;
 }
 
 // Workgroups of the table-free fused kernel over elements [e0, e1) of the arenas: chunks counted from the multiple of `line`
