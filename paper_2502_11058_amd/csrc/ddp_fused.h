@@ -191,12 +191,17 @@ __device__ __forceinline__ void fused_body(const Streams<GBF16> c, int64_t fo, c
         // 226^2, N = 32 bf16 16.3 / 9.7, 5 of 282^2, AdamW, N = 6 7.2 / 6.3, 15 of 166^2, AdamW, N = 24 13.7 / 11.2 (all at once 9.8, but the scalar
         // registers that the kernels for 17 to 31 spill then cost 10 layers of 3000^2 845 / 850), N = 40 27.6 / 23.1.
         constexpr bool kTogether = NREP > 1 && (EXACT || NREP <= 16);
+        // The table-driven kernels of 9 and more replicas read the peers' pointers again: kept over the vector loop, for a handful of elements, they
+        // made up to 94 scalar registers spill (12 layers of 2304^2, separate tensors, bf16 peers, us kept / read again: SGD, N = 12 269.1 / 262.0,
+        // N = 32 387.0 / 373.2, layer by layer 441.0 / 418.5).  The table-free ones keep them without, and read again a short call is slower (15 layers
+        // of 166^2, AdamW, N = 32 bf16 9.2 / 9.9).
+        constexpr bool kAgain = !BUF && NREP >= 16;
         xelem peer[kTogether ? NREP - 1 : 1];
         if constexpr (kTogether) {
 #pragma unroll
             for (int j = 0; j < NREP - 1; ++j) {
                 peer[j] = xelem{};
-                if (j < kPeersAlways<NREP, EXACT> || j < nrep - 1) peer[j] = ld1(reinterpret_cast<const xelem *>(a.x[j]) + fo, i);
+                if (j < kPeersAlways<NREP, EXACT> || j < nrep - 1) peer[j] = ld1(reinterpret_cast<const xelem *>(a.x[kAgain ? fresh(j) : j]) + fo, i);
             }
         }
         float pl = ld1(c.p, i), av = ld1(c.s0, i), bv = ADAM ? ld1(c.s1, i) : 0.0f;

@@ -1,5 +1,6 @@
 """What the compiler gives the averaging kernels (its own resource report): none touches scratch memory, and only those laid out for
-more replicas than they have, whose conditions take scalar registers, spill any."""
+more replicas than they have, whose conditions take scalar registers, spill any.  And the table-driven fused kernels of up to 16 and of 32
+replicas: their single elements' code does not keep the peers' pointers in scalar registers over the vector loop."""
 import os
 import re
 import shutil
@@ -30,3 +31,40 @@ def test_averaging_kernels(tmp_path):
     assert {k: v for k, v in seen.items() if v["ScratchSize"] or v["VGPRs Spill"]} == {}
     # (mean_kernel<NREP, EXACT, ...>; 44 is the most that the form for 17..31 replicas has ever had)
     assert {k: v for k, v in means.items() if v["SGPRs Spill"] > (0 if re.search(r"ILi\d+ELb1E", k) else 44)} == {}
+
+
+# the fused kernel's source with the instances of a few replica counts in place of all
+FUSED = """
+#define DDP_FUSED_ADAM 0
+#include "ddp_fused.h"
+namespace ddp { namespace {
+template <bool A, class K> int few(const FusedLaunch &f, const K &k) {
+    return k.template go<A, false, false, 8, true, true, false, false, false>(0) + k.template go<A, false, false, 8, false, true, true, false, false>(0) +
+           k.template go<A, false, false, 16, true, true, false, false, false>(0) + k.template go<A, false, false, 16, true, true, true, false, true>(0) +
+           k.template go<A, false, false, 16, false, true, true, false, false>(0) + k.template go<A, false, false, 32, true, true, false, false, false>(0) +
+           k.template go<A, false, false, 32, true, true, true, false, true>(0);
+} } }
+#define dispatch_fused few
+#include "ddp_kernels_fused.hip"
+"""
+
+
+@pytest.mark.timeout(600)
+def test_fused_kernels(tmp_path):
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not shutil.which(hipcc):
+        pytest.skip("no hipcc")
+    (tmp_path / "few.hip").write_text(FUSED)
+    r = subprocess.run([hipcc] + build.FLAGS + ["--cuda-device-only", "-Rpass-analysis=kernel-resource-usage", "-x", "hip", "-c", str(tmp_path / "few.hip"),
+                                                "-o", str(tmp_path / "few.o")], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    seen, kernel = {}, ""
+    for ln in r.stderr.splitlines():
+        if m := re.search(r"remark: .*Function Name: (\S+)", ln):
+            kernel = m[1]
+        elif m := re.search(r"remark: .* (SGPRs Spill|VGPRs Spill|ScratchSize)[^:]*: (\d+)", ln):
+            seen.setdefault(kernel, {})[m[1]] = int(m[2])
+    assert len(seen) == 7 and all("fused_kernel" in k and len(v) == 3 for k, v in seen.items())
+    assert {k: v for k, v in seen.items() if v["ScratchSize"] or v["VGPRs Spill"]} == {}
+    # two scalar registers a peer: 28 to 99 with the pointers kept, at most 15 without
+    assert {k: v["SGPRs Spill"] for k, v in seen.items() if v["SGPRs Spill"] > 20} == {}
