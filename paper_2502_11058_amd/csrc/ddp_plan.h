@@ -180,8 +180,8 @@ inline bool halves_fit(int64_t n_update) { return 2 * n_update < (int64_t)1 << 2
 // So four with SGD and less than 96 bytes a vector, with AdamW, a third more bytes to write, for three bf16 replicas; else three.
 // Four also in short AdamW calls, of 6 to 24 chunks (2048 elements) per CU, which are too few rounds of workgroups for three:
 //     580^2 (7.7), N = 24, bf16 33.6 / 33.4, 640^2 (9.4), N = 12 36.0 / 35.6, N = 24, bf16 38.7 / 37.1, 760^2 (13.2), N = 4 39.3 / 38.9, N = 8 44.6 / 44.1,
-//     N = 16, bf16 44.9 / 44.4, 900^2 (18.6), N = 8, bf16 53.0 / 52.6, 5 layers of 1100^2 (11.6), N = 8, bf16 34.4 / 33.6; below, 460^2 (4.8), N = 8
-//     16.6 / 17.6, 5 of 750^2 (5.4), N = 6 16.5 / 17.1
+//     N = 16, bf16 44.9 / 44.4, 900^2 (18.6), N = 8, bf16 53.0 / 52.6, 5 layers of 1100^2 (11.6), N = 8, bf16 34.4 / 33.6; below 6 only with less than 96
+//     bytes, 460^2 (4.8), N = 2 13.5 / 12.8, N = 8 16.6 / 17.6, 5 of 750^2 (5.4), N = 6 16.5 / 17.1
 // and where the call is then one round: layer by layer, 1024^2, SGD, N = 8 86.5 / 84.9, bf16, N = 12 90.3 / 87.7, AdamW, N = 8 109.9 / 108.3.
 // Two over dense arenas in calls on 64 M elements and more of 16 to 32 fp32 replicas, whose three would have over 200 KB in flight per CU.
 // Halves and three / halves and two, 10 layers:
@@ -196,8 +196,9 @@ inline int fused_wg_per_cu(int cus, bool dense, int N, bool wire16, bool adamw, 
     if (dense && !wire16 && N >= 16 && N <= 32 && elements >= (int64_t)1 << 26) return 2;
     if (halves > 3 * (int64_t)cus && halves <= 4 * (int64_t)cus) return 4;
     const int64_t chunks = (elements + 2047) / 2048;
-    if (adamw) return (N == 3 && wire16) || (chunks >= 6 * (int64_t)cus && chunks < 24 * (int64_t)cus) ? 4 : 3;
-    return vector_bytes(N, wire16, adamw, grad16) < 96 ? 4 : 3;
+    const bool little = vector_bytes(N, wire16, adamw, grad16) < 96;
+    if (adamw) return (N == 3 && wire16) || (chunks < 24 * (int64_t)cus && (little || chunks >= 6 * (int64_t)cus)) ? 4 : 3;
+    return little ? 4 : 3;
 }
 
 // Workgroups of the table-free fused kernel over elements [e0, e1) of the arenas: chunks counted from the multiple of `line`

@@ -70,15 +70,16 @@ int main() {
             if (!st.dense_passes.empty()) CHECK(at == e1);
         }
     }
-    // workgroups per CU: with SGD four below 96 bytes per thread, with AdamW for three bf16 replicas and in calls of 6 to 24 chunks per CU, and where that
-    // makes the call one round of them; else three; two over dense arenas for 16 to 32 fp32 replicas from 64 M elements on
+    // workgroups per CU: with SGD four below 96 bytes per thread, with AdamW for three bf16 replicas and in calls of up to 24 chunks per CU (below 6 only
+    // with less than 96 bytes), and where that makes the call one round of them; else three; two over dense arenas for 16 to 32 fp32 replicas from 64 M elements on
     const int64_t some = 1, large = (int64_t)1 << 26, cu = 256 * 2048;
     auto sgd = [&](int N, bool wire16, bool grad16 = false) { return fused_wg_per_cu(256, true, N, wire16, false, grad16, 1 << 24, some); };
     CHECK(sgd(2, false) == 4 && sgd(3, false) == 4 && sgd(4, false) == 3 && sgd(5, false) == 3 && sgd(8, false) == 3);  // 64, 80, 96, 112, 160 bytes
     CHECK(sgd(6, true) == 4 && sgd(7, true) == 3 && sgd(7, true, true) == 4 && sgd(8, true, true) == 3 && sgd(64, true) == 3);  // 88, 96, 88, 96
     for (bool dense : {true, false}) {
         auto adamw = [&](int N, bool wire16, int64_t e) { return fused_wg_per_cu(256, dense, N, wire16, true, true, e, some); };
-        CHECK(adamw(2, true, 1) == 3 && adamw(3, true, 1) == 4 && adamw(3, false, 1) == 3 && adamw(4, true, 1) == 3 && adamw(3, true, large) == 4);
+        CHECK(adamw(2, true, large) == 3 && adamw(3, true, large) == 4 && adamw(3, false, large) == 3 && adamw(4, true, large) == 3);
+        CHECK(adamw(3, false, 1) == 4 && adamw(4, false, 1) == 3 && adamw(6, true, 1) == 3 && adamw(5, true, 1) == 4 && adamw(2, true, 24 * cu) == 3);  // 88, 104, 96
         CHECK(adamw(8, false, 6 * cu - 2048) == 3 && adamw(8, false, 6 * cu) == 4 && adamw(32, true, 24 * cu - 2048) == 4 && adamw(32, true, 24 * cu) == 3);
         CHECK(adamw(16, false, large) == (dense ? 2 : 3) && adamw(16, false, large - 1) == 3 && adamw(15, false, large) == 3 && adamw(16, true, large) == 3);
         CHECK(adamw(32, false, large) == (dense ? 2 : 3) && adamw(33, false, large) == 3 && adamw(64, false, large) == 3);
