@@ -129,7 +129,7 @@ static int residency_pad(const ddp_ctx *c, int wg_per_cu) {
 // The residency request of the update, and of the fused step (fused_wg_per_cu).
 static int update_lds(const ddp_ctx *c) { return c->small && !c->update_lds_set ? 0 : c->update_lds; }
 static int fused_lds(const ddp_ctx *c, bool halved, int N, bool wire16, bool adamw, int64_t elements, int64_t halves) {
-    if (!halved || c->update_lds_set) return update_lds(c);
+    if (!halved) return update_lds(c);
     return residency_pad(c, fused_wg_per_cu(c->cus, c->dense, N, wire16, adamw, c->grad_dtype == DDP_BF16, elements, halves));
 }
 
@@ -868,7 +868,8 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     // Statistics: one reduction per run of consecutive slot positions inside the range (a schedule in backward order gives a
     // single run).
     const bool adamw = opt->kind == DDP_OPT_ADAMW;
-    const bool halved = ctx->halves && call_takes_halves(ctx->cus, layer_elem0(ctx, ctx->L), ctx->dense, N, wire16, adamw, ctx->grad_dtype == DDP_BF16);
+    // (a residency that the caller gives is one of whole chunks)
+    const bool halved = ctx->halves && !ctx->update_lds_set && call_takes_halves(ctx->cus, layer_elem0(ctx, ctx->L), ctx->dense, N, wire16, adamw, ctx->grad_dtype == DDP_BF16);
     const FusedPlan &plan = halved ? st->halves : *st;
     const int64_t chunks = (halved ? 2 : 1) * (c1 - c0);
     const int nl = (int)st->layers.size();

@@ -1,9 +1,12 @@
 """The fused step's chunks of 1024 elements, the update's and the unscheduled pieces' of two of them, with default options: layers around
 one and several of both, and statistics of up to and beyond 5/2 workgroups per CU with a pair; the four calls and the fused step, whole
 and layer by layer, dense and through the table.  Every element against the oracle, bit for bit, statistics to 1e-10."""
+import numpy as np
 import pytest
+import torch
 
 from paper_2502_11058_amd import workloads as W
+from paper_2502_11058_amd.harness import DeviceReplica
 from test_gpu_parity import run_trajectory
 
 pytestmark = pytest.mark.gpu
@@ -22,3 +25,29 @@ def test_chunks_and_pairs(oracle, n, wire16, chunks, fused, layerwise, dense_pat
                    lr=1e-2, sigma_drift=1e-3, iterations=3, policy="round_robin" if chunks is AROUND else "every")
     iters = 3 if chunks is AROUND else 1
     assert run_trajectory(oracle, w, iters=iters, fused=fused, wire16=wire16, layerwise=layerwise, options={"dense_path": dense_path}).frac() == 1.0
+
+
+@pytest.mark.parametrize("dense_path", [1, 0])
+@pytest.mark.parametrize("given", [{"update_wg_per_cu": 2}, {"update_lds": 64512}])
+def test_a_given_residency_is_one_of_whole_chunks(given, dense_path):
+    """update_wg_per_cu or update_lds without update_chunk: the fused step keeps the chunks of 2048 elements that the option is stated for.  The
+    statistics' partial sums are a chunk's, so their last bits tell."""
+    assert torch.cuda.is_available(), "no GPU visible"
+    ts = [W.TensorSpec(f"l{l}", l, k) for l, k in enumerate([100_003, 250_007, 65_537, 180_001])]
+    w = W.Workload("given", ts, n_replicas=4, period=1, optimizer="sgdm", param_dtype="f32", lr=1e-2, sigma_drift=1e-3, policy="every")
+
+    def stats(options):
+        rep = DeviceReplica(w, 0, options=dict(options, dense_path=dense_path))
+        rep.init_params()
+        rep.fill_grads(0)
+        flat = torch.cat([rep.sync[l] for l in rep.sets[0]])
+        rep.fill_peers_from(flat, 0, flat.numel())
+        rep.fused_step(0)
+        out = rep.stats.cpu().numpy()[:2 * len(ts)].copy()
+        rep.close()
+        return out
+
+    whole, halves = stats({"update_chunk": 2048}), stats({})
+    np.testing.assert_allclose(halves, whole, rtol=1e-12)
+    assert not np.array_equal(halves, whole)             # seen for these seeded inputs: the shapes can be told apart
+    assert np.array_equal(stats(given), whole)
