@@ -51,3 +51,46 @@ def test_a_given_residency_is_one_of_whole_chunks(given, dense_path):
     np.testing.assert_allclose(halves, whole, rtol=1e-12)
     assert not np.array_equal(halves, whole)             # seen for these seeded inputs: the shapes can be told apart
     assert np.array_equal(stats(given), whole)
+
+
+@pytest.mark.parametrize("dense_path", [1, 0])
+def test_captured_ranges_in_halves(dense_path):
+    """Range calls with default options in a captured graph, replayed between eager calls: the bits of the eager ones, statistics too."""
+    assert torch.cuda.is_available(), "no GPU visible"
+    ts = [W.TensorSpec(f"l{l}", l, k) for l, k in enumerate([1021, 100_003, 2049, 250_007, 64, 65_537])]
+    L, n = len(ts), 5
+    w = W.Workload("captured", ts, n_replicas=n, period=2, optimizer="sgdm", param_dtype="f32", lr=1e-2, sigma_drift=1e-3, policy="round_robin")
+    rep = DeviceReplica(w, 0, options={"dense_path": dense_path})
+    rep.init_params()
+    rep.fill_grads(0)
+    rep.fill_peers_from(torch.cat([rep.sync[l] for l in rep.sets[1]]), 1, rep.slot_numel[1])
+    saved, opt, s = [a.clone() for a in (rep.a_sync, rep.a_s0)], rep.opt_struct(1), torch.cuda.Stream()
+
+    def calls(stream):
+        for l in range(L - 1, -1, -1):
+            rep.ctx.ddp_fused_sync_update_layers(1, l, 1, rep.peers, 0, 0, n, 0, rep.stats, opt, stream)
+
+    def fresh():
+        rep.a_sync.copy_(saved[0])
+        rep.a_s0.copy_(saved[1])
+        rep.stats.fill_(-1.0)
+        torch.cuda.synchronize()
+
+    def result():
+        torch.cuda.synchronize()
+        return [a.clone() for a in (rep.a_sync, rep.a_s0, rep.stats)]
+
+    fresh()
+    calls(None)
+    first = result()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        calls(s)
+    for _ in range(3):
+        fresh()
+        g.replay()
+        assert all(torch.equal(a, b) for a, b in zip(result(), first))
+        fresh()
+        calls(None)
+        assert all(torch.equal(a, b) for a, b in zip(result(), first))
+    rep.close()

@@ -20,3 +20,13 @@ def test_layers_around_lines_and_chunks(oracle, optimizer, dtype, n, wire16, fus
                    policy="round_robin")
     options = {"update_chunk": 1024, "mean_chunk": 1024, "copy_chunk": 1024, "dense_path": dense_path}
     assert run_trajectory(oracle, w, iters=2, fused=fused, wire16=wire16, layerwise=layerwise, options=options).frac() == 1.0
+
+
+@pytest.mark.parametrize("dense_path", [1, 0])
+@pytest.mark.parametrize("layerwise", [0, 1, 3])
+@pytest.mark.parametrize("n,wire16", [(3, False), (8, True), (12, False), (32, True)])
+def test_default_halves_around_lines_and_chunks(oracle, n, wire16, layerwise, dense_path):
+    ts = [W.TensorSpec(f"l{l}", l, k) for l, k in enumerate(SIZES)]
+    w = W.Workload("lines_default", ts, n_replicas=n, period=2, optimizer="sgdm", param_dtype="f32", lr=1e-3, sigma_drift=1e-3, iterations=2,
+                   policy="round_robin")
+    assert run_trajectory(oracle, w, iters=2, fused=True, wire16=wire16, layerwise=layerwise, options={"dense_path": dense_path}).frac() == 1.0

@@ -1,5 +1,5 @@
 """Statistics that the workgroups put together themselves (launches in which up to 5/4 workgroups per CU have a
-share) and those of a launch of their own, on both sides of the rule's lines: against the oracle, the same bits on every
+share; the fused step up to 5/2 beside as many chunks without one) and those of a launch of their own, on both sides of the rule's lines: against the oracle, the same bits on every
 repetition, the same bits for the allocation-free entry point (which never folds), and through a captured graph that is
 replayed between eager calls."""
 import numpy as np
@@ -77,16 +77,19 @@ def test_both_sides_of_the_line(oracle, per_layer):
     rep.close()
 
 
+@pytest.mark.parametrize("default", [False, True])
 @pytest.mark.parametrize("dense_path", [1, 0])
-@pytest.mark.parametrize("per_layer", [[60, 4097, 3, 120, 7, 300], [60, 4096, 3, 120, 7, 300]])
-def test_small_layers_beside_a_large_one(per_layer, dense_path):
-    """One layer on either side of the number of partials from which a slot's statistics take the two-stage reduction: the
-    small layers' statistics have the same bits from the whole-model call and from every partition into ranges."""
+@pytest.mark.parametrize("per_layer", [[60, 4097, 3, 120, 7, 300], [60, 4096, 3, 120, 7, 300], [60, 8193, 3, 120, 7, 300], [60, 8192, 3, 120, 7, 300]])
+def test_small_layers_beside_a_large_one(per_layer, dense_path, default):
+    """One layer on either side of the number of partials (8192) from which a slot's statistics take the two-stage reduction: the
+    small layers' statistics have the same bits from the whole-model call and from every partition into ranges.  In chunks of 1024
+    elements that the caller gives, and in those that the fused step takes by itself, halves of chunks of 2048 (with 4096, whole ones)."""
     assert torch.cuda.is_available(), "no GPU visible"
     ts = [W.TensorSpec(f"l{l}", l, 1024 * k) for l, k in enumerate(per_layer)]
     w = W.Workload(f"order{per_layer[1]}", ts, n_replicas=3, period=1, optimizer="sgdm", param_dtype="f32", lr=1e-2, sigma_drift=1e-3,
                    policy="every")
-    rep = DeviceReplica(w, 0, options={"update_chunk": 1024, "mean_chunk": 1024, "dense_path": dense_path})
+    given = {} if default else {"update_chunk": 1024, "mean_chunk": 1024}
+    rep = DeviceReplica(w, 0, options=dict(given, dense_path=dense_path))
     rep.init_params()
     rep.fill_grads(0)
     S = rep.sets[0]
@@ -110,16 +113,19 @@ def test_small_layers_beside_a_large_one(per_layer, dense_path):
     rep.close()
 
 
+@pytest.mark.parametrize("default", [False, True])
 @pytest.mark.parametrize("dense_path", [1, 0])
 @pytest.mark.parametrize("per_layer", [[30] * 12, [128, 1, 127, 64, 3, 100]])
-def test_ranges_in_flight_on_two_streams(per_layer, dense_path):
+def test_ranges_in_flight_on_two_streams(per_layer, dense_path, default):
     """Range calls that put their statistics together themselves, disjoint ones in flight at the same time on two streams (each
-    layer has its own counter and partials): the bits of the calls one after the other, on every repetition."""
+    layer has its own counter and partials): the bits of the calls one after the other, on every repetition.  In chunks that the
+    caller gives and in halves of the default ones."""
     assert torch.cuda.is_available(), "no GPU visible"
     L = len(per_layer)
     ts = [W.TensorSpec(f"l{l}", l, 1024 * k - (l % 3)) for l, k in enumerate(per_layer)]
     w = W.Workload(f"streams{L}", ts, n_replicas=4, period=1, optimizer="sgdm", param_dtype="f32", lr=1e-2, sigma_drift=1e-3, policy="every")
-    rep = DeviceReplica(w, 0, options={"update_chunk": 1024, "mean_chunk": 1024, "dense_path": dense_path})
+    given = {} if default else {"update_chunk": 1024, "mean_chunk": 1024}
+    rep = DeviceReplica(w, 0, options=dict(given, dense_path=dense_path))
     rep.init_params()
     rep.fill_grads(0)
     flat = torch.cat([rep.sync[l] for l in rep.sets[0]])
