@@ -754,12 +754,12 @@ static int update_dense(const ddp_ctx *ctx, int kind, DenseLaunch d, const Updat
                                small && !ctx->update_lds_set ? 0 : update_lds(ctx), stream);
 }
 
-// The streams of layers [first, first + count) as one dense range, if the model is registered that way, the option
-// allows it and the range starts on a vector boundary.
+// The streams of layers [first, first + count) as one dense range, if the model is registered that way and the option allows it, wherever in
+// a vector the range starts.  Ranges that start inside one, through the table / so, us a call: AdamW, layers of 0.07 M elements 4.5 / 3.7, 0.26 M 4.5 /
+// 3.7, 0.64 M 5.6 / 5.1, 1.05 M 8.0 / 7.9, 2.35 M 13.2 / 13.2, 17 M 77.6 / 77.2; SGD 0.07 M 3.8 / 3.7, 1.05 M 5.5 / 5.5, 50 M 157 / 157.
 static bool dense_range(const ddp_ctx *ctx, int first, int count, DenseLaunch &d) {
     if (!ctx->dense || !ctx->dense_path) return false;
     const int64_t e0 = layer_elem0(ctx, first), e1 = layer_elem0(ctx, first + count);
-    if (e0 % 4 != 0) return false;
     const TensorDesc &t0 = ctx->tensors[0];
     d.p = t0.sync + e0;
     d.s0 = t0.state0 + e0;
