@@ -136,7 +136,10 @@ int ddp_destroy(ddp_ctx *ctx);
  *                                               defaults 2048 / 2048 / 2048; update_chunk, unless the caller sets it, 1024
  *                                               for models of up to 4.5 chunks of 2048 per CU: with a second moment all of
  *                                               them, without one those above 5/4), and for AdamW updates of arenas in
- *                                               launches of up to 7/4
+ *                                               launches of up to 7/4; a workgroup of the fused step takes 1024 of the default
+ *                                               2048 for most replica counts, wires and sizes, at two to four workgroups per
+ *                                               CU, unless the caller sets update_chunk, update_wg_per_cu or update_lds, even
+ *                                               to its default)
  *   "dispatch_ways"                             1..4096 (default 1): launch order of the workgroups; w > 1 cuts every
  *                                               chunk table into w contiguous segments and visits them round-robin
  *   "update_wg_per_cu", "mean_wg_per_cu",       0..32 (defaults 2 / 2 / 6; 0 = no cap): most workgroups of that kernel family resident per
@@ -148,7 +151,8 @@ int ddp_destroy(ddp_ctx *ctx);
  *                                               average runs at twice mean_wg_per_cu (half the bytes per workgroup in flight).
  *                                               Unless the caller sets it, averages of up to 4 replicas run at 3 and of up to
  *                                               2 at 4: less would be in flight than the memory needs.  Unless the caller sets
- *                                               it, what takes update chunks of 1024 by itself runs uncapped
+ *                                               it, models and updates that take chunks of 1024 by themselves run uncapped, and the
+ *                                               fused step's halves of 2048 at two to four by replicas, wire, optimizer and size
  *   "update_lds", "mean_lds", "copy_lds"        0..65536: the same cap given directly as bytes of LDS per workgroup (for sweeps)
  *   "nontemporal"                               0/1 (default 1): streaming cache hints on loads and stores
  *   "dense_path"                                0/1 (default 1): when the registered tensors lie back to back in every

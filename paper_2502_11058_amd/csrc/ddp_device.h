@@ -577,7 +577,7 @@ __device__ __forceinline__ void update_body(const Streams<GBF16> c, const Update
 // ---------------------------------------------------------------------------------------------------------------
 
 struct DenseArgs {
-    const void *g;  // the five streams at the first element of the range, each aligned for 128-bit (bf16: 64-bit) access
+    const void *g;  // the five streams at the first element of the range, any of arenas that are aligned for 128-bit (bf16: 64-bit) access
     float *p;
     float *s0;
     float *s1;

@@ -213,8 +213,8 @@ struct FusedTable : FusedLaunch {
     bool halved;  // two workgroups a chunk
 };
 int launch_fused(const FusedTable &f, void *stream);
-// The update over tensors that lie back to back in every stream: the range's first element in each stream (aligned
-// for 128-bit access, bf16 streams for 64-bit), its length, the elements per workgroup and where in a line (kLine) it starts.
+// The update over tensors that lie back to back in every stream: the range's first element in each stream (any element of arenas
+// that are aligned for 128-bit access, bf16 ones for 64-bit), its length, the elements per workgroup and where in a line (kLine) it starts.
 struct DenseLaunch {
     const void *g;
     float *p, *s0, *s1;

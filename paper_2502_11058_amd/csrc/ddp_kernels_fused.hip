@@ -17,7 +17,7 @@ struct FusedArgs {
     const UpdateChunk *chunks;
     const RunSlot *run_slot;
     const int32_t *run_chunk_base;      // per run: index of its first chunk in registration order
-    StatsLaunch st;                     // partials: [n_chunks][2], only touched for scheduled chunks
+    StatsLaunch st;                     // partials: a pair per scheduled chunk, or per half of one
     UpdateScalars s;
     int chunk_elems;
     int halved;  // 1: two workgroups a chunk
@@ -28,7 +28,7 @@ struct FusedArgs {
 template <bool ADAM, bool GBF16, bool MODEL, int NREP, bool EXACT, bool STATS, bool W16, bool UTS, bool PAIRS>
 __global__ __launch_bounds__(kThreads, 2) void fused_kernel(const FusedArgs a) {
     __shared__ double lds[2][kThreads / kWave];
-    const bool paced = ADAM && long_launch();
+    const bool paced = ADAM && long_launch();  // (of use to whole chunks: half a chunk is one vector a thread)
     UpdateChunk ch = a.chunks[blockIdx.x >> a.halved];
     const TensorDesc td = a.runs[ch.run];
     const RunSlot ts = a.run_slot[ch.run];

@@ -15,8 +15,8 @@ __global__ __launch_bounds__(kThreads) void update_kernel(const TensorDesc *__re
 
 // The update when the registered tensors lie back to back in every stream (one arena per stream): workgroup b takes
 // elements [b * chunk, (b + 1) * chunk) of the arenas, counted from the cache line (kLine) that the range starts in, addresses
-// follow from the block index alone (no table), and every chunk starts aligned, so there is no head; only the last workgroup
-// has a tail of fewer than four elements.
+// follow from the block index alone (no table), and chunks end on lines: only the first workgroup of a range that starts inside a
+// vector has a head, of up to three elements, and only the last a tail.
 // Same operations per element as update_kernel, hence the same bits.
 // PAST: the range starts inside a line.  (A kernel of its own: the 15 ns that the first chunk's correction costs each workgroup
 // before its first load are 0.3 % of TinyLlama-1.1B's update.)

@@ -23,7 +23,8 @@ namespace ddp {
 //                       352  11.03 / 11.27   23.1 / 23.1     11.4 / 11.5
 //     average, N = 8    396   9.05 /  8.88   21.2 / 21.2      9.5 /  9.3
 //                       513  10.98 / 11.41   22.5 / 22.9     11.8 / 12.2
-// One line for both kernels, drawn where the average crosses; the fused step, whose workgroups have more to do, still gains at 352.
+// The line is drawn where the average crosses, and no layer has more than 256 CUs allow in all, whatever the device; the fused step, whose
+// workgroups have more to do, still gains at 352 and has a line of its own.
 inline bool folds(int cus, int64_t partials, int64_t most) { return 4 * partials <= 5 * (int64_t)cus && most <= 320; }
 // The fused step, whose chunks are half the size (kSmallChunk), up to 5/2 per CU with a pair where at least as many others hide what the
 // folding ones wait for.  Launch of their own / folded in us:
@@ -66,8 +67,8 @@ inline int mean_pairs(int cus, int64_t chunk, int64_t n_chunks, int64_t n_layers
     return mean_cut(cus, chunk, n_chunks, n_layers, 32, true) ? 2 : 1;
 }
 
-// Whether a model is so small that its update takes chunks of kSmallChunk elements, as every fused step does, and neither has a cap on
-// the workgroups per CU: at two workgroups per CU and 2048 elements each it is one or two rounds of them, the second half empty.
+// Whether a model is so small that its update and fused step take chunks of kSmallChunk elements and neither has a cap on the workgroups
+// per CU: at two workgroups per CU and 2048 elements each it is one or two rounds of them, the second half empty.
 // That shape / this one in us, 8 layers, fused, back to back:
 //     chunks of 2048           129          257          513         1026         1409         2050
 //     AdamW, N = 8          6.5 / 6.3    8.4 / 7.8   11.1 / 10.4  17.4 / 16.3  22.0 / 22.2  28.7 / 29.0
@@ -89,10 +90,12 @@ inline bool small_model(int cus, int64_t numel, bool second_moment) {
 // just one round, 72.3 / 73.2; SGD 886^2 47.1 / 47.0.
 inline bool short_update(int cus, int64_t numel, bool adamw) { return adamw && 4 * ((numel + 2047) / 2048) <= 7 * (int64_t)cus; }
 
-// Whether, in chunks that were given by the caller and are large enough, the fused step of N bf16 replicas has two vectors of all streams in flight per thread (fused_body), in a call on `all`
+// Whether the fused step of N bf16 replicas has two vectors of all streams in flight per thread (fused_body), in a call on `all`
 // chunks, `scheduled` of them of the slot's layers: in kernels laid out for 16 and 32 replicas, where a chunk has a second vector for
-// each thread.  That takes up to twice the registers and makes every workgroup's ramp longer, which a call of a few rounds of
-// workgroups does not hide.  One vector / two in us (scheduled of all chunks per CU):
+// each thread, so not in halves of chunks (call_takes_halves) but in whole ones: where the caller gives chunks, in models with a layer of 128 M
+// elements, with SGD over separate tensors, and in models of 6 to 10 chunks per CU up to 200 bytes a vector.  That takes up to twice the
+// registers and makes every workgroup's ramp longer, which a call of a few rounds of workgroups does not hide.  One vector / two, in chunks of
+// 2048 all, us (scheduled of all chunks per CU):
 //     8 layers, fused       N = 24, SGD       N = 24, AdamW     N = 32, AdamW
 //     543^2  (1.1 of 4.5)   21.3 /  23.5      24.4 /  26.8      27.2 /  30.4
 //     640^2  (1.6 of 6.3)   24.0 /  25.4      29.5 /  30.1      31.2 /  33.0
@@ -121,6 +124,9 @@ inline bool takes_pairs(int cus, int64_t chunk, int64_t all, int64_t scheduled, 
 // One such layer decides for the whole model: eight blocks of 20 M beside an embedding of 150 M, N = 8, SGD 1283 / 1283, AdamW
 // 1650 / 1650, bf16 peers 1511 / 1502, so nothing is to be had from choosing launch by launch.  Nor over separate tensors with SGD from 16 M elements
 // on, where unscheduled layers want whole chunks (GPT-2 small, N = 8 538 / 557, 13 blocks of 1536 1691 / 1746, 12 layers of 1378^2, N = 16 bf16 112 / 117).
+// With AdamW over separate tensors the halves, which have nothing to pace (long_launch), gain more than they lose: paced whole chunks and two
+// per CU / halves and three, N = 2 and 8, 12 layers of 3000^2 504 / 496, 615 / 598, of 5000^2 1421 / 1375, 1733 / 1714, seven blocks of 44 M 2084 / 2025, 2447 / 2384,
+// TinyLlama-1.1B 5257 / 5041, 6450 / 6227, layer by layer 5142 / 5107, 6157 / 6107; but GPT-2 small 581 / 590, 702 / 700, 12 layers of 4096^2 972 / 993, 1184 / 1209.
 inline bool takes_halves(int64_t numel, int64_t largest_layer, bool dense, bool second_moment) {
     return largest_layer < (int64_t)1 << 27 && (dense || second_moment || numel < (int64_t)1 << 24);
 }
