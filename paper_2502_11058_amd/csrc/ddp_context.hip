@@ -497,7 +497,9 @@ extern "C" int ddp_set_schedule(ddp_ctx *ctx, int H, const int32_t *set_ptr, con
                 return rc;
             }
         }
-        const int64_t max_pairs = std::max(max_mean_pairs, (ctx->halves ? 2 : 1) * ctx->n_update);  // the fused step keeps one per workgroup
+        // The fused step keeps one per workgroup.  Halves have places of their own behind the whole chunks': calls on disjoint layers may be in flight
+        // at the same time, and those on bf16 and on fp32 peers need not have the same size of chunk.
+        const int64_t max_pairs = std::max(max_mean_pairs, (ctx->halves ? 3 : 1) * ctx->n_update);
         if (max_pairs > 0) {
             const size_t line = kFoldLine * sizeof(int32_t) / sizeof(double);  // the counters start on a cache line
             const size_t sums = (((size_t)max_pairs + (size_t)ctx->L * kStatSlices) * 2 + line - 1) / line * line;
@@ -895,7 +897,7 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     f.grad_dtype = ctx->grad_dtype;
     f.with_model = ctx->param_dtype == DDP_BF16;
     f.s = s;
-    f.st = {any ? ctx->d_partials : nullptr, layer_stats, fold ? ctx->d_counters : nullptr};
+    f.st = {any ? ctx->d_partials + (halved ? 2 * ctx->n_update : 0) : nullptr, layer_stats, fold ? ctx->d_counters : nullptr};
     const int64_t e0 = layer_elem0(ctx, first), e1 = layer_elem0(ctx, first + count);
     f.lds_pad = fused_lds(ctx, halved, N, wire16, adamw, e1 - e0, chunks);
     const auto at = first_pass(plan, e0);

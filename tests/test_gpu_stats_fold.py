@@ -146,3 +146,36 @@ def test_ranges_in_flight_on_two_streams(per_layer, dense_path, default):
         seen.append([rep.stats.clone(), rep.a_sync.clone(), rep.a_s0.clone()])
         assert all(torch.equal(a, b) for a, b in zip(seen[-1], seen[0])), turn
     rep.close()
+
+
+@pytest.mark.parametrize("dense_path", [1, 0])
+def test_both_wires_in_flight_on_two_streams(dense_path):
+    """Range calls of one worker on fp32 and on bf16 peers, in flight at the same time on two streams, with default options in a model for which
+    eleven fp32 replicas take halves of chunks and eleven bf16 ones whole chunks: the bits of the calls one after the other."""
+    assert torch.cuda.is_available(), "no GPU visible"
+    n, L = 11, 12
+    ts = [W.TensorSpec(f"l{l}", l, 300_001 + 1000 * l) for l in range(L)]                # 3.67 M elements, 7 chunks of 2048 per CU
+    w = W.Workload("wires", ts, n_replicas=n, period=1, optimizer="sgdm", param_dtype="f32", lr=1e-2, sigma_drift=1e-3, policy="every")
+    rep = DeviceReplica(w, 0, options={"dense_path": dense_path}, wire16=True)
+    rep.init_params()
+    rep.fill_grads(0)
+    flat = torch.cat([rep.sync[l] for l in rep.sets[0]])
+    rep.fill_peers16_from(flat, 0, flat.numel())
+    saved = [a.clone() for a in (rep.a_sync, rep.a_s0)]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    opt = rep.opt_struct(1)
+    seen = []
+    for turn in range(12):
+        rep.a_sync.copy_(saved[0])
+        rep.a_s0.copy_(saved[1])
+        rep.stats.fill_(-1.0)
+        torch.cuda.synchronize()
+        for l in range(L):
+            wire = l % 2
+            rep.ctx.ddp_fused_sync_update_layers(0, l, 1, rep._peers16_arr if wire else rep._peers_arr, wire, 0, n, 0, rep.stats, opt,
+                                                 streams[wire] if turn else streams[0])
+        torch.cuda.synchronize()
+        seen.append([rep.stats.clone(), rep.a_sync.clone(), rep.a_s0.clone()])
+        assert (seen[-1][0][:2 * L] > 0.0).all()
+        assert all(torch.equal(a, b) for a, b in zip(seen[-1], seen[0])), turn
+    rep.close()
