@@ -311,18 +311,21 @@ __device__ __forceinline__ void block_sum2(double &g, double &m, double (*lds)[W
 }
 
 // The sums of a layer from its partials by a workgroup of kSumThreads, in a fixed order: thread-strided, then the workgroup tree.
-// Eight pairs in flight per thread, all that a layer summed in one launch has: the loop is bound by latency.
+// Eight pairs in flight per thread, all that a layer summed in one launch has: the loop is bound by latency.  Up to kThreads partials are
+// added to the same bits by THREADS = kThreads: a thread has one of them, and what the other wavefronts would have added are zeros.
 constexpr int kSumThreads = 1024;
-__device__ __forceinline__ void sum_partials(const double *partials, int64_t c0, int64_t c1, int n_replicas, double *stats, double (*lds)[kSumThreads / kWave]) {
+template <int THREADS>
+__device__ __forceinline__ void sum_partials(const double *partials, int64_t c0, int64_t c1, int n_replicas, double *stats, double (*lds)[THREADS / kWave]) {
+    static_assert(THREADS == kSumThreads || THREADS == kThreads, "of two widths");
     double g = 0.0, m = 0.0;
     typedef double f64x2 __attribute__((ext_vector_type(2)));
-    constexpr int U = (int)(kStatSingleMax / kSumThreads);  // pairs in flight per thread
-    for (int64_t c = c0 + (int64_t)threadIdx.x; c < c1; c += U * kSumThreads) {
+    constexpr int U = THREADS == kSumThreads ? (int)(kStatSingleMax / kSumThreads) : 1;  // pairs in flight per thread
+    for (int64_t c = c0 + (int64_t)threadIdx.x; c < c1; c += U * THREADS) {
         f64x2 x[U];
 #pragma unroll
         for (int j = 0; j < U; ++j) {
             x[j] = f64x2{};
-            if (c + j * kSumThreads < c1) x[j] = reinterpret_cast<const f64x2 *>(partials)[c + j * kSumThreads];
+            if (c + j * THREADS < c1) x[j] = reinterpret_cast<const f64x2 *>(partials)[c + j * THREADS];
         }
 #pragma unroll
         for (int j = 0; j < U; ++j) {  // (both sums are of squares: adding zero changes nothing)
@@ -330,7 +333,7 @@ __device__ __forceinline__ void sum_partials(const double *partials, int64_t c0,
             m += x[j].y;
         }
     }
-    block_sum2<kSumThreads / kWave>(g, m, lds);
+    block_sum2<THREADS / kWave>(g, m, lds);
     if (threadIdx.x == 0) {
         stats[0] = g / (double)n_replicas;
         stats[1] = m;

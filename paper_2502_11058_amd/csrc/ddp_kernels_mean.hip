@@ -233,12 +233,15 @@ __global__ __launch_bounds__(kWave) void stats_finalize_kernel(const double *__r
 }
 
 // The same reduction in one launch, for layers with few partials (launch-bound slots): one workgroup per layer adds the
-// layer's partials thread-strided, then the workgroup tree.  Fixed order as well.
-__global__ __launch_bounds__(kSumThreads) void stats_single_kernel(const double *__restrict__ partials, const int32_t *__restrict__ ranges,
-                                                                int pairs, int n_replicas, double *__restrict__ stats) {
-    __shared__ double lds[2][kSumThreads / kWave];
+// layer's partials thread-strided, then the workgroup tree.  Fixed order as well.  Bound by the start of the workgroups where layers are many: those of
+// up to kThreads partials each take workgroups of that size (average, N = 4, 1024 threads / 256, us: 1000 layers of 700 elements 9.0 / 7.3, 500 of 2000
+// 7.7 / 7.1, 200 of 5000 6.8 / 6.6, 100 of 40000 16.0 / 15.8).
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void stats_single_kernel(const double *__restrict__ partials, const int32_t *__restrict__ ranges,
+                                                               int pairs, int n_replicas, double *__restrict__ stats) {
+    __shared__ double lds[2][THREADS / kWave];
     const int l = blockIdx.x;
-    sum_partials(partials, (int64_t)pairs * ranges[2 * l], (int64_t)pairs * ranges[2 * l + 1], n_replicas, stats + 2 * l, lds);
+    sum_partials<THREADS>(partials, (int64_t)pairs * ranges[2 * l], (int64_t)pairs * ranges[2 * l + 1], n_replicas, stats + 2 * l, lds);
 }
 
 // Dynamic LDS of a launch: the residency pad, or the staging area of the run-time replica count if that is larger.
@@ -285,8 +288,9 @@ int launch_stats(const double *partials, double *slice_sums, const int32_t *rang
                  int64_t max_partials_per_layer, void *stream) {
     if (n_layers <= 0) return 0;
     if (max_partials_per_layer <= kStatSingleMax) {
-        hipLaunchKernelGGL(stats_single_kernel, dim3((unsigned)n_layers), dim3(kSumThreads), 0, (hipStream_t)stream, partials, ranges,
-                           pairs, n_replicas, stats);
+        const int threads = max_partials_per_layer <= kThreads ? kThreads : kSumThreads;
+        hipLaunchKernelGGL(threads == kThreads ? stats_single_kernel<kThreads> : stats_single_kernel<kSumThreads>, dim3((unsigned)n_layers),
+                           dim3((unsigned)threads), 0, (hipStream_t)stream, partials, ranges, pairs, n_replicas, stats);
         return (int)hipGetLastError();
     }
     hipLaunchKernelGGL(stats_slices_kernel, dim3(kStatSlices, (unsigned)n_layers), dim3(kThreads), 0, (hipStream_t)stream, partials,

@@ -179,3 +179,43 @@ def test_both_wires_in_flight_on_two_streams(dense_path):
         assert (seen[-1][0][:2 * L] > 0.0).all()
         assert all(torch.equal(a, b) for a, b in zip(seen[-1], seen[0])), turn
     rep.close()
+
+
+@pytest.mark.parametrize("per_layer", [[200, 256, 1, 64, 65, 255], [1] * 330, [256, 256], [63, 127, 128, 129, 192, 193], [256] * 40])
+def test_narrow_and_wide_workgroups(per_layer):
+    """Layers of up to 256 partial pairs, which a launch of its own adds up by workgroups of 256 threads; beside one layer of 257, by workgroups
+    of 1024: the same bits, from the average and from the fused step."""
+    assert torch.cuda.is_available(), "no GPU visible"
+    n, seen = 3, []
+    sizes = [1024 * k - (l % 3) for l, k in enumerate(per_layer)]
+    total = sum(sizes)
+    data = [torch.randn(total + 257 * 1024, device="cuda", generator=torch.Generator("cuda").manual_seed(k)) for k in range(n)]
+    for numel in (sizes, sizes + [257 * 1024]):
+        L = len(numel)
+        ts = [W.TensorSpec(f"l{l}", l, k) for l, k in enumerate(numel)]
+        w = W.Workload(f"wide{len(sizes)}_{L}", ts, n_replicas=n, period=1, optimizer="sgdm", param_dtype="f32", lr=1e-2, sigma_drift=1e-3, policy="every")
+        rep = DeviceReplica(w, 0, options={"update_chunk": 1024, "mean_chunk": 1024})
+        rep.install_schedule([0, L], list(range(L)))
+        rep.fill_grads(0)
+        at = 0
+        for l, k in enumerate(numel):
+            rep.sync[l].copy_(data[0][at:at + k])
+            at += k
+        src, out = torch.zeros_like(rep.flat), torch.zeros_like(rep.flat)
+        src[:at] = data[0][:at]
+        for p, d in zip(rep.peers, data[1:]):
+            p[:at] = d[:at]
+        rep.stats.fill_(-1.0)
+        rep.ctx.ddp_partial_average(0, src, rep._peers_arr, n, 0, out, rep.stats)
+        seen.append(rep.stats.cpu().numpy()[:2 * len(sizes)].copy())
+        rep.stats.fill_(-1.0)
+        rep.fused_step(0)
+        seen.append(rep.stats.cpu().numpy()[:2 * len(sizes)].copy())
+        rep.close()
+    a = torch.stack([d[:total] for d in data]).double()
+    mean = a.sum(0) / n
+    ref = [((a - mean) ** 2).sum(0) / n, mean ** 2]
+    ref = np.array([r[b:b + k].sum().item() for b, k in zip(np.cumsum([0] + sizes), sizes) for r in ref])
+    for s in seen:
+        np.testing.assert_allclose(s, ref, rtol=1e-5)            # (the device's mean is rounded to 32 bits: 2^-24 of it in each difference)
+    assert np.array_equal(seen[0], seen[2]) and np.array_equal(seen[1], seen[3])
