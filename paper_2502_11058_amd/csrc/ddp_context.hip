@@ -906,6 +906,8 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     } else if (scheduled == 0) {
         rc = launch_update(f.kind, ctx->grad_dtype, f.with_model, ctx->d_runs, ctx->d_update + c0, c1 - c0, s, true, update_lds(ctx), stream);
     } else {
+        if (ctx->small && !ctx->update_lds_set)
+            f.lds_pad = residency_pad(ctx, small_wg_per_cu(ctx->cus, N, wire16, adamw, ctx->grad_dtype == DDP_BF16, chunks));
         f.runs = ctx->d_runs;
         f.chunks = ctx->d_update + c0;
         f.n_chunks = c1 - c0;

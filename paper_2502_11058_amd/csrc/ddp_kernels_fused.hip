@@ -23,10 +23,14 @@ struct FusedArgs {
     int halved;  // 1: two workgroups a chunk
 };
 
-// A chunk of a scheduled run takes fused_body, every other chunk the optimizer step only.  At least two wavefronts per
-// SIMD (the launch bounds): the residency that the launch asks for.
+// At least two wavefronts per SIMD (the launch bounds), the residency that the launch asks for.  SGD on 16 fp32 replicas with fp32 gradients: four,
+// which its 128 to 130 registers otherwise have or miss with any change (small_wg_per_cu, where both are measured).
+template <bool ADAM, bool GBF16, int NREP, bool EXACT, bool W16>
+constexpr int kWavesPerSimd = !ADAM && !GBF16 && NREP == 16 && EXACT && !W16 ? 4 : 2;
+
+// A chunk of a scheduled run takes fused_body, every other chunk the optimizer step only.
 template <bool ADAM, bool GBF16, bool MODEL, int NREP, bool EXACT, bool STATS, bool W16, bool UTS, bool PAIRS>
-__global__ __launch_bounds__(kThreads, 2) void fused_kernel(const FusedArgs a) {
+__global__ __launch_bounds__(kThreads, (kWavesPerSimd<ADAM, GBF16, NREP, EXACT, W16>)) void fused_kernel(const FusedArgs a) {
     __shared__ double lds[2][kThreads / kWave];
     const bool paced = ADAM && long_launch();  // (of use to whole chunks: half a chunk is one vector a thread)
     UpdateChunk ch = a.chunks[blockIdx.x >> a.halved];

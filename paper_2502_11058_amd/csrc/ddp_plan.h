@@ -207,6 +207,21 @@ inline int fused_wg_per_cu(int cus, bool dense, int N, bool wire16, bool adamw, 
     return little ? 4 : 3;
 }
 
+// Workgroups per CU that the table-driven fused step of a small model asks for, in a call of `chunks` workgroups (0: as many as its registers leave
+// room for).  SGD with fp32 gradients on 16 fp32 replicas has room for four: where the call is two rounds of those as well as of three, from 45/8 per CU
+// on, three are better.  On 32 bf16 replicas, the update first, it has room for five (the average first, for four): from 7 per CU on four.
+// As many as there is room for / three and four, separate tensors, us:
+//     N = 16, workgroups per CU   4.7 (18 x 260^2)   5.2 (20 x 260^2)   5.5 (9 x 400^2)   6.1 (10 x 400^2)   6.3 (24 x 260^2)   8.0 (13 x 400^2)
+//                                   10.1 / 12.2        10.4 / 12.3        10.5 / 12.3       14.6 / 13.8        15.2 / 13.8        16.5 / 15.1
+//     N = 32                      6.1 (10 x 400^2)   6.3 (24 x 260^2)   6.8 (26 x 260^2)  7.9 (30 x 260^2)   8.0 (13 x 400^2)
+//                                   14.6 / 17.7        14.1 / 18.0        16.5 / 18.7       22.1 / 19.7        21.5 / 19.6
+// and many layers of one to four chunks: N = 16 5.3 (340 x 60^2) 12.6 / 12.0, 5.6 (360 x 60^2) 13.2 / 12.2, 9.0 (230 x 100^2) 17.7 / 16.5.
+inline int small_wg_per_cu(int cus, int N, bool wire16, bool adamw, bool grad16, int64_t chunks) {
+    if (adamw || grad16) return 0;
+    if (N == 16 && !wire16 && 8 * chunks >= 45 * (int64_t)cus) return 3;
+    return N == 32 && wire16 && chunks >= 7 * (int64_t)cus ? 4 : 0;
+}
+
 // Workgroups of the table-free fused kernel over elements [e0, e1) of the arenas: chunks counted from the multiple of `line`
 // (kLine) at or below e0.
 inline int64_t dense_workgroups(int64_t e0, int64_t e1, int64_t chunk, int64_t line) { return (e1 - e0 / line * line + chunk - 1) / chunk; }

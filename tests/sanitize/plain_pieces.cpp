@@ -88,6 +88,14 @@ int main() {
             CHECK(round(256, 768) == 3 && round(256, 769) == 4 && round(256, 1024) == 4 && round(256, 1025) == 3 && round(304, 1216) == 4);
         }
     }
+    // small models, table-driven, SGD with fp32 gradients: three for 16 fp32 replicas from 45/8 workgroups per CU on, four for 32 bf16 ones from 7 on
+    CHECK(small_wg_per_cu(256, 16, false, false, false, 1439) == 0 && small_wg_per_cu(256, 16, false, false, false, 1440) == 3);
+    CHECK(small_wg_per_cu(256, 32, true, false, false, 1791) == 0 && small_wg_per_cu(256, 32, true, false, false, 1792) == 4);
+    for (int N : {2, 8, 15, 16, 17, 31, 32, 33})
+        for (int k = 0; k < 8; ++k) {
+            const bool w = k & 1, adamw = k & 2, g = k & 4, has = !adamw && !g && N == (w ? 32 : 16);
+            CHECK((small_wg_per_cu(256, N, w, adamw, g, 1 << 20) != 0) == has);
+        }
     // halves of chunks: no layer of 128 M elements, over separate tensors with one moment fewer than 16 M elements
     const int64_t layer = (int64_t)1 << 27, model = (int64_t)1 << 24;
     CHECK(takes_halves(1, 1, true, false) && takes_halves(100 * layer, layer - 1, true, false) && !takes_halves(layer, layer, true, true));

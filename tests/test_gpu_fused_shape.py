@@ -94,3 +94,14 @@ def test_captured_ranges_in_halves(dense_path):
         calls(None)
         assert all(torch.equal(a, b) for a, b in zip(result(), first))
     rep.close()
+
+
+@pytest.mark.parametrize("layerwise", [0, 2])
+@pytest.mark.parametrize("order", [0, 1])
+@pytest.mark.parametrize("n,wire16,chunks", [(16, False, 1439), (16, False, 1440), (32, True, 1791), (32, True, 1792)])
+def test_small_models_by_their_workgroups(oracle, n, wire16, chunks, order, layerwise):
+    """Small models over the table, on both sides of the lines in workgroups (45/8 and 7 per CU of 256) from which three and four of them take a CU."""
+    sizes = [1024 * k - (l % 3) for l, k in enumerate([1, chunks - 703, 2, 700])]
+    ts = [W.TensorSpec(f"l{l}", l, k) for l, k in enumerate(sizes)]
+    w = W.Workload(f"small{chunks}", ts, n_replicas=n, period=2, optimizer="sgdm", param_dtype="f32", lr=1e-2, sigma_drift=1e-3, iterations=2, policy="round_robin")
+    assert run_trajectory(oracle, w, iters=2, fused=True, wire16=wire16, layerwise=layerwise, order=order, options={"dense_path": 0}).frac() == 1.0

@@ -42,7 +42,7 @@ template <bool A, class K> int few(const FusedLaunch &f, const K &k) {
     return k.template go<A, false, false, 8, true, true, false, false, false>(0) + k.template go<A, false, false, 8, false, true, true, false, false>(0) +
            k.template go<A, false, false, 16, true, true, false, false, false>(0) + k.template go<A, false, false, 16, true, true, true, false, true>(0) +
            k.template go<A, false, false, 16, false, true, true, false, false>(0) + k.template go<A, false, false, 32, true, true, false, false, false>(0) +
-           k.template go<A, false, false, 32, true, true, true, false, true>(0);
+           k.template go<A, false, false, 32, true, true, true, false, true>(0) + k.template go<A, false, false, 16, true, true, false, true, false>(0);
 } } }
 #define dispatch_fused few
 #include "ddp_kernels_fused.hip"
@@ -62,9 +62,12 @@ def test_fused_kernels(tmp_path):
     for ln in r.stderr.splitlines():
         if m := re.search(r"remark: .*Function Name: (\S+)", ln):
             kernel = m[1]
-        elif m := re.search(r"remark: .* (SGPRs Spill|VGPRs Spill|ScratchSize)[^:]*: (\d+)", ln):
+        elif m := re.search(r"remark: .* (SGPRs Spill|VGPRs Spill|ScratchSize|Occupancy)[^:]*: (\d+)", ln):
             seen.setdefault(kernel, {})[m[1]] = int(m[2])
-    assert len(seen) == 7 and all("fused_kernel" in k and len(v) == 3 for k, v in seen.items())
-    assert {k: v for k, v in seen.items() if v["ScratchSize"] or v["VGPRs Spill"]} == {}
+    assert len(seen) == 8 and all("fused_kernel" in k and len(v) == 4 for k, v in seen.items())
+    # SGD on 16 fp32 replicas: four workgroups per CU, the average first and the update first, for one register of the latter
+    sixteen = [v for k, v in seen.items() if re.search(r"Li16ELb1ELb1ELb0ELb[01]ELb0E", k)]
+    assert len(sixteen) == 2 and all(v["Occupancy"] == 4 for v in sixteen)
+    assert {k: v for k, v in seen.items() if v["VGPRs Spill"] > (v in sixteen) or v["ScratchSize"] > 8 * v["VGPRs Spill"]} == {}
     # two scalar registers a peer: 28 to 99 with the pointers kept, at most 15 without
     assert {k: v["SGPRs Spill"] for k, v in seen.items() if v["SGPRs Spill"] > 20} == {}
