@@ -886,7 +886,9 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     const bool any = layer_stats && scheduled > 0;
     // One order of summation for a slot, whatever range the call has: the workgroups add a layer's partials up in the order of
     // the one-launch reduction, so they do it only in slots that this reduction serves.
-    const bool fold = any && plan.max_update_partials <= kStatSingleMax && folds_fused(ctx->cus, scheduled, most, chunks);
+    const int64_t e0 = layer_elem0(ctx, first), e1 = layer_elem0(ctx, first + count);
+    const int64_t bytes = (e1 - e0) / 4 * vector_bytes(N, wire16, adamw, ctx->grad_dtype == DDP_BF16);
+    const bool fold = any && plan.max_update_partials <= kStatSingleMax && folds_fused(ctx->cus, scheduled, most, chunks, bytes);
     f.wire16 = wire16;
     f.pairs = takes_pairs(ctx->cus, fused_chunk(ctx, halved), c1 - c0, scheduled, N, wire16);
     f.update_first = update_first;
@@ -898,7 +900,6 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     f.with_model = ctx->param_dtype == DDP_BF16;
     f.s = s;
     f.st = {any ? ctx->d_partials + (halved ? 2 * ctx->n_update : 0) : nullptr, layer_stats, fold ? ctx->d_counters : nullptr};
-    const int64_t e0 = layer_elem0(ctx, first), e1 = layer_elem0(ctx, first + count);
     f.lds_pad = fused_lds(ctx, halved, N, wire16, adamw, e1 - e0, chunks);
     const auto at = first_pass(plan, e0);
     if (ctx->dense_path && takes_pieces(plan, at, e1)) {

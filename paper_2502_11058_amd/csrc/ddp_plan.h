@@ -26,8 +26,10 @@ namespace ddp {
 // The line is drawn where the average crosses, and no layer has more than 256 CUs allow in all, whatever the device; the fused step, whose
 // workgroups have more to do, still gains at 352 and has a line of its own.
 inline bool folds(int cus, int64_t partials, int64_t most) { return 4 * partials <= 5 * (int64_t)cus && most <= 320; }
-// The fused step, whose chunks are half the size (kSmallChunk), up to 5/2 per CU with a pair where at least as many others hide what the
-// folding ones wait for.  Launch of their own / folded in us:
+// Bytes that a thread of the fused step asks for with one vector of all streams.
+inline int vector_bytes(int N, bool wire16, bool adamw, bool grad16) { return (wire16 ? 8 : 16) * (N - 1) + (adamw ? 48 : 32) + (grad16 ? 8 : 16); }
+
+// The fused step, whose chunks are half the size (kSmallChunk), up to 5/2 per CU with a pair.  Launch of their own / folded in us:
 //     8 layers, one of them scheduled, pairs      257             401             565             626
 //         SGD, N = 4                         10.6 /  9.8     15.2 / 13.4     19.7 / 18.1     21.4 / 19.6
 //         AdamW, N = 8                       14.8 / 13.7     20.5 / 18.8     28.0 / 26.1     30.6 / 28.8
@@ -35,12 +37,24 @@ inline bool folds(int cus, int64_t partials, int64_t most) { return 4 * partials
 //         SGD, N = 4                          8.9 /  7.1     10.0 /  9.8     12.5 / 12.6     13.6 / 12.5
 //         AdamW, N = 8                       10.4 / 10.5     14.0 / 14.3     18.2 / 18.0     18.8 / 17.1
 //         SGD, N = 16                        10.4 / 10.4     13.8 / 14.1     19.6 / 20.2     19.0 / 18.6
-// Where every chunk of the call has a pair, up to 5/4 as above.  12 layers, layer by layer:
-//                                pairs            479             564             625      whole chunks, 512             634
-//         SGD, N = 4                         51.2 / 52.8     57.1 / 59.5     61.1 / 63.3     77.1 / 79.4     92.5 / 94.5
-//         AdamW, N = 8                       66.7 / 68.2     79.1 / 80.5     80.7 / 83.2    109.0 / 111.2   134.8 / 137.7
-inline bool folds_fused(int cus, int64_t partials, int64_t most, int64_t chunks) {
-    return 2 * partials <= 5 * (int64_t)cus && (4 * partials <= 5 * (int64_t)cus || 2 * partials <= chunks) && most <= kFoldGroup * kFoldGroups;
+// Where every chunk of the call has a pair, and the call asks for 24 MB and more, layers of up to 5/4 as above: the kernel hides the host's time of another
+// launch, and a larger layer's counters make its workgroups wait longer.  In smaller calls that launch costs 2 us.  14 to 10 layers, layer by layer (MB a call):
+//     all scheduled               14 x 640^2 (400 pairs)           12 x 700^2 (479)                10 x 760^2 (565)
+//         SGD, N = 2                  (6.6) 117   /  93.1              (7.8) 102.7 /  85.5             (9.2)  81.7 /  77.5
+//         SGD, N = 4                  (9.8) 118.2 /  99.3             (11.8) 104.1 /  92.7            (13.9)  81.8 /  85.3
+//         SGD, N = 8                 (16.4) 111.8 / 115.3             (19.6) 113.8 / 109.2            (23.1)  97.3 / 104.1
+//         AdamW, N = 8               (17.2) 126.2 / 130.0             (20.6) 120.7 / 125.2            (24.3) 115.3 / 121.4
+//         AdamW, N = 16, bf16        (18.0) 145.8 / 150.2             (21.6) 139.1 / 147.0            (25.5) 134.3 / 141.5
+//     a quarter or third
+//         SGD, N = 4                  (9.8)  65.0 /  56.4             (11.8)  54.7 /  52.2            (13.9)  50.4 /  51.7
+//         SGD, N = 8                 (16.4)  65.9 /  61.1             (19.6)  59.2 /  56.3            (23.1)  55.7 /  57.2
+//         AdamW, N = 8               (17.2)  72.8 /  73.9             (20.6)  66.6 /  68.1            (24.3)  69.5 /  71.2
+//     one
+//         SGD, N = 8                 (16.4)  53.9 /  51.0             (19.6)  47.7 /  45.0            (23.1)  43.8 /  43.7
+// and small models, all scheduled, AdamW, N = 8: 12 x 200^2 (480 pairs, 40 a layer, 20.2 MB) 9.2 / 7.4, 6 x 300^2 (528, 88) 8.8 / 8.4; 1 x 700^2 (479, 20.6 MB) 8.8 / 7.5.
+inline bool folds_fused(int cus, int64_t partials, int64_t most, int64_t chunks, int64_t bytes) {
+    const bool waits = 4 * most > 5 * (int64_t)cus && 2 * partials > chunks;
+    return 2 * partials <= 5 * (int64_t)cus && !(waits && bytes >= 24'000'000) && most <= kFoldGroup * kFoldGroups;
 }
 
 // Where the average of N replicas cuts its chunks of `chunk` elements in two, a workgroup each (0: not).  The kernel for more than
@@ -130,9 +144,6 @@ inline bool takes_pairs(int cus, int64_t chunk, int64_t all, int64_t scheduled, 
 inline bool takes_halves(int64_t numel, int64_t largest_layer, bool dense, bool second_moment) {
     return largest_layer < (int64_t)1 << 27 && (dense || second_moment || numel < (int64_t)1 << 24);
 }
-
-// Bytes that a thread of the fused step asks for with one vector of all streams.
-inline int vector_bytes(int N, bool wire16, bool adamw, bool grad16) { return (wire16 ? 8 : 16) * (N - 1) + (adamw ? 48 : 32) + (grad16 ? 8 : 16); }
 
 // Whether a call on a slot of such a model, or on a range of its layers, takes halves: one answer for all of a worker's calls, whatever the
 // range, so that a slot's statistics have one order of summation.  Halves have more in flight, whole chunks fewer workgroups to start

@@ -118,11 +118,14 @@ int main() {
     CHECK(call_takes_halves(256, 10 * per, false, 3, false, false, false) && !call_takes_halves(256, 10 * per, false, 4, false, false, false));     // 80, 96
     // ... and a grid of less than 2^32 threads
     CHECK(halves_fit(1) && halves_fit(((int64_t)1 << 23) - 1) && !halves_fit((int64_t)1 << 23) && !halves_fit(INT32_MAX));
-    // statistics put together in the launch: 5/2 pairs per CU, 5/4 where less than half the call's chunks have none
-    const int64_t beside = 1 << 20;
-    CHECK(folds_fused(256, 640, 640, beside) && !folds_fused(256, 641, 1, beside) && !folds_fused(304, 641, 641, beside) && folds_fused(304, 760, 640, beside));
-    CHECK(folds_fused(256, 640, 640, 1280) && !folds_fused(256, 640, 640, 1279) && folds_fused(256, 320, 320, 320) && !folds_fused(256, 321, 321, 321));
-    CHECK(folds_fused(256, 321, 321, 642) && !folds_fused(256, 321, 321, 641) && folds_fused(304, 380, 380, 380) && !folds_fused(304, 381, 381, 381));
+    // statistics put together in the launch: 5/2 pairs per CU, 5/4 a layer where less than half the call's chunks have none and the call is one of 24 MB
+    const int64_t beside = 1 << 20, mb = 1000000;
+    CHECK(folds_fused(256, 640, 640, beside, 0) && !folds_fused(256, 641, 1, beside, 0) && !folds_fused(304, 641, 641, beside, 0));
+    CHECK(folds_fused(304, 760, 640, beside, 99 * mb) && folds_fused(256, 640, 640, 640, 24 * mb - 1) && !folds_fused(256, 641, 641, 641, 1));
+    auto of_24 = [&](int cus, int64_t partials, int64_t chunks) { return folds_fused(cus, partials, partials, chunks, 24 * mb); };
+    CHECK(of_24(256, 640, 1280) && !of_24(256, 640, 1279) && of_24(256, 320, 320) && !of_24(256, 321, 321));
+    CHECK(folds_fused(256, 640, 320, 640, 99 * mb) && !folds_fused(256, 640, 321, 640, 99 * mb));
+    CHECK(of_24(256, 321, 642) && !of_24(256, 321, 641) && of_24(304, 380, 380) && !of_24(304, 381, 381));
     std::printf("plain pieces ok: %ld calls\n", calls);
     return 0;
 }

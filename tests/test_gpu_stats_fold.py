@@ -1,5 +1,5 @@
 """Statistics that the workgroups put together themselves (launches in which up to 5/4 workgroups per CU have a
-share; the fused step up to 5/2 beside as many chunks without one) and those of a launch of their own, on both sides of the rule's lines: against the oracle, the same bits on every
+share; the fused step up to 5/2, large layers in calls of 24 MB beside as many chunks without one) and those of a launch of their own, on both sides of the rule's lines: against the oracle, the same bits on every
 repetition, the same bits for the allocation-free entry point (which never folds), and through a captured graph that is
 replayed between eager calls."""
 import numpy as np

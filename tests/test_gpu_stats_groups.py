@@ -1,6 +1,6 @@
 """Statistics that the workgroups put together themselves, counted in groups of 32 partial pairs: layers on both sides of a full
 group, of several groups, and of the line in pairs (320, 5/4 workgroups per CU), beside layers of one pair; and in the fused step, up to
-640 pairs (5/2 per CU) beside as many chunks without one, the most groups a layer has (20)."""
+640 pairs (5/2 per CU; layers beyond 320 in calls of 24 MB beside as many chunks without one), the most groups a layer has (20)."""
 import numpy as np
 import pytest
 import torch
@@ -20,13 +20,15 @@ def test_groups(oracle, per_layer):
 
 @pytest.mark.parametrize("default", [False, True])
 @pytest.mark.parametrize("dense_path", [1, 0])
-@pytest.mark.parametrize("pairs", [[321], [608], [609], [639], [640], [641], [320, 320], [320, 321], [577, 63], [1] * 20 + [600, 20]])
-def test_groups_beside_unscheduled_layers(oracle, pairs, dense_path, default):
-    """A slot of half the model: whole, its statistics are folded up to 640 pairs; range by range, where every chunk has a pair, up to 320, and
-    beyond by a launch of their own.  All of them give the same bits, and the oracle's values to 1e-10.  In chunks of 1024 elements that the caller
-    gives, and in the halves that the fused step takes by itself (six replicas, 128 bytes a vector)."""
+@pytest.mark.parametrize("n,pairs", [(6, p) for p in ([321], [608], [609], [639], [640], [641], [320, 320], [320, 321], [577, 63], [1] * 20 + [600, 20])] +
+                         [(8, p) for p in ([585], [586], [640], [641], [320, 320], [1] * 20 + [600, 20])])
+def test_groups_beside_unscheduled_layers(oracle, n, pairs, dense_path, default):
+    """A slot of half the model: whole, its statistics are folded up to 640 pairs; range by range, where every chunk has a pair, layers beyond 320 only in
+    calls of less than 24 MB (eight replicas: up to 585 pairs), else by a launch of their own.  All of them give the same bits, and the oracle's
+    values to 1e-10.  In chunks of 1024 elements that the caller gives, and in the halves that the fused step takes by itself (128 and 160 bytes
+    a vector)."""
     assert torch.cuda.is_available(), "no GPU visible"
-    n, L = 6, len(pairs)
+    L = len(pairs)
     sizes = [1024 * k - (l % 3) for l, k in enumerate(pairs)]
     rest = 2_400_000 if default else sum(sizes) + 2048          # (2.4 to 3.1 M elements: past the small models, short of whole chunks)
     ts = [W.TensorSpec(f"l{l}", l, k) for l, k in enumerate(sizes)] + [W.TensorSpec("rest", L, rest)]
