@@ -128,9 +128,9 @@ static int residency_pad(const ddp_ctx *c, int wg_per_cu) {
 
 // The residency request of the update, and of the fused step (fused_wg_per_cu).
 static int update_lds(const ddp_ctx *c) { return c->small && !c->update_lds_set ? 0 : c->update_lds; }
-static int fused_lds(const ddp_ctx *c, bool halved, int N, bool wire16, bool adamw, int64_t elements, int64_t halves) {
+static int fused_lds(const ddp_ctx *c, bool halved, int N, bool wire16, bool adamw, int64_t elements, int64_t halves, int64_t slot) {
     if (!halved) return update_lds(c);
-    return residency_pad(c, fused_wg_per_cu(c->cus, c->dense, N, wire16, adamw, c->grad_dtype == DDP_BF16, elements, halves));
+    return residency_pad(c, fused_wg_per_cu(c->cus, c->dense, N, wire16, adamw, c->grad_dtype == DDP_BF16, elements, halves, slot));
 }
 
 // Elements per workgroup of the fused step.
@@ -871,7 +871,8 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     // single run).
     const bool adamw = opt->kind == DDP_OPT_ADAMW;
     // (a residency that the caller gives is one of whole chunks)
-    const bool halved = ctx->halves && !ctx->update_lds_set && call_takes_halves(ctx->cus, layer_elem0(ctx, ctx->L), ctx->dense, N, wire16, adamw, ctx->grad_dtype == DDP_BF16);
+    const bool halved = ctx->halves && !ctx->update_lds_set && call_takes_halves(ctx->cus, layer_elem0(ctx, ctx->L), st->numel, st->max_update_partials, ctx->dense, N, wire16,
+                                                                                       adamw, ctx->grad_dtype == DDP_BF16);
     const FusedPlan &plan = halved ? st->halves : *st;
     const int64_t chunks = (halved ? 2 : 1) * (c1 - c0);
     const int nl = (int)st->layers.size();
@@ -900,7 +901,7 @@ static int fused_impl(ddp_ctx *ctx, const char *who, bool wire16, bool update_fi
     f.with_model = ctx->param_dtype == DDP_BF16;
     f.s = s;
     f.st = {any ? ctx->d_partials + (halved ? 2 * ctx->n_update : 0) : nullptr, layer_stats, fold ? ctx->d_counters : nullptr};
-    f.lds_pad = fused_lds(ctx, halved, N, wire16, adamw, e1 - e0, chunks);
+    f.lds_pad = fused_lds(ctx, halved, N, wire16, adamw, e1 - e0, chunks, st->numel);
     const auto at = first_pass(plan, e0);
     if (ctx->dense_path && takes_pieces(plan, at, e1)) {
         rc = fused_dense(ctx, plan, halved, at, e0, e1, f, stream);

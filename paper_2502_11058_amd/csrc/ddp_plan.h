@@ -146,8 +146,9 @@ inline bool takes_halves(int64_t numel, int64_t largest_layer, bool dense, bool 
 }
 
 // Whether a call on a slot of such a model, or on a range of its layers, takes halves: one answer for all of a worker's calls, whatever the
-// range, so that a slot's statistics have one order of summation.  Halves have more in flight, whole chunks fewer workgroups to start
-// and half the partial sums, which decides in models of a few chunks (2048 elements) per CU as long as a vector is small.
+// range, so that a slot's statistics have one order of summation.  slot: its elements, layer: the chunks of its largest layer.  Halves have more
+// in flight, whole chunks fewer workgroups to start and half the partial sums, which decides in models of a few chunks (2048 elements) per CU
+// as long as a vector is small.
 // Fused step, whole chunks and two workgroups per CU / halves and three, us, dense arenas, a quarter or a fifth of the layers scheduled:
 //         chunks per CU               4.8 (12 x 460^2)   5.4 (5 x 750^2)   7.7 (12 x 580^2)   9.4 (12 x 640^2)  13.2 (12 x 760^2)  18.6 (12 x 900^2)
 //     AdamW, N =  4, fp32 (104 bytes)    14.7 / 14.8       15.4 / 15.1       22.5 / 25.0        26.5 / 28.5        38.1 / 39.3        51.9 / 51.8
@@ -160,19 +161,35 @@ inline bool takes_halves(int64_t numel, int64_t largest_layer, bool dense, bool 
 //     SGD,   N =  8, fp32 (160)          13.8 / 12.5       14.1 / 12.9       19.4 / 21.2        24.2 / 24.3        33.5 / 33.0        44.6 / 44.6
 //     SGD,   N = 16, fp32 (288)          18.8 / 17.5       20.0 / 17.8       26.4 / 27.7        34.4 / 31.7        44.6 / 43.6        61.9 / 59.9
 // So whole chunks from 6 to 10 chunks per CU, up to 200 bytes a vector, and with SGD below 6 too up to 120 bytes (in models of less than 5/4
-// chunks per CU halves: 12 layers of 200^2, N = 4 4.9 / 4.9, N = 16 7.3 / 6.4).  Layer by layer the halves would be the better ones with AdamW,
-// 640^2, N = 4 58.8 / 58.1, N = 8 63.8 / 61.9, but what the whole-model call gains is more; beyond 10 it is less, and four workgroups per CU
-// give most of it (fused_wg_per_cu).  Over separate tensors with SGD, where the unscheduled layers come in halves too, whole chunks from
-// 5/4 on: N = 8 5.4 per CU 14.3 / 14.3, 7.2 18.3 / 20.7, 18.6 44.6 / 45.8, bf16 39.6 / 41.2, 27.7 58.2 / 60.8, N = 16 24.8 / 27.7 and 88.0 / 89.7; but
-// halves for the largest vectors (N = 24, 9.4 per CU 45.2 / 41.9, 14.7 63.1 / 60.5) and, from 10 on, the smallest, at four per CU (N = 2, 18.6 35.2 / 35.0,
-// bf16 27.7 50.9 / 50.4).
-inline bool call_takes_halves(int cus, int64_t numel, bool dense, int N, bool wire16, bool adamw, bool grad16) {
+// chunks per CU only with a layer of half a chunk per CU: 700^2, N = 2 5.6 / 6.0, separate tensors N = 4 5.7 / 6.4, two of 520^2,
+// N = 8 bf16 7.5 / 7.1, 12 layers of 200^2, N = 4 4.9 / 4.9, N = 16 7.3 / 6.4).  Beyond 10 they gain less, and four
+// workgroups per CU give most of it (fused_wg_per_cu).  Over dense arenas only for slots of some size: with a small one most of the call are unscheduled
+// layers, which are the faster for three workgroups per CU, with a large one the second vector's wait is most of it.  Whole / halves again, by the chunks
+// per CU of the slot:
+//     12 x 580^2                  0.6           1.3           1.9           3.9         12 x 490^2 (5.5 per CU)    0.5           0.9           1.4           2.7
+//         SGD, N = 4          16.9 / 15.8   16.7 / 17.0   16.3 / 17.9   20.1 / 20.7         SGD, N = 4         12.5 / 11.6   12.7 / 11.7   12.2 / 13.2   15.3 / 15.3
+//         SGD, N = 8          19.0 / 17.8   20.0 / 19.6   19.6 / 21.4   25.4 / 25.9         N = 4 by layers                                              55.0 / 51.6
+//         AdamW, N = 4        23.4 / 23.9   23.0 / 24.6   22.6 / 25.1   26.6 / 26.8         SGD, N = 8 bf16    13.3 / 12.4   13.6 / 12.7   13.3 / 14.3   16.1 / 17.2
+//         AdamW, N = 8        25.8 / 25.7   26.6 / 26.8   26.2 / 28.6   32.8 / 32.6
+//         AdamW, N = 16 bf16  27.6 / 27.6   28.1 / 28.2   27.2 / 29.7   33.9 / 35.8
+// and AdamW, 6 x 880^2, 3.0, N = 2 25.7 / 25.1, N = 8 34.5 / 32.9, by layers 47.8 / 45.2.  Layer by layer AdamW prefers halves throughout (12 x 580^2, 1.9, N = 4
+// 57.7 / 57.2, N = 8 62.1 / 60.5), but what the whole-model call gains is more; not with layers of less than half a chunk per CU: 24 x 420^2, 1.4, N = 4
+// 23.3 / 24.1 and 90.2 / 87.3, N = 8 27.3 / 26.3 and 97.2 / 89.7, separate tensors, 0.7, N = 8 25.9 / 25.0.
+// Over separate tensors, where the unscheduled layers come in halves too, whole chunks whatever the slot (7.7 per CU, slot 0.6, N = 8 SGD 18.9 / 20.0, AdamW
+// 25.5 / 26.0), with SGD from 5/4 on: N = 8 5.4 per CU 14.3 / 14.3, 7.2 18.3 / 20.7, 18.6 44.6 / 45.8, bf16 39.6 / 41.2, 27.7 58.2 / 60.8, N = 16
+// 24.8 / 27.7 and 88.0 / 89.7, N = 2, 13.2 25.0 / 26.0; but halves for the largest vectors (N = 24, 9.4 per CU 45.2 / 41.9, 14.7 63.1 / 60.5).
+inline bool call_takes_halves(int cus, int64_t numel, int64_t slot, int64_t layer, bool dense, int N, bool wire16, bool adamw, bool grad16) {
     const int64_t chunks = (numel + 2047) / 2048, bytes = vector_bytes(N, wire16, adamw, grad16);
-    const bool below_6 = chunks < 6 * (int64_t)cus, below_10 = chunks < 10 * (int64_t)cus;
-    if (adamw) return below_6 || !below_10 || bytes >= 200;
-    if (4 * chunks <= 5 * (int64_t)cus || bytes >= 300) return true;
-    if (below_10) return dense && bytes >= (below_6 ? 120 : 200);
-    return dense || bytes < 96;
+    const bool below_6 = chunks < 6 * (int64_t)cus, below_10 = chunks < 10 * (int64_t)cus, large = bytes >= 150, many16 = wire16 && bytes >= 96;
+    auto slot_from = [&](int quarters) { return 4 * ((slot + 2047) / 2048) >= quarters * (int64_t)cus; };  // quarters of a chunk per CU
+    if (adamw) {
+        if (below_6 || !below_10 || bytes >= 200 || 2 * layer < cus) return true;
+        return dense && (!slot_from(large ? 6 : 3) || (slot_from(10) && !many16));
+    }
+    if (bytes >= 300) return true;
+    if (4 * chunks <= 5 * (int64_t)cus) return 2 * layer < cus || bytes >= 120 || many16;
+    if (!dense) return false;
+    return !below_10 || bytes >= (below_6 ? 120 : 200) || !slot_from(large ? 7 : 5) || (below_6 && slot_from(10));
 }
 
 // A launch has less than 2^32 threads in x (hipErrorInvalidConfiguration from there on, measured: 2^24 - 1 workgroups of 256 run, 2^24 are
@@ -195,10 +212,11 @@ inline bool halves_fit(int64_t n_update) { return 2 * n_update < (int64_t)1 << 2
 //     AdamW, N =  4, bf16       72    62.5 /  62.7    133.2 / 134.7    298.8 / 299.8    743.5 /  746.5
 //     AdamW, N =  8, fp32      168    74.7 /  75.5    159.5 / 165.0    356.1 / 360.4    878.5 /  887.3
 // So four with SGD and less than 96 bytes a vector, with AdamW, a third more bytes to write, for three bf16 replicas; else three.
-// Four also in short AdamW calls, of 6 to 24 chunks (2048 elements) per CU, which are too few rounds of workgroups for three:
-//     580^2 (7.7), N = 24, bf16 33.6 / 33.4, 640^2 (9.4), N = 12 36.0 / 35.6, N = 24, bf16 38.7 / 37.1, 760^2 (13.2), N = 4 39.3 / 38.9, N = 8 44.6 / 44.1,
-//     N = 16, bf16 44.9 / 44.4, 900^2 (18.6), N = 8, bf16 53.0 / 52.6, 5 layers of 1100^2 (11.6), N = 8, bf16 34.4 / 33.6; below 6 only with less than 96
-//     bytes, 460^2 (4.8), N = 2 13.5 / 12.8, N = 8 16.6 / 17.6, 5 of 750^2 (5.4), N = 6 16.5 / 17.1
+// Four also in short AdamW calls over dense arenas, of 6 to 16 chunks (2048 elements) per CU, which are too few rounds of workgroups for three, if the slot has 3/2
+// and more per CU: 760^2 (13.2), slot 3.3, N = 4 39.3 / 38.9, N = 8 44.6 / 44.1, N = 16, bf16 44.9 / 44.4, slot 2.2, N = 8 41.9 / 40.9, N = 16, bf16 44.7 / 43.2, slot 1.1
+// 39.2 / 39.5, 41.0 / 41.5, 5 layers of 1100^2 (11.6), N = 8, bf16 34.4 / 33.6, 24 of 640^2 (18.8), slot 3.1, N = 4 50.8 / 51.1, slot 0.8, N = 16, bf16 51.6 / 52.8,
+// separate tensors 760^2, slot 3.3, N = 8 43.7 / 44.6, slot 1.1 38.1 / 39.4.  With less than 96 bytes up to 24 in all cases, 460^2 (4.8), N = 2 13.5 / 12.8
+// (N = 8 16.6 / 17.6),
 // and where the call is then one round: layer by layer, 1024^2, SGD, N = 8 86.5 / 84.9, bf16, N = 12 90.3 / 87.7, AdamW, N = 8 109.9 / 108.3.
 // Two over dense arenas in calls on 64 M elements and more of 16 to 32 fp32 replicas, whose three would have over 200 KB in flight per CU.
 // Halves and three / halves and two, 10 layers:
@@ -209,13 +227,14 @@ inline bool halves_fit(int64_t n_update) { return 2 * n_update < (int64_t)1 << 2
 //     N = 32, AdamW  272 / 280      1063 / 1055     1908 / 1880       (N = 12, AdamW 164 / 180, 1140 / 1157)
 // (more replicas, through LDS: 12 of 3600^2, N = 40, SGD 1579 / 1769, N = 64 2953 / 3920; separate tensors, N = 16, AdamW, 12 of 3000^2 775 / 798, 12 of
 // 6500^2 3728 / 3819).
-inline int fused_wg_per_cu(int cus, bool dense, int N, bool wire16, bool adamw, bool grad16, int64_t elements, int64_t halves) {
+inline int fused_wg_per_cu(int cus, bool dense, int N, bool wire16, bool adamw, bool grad16, int64_t elements, int64_t halves, int64_t slot) {
     if (dense && !wire16 && N >= 16 && N <= 32 && elements >= (int64_t)1 << 26) return 2;
     if (halves > 3 * (int64_t)cus && halves <= 4 * (int64_t)cus) return 4;
     const int64_t chunks = (elements + 2047) / 2048;
     const bool little = vector_bytes(N, wire16, adamw, grad16) < 96;
-    if (adamw) return (N == 3 && wire16) || (chunks < 24 * (int64_t)cus && (little || chunks >= 6 * (int64_t)cus)) ? 4 : 3;
-    return little ? 4 : 3;
+    if (!adamw) return little ? 4 : 3;
+    if ((N == 3 && wire16) || (little && chunks < 24 * (int64_t)cus)) return 4;
+    return dense && chunks >= 6 * (int64_t)cus && chunks < 16 * (int64_t)cus && 2 * ((slot + 2047) / 2048) >= 3 * (int64_t)cus ? 4 : 3;
 }
 
 // Workgroups per CU that the table-driven fused step of a small model asks for, in a call of `chunks` workgroups (0: as many as its registers leave

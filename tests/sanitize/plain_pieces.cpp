@@ -70,21 +70,24 @@ int main() {
             if (!st.dense_passes.empty()) CHECK(at == e1);
         }
     }
-    // workgroups per CU: with SGD four below 96 bytes per thread, with AdamW for three bf16 replicas and in calls of up to 24 chunks per CU (below 6 only
-    // with less than 96 bytes), and where that makes the call one round of them; else three; two over dense arenas for 16 to 32 fp32 replicas from 64 M elements on
+    // workgroups per CU: with SGD four below 96 bytes per thread, with AdamW for three bf16 replicas, in calls of up to 24 chunks per CU with less than 96 bytes,
+    // over dense arenas from 6 to 16 chunks per CU in slots of 3/2, and where that makes the call one round of them; else three; two over dense arenas for
+    // 16 to 32 fp32 replicas from 64 M elements on
     const int64_t some = 1, large = (int64_t)1 << 26, cu = 256 * 2048;
-    auto sgd = [&](int N, bool wire16, bool grad16 = false) { return fused_wg_per_cu(256, true, N, wire16, false, grad16, 1 << 24, some); };
+    auto sgd = [&](int N, bool wire16, bool grad16 = false) { return fused_wg_per_cu(256, true, N, wire16, false, grad16, 1 << 24, some, 1 << 24); };
     CHECK(sgd(2, false) == 4 && sgd(3, false) == 4 && sgd(4, false) == 3 && sgd(5, false) == 3 && sgd(8, false) == 3);  // 64, 80, 96, 112, 160 bytes
     CHECK(sgd(6, true) == 4 && sgd(7, true) == 3 && sgd(7, true, true) == 4 && sgd(8, true, true) == 3 && sgd(64, true) == 3);  // 88, 96, 88, 96
     for (bool dense : {true, false}) {
-        auto adamw = [&](int N, bool wire16, int64_t e) { return fused_wg_per_cu(256, dense, N, wire16, true, true, e, some); };
+        auto adamw = [&](int N, bool wire16, int64_t e, int64_t slot = 3 * 128 * 2048) { return fused_wg_per_cu(256, dense, N, wire16, true, true, e, some, slot); };
         CHECK(adamw(2, true, large) == 3 && adamw(3, true, large) == 4 && adamw(3, false, large) == 3 && adamw(4, true, large) == 3);
         CHECK(adamw(3, false, 1) == 4 && adamw(4, false, 1) == 3 && adamw(6, true, 1) == 3 && adamw(5, true, 1) == 4 && adamw(2, true, 24 * cu) == 3);  // 88, 104, 96
-        CHECK(adamw(8, false, 6 * cu - 2048) == 3 && adamw(8, false, 6 * cu) == 4 && adamw(32, true, 24 * cu - 2048) == 4 && adamw(32, true, 24 * cu) == 3);
+        const int four = dense ? 4 : 3;
+        CHECK(adamw(8, false, 6 * cu - 2048) == 3 && adamw(8, false, 6 * cu) == four && adamw(32, true, 16 * cu - 2048) == four && adamw(32, true, 16 * cu) == 3);
+        CHECK(adamw(8, false, 6 * cu, 3 * cu / 2 - 2048) == 3 && adamw(3, false, 24 * cu - 2048, 0) == 4 && adamw(3, false, 24 * cu, 0) == 3);
         CHECK(adamw(16, false, large) == (dense ? 2 : 3) && adamw(16, false, large - 1) == 3 && adamw(15, false, large) == 3 && adamw(16, true, large) == 3);
         CHECK(adamw(32, false, large) == (dense ? 2 : 3) && adamw(33, false, large) == 3 && adamw(64, false, large) == 3);
         for (int N : {8, 40}) {
-            auto round = [&](int cus, int64_t halves) { return fused_wg_per_cu(cus, dense, N, false, N == 8, true, 1, halves); };
+            auto round = [&](int cus, int64_t halves) { return fused_wg_per_cu(cus, dense, N, false, N == 8, true, 1, halves, 1); };
             CHECK(round(256, 768) == 3 && round(256, 769) == 4 && round(256, 1024) == 4 && round(256, 1025) == 3 && round(304, 1216) == 4);
         }
     }
@@ -101,21 +104,28 @@ int main() {
     CHECK(takes_halves(1, 1, true, false) && takes_halves(100 * layer, layer - 1, true, false) && !takes_halves(layer, layer, true, true));
     CHECK(takes_halves(model - 1, 1, false, false) && !takes_halves(model, 1, false, false) && takes_halves(model, 1, false, true));
     // ... in calls as measured: whole chunks from 6 to 10 chunks of 2048 per CU for vectors of less than 200 bytes, with SGD below 6 too for less than
-    // 120; over separate tensors with SGD from 5/4 on, but for vectors of 300 bytes and more and, from 10 on, of less than 96
+    // 120, in slots of some size; over separate tensors whatever the slot, with SGD from 5/4 on, but for vectors of 300 bytes and more
     const int64_t per = 256 * 2048;
     for (bool dense : {true, false}) {
-        CHECK(call_takes_halves(256, 6 * per - 2048, dense, 4, false, true, true) && !call_takes_halves(256, 6 * per, dense, 4, false, true, true));
-        CHECK(!call_takes_halves(256, 10 * per - 2048, dense, 4, false, true, true) && call_takes_halves(256, 10 * per, dense, 4, false, true, true));
-        CHECK(!call_takes_halves(256, 8 * per, dense, 9, false, true, true) && call_takes_halves(256, 8 * per, dense, 10, false, true, true));     // 184, 200 bytes
-        CHECK(!call_takes_halves(256, 8 * per, dense, 18, true, true, true) && call_takes_halves(256, 8 * per, dense, 19, true, true, true));      // 192, 200
-        CHECK(call_takes_halves(256, per * 5 / 4, dense, 4, false, false, false) && !call_takes_halves(256, per * 5, dense, 4, false, false, false));
-        CHECK(!call_takes_halves(256, 10 * per - 2048, dense, 5, false, false, false) && call_takes_halves(256, 10 * per, dense, 4, true, false, false));
-        CHECK(call_takes_halves(256, 5 * per, dense, 32, false, false, false) && call_takes_halves(256, 9 * per, dense, 18, false, false, false));  // 544, 320
+        auto halves = [&](int64_t numel, int N, bool wire16, bool adamw, int64_t slot = 2 * 256 * 2048, int64_t layer = 128) {
+            return call_takes_halves(256, numel, slot, layer, dense, N, wire16, adamw, adamw);
+        };
+        CHECK(halves(6 * per - 2048, 4, false, true) && !halves(6 * per, 4, false, true) && !halves(10 * per - 2048, 4, false, true) && halves(10 * per, 4, false, true));
+        CHECK(!halves(8 * per, 9, false, true) && halves(8 * per, 10, false, true) && !halves(8 * per, 18, true, true) && halves(8 * per, 19, true, true));  // 184, 200, 192, 200
+        CHECK(halves(8 * per, 4, false, true, 2 * per, 127));                                                                     // layers of less than half a chunk per CU
+        CHECK(halves(8 * per, 4, false, true, 3 * per / 4 - 2048) == dense && !halves(8 * per, 4, false, true, 3 * per / 4));
+        CHECK(halves(8 * per, 8, false, true, 3 * per / 2 - 2048) == dense && !halves(8 * per, 8, false, true, 3 * per / 2));     // 168 bytes
+        CHECK(!halves(8 * per, 4, false, true, 5 * per / 2 - 2048) && halves(8 * per, 4, false, true, 5 * per / 2) == dense);
+        CHECK(halves(8 * per, 5, true, true, 5 * per / 2) == dense && !halves(8 * per, 6, true, true, 5 * per / 2));              // 88, 96
+        CHECK(halves(per * 5 / 4, 4, false, false, per, 127) && !halves(per * 5 / 4, 4, false, false, per, 128) && halves(per * 5 / 4, 6, false, false, per, 128) &&
+              halves(per * 5 / 4, 8, true, false, per, 128) && halves(per * 5 / 4, 7, true, false, per, 128) && !halves(per * 5 / 4, 6, true, false, per, 128));
+        CHECK(!halves(per * 5, 4, false, false) && halves(5 * per, 32, false, false) && halves(9 * per, 18, false, false));
+        CHECK(halves(8 * per, 4, false, false, 5 * per / 4 - 2048) == dense && !halves(8 * per, 4, false, false, 5 * per / 4) && !halves(8 * per, 4, false, false, 6 * per));
+        CHECK(halves(8 * per, 8, false, false, 7 * per / 4 - 2048) == dense && !halves(8 * per, 8, false, false, 7 * per / 4));   // 160
+        CHECK(!halves(5 * per, 4, false, false, 5 * per / 2 - 2048) && halves(5 * per, 4, false, false, 5 * per / 2) == dense);
+        CHECK(!halves(5 * per, 5, false, false) && halves(5 * per, 6, false, false) == dense && halves(6 * per, 11, false, false) == dense);  // 112, 128, 208
+        CHECK(!halves(10 * per - 2048, 4, false, false) && halves(10 * per, 4, false, false) == dense && halves(10 * per, 2, true, false) == dense);
     }
-    CHECK(!call_takes_halves(256, 5 * per, true, 5, false, false, false) && call_takes_halves(256, 5 * per, true, 6, false, false, false));          // 112, 128
-    CHECK(!call_takes_halves(256, 6 * per, true, 10, false, false, false) && call_takes_halves(256, 6 * per, true, 11, false, false, false));       // 192, 208
-    CHECK(call_takes_halves(256, 10 * per, true, 16, false, false, false) && !call_takes_halves(256, 10 * per, false, 16, false, false, false));    // 288
-    CHECK(call_takes_halves(256, 10 * per, false, 3, false, false, false) && !call_takes_halves(256, 10 * per, false, 4, false, false, false));     // 80, 96
     // ... and a grid of less than 2^32 threads
     CHECK(halves_fit(1) && halves_fit(((int64_t)1 << 23) - 1) && !halves_fit((int64_t)1 << 23) && !halves_fit(INT32_MAX));
     // statistics put together in the launch: 5/2 pairs per CU, 5/4 a layer where less than half the call's chunks have none and the call is one of 24 MB

@@ -105,3 +105,15 @@ def test_small_models_by_their_workgroups(oracle, n, wire16, chunks, order, laye
     ts = [W.TensorSpec(f"l{l}", l, k) for l, k in enumerate(sizes)]
     w = W.Workload(f"small{chunks}", ts, n_replicas=n, period=2, optimizer="sgdm", param_dtype="f32", lr=1e-2, sigma_drift=1e-3, iterations=2, policy="round_robin")
     assert run_trajectory(oracle, w, iters=2, fused=True, wire16=wire16, layerwise=layerwise, order=order, options={"dense_path": 0}).frac() == 1.0
+
+
+@pytest.mark.parametrize("dense_path", [1, 0])
+@pytest.mark.parametrize("layerwise", [0, 1])
+@pytest.mark.parametrize("optimizer", ["sgdm", "adamw"])
+@pytest.mark.parametrize("period", [10, 5, 2])
+def test_slots_of_all_sizes(oracle, period, optimizer, layerwise, dense_path):
+    """A model of 7.6 chunks of 2048 elements per CU: slots of 0.8, 1.5 and 3.8, which take halves of chunks, whole ones, and either by the optimizer."""
+    ts = [W.TensorSpec(f"l{l}", l, 400_001 + 7 * l) for l in range(10)]
+    w = W.Workload(f"slots{period}", ts, n_replicas=4, period=period, optimizer=optimizer, param_dtype="bf16" if optimizer == "adamw" else "f32", lr=1e-3,
+                   sigma_drift=1e-3, iterations=1, policy="round_robin")
+    assert run_trajectory(oracle, w, iters=1, fused=True, layerwise=layerwise, options={"dense_path": dense_path}).frac() == 1.0
