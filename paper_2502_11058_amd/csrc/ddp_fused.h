@@ -19,7 +19,16 @@ struct Peers {
     int stage_threads;  // run-time replica count with statistics: threads that take part in the vector loop
 };
 
-// (entries from N-1 on are never read)
+// The peers' pointers as they lie in the launch's arguments, whose first bytes they are in every fused kernel, as an address that the compiler takes for
+// a new one: what it has in registers from an earlier read is not kept for this one.
+typedef const void *const __attribute__((address_space(4))) *PeerPointers;
+__device__ __forceinline__ PeerPointers peers_again() {
+    auto p = (PeerPointers)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
+// (entries from N-1 on are never used)
 inline void fill_peers(Peers &p, const FusedLaunch &f) {
     for (int k = 0; k + 1 < f.n_replicas; ++k) p.x[k] = f.x[k];
     p.inv_n = f.inv_n;
@@ -194,14 +203,18 @@ __device__ __forceinline__ void fused_body(const Streams<GBF16> c, int64_t fo, c
         // The table-driven kernels of 9 and more replicas read the peers' pointers again: kept over the vector loop, for a handful of elements, they
         // made up to 94 scalar registers spill (12 layers of 2304^2, separate tensors, bf16 peers, us kept / read again: SGD, N = 12 269.1 / 262.0,
         // N = 32 387.0 / 373.2, layer by layer 441.0 / 418.5).  The table-free ones keep them without, and read again a short call is slower (15 layers
-        // of 166^2, AdamW, N = 32 bf16 9.2 / 9.9).
+        // of 166^2, AdamW, N = 32 bf16 9.2 / 9.9).  Eight pointers are read at a time: one by one each element waits for its pointer (13 layers of 142^2,
+        // separate tensors, one by one / eight, AdamW, N = 12 bf16 7.7 / 7.4, N = 32 bf16 9.3 / 8.5, SGD 8.6 / 8.1; large calls alike).
         constexpr bool kAgain = !BUF && NREP >= 16;
         xelem peer[kTogether ? NREP - 1 : 1];
         if constexpr (kTogether) {
+            PeerPointers again = nullptr;
 #pragma unroll
             for (int j = 0; j < NREP - 1; ++j) {
+                if constexpr (kAgain)
+                    if (j % 8 == 0) again = peers_again();
                 peer[j] = xelem{};
-                if (j < kPeersAlways<NREP, EXACT> || j < nrep - 1) peer[j] = ld1(reinterpret_cast<const xelem *>(a.x[kAgain ? fresh(j) : j]) + fo, i);
+                if (j < kPeersAlways<NREP, EXACT> || j < nrep - 1) peer[j] = ld1(reinterpret_cast<const xelem *>(kAgain ? again[j] : a.x[j]) + fo, i);
             }
         }
         float pl = ld1(c.p, i), av = ld1(c.s0, i), bv = ADAM ? ld1(c.s1, i) : 0.0f;

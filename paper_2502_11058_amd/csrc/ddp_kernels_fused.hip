@@ -22,6 +22,7 @@ struct FusedArgs {
     int chunk_elems;
     int halved;  // 1: two workgroups a chunk
 };
+static_assert(offsetof(FusedArgs, peers) == 0 && offsetof(Peers, x) == 0, "peers_again reads them at the start of the arguments");
 
 // At least two wavefronts per SIMD (the launch bounds), the residency that the launch asks for.  SGD on 16 fp32 replicas with fp32 gradients: four,
 // which its 128 to 130 registers otherwise have or miss with any change (small_wg_per_cu, where both are measured).

@@ -69,5 +69,5 @@ def test_fused_kernels(tmp_path):
     sixteen = [v for k, v in seen.items() if re.search(r"Li16ELb1ELb1ELb0ELb[01]ELb0E", k)]
     assert len(sixteen) == 2 and all(v["Occupancy"] == 4 for v in sixteen)
     assert {k: v for k, v in seen.items() if v["VGPRs Spill"] > (v in sixteen) or v["ScratchSize"] > 8 * v["VGPRs Spill"]} == {}
-    # two scalar registers a peer: 28 to 99 with the pointers kept, at most 15 without
-    assert {k: v["SGPRs Spill"] for k, v in seen.items() if v["SGPRs Spill"] > 20} == {}
+    # two scalar registers a peer: 28 to 99 with the pointers kept, at most 26 with eight of them read at a time
+    assert {k: v["SGPRs Spill"] for k, v in seen.items() if v["SGPRs Spill"] > 27} == {}
