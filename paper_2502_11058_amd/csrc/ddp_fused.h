@@ -205,16 +205,18 @@ __device__ __forceinline__ void fused_body(const Streams<GBF16> c, int64_t fo, c
         // N = 32 387.0 / 373.2, layer by layer 441.0 / 418.5).  The table-free ones keep them without, and read again a short call is slower (15 layers
         // of 166^2, AdamW, N = 32 bf16 9.2 / 9.9).  Eight pointers are read at a time: one by one each element waits for its pointer (13 layers of 142^2,
         // separate tensors, one by one / eight, AdamW, N = 12 bf16 7.7 / 7.4, N = 32 bf16 9.3 / 8.5, SGD 8.6 / 8.1; large calls alike).
-        constexpr bool kAgain = !BUF && NREP >= 16;
+        // With two vectors in flight, which only long calls have, one by one: eight would make up to 86 more spill.
+        constexpr bool kAgain = !BUF && NREP >= 16, kEight = kAgain && !PAIRS;
         xelem peer[kTogether ? NREP - 1 : 1];
         if constexpr (kTogether) {
             PeerPointers again = nullptr;
 #pragma unroll
             for (int j = 0; j < NREP - 1; ++j) {
-                if constexpr (kAgain)
+                if constexpr (kEight)
                     if (j % 8 == 0) again = peers_again();
                 peer[j] = xelem{};
-                if (j < kPeersAlways<NREP, EXACT> || j < nrep - 1) peer[j] = ld1(reinterpret_cast<const xelem *>(kAgain ? again[j] : a.x[j]) + fo, i);
+                if (j < kPeersAlways<NREP, EXACT> || j < nrep - 1)
+                    peer[j] = ld1(reinterpret_cast<const xelem *>(kEight ? again[j] : a.x[kAgain ? fresh(j) : j]) + fo, i);
             }
         }
         float pl = ld1(c.p, i), av = ld1(c.s0, i), bv = ADAM ? ld1(c.s1, i) : 0.0f;
